@@ -220,7 +220,10 @@ typedef struct {
   int32_t precision;
   int32_t fell_back; /* ENT_AUTO: 1 if the a-posteriori check failed and the
                         plain schedule was run                                */
-  int32_t products;  /* R.V products of the recurrence (all passes)          */
+  int32_t products;  /* R.V products of the plain recurrence, one per moment
+                        (all passes); for a symmetric R the forward schedule
+                        takes two moments from each product (below) and runs
+                        half as many                                         */
 } ent_result;
 
 /* Fill *opt with the defaults listed above. */
@@ -240,6 +243,13 @@ void ent_options_default(ent_options *opt);
  * opt may be NULL (defaults).  Returns ENT_EINVAL for bad arguments,
  * ENT_ENOTDENSITY if the trace check fails, ENT_ENUMERIC if p~1 <= 0 or the
  * estimate is not finite.
+ *
+ * Forward schedules (Taylor, Chebyshev): for a real R equal to its transpose
+ * (checked in every call, entry by entry) the vectors of step k give two
+ * moments, V_k.V_{k+1} and V_{k+1}.V_{k+1} (T_a T_b = (T_{a+b} + T_{|a-b|})/2;
+ * Taylor: W_k.Y_k and W_{k+1}.Y_k), so m moments take about m / 2 products; the
+ * values are those of one moment per product up to rounding.  Any other R
+ * takes one product per moment, as it is given.
  *
  * ENT_FLAG_CLENSHAW (Chebyshev, single estimates): y_{m+1} = y_{m+2} = 0,
  * y_k = alpha_k g + 2 X y_{k+1} - y_{k+2} for k = m..0 (m + 1 products, the

@@ -142,6 +142,11 @@ struct DeviceWorkspace {
   std::mutex mu;
   void *ptr = nullptr;
   size_t bytes = 0;
+  // Answer of a device-side check that the host needs in mid-estimate: a word
+  // of pinned memory the check's kernel stores to, and the event recorded
+  // behind it (made on first use, released with the workspace).
+  int32_t *word = nullptr;
+  hipEvent_t word_ready = nullptr;
 };
 
 std::mutex g_ws_mu;
@@ -242,6 +247,10 @@ StagingBuffer *staging_for(int dev) {
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 constexpr int kScalarDoubles = 8192;
+
+// Largest dense n whose symmetry is checked: the check keeps the traces of its
+// 64-row tiles in 4096 scratch scalars (an FP32 R of this order has 275 GB).
+constexpr int64_t kDenseCheckMaxN = 64 * 4096;
 
 bool is_complex(const ent_matrix *R) {
   return R->dtype == ENT_STORE_C128 || R->dtype == ENT_STORE_C64;
@@ -436,6 +445,23 @@ struct WsLease {
     return ENT_OK;
   }
   void *ptr() const { return fixed ? fixed : ws->ptr; }
+  // The device's answer word, or null (the no-allocation entry point; no
+  // pinned memory left): the caller then copies the answer from the device.
+  int32_t *answer_word() {
+    if (fixed) return nullptr;
+    if (!ws->word) {
+      if (hipHostMalloc((void **)&ws->word, sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        ws->word = nullptr;
+      } else if (hipEventCreateWithFlags(&ws->word_ready, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipHostFree(ws->word);
+        ws->word = nullptr;
+        ws->word_ready = nullptr;
+      }
+    }
+    return ws->word;
+  }
   ent_status ensure(size_t need) {
     if (fixed) {
       if (need > ent::kNoAllocScratchBytes)
@@ -446,6 +472,87 @@ struct WsLease {
     return ensure_workspace(ws, need);
   }
 };
+
+// An int32 a device-side check leaves in the scalar block, brought to the
+// host without draining the stream: the check's kernel also stores it to the
+// workspace's answer word, the event is recorded behind that kernel, and the
+// host waits for the event after it has enqueued the work that does not
+// depend on the answer (the power method), so the device stays busy.
+struct DeviceAnswer {
+  int32_t *word = nullptr;  // null: read() copies from the device
+  hipEvent_t ready = nullptr;
+  const int32_t *dev = nullptr;
+  void attach(WsLease &ws, const void *slot) {
+    word = ws.answer_word();
+    ready = word ? ws.ws->word_ready : nullptr;
+    dev = (const int32_t *)slot;
+  }
+  ent_status mark(hipStream_t st) {
+    if (word) HIP_TRY(hipEventRecord(ready, st));
+    return ENT_OK;
+  }
+  ent_status read(hipStream_t st, int32_t *v) {
+    if (word) {
+      HIP_TRY(hipEventSynchronize(ready));
+      *v = *(volatile int32_t *)word;
+      return ENT_OK;
+    }
+    HIP_TRY(hipMemcpyAsync(v, dev, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    return ENT_OK;
+  }
+};
+
+// The scalars of one step of the polynomial recurrence, z = c1 y + c2 b V_k +
+// cw V_{k-1} (+ *cg g), and where its dot products go.
+struct StepScalars {
+  double c1 = 0, c2 = 0, cw = 0;
+  int32_t dot_y = 0, slot = -1, slot_gg = -1, slot_b = -1;
+  bool write = true;  // a later step reads the result
+  const double *cg = nullptr;
+};
+
+// Products of the recurrence: one per moment (Chebyshev: degrees 1..m;
+// Taylor: slots 0..m), half as many when each gives two.
+int32_t recurrence_products(int32_t method, int32_t m, bool pairs) {
+  const int32_t moments = method == ENT_CHEBYSHEV ? m : m + 1;
+  return pairs ? (moments + 1) / 2 : moments;
+}
+
+// Step k of the forward recurrence of degree m; last: no later step reads its
+// result.
+StepScalars forward_step(int32_t method, int32_t m, int32_t k, bool pairs, bool last) {
+  StepScalars r;
+  r.write = !last;
+  if (method == ENT_CHEBYSHEV) {
+    if (k == 0) {
+      r.c1 = 1.0; r.c2 = -1.0; r.cw = 0.0;
+      r.slot_gg = 0;
+    } else {
+      r.c1 = 2.0; r.c2 = -2.0; r.cw = -1.0;
+    }
+    r.slot = pairs ? 2 * k + 1 : k + 1;
+    r.slot_b = pairs && 2 * k + 2 <= m ? 2 * k + 2 : -1;
+  } else {
+    r.c1 = -1.0; r.c2 = 1.0; r.cw = 0.0;
+    r.dot_y = 1;
+    r.slot = pairs ? 2 * k : k;
+    r.slot_b = pairs && 2 * k + 1 <= m ? 2 * k + 1 : -1;
+  }
+  return r;
+}
+
+// Step k of Clenshaw's m + 1 (y_k index m - k; alpha at scal[S_ALPHA]).
+StepScalars clenshaw_step(int32_t m, int32_t k, const double *alpha) {
+  StepScalars r;
+  const int32_t kk = m - k;
+  r.c1 = 2.0; r.c2 = -2.0; r.cw = k == 0 ? 0.0 : -1.0;
+  r.slot = kk;
+  r.slot_gg = k == 0 ? m + 1 : -1;
+  r.cg = alpha + kk;
+  r.write = kk > 0;
+  return r;
+}
 
 Opts resolve_options(const ent_options *opt) {
   Opts r;
@@ -785,12 +892,28 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   // trace check (or the trace that normalises R)
   const bool normalize = (o.flags & ENT_FLAG_NORMALIZE) != 0;
   const bool check_trace = !(o.flags & ENT_FLAG_SKIP_TRACE_CHECK) && !normalize;
+  // dots in pairs halve the products, for a symmetric R only: whether R is
+  // one comes with the trace, from one pass over R
+  bool pairs = dense && !clenshaw && n <= kDenseCheckMaxN &&
+               recurrence_products(method, m, true) < recurrence_products(method, m, false);
+  DeviceAnswer asym;
+  if (pairs) {
+    asym.attach(ws, scal + ent::S_SYM);
+    if (R->dtype == ENT_STORE_F64)
+      HIP_TRY(ent::launch_dense_check<double>((const double *)R->values, R->ld, n, scal, asym.word, st));
+    else
+      HIP_TRY(ent::launch_dense_check<float>((const float *)R->values, R->ld, n, scal, asym.word, st));
+    rc = asym.mark(st);
+    if (rc != ENT_OK) return rc;
+  }
   if (check_trace || normalize) {
     if (dense) {
-      if (R->dtype == ENT_STORE_F64)
-        HIP_TRY(ent::launch_trace_dense<double>((const double *)R->values, R->ld, n, scal, st));
-      else
-        HIP_TRY(ent::launch_trace_dense<float>((const float *)R->values, R->ld, n, scal, st));
+      if (!pairs) {
+        if (R->dtype == ENT_STORE_F64)
+          HIP_TRY(ent::launch_trace_dense<double>((const double *)R->values, R->ld, n, scal, st));
+        else
+          HIP_TRY(ent::launch_trace_dense<float>((const float *)R->values, R->ld, n, scal, st));
+      }
     } else if (!tri) {  // the tridiagonal pack below sums the diagonal itself
       if (R->dtype == ENT_STORE_F64)
         HIP_TRY(ent::launch_trace_csr<double>(R->row_ptr, R->col_idx, (const double *)R->values, n, R->nnz,
@@ -840,7 +963,17 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   if (tprep) HIP_TRY(ent::launch_tri_prepare<T>(trid, scal, n, tprep, st));
 
   // recurrence
-  const int32_t nsteps = clenshaw ? m + 1 : (method == ENT_CHEBYSHEV) ? m : m + 1;
+  if (pairs) {
+    int32_t differs = 0;
+    rc = asym.read(st, &differs);
+    if (rc != ENT_OK) return rc;
+    pairs = differs == 0;
+  }
+  const int32_t nsteps = clenshaw ? m + 1 : recurrence_products(method, m, pairs);
+  auto step_scalars = [&](int32_t k) {
+    return clenshaw ? clenshaw_step(m, k, scal + ent::S_ALPHA)
+                    : forward_step(method, m, k, pairs, !stg && k == nsteps - 1);
+  };
   const T *Vk = dense || !rad ? G : nullptr;  // null: expand the sign block
   const T *Vkm1 = nullptr;
   T *bufs[2] = {VA, VB};
@@ -886,70 +1019,38 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
         if (b && b != x && b != y && b != z) return b;
       return nullptr;
     };
-    auto params = [&](int32_t k, double *c1, double *c2, double *cw, int32_t *dot_y, int32_t *slot,
-                      int32_t *slot_gg, const double **cg, bool *write) {
-      *cg = nullptr;
-      *slot_gg = -1;
-      *write = true;
-      if (clenshaw) {
-        const int32_t kk = m - k;
-        *c1 = 2.0; *c2 = -2.0; *cw = k == 0 ? 0.0 : -1.0; *dot_y = 0; *slot = kk;
-        *slot_gg = k == 0 ? m + 1 : -1;
-        *cg = scal + ent::S_ALPHA + kk;
-      } else if (method == ENT_CHEBYSHEV) {
-        if (k == 0) {
-          *c1 = 1.0; *c2 = -1.0; *cw = 0.0; *slot_gg = 0;
-        } else {
-          *c1 = 2.0; *c2 = -2.0; *cw = -1.0;
-        }
-        *dot_y = 0;
-        *slot = k + 1;
-      } else {
-        *c1 = -1.0; *c2 = 1.0; *cw = 0.0; *dot_y = 1; *slot = k;
-        *write = k < nsteps - 1;
-      }
-    };
     int32_t k = 0;
     for (const int32_t len : sizes) {
-      double c1, c2, cw;
-      int32_t dot_y, slot, slot_gg;
-      const double *cg;
-      bool write;
-      params(k, &c1, &c2, &cw, &dot_y, &slot, &slot_gg, &cg, &write);
+      const StepScalars q = step_scalars(k);
       if (len >= 2) {
         // per-step scalars of steps k .. k + len - 1
-        double c1s[ent::kTriMaxFuse], c2s[ent::kTriMaxFuse], cws[ent::kTriMaxFuse];
-        int32_t dys[ent::kTriMaxFuse], slots[ent::kTriMaxFuse];
-        const double *cgs[ent::kTriMaxFuse];
-        bool last_write = write;
-        for (int32_t j = 0; j < len; ++j) {
-          int32_t gg;
-          params(k + j, &c1s[j], &c2s[j], &cws[j], &dys[j], &slots[j], &gg, &cgs[j], &last_write);
-        }
+        StepScalars qs[ent::kTriMaxFuse];
+        for (int32_t j = 0; j < len; ++j) qs[j] = step_scalars(k + j);
+        const bool last_write = qs[len - 1].write;
         T *outA = free_buf(Vk, Vkm1, nullptr);
         T *outB = free_buf(Vk, Vkm1, outA);
         const int e0 = pe.mark();
         if (tri_fused) {
           ent::TriFusedArgs ta{};
           ta.diag = trid; ta.prep = tprep; ta.n = n; ta.ldv = ldv; ta.ldb = ldb; ta.s = s;
-          ta.Vk = Vk; ta.Vkm1 = cw != 0.0 ? Vkm1 : nullptr;
+          ta.Vk = Vk; ta.Vkm1 = q.cw != 0.0 ? Vkm1 : nullptr;
           ta.VoutA = outA; ta.VoutB = last_write ? outB : nullptr;
           ta.signs = rad ? signs : nullptr; ta.G = rad ? nullptr : G;
-          ta.scal = scal; ta.part = part; ta.nblk = ntile; ta.slot_gg = slot_gg;
+          ta.scal = scal; ta.part = part; ta.nblk = ntile; ta.slot_gg = q.slot_gg;
           for (int32_t j = 0; j < len; ++j) {
-            ta.c1[j] = c1s[j]; ta.c2[j] = c2s[j]; ta.cw[j] = cws[j];
-            ta.dot_y[j] = dys[j]; ta.slot[j] = slots[j]; ta.cg[j] = cgs[j];
+            ta.c1[j] = qs[j].c1; ta.c2[j] = qs[j].c2; ta.cw[j] = qs[j].cw;
+            ta.dot_y[j] = qs[j].dot_y; ta.slot[j] = qs[j].slot; ta.cg[j] = qs[j].cg;
           }
           HIP_TRY(ent::launch_tri_fused<T>(ta, len, st));
         } else {
           ent::BandPairArgs pa{};
           pa.band = band; pa.n = n; pa.ldv = ldv;
-          pa.Vk = Vk; pa.Vkm1 = cw != 0.0 ? Vkm1 : nullptr;
+          pa.Vk = Vk; pa.Vkm1 = q.cw != 0.0 ? Vkm1 : nullptr;
           pa.signs = rad ? signs : nullptr; pa.G = rad ? nullptr : G;
-          pa.scal = scal; pa.part = part; pa.nwave = ntile; pa.slot_gg = slot_gg;
+          pa.scal = scal; pa.part = part; pa.nwave = ntile; pa.slot_gg = q.slot_gg;
           for (int32_t j = 0; j < 2; ++j) {
-            pa.c1[j] = c1s[j]; pa.c2[j] = c2s[j]; pa.cw[j] = cws[j];
-            pa.dot_y[j] = dys[j]; pa.slot[j] = slots[j]; pa.cg[j] = cgs[j];
+            pa.c1[j] = qs[j].c1; pa.c2[j] = qs[j].c2; pa.cw[j] = qs[j].cw;
+            pa.dot_y[j] = qs[j].dot_y; pa.slot[j] = qs[j].slot; pa.cg[j] = qs[j].cg;
           }
           pa.VoutA = outA;
           pa.VoutB = last_write ? outB : nullptr;
@@ -963,21 +1064,21 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
       } else if (tri_fused) {
         ent::TriStepArgs a{};
         a.diag = trid; a.n = n; a.ldv = ldv; a.ldb = ldb; a.s = s;
-        a.Vk = Vk; a.Vkm1 = cw != 0.0 ? Vkm1 : nullptr;
-        a.Vkp1 = write ? free_buf(Vk, Vkm1, nullptr) : nullptr;
+        a.Vk = Vk; a.Vkm1 = q.cw != 0.0 ? Vkm1 : nullptr;
+        a.Vkp1 = q.write ? free_buf(Vk, Vkm1, nullptr) : nullptr;
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
-        a.scal = scal; a.c1 = c1; a.c2 = c2; a.cw = cw; a.dot_y = dot_y;
-        a.slot = slot; a.slot_gg = slot_gg; a.part = part; a.nblk = ntile; a.cg = cg;
+        a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
+        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nblk = ntile; a.cg = q.cg;
         HIP_TRY(ent::launch_tri_step<T>(a, st));
         k += 1;
       } else {
         ent::BandStepArgs a{};
         a.band = band; a.n = n; a.ldv = ldv;
-        a.Vk = Vk; a.Vkm1 = cw != 0.0 ? Vkm1 : nullptr;
-        a.Vkp1 = write ? free_buf(Vk, Vkm1, nullptr) : nullptr;
+        a.Vk = Vk; a.Vkm1 = q.cw != 0.0 ? Vkm1 : nullptr;
+        a.Vkp1 = q.write ? free_buf(Vk, Vkm1, nullptr) : nullptr;
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
-        a.scal = scal; a.c1 = c1; a.c2 = c2; a.cw = cw; a.dot_y = dot_y;
-        a.slot = slot; a.slot_gg = slot_gg; a.part = part; a.nwave = ntile; a.cg = cg;
+        a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
+        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nwave = ntile; a.cg = q.cg;
         HIP_TRY(ent::launch_band_step<T>(a, hp, st));
         k += 1;
       }
@@ -985,123 +1086,66 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     pe.steps_end = pe.mark();
   }
   int32_t k_begin = (band_pairs || tri_fused) ? nsteps : 0;
+  const int32_t final_code = clenshaw ? ent::FINAL_CLENSHAW
+                             : pairs && method == ENT_CHEBYSHEV ? ent::FINAL_CHEB_PAIRS : method;
   int32_t m_run = stg ? stg->deg[0] : m;  // degree of the estimate
   int32_t stage = 0;
   for (;;) {
-    const int32_t k_end = stg ? m_run : nsteps;
+    const int32_t k_end = stg ? recurrence_products(method, m_run, pairs) : nsteps;
     for (int32_t k = k_begin; k < k_end; ++k) {
-      if (clenshaw) {
-        const int32_t kk = m - k;  // index of the y computed by this launch
-        T *Vout = (T *)Vkm1;
-        if (dense) {
-          ent::DenseStepArgs a{};
-          a.R = Rt; a.ldr = ldr; a.n = n; a.ldv = ldv;
-          a.Vk = Vk; a.Vkm1 = Vkm1; a.Vkp1 = Vout; a.G = G;
-          a.scal = scal; a.c1 = 2.0; a.c2 = -2.0; a.cw = k == 0 ? 0.0 : -1.0; a.dot_y = 0;
-          a.slot = kk; a.slot_gg = k == 0 ? m + 1 : -1; a.part = part; a.ntile = ntile; a.bn = bn;
-          a.cg = scal + ent::S_ALPHA + kk;
-          a.ksplit = ksplit; a.kper = kper; a.party = party; a.nptile = npart;
-          HIP_TRY(dense_step(a));
-        } else if (banded) {
-          ent::BandStepArgs a{};
-          a.band = band; a.n = n; a.ldv = ldv;
-          a.Vk = Vk; a.Vkm1 = k == 0 ? nullptr : Vkm1; a.Vkp1 = Vout;
-          a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
-          a.scal = scal; a.c1 = 2.0; a.c2 = -2.0; a.cw = k == 0 ? 0.0 : -1.0; a.dot_y = 0;
-          a.slot = kk; a.slot_gg = k == 0 ? m + 1 : -1; a.part = part; a.nwave = ntile;
-          a.cg = scal + ent::S_ALPHA + kk;
-          HIP_TRY(ent::launch_band_step<T>(a, hp, st));
-        } else if (tri) {
-          ent::TriStepArgs a{};
-          a.diag = trid; a.n = n; a.ldv = ldv; a.ldb = ldb; a.s = s;
-          a.Vk = Vk; a.Vkm1 = k == 0 ? nullptr : Vkm1; a.Vkp1 = Vout;
-          a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
-          a.scal = scal; a.c1 = 2.0; a.c2 = -2.0; a.cw = k == 0 ? 0.0 : -1.0; a.dot_y = 0;
-          a.slot = kk; a.slot_gg = k == 0 ? m + 1 : -1; a.part = part; a.nblk = ntile;
-          a.cg = scal + ent::S_ALPHA + kk;
-          HIP_TRY(ent::launch_tri_step<T>(a, st));
-        } else {
-          ent::CsrStepArgs a{};
-          a.row_ptr = R->row_ptr; a.col_idx = R->col_idx; a.values = R->values; a.n = n; a.ldv = ldv;
-          a.Vk = Vk; a.Vkm1 = k == 0 ? nullptr : Vkm1; a.Vkp1 = Vout;
-          a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
-          a.scal = scal; a.c1 = 2.0; a.c2 = -2.0; a.cw = k == 0 ? 0.0 : -1.0; a.dot_y = 0;
-          a.slot = kk; a.slot_gg = k == 0 ? m + 1 : -1; a.part = part; a.nblk = ntile; a.win = cwin;
-          a.cg = scal + ent::S_ALPHA + kk;
-          a.s = s;
-          HIP_TRY(ent::launch_csr_step<T>(a, st));
-        }
-        Vkm1 = Vk;
-        Vk = Vout;
-        const int e = pe.mark();
-        if (k == nsteps - 1) pe.steps_end = e;
-        end_step(e);
-        continue;
-      }
-      T *Vout = bufs[k & 1];
-      double c1, c2, cw;
-      int32_t dot_y, slot, slot_gg = -1;
-      bool write = true;
-      if (method == ENT_CHEBYSHEV) {
-        if (k == 0) {
-          c1 = 1.0; c2 = -1.0; cw = 0.0;
-          slot_gg = 0;
-        } else {
-          c1 = 2.0; c2 = -2.0; cw = -1.0;
-        }
-        dot_y = 0;
-        slot = k + 1;
-      } else {
-        c1 = -1.0; c2 = 1.0; cw = 0.0;
-        dot_y = 1;
-        slot = k;
-        write = k < nsteps - 1;
-      }
+      const StepScalars q = step_scalars(k);
+      // Clenshaw: each y_k is written over y_{k+2}, the operand in V_{k-1}'s
+      // place.  Chebyshev: V_{k+1} is written over V_{k-1} (same element, same
+      // thread), so two buffers plus the probe block suffice.  Taylor: W_{k+1}
+      // may not overwrite W_k (read by every tile), so outputs alternate.
+      T *Vout = clenshaw ? (T *)Vkm1 : bufs[k & 1];
+      T *Vw = q.write ? Vout : nullptr;
+      // V_{k-1} where the step has such a term (null with cw != 0 on the
+      // sparse paths: the sign block)
+      const T *Vm = clenshaw && k == 0 && !dense ? nullptr : Vkm1;
       if (dense) {
         ent::DenseStepArgs a{};
         a.R = Rt; a.ldr = ldr; a.n = n; a.ldv = ldv;
-        a.Vk = Vk; a.Vkm1 = Vkm1; a.Vkp1 = write ? Vout : nullptr; a.G = G;
-        a.scal = scal; a.c1 = c1; a.c2 = c2; a.cw = cw; a.dot_y = dot_y;
-        a.slot = slot; a.slot_gg = slot_gg; a.part = part; a.ntile = ntile; a.bn = bn;
+        a.Vk = Vk; a.Vkm1 = Vm; a.Vkp1 = Vw; a.G = G;
+        a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
+        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.ntile = ntile; a.bn = bn;
+        a.pair = pairs; a.slot_b = q.slot_b; a.cg = q.cg;
         a.ksplit = ksplit; a.kper = kper; a.party = party; a.nptile = npart;
         HIP_TRY(dense_step(a));
       } else if (banded) {
         ent::BandStepArgs a{};
         a.band = band; a.n = n; a.ldv = ldv;
-        a.Vk = Vk; a.Vkm1 = Vkm1; a.Vkp1 = write ? Vout : nullptr;
+        a.Vk = Vk; a.Vkm1 = Vm; a.Vkp1 = Vw;
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
-        a.scal = scal; a.c1 = c1; a.c2 = c2; a.cw = cw; a.dot_y = dot_y;
-        a.slot = slot; a.slot_gg = slot_gg; a.part = part; a.nwave = ntile;
+        a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
+        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nwave = ntile; a.cg = q.cg;
         HIP_TRY(ent::launch_band_step<T>(a, hp, st));
       } else if (tri) {
         ent::TriStepArgs a{};
         a.diag = trid; a.n = n; a.ldv = ldv; a.ldb = ldb; a.s = s;
-        a.Vk = Vk; a.Vkm1 = Vkm1; a.Vkp1 = write ? Vout : nullptr;
+        a.Vk = Vk; a.Vkm1 = Vm; a.Vkp1 = Vw;
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
-        a.scal = scal; a.c1 = c1; a.c2 = c2; a.cw = cw; a.dot_y = dot_y;
-        a.slot = slot; a.slot_gg = slot_gg; a.part = part; a.nblk = ntile;
+        a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
+        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nblk = ntile; a.cg = q.cg;
         HIP_TRY(ent::launch_tri_step<T>(a, st));
       } else {
         ent::CsrStepArgs a{};
         a.row_ptr = R->row_ptr; a.col_idx = R->col_idx; a.values = R->values; a.n = n; a.ldv = ldv;
-        a.Vk = Vk; a.Vkm1 = Vkm1; a.Vkp1 = write ? Vout : nullptr;
+        a.Vk = Vk; a.Vkm1 = Vm; a.Vkp1 = Vw;
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
-        a.scal = scal; a.c1 = c1; a.c2 = c2; a.cw = cw; a.dot_y = dot_y;
-        a.slot = slot; a.slot_gg = slot_gg; a.part = part; a.nblk = ntile; a.win = cwin;
-        a.s = s;
+        a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
+        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nblk = ntile; a.win = cwin;
+        a.cg = q.cg; a.s = s;
         HIP_TRY(ent::launch_csr_step<T>(a, st));
       }
-      // Chebyshev: V_{k+1} is written over V_{k-1} (same element, same thread),
-      // so two buffers plus the probe block suffice.  Taylor: W_{k+1} may not
-      // overwrite W_k (read by every tile), so outputs alternate.
-      if (method == ENT_CHEBYSHEV) Vkm1 = Vk;
+      if (clenshaw || method == ENT_CHEBYSHEV) Vkm1 = Vk;
       Vk = Vout;
       const int e = pe.mark();
       if (k == k_end - 1) pe.steps_end = e;
       end_step(e);
     }
     HIP_TRY(ent::launch_reduce_moments(part, stg ? m_run + 1 : nslot, npart, ldv, s, d, st));
-    HIP_TRY(ent::launch_final(d, scal, clenshaw ? ent::FINAL_CLENSHAW : method, m_run, s, h, st));
+    HIP_TRY(ent::launch_final(d, scal, final_code, m_run, s, h, st));
     if (!stg) break;
     // the check on the host; on rejection the recurrence continues from V_k, V_{k-1}
     std::vector<double> smom((size_t)(m_run + 1) * s), salpha(m_run + 1);
@@ -1236,7 +1280,19 @@ ent_status run_bf16x3(const ent_matrix *R, int32_t method, int32_t m, int32_t s,
   HIP_TRY(ent::launch_zero(scal, sizeof(double) * 64, st));
   const bool normalize = (o.flags & ENT_FLAG_NORMALIZE) != 0;
   const bool check_trace = !(o.flags & ENT_FLAG_SKIP_TRACE_CHECK) && !normalize;
-  if (check_trace || normalize) {
+  // dots in pairs for a symmetric R (see run_poly)
+  bool pairs = !clenshaw && n <= kDenseCheckMaxN &&
+               recurrence_products(method, m, true) < recurrence_products(method, m, false);
+  DeviceAnswer asym;
+  if (pairs) {
+    asym.attach(ws, scal + ent::S_SYM);
+    if (f64)
+      HIP_TRY(ent::launch_dense_check<double>((const double *)R->values, R->ld, n, scal, asym.word, st));
+    else
+      HIP_TRY(ent::launch_dense_check<float>((const float *)R->values, R->ld, n, scal, asym.word, st));
+    rc = asym.mark(st);
+    if (rc != ENT_OK) return rc;
+  } else if (check_trace || normalize) {
     if (f64)
       HIP_TRY(ent::launch_trace_dense<double>((const double *)R->values, R->ld, n, scal, st));
     else
@@ -1261,7 +1317,13 @@ ent_status run_bf16x3(const ent_matrix *R, int32_t method, int32_t m, int32_t s,
   HIP_TRY(ent::launch_setup_interval(scal, method, m, o.u_factor, o.u_fixed, o.cutoff, st,
                                      normalize ? op.trace_div : 0.0));
 
-  const int32_t nsteps = clenshaw ? m + 1 : (method == ENT_CHEBYSHEV) ? m : m + 1;
+  if (pairs) {
+    int32_t differs = 0;
+    rc = asym.read(st, &differs);
+    if (rc != ENT_OK) return rc;
+    pairs = differs == 0;
+  }
+  const int32_t nsteps = clenshaw ? m + 1 : recurrence_products(method, m, pairs);
   const float *Vk = G, *Vkm1 = nullptr;
   float *bufs[2] = {VA, VB};
   if (clenshaw) {
@@ -1275,50 +1337,9 @@ ent_status run_bf16x3(const ent_matrix *R, int32_t method, int32_t m, int32_t s,
   }
   pe.steps_begin = pe.mark();
   for (int32_t k = 0; k < nsteps; ++k) {
-    if (clenshaw) {
-      const int32_t kk = m - k;
-      float *Vout = (float *)Vkm1;
-      ent::Bf16GemmArgs ga{};
-      ga.A_hi = Ahi; ga.A_lo = Alo; ga.V_hi = Vhi; ga.V_lo = Vlo; ga.part_y = party;
-      ga.n_pad = n_pad; ga.ldv = ldv; ga.k_per_split = kps; ga.splits = splits; ga.bn = bn;
-      const int e0 = pe.mark();
-      HIP_TRY(ent::launch_bf16x3_gemm(ga, st));
-      const int e1 = pe.mark();
-      ent::Bf16EpiArgs ea{};
-      ea.part_y = party; ea.splits = splits; ea.Vk = Vk; ea.Vkm1 = k == 0 ? nullptr : Vkm1;
-      ea.Vkp1 = Vout; ea.V_hi = Vhi; ea.V_lo = Vlo; ea.G = G; ea.scal = scal;
-      ea.c1 = 2.0; ea.c2 = -2.0; ea.cw = k == 0 ? 0.0 : -1.0; ea.dot_y = 0; ea.slot = kk;
-      ea.slot_gg = k == 0 ? m + 1 : -1; ea.scale_y = 1; ea.cg = scal + ent::S_ALPHA + kk;
-      ea.part = part; ea.nblk = nblk; ea.n_pad = n_pad; ea.ldv = ldv;
-      HIP_TRY(ent::launch_bf16x3_epilogue(ea, st));
-      const int e2 = pe.mark();
-      if (pe.on) {
-        pe.main_spans.push_back({e0, e1});
-        pe.epi_spans.push_back({e1, e2});
-      }
-      Vkm1 = Vk;
-      Vk = Vout;
-      continue;
-    }
-    float *Vout = bufs[k & 1];
-    double c1, c2, cw;
-    int32_t dot_y, slot, slot_gg = -1;
-    bool write = true;
-    if (method == ENT_CHEBYSHEV) {
-      if (k == 0) {
-        c1 = 1.0; c2 = -1.0; cw = 0.0;
-        slot_gg = 0;
-      } else {
-        c1 = 2.0; c2 = -2.0; cw = -1.0;
-      }
-      dot_y = 0;
-      slot = k + 1;
-    } else {
-      c1 = -1.0; c2 = 1.0; cw = 0.0;
-      dot_y = 1;
-      slot = k;
-      write = k < nsteps - 1;
-    }
+    const StepScalars q = clenshaw ? clenshaw_step(m, k, scal + ent::S_ALPHA)
+                                   : forward_step(method, m, k, pairs, k == nsteps - 1);
+    float *Vout = clenshaw ? (float *)Vkm1 : bufs[k & 1];
     ent::Bf16GemmArgs ga{};
     ga.A_hi = Ahi; ga.A_lo = Alo; ga.V_hi = Vhi; ga.V_lo = Vlo; ga.part_y = party;
     ga.n_pad = n_pad; ga.ldv = ldv; ga.k_per_split = kps; ga.splits = splits; ga.bn = bn;
@@ -1326,10 +1347,10 @@ ent_status run_bf16x3(const ent_matrix *R, int32_t method, int32_t m, int32_t s,
     HIP_TRY(ent::launch_bf16x3_gemm(ga, st));
     const int e1 = pe.mark();
     ent::Bf16EpiArgs ea{};
-    ea.part_y = party; ea.splits = splits; ea.Vk = Vk; ea.Vkm1 = Vkm1;
-    ea.Vkp1 = write ? Vout : nullptr; ea.V_hi = Vhi; ea.V_lo = Vlo; ea.G = G; ea.scal = scal;
-    ea.c1 = c1; ea.c2 = c2; ea.cw = cw; ea.dot_y = dot_y; ea.slot = slot; ea.slot_gg = slot_gg;
-    ea.scale_y = 1;
+    ea.part_y = party; ea.splits = splits; ea.Vk = Vk; ea.Vkm1 = clenshaw && k == 0 ? nullptr : Vkm1;
+    ea.Vkp1 = q.write ? Vout : nullptr; ea.V_hi = Vhi; ea.V_lo = Vlo; ea.G = G; ea.scal = scal;
+    ea.c1 = q.c1; ea.c2 = q.c2; ea.cw = q.cw; ea.dot_y = q.dot_y; ea.slot = q.slot; ea.slot_gg = q.slot_gg;
+    ea.pair = pairs; ea.slot_b = q.slot_b; ea.scale_y = 1; ea.cg = q.cg;
     ea.part = part; ea.nblk = nblk; ea.n_pad = n_pad; ea.ldv = ldv;
     HIP_TRY(ent::launch_bf16x3_epilogue(ea, st));
     const int e2 = pe.mark();
@@ -1337,12 +1358,15 @@ ent_status run_bf16x3(const ent_matrix *R, int32_t method, int32_t m, int32_t s,
       pe.main_spans.push_back({e0, e1});
       pe.epi_spans.push_back({e1, e2});
     }
-    if (method == ENT_CHEBYSHEV) Vkm1 = Vk;
+    if (clenshaw || method == ENT_CHEBYSHEV) Vkm1 = Vk;
     Vk = Vout;
   }
   pe.steps_end = pe.mark();
   HIP_TRY(ent::launch_reduce_moments(part, nslot, nblk, ldv, s, d, st));
-  HIP_TRY(ent::launch_final(d, scal, clenshaw ? ent::FINAL_CLENSHAW : method, m, s, h, st));
+  HIP_TRY(ent::launch_final(d, scal,
+                            clenshaw ? ent::FINAL_CLENSHAW
+                            : pairs && method == ENT_CHEBYSHEV ? ent::FINAL_CHEB_PAIRS : method,
+                            m, s, h, st));
   if (hook && hook->alpha_host)
     HIP_TRY(hipMemcpyAsync(hook->alpha_host, scal + ent::S_ALPHA, sizeof(double) * (m + 1),
                            hipMemcpyDeviceToHost, st));
@@ -2720,6 +2744,20 @@ ent_status free_buffers(std::mutex &map_mu, std::map<int, Buf *> &bufs) {
   return rc;
 }
 
+// The workspaces' answer words and events (nothing is in flight between calls).
+void free_answer_words() {
+  std::lock_guard<std::mutex> lk(g_ws_mu);
+  for (auto &kv : g_ws) {
+    std::lock_guard<std::mutex> l2(kv.second->mu);
+    if (!kv.second->word) continue;
+    (void)hipSetDevice(kv.first);
+    (void)hipEventDestroy(kv.second->word_ready);
+    (void)hipHostFree(kv.second->word);
+    kv.second->word = nullptr;
+    kv.second->word_ready = nullptr;
+  }
+}
+
 // Algorithm 4 on a device-resident R (validated, arrays checked).
 ent_status power_method_device(const ent_matrix *R, int32_t t, int32_t q, uint64_t seed, void *stream,
                                double *p1) {
@@ -3193,6 +3231,7 @@ ent_status ent_release_workspace(void) {
   int cur = 0;
   HIP_TRY(hipGetDevice(&cur));
   const ent_status r1 = free_buffers(g_ws_mu, g_ws);
+  free_answer_words();
   const ent_status r2 = free_buffers(g_rf_mu, g_rf);
   const ent_status r3 = free_buffers(g_stage_mu, g_stage);
   const hipError_t e = hipSetDevice(cur);

@@ -23,11 +23,27 @@ enum ScalarSlot {
                 // factor (div / tr R); 0: R as given
   S_ENT = 8,    // estimate
   S_SE = 9,     // standard error
+  S_SYM = 10,   // int32: nonzero if R differs from its transpose somewhere
   S_ALPHA = 16  // alpha_0 .. alpha_m (Chebyshev) follow
 };
 
 // launch_final's method code for the Clenshaw schedule (0 Taylor, 1 Chebyshev).
 constexpr int32_t FINAL_CLENSHAW = 2;
+// launch_final's method code for Chebyshev dots taken in pairs (below): slot
+// w >= 2 of d holds half of d_w + d_{w mod 2} and is replaced by d_w.
+constexpr int32_t FINAL_CHEB_PAIRS = 3;
+
+// Dots in pairs.  For a symmetric R every step's vectors give two moments of
+// the polynomial, so m of them take ceil(m / 2) products instead of m:
+//   Chebyshev, V_k = T_k(X) g:  V_k.V_{k+1} = (d_{2k+1} + d_1) / 2,
+//                               V_{k+1}.V_{k+1} = (d_{2k+2} + d_0) / 2
+//     (T_a T_b = (T_{a+b} + T_{|a-b|}) / 2 and X = X^T);
+//   Taylor, W_k = (I - R/u)^k g, Y_k = (R/u) W_k:  W_k.Y_k = e_{2k},
+//                                                 W_{k+1}.Y_k = e_{2k+1}.
+// Step kernels with `pair` set take their main dot with V_k instead of g (and
+// g.g as V_k.V_k, on step 0, where V_0 = g), and a second dot of the step's
+// result into slot_b.  Where R differs from its transpose in any entry these
+// identities do not hold and every step takes one dot with g.
 
 struct DenseStepArgs {
   const void *R;      // n x n, row-major, element type T
@@ -46,6 +62,8 @@ struct DenseStepArgs {
   double *part;       // partials [slot][row tile][ldv]
   int32_t ntile;      // number of row tiles (partial stride)
   int32_t bn;         // column tile width (64, 128 or 256)
+  int32_t pair;       // 1: dots in pairs (main dot with V_k)
+  int32_t slot_b;     // pair: slot of z.z (Chebyshev) or z.y (Taylor); -1: none
   const double *cg;   // device scalar: z += (*cg) g (Clenshaw's alpha_k term); null: none
   // Split-K (ksplit > 1): the product runs over ksplit ranges of kper
   // columns into party[ks][row][ldv] (element type T, n_pad rows), and a
@@ -152,6 +170,12 @@ hipError_t launch_set_norm(double *scal, double norm_div, hipStream_t st);
 // ---- trace check -----------------------------------------------------------
 template <typename T>
 hipError_t launch_trace_dense(const T *R, int64_t ldr, int64_t n, double *scal, hipStream_t st);
+// The trace and, in the same pass over R, whether R equals its transpose: a
+// mismatch sets the int32 at scal[S_SYM] (which must start at 0).  host_flag
+// (pinned host memory, may be null) receives that int32 too.
+template <typename T>
+hipError_t launch_dense_check(const T *R, int64_t ldr, int64_t n, double *scal, int32_t *host_flag,
+                              hipStream_t st);
 template <typename T>
 hipError_t launch_trace_csr(const int64_t *rp, const int32_t *ci, const T *val, int64_t n, int64_t nnz,
                             double *scal, hipStream_t st);
@@ -374,6 +398,7 @@ struct Bf16EpiArgs {
   const double *scal;
   double c1, c2, cw;
   int32_t dot_y, slot, slot_gg;
+  int32_t pair, slot_b;         // dots in pairs, as in DenseStepArgs
   int32_t scale_y;              // 1: y *= scal[S_A] (the split is of R itself)
   double *part;                 // [slot][nblk][ldv]
   int32_t nblk;
@@ -504,7 +529,7 @@ hipError_t launch_batch_setup(const BatchMat *mats, int32_t count, int32_t metho
                               double norm_div = 0.0);
 hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double *part,
                                int32_t nslot, int64_t ldv, int32_t s, double *d, hipStream_t st);
-hipError_t launch_batch_final(const BatchMat *mats, int32_t count, const double *d, int32_t method,
+hipError_t launch_batch_final(const BatchMat *mats, int32_t count, double *d, int32_t method,
                               int32_t m, int32_t s, double *h, hipStream_t st);
 
 // ---- random projection (Algorithm 3) -----------------------------------------
@@ -547,7 +572,7 @@ hipError_t launch_selector_features(const double *scal, const double *d, int32_t
 hipError_t launch_reduce_moments(const double *part, int32_t nslot, int32_t ntile, int64_t ldv,
                                  int32_t s, double *d, hipStream_t st);
 // Per-probe values and the estimate (Algorithms 1-2 output line).
-hipError_t launch_final(const double *d, double *scal, int32_t method, int32_t m, int32_t s,
+hipError_t launch_final(double *d, double *scal, int32_t method, int32_t m, int32_t s,
                         double *h, hipStream_t st);
 
 // ---- fixed scratch of the no-allocation entry point ---------------------------

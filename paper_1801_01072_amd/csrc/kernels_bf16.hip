@@ -840,13 +840,14 @@ hipError_t launch_bf16x3_gemm(const Bf16GemmArgs &a, hipStream_t st) {
 // Thread = (probe j, 8 consecutive rows); block = 256 threads of one probe.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void bf16x3_epilogue_body(const Bf16EpiArgs &a, int64_t blk, int64_t j) {
-  __shared__ double red[2][4];
+  __shared__ double red[3][4];
   const int64_t npad = a.n_pad;
   const int64_t i0 = (blk * blockDim.x + threadIdx.x) * 8;
   const float c1 = (float)a.c1, c2b = (float)(a.c2 * a.scal[S_B]), cw = (float)a.cw;
   const float ys = a.scale_y ? (float)a.scal[S_A] : 1.f;
   const float cg = a.cg ? (float)a.cg[0] : 0.f;
-  double ds = 0.0, gs = 0.0;
+  const bool pair = a.pair != 0;
+  double ds = 0.0, gs = 0.0, bs = 0.0;
   if (i0 < npad) {
     const int64_t off = j * npad + i0;
     float y[8];
@@ -871,8 +872,9 @@ __device__ __forceinline__ void bf16x3_epilogue_body(const Bf16EpiArgs &a, int64
       vm0 = vm[0];
       vm1 = vm[1];
     }
-    const f32x4 *gp = (const f32x4 *)(a.G + off);
-    const f32x4 g0 = gp[0], g1 = gp[1];
+    // dots in pairs are taken with V_k: g is not read
+    const f32x4 *gp = pair ? vk : (const f32x4 *)(a.G + off);
+    const f32x4 g0 = pair ? vk0 : gp[0], g1 = pair ? vk1 : gp[1];
     float z[8];
     u16x8 zh, zl;
 #pragma unroll
@@ -886,8 +888,10 @@ __device__ __forceinline__ void bf16x3_epilogue_body(const Bf16EpiArgs &a, int64
       zh[e] = h;
       zl[e] = bf16_rne(z[e] - bf16_to_f32(h));
       if (a.slot >= 0) {
-        ds += (double)ge * (double)(a.dot_y ? y[e] : z[e]);
+        const double q = (double)(a.dot_y ? y[e] : z[e]);
+        ds += (double)ge * q;
         gs += (double)ge * (double)ge;
+        bs += (double)z[e] * q;
       }
     }
     if (a.Vkp1) {
@@ -901,22 +905,26 @@ __device__ __forceinline__ void bf16x3_epilogue_body(const Bf16EpiArgs &a, int64
   }
   if (a.slot < 0) return;
   ds = wave_sum(ds);
-  gs = wave_sum(gs);
+  if (a.slot_gg >= 0) gs = wave_sum(gs);
+  if (pair) bs = wave_sum(bs);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if (lane == 0) {
     red[0][w] = ds;
     red[1][w] = gs;
+    red[2][w] = bs;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     const int nwv = blockDim.x >> 6;
-    double t0 = 0.0, t1 = 0.0;
+    double t0 = 0.0, t1 = 0.0, t2 = 0.0;
     for (int q = 0; q < nwv; ++q) {
       t0 += red[0][q];
       t1 += red[1][q];
+      t2 += red[2][q];
     }
     a.part[((int64_t)a.slot * a.nblk + blk) * a.ldv + j] = t0;
     if (a.slot_gg >= 0) a.part[((int64_t)a.slot_gg * a.nblk + blk) * a.ldv + j] = t1;
+    if (pair && a.slot_b >= 0) a.part[((int64_t)a.slot_b * a.nblk + blk) * a.ldv + j] = t2;
   }
 }
 

@@ -5,6 +5,7 @@
 //   Y = a * (R V_k)                                  (MFMA, K = n)
 //   Z = c1*Y + c2*b*V_k + cw*V_{k-1}  -> V_{k+1}      (epilogue)
 //   part[slot][tile][j] = sum_{rows of tile} g_ij * (dot_y ? Y : Z)_ij
+//   (pair: V_k in place of g, and Z_ij * (dot_y ? Y : Z)_ij into slot_b)
 //
 // Chebyshev (Algorithm 2 via the forward three-term recurrence of T_w,
 // Section 3 / Appendix B): a = 2/(u-lo), b = (u+lo)/(u-lo); step 0 has
@@ -110,7 +111,7 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
   // one LDS array (the epilogue's per-wave dot sums reuse it after the
   // products): with a single LDS object the compiler adds no waits of its own
   // between the direct loads into one stage and the reads of another
-  static_assert(NST * STAGE >= 2 * 4 * BN * 8, "the dot sums fit in the stages");
+  static_assert(NST * STAGE >= 3 * 4 * BN * 8, "the dot sums fit in the stages");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
   double(*red)[4][BN] = (double(*)[4][BN])lds;
 
@@ -290,7 +291,10 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
   const bool use_m1 = (a.cw != 0.0) && Vkm1;
   const bool want_dot = a.slot >= 0;
   const bool want_gg = a.slot_gg >= 0;
+  const bool pair = a.pair != 0;
+  const bool want_b = pair && a.slot_b >= 0;
   const bool use_cg = a.cg != nullptr;
+  const bool use_g = use_cg || (want_dot && !pair);
   const T tcg = use_cg ? (T)a.cg[0] : T(0);
   // The operands of EC column groups are loaded together before any of their
   // results is stored: V_{k+1} may be written over V_{k-1}, so loads left
@@ -309,12 +313,12 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
           const int64_t off = (wrow0 + 16 * f + M::drow(kq, r)) * ldv + col0 + 16 * (cb + e) + m16;
           vk[e][f][r] = Vk[off];
           vm[e][f][r] = use_m1 ? Vkm1[off] : T(0);
-          gv[e][f][r] = want_dot || use_cg ? G[off] : T(0);
+          gv[e][f][r] = use_g ? G[off] : vk[e][f][r];
         }
 #pragma unroll
     for (int e = 0; e < EC; ++e) {
       const int c = cb + e;
-      double ds = 0.0, gs = 0.0;
+      double ds = 0.0, gs = 0.0, bs = 0.0;
 #pragma unroll
       for (int f = 0; f < WR; ++f)
 #pragma unroll
@@ -326,18 +330,23 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
           if (use_cg) z += tcg * gv[e][f][r];
           if (Vkp1) Vkp1[row * ldv + col0 + 16 * c + m16] = z;
           if (want_dot) {
-            const double g = (double)gv[e][f][r];
-            ds += g * (double)(a.dot_y ? y : z);
+            const double g = (double)(pair ? vk[e][f][r] : gv[e][f][r]);
+            const double q = (double)(a.dot_y ? y : z);
+            ds += g * q;
             if (want_gg) gs += g * g;
+            if (want_b) bs += (double)z * q;
           }
         }
       ds += __shfl_xor(ds, 16, 64);
       ds += __shfl_xor(ds, 32, 64);
       gs += __shfl_xor(gs, 16, 64);
       gs += __shfl_xor(gs, 32, 64);
+      bs += __shfl_xor(bs, 16, 64);
+      bs += __shfl_xor(bs, 32, 64);
       if (kq == 0) {
         red[0][w][16 * c + m16] = ds;
         red[1][w][16 * c + m16] = gs;
+        red[2][w][16 * c + m16] = bs;
       }
     }
   }
@@ -349,6 +358,10 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
     if (want_gg) {
       const double g2 = red[1][0][col] + red[1][1][col] + red[1][2][col] + red[1][3][col];
       a.part[((int64_t)a.slot_gg * a.ntile + tm) * ldv + col0 + col] = g2;
+    }
+    if (want_b) {
+      const double b2 = red[2][0][col] + red[2][1][col] + red[2][2][col] + red[2][3][col];
+      a.part[((int64_t)a.slot_b * a.ntile + tm) * ldv + col0 + col] = b2;
     }
   }
 }
@@ -382,7 +395,7 @@ __global__ __launch_bounds__(256) void dense_step_split_kernel(DenseStepArgs a) 
 // together.
 template <typename T>
 __global__ __launch_bounds__(256) void dense_split_epilogue_kernel(DenseStepArgs a) {
-  __shared__ double red[2][4][64];
+  __shared__ double red[3][4][64];
   const int tp = blockIdx.x, tid = threadIdx.x, pl = tid & 63, rq = tid >> 6;
   const int64_t ldv = a.ldv, col = (int64_t)blockIdx.y * 64 + pl;
   const int64_t pstride = (int64_t)a.ntile * 64 * ldv;
@@ -394,6 +407,7 @@ __global__ __launch_bounds__(256) void dense_split_epilogue_kernel(DenseStepArgs
   const T tc1 = (T)a.c1, tcw = (T)a.cw;
   const bool use_m1 = (a.cw != 0.0) && Vkm1;
   const bool want_dot = a.slot >= 0, want_gg = a.slot_gg >= 0;
+  const bool pair = a.pair != 0, want_b = pair && a.slot_b >= 0;
   const bool use_cg = a.cg != nullptr;
   const T tcg = use_cg ? (T)a.cg[0] : T(0);
   int64_t off[4];
@@ -410,23 +424,35 @@ __global__ __launch_bounds__(256) void dense_split_epilogue_kernel(DenseStepArgs
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] += pv[i];
   }
-  double ds = 0.0, gs = 0.0;
+  const bool use_g = use_cg || (want_dot && !pair);
+  double ds = 0.0, gs = 0.0, bs = 0.0;
+  // operands of every row before the first store (V_{k+1} may overwrite V_{k-1})
+  T vk[4], vm[4], gv[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    vk[i] = Vk[off[i]];
+    vm[i] = use_m1 ? Vkm1[off[i]] : T(0);
+    gv[i] = use_g ? G[off[i]] : vk[i];
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const T y = ta * acc[i];
-    T z = tc1 * y + tb * Vk[off[i]];
-    if (use_m1) z += tcw * Vkm1[off[i]];
-    if (use_cg) z += tcg * G[off[i]];
+    T z = tc1 * y + tb * vk[i];
+    if (use_m1) z += tcw * vm[i];
+    if (use_cg) z += tcg * gv[i];
     if (Vkp1) Vkp1[off[i]] = z;
     if (want_dot) {
-      const T g = G[off[i]];
-      ds += (double)g * (double)(a.dot_y ? y : z);
-      if (want_gg) gs += (double)g * (double)g;
+      const double g = (double)(pair ? vk[i] : gv[i]);
+      const double q = (double)(a.dot_y ? y : z);
+      ds += g * q;
+      if (want_gg) gs += g * g;
+      if (want_b) bs += (double)z * q;
     }
   }
   if (!want_dot) return;
   red[0][rq][pl] = ds;
   red[1][rq][pl] = gs;
+  red[2][rq][pl] = bs;
   __syncthreads();
   if (rq == 0) {
     const double s0 = red[0][0][pl] + red[0][1][pl] + red[0][2][pl] + red[0][3][pl];
@@ -434,6 +460,10 @@ __global__ __launch_bounds__(256) void dense_split_epilogue_kernel(DenseStepArgs
     if (want_gg) {
       const double s1 = red[1][0][pl] + red[1][1][pl] + red[1][2][pl] + red[1][3][pl];
       a.part[((int64_t)a.slot_gg * a.nptile + tp) * ldv + col] = s1;
+    }
+    if (want_b) {
+      const double s2 = red[2][0][pl] + red[2][1][pl] + red[2][2][pl] + red[2][3][pl];
+      a.part[((int64_t)a.slot_b * a.nptile + tp) * ldv + col] = s2;
     }
   }
 }

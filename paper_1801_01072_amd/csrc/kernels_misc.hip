@@ -466,6 +466,76 @@ hipError_t launch_trace_dense(const T *R, int64_t ldr, int64_t n, double *scal, 
 template hipError_t launch_trace_dense<double>(const double *, int64_t, int64_t, double *, hipStream_t);
 template hipError_t launch_trace_dense<float>(const float *, int64_t, int64_t, double *, hipStream_t);
 
+// Trace and symmetry in one pass over R (HBM-bound: every element is read
+// once).  A workgroup takes a 64 x 64 tile (bi, bj),
+// bi <= bj, and its mirror image, both read along rows; the tile is compared
+// with the mirror's transpose through LDS (rows padded by one element: no
+// bank conflicts down a column).  Diagonal tiles leave their part of the
+// trace in tmp[bi].
+template <typename T>
+__global__ __launch_bounds__(256) void dense_check_kernel(const T *__restrict__ R, int64_t ldr, int64_t n,
+                                                          double *__restrict__ tmp, int32_t *__restrict__ asym) {
+  __shared__ T tile[64][65];
+  const int64_t t = blockIdx.x;
+  int64_t bj = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
+  while (bj * (bj + 1) / 2 > t) --bj;
+  while ((bj + 1) * (bj + 2) / 2 <= t) ++bj;
+  const int64_t bi = t - bj * (bj + 1) / 2;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t r0 = 64 * bi, c0 = 64 * bj;
+  T x[16], y[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int64_t r = r0 + 16 * w + i, c = c0 + lane;  // (r, c) of the tile
+    x[i] = r < n && c < n ? R[r * ldr + c] : T(0);
+    const int64_t rm = c0 + 16 * w + i, cm = r0 + lane;  // of the mirror
+    y[i] = rm < n && cm < n ? R[rm * ldr + cm] : T(0);
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) tile[16 * w + i][lane] = x[i];
+  __syncthreads();
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (!(tile[lane][16 * w + i] == y[i])) bad = true;  // also where either is NaN
+  if (__any(bad) && lane == 0) atomicOr(asym, 1);
+  if (bi == bj && w == 0) {
+    const double d = wave_sum((double)tile[lane][lane]);
+    if (lane == 0) tmp[bi] = d;
+  }
+}
+
+__global__ __launch_bounds__(256) void dense_check_finish_kernel(const double *__restrict__ tmp, int32_t cnt,
+                                                                 double *__restrict__ scal,
+                                                                 int32_t *__restrict__ host_flag) {
+  __shared__ double red[4];
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < cnt; i += 256) acc += tmp[i];
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  scal[S_TRACE] = red[0] + red[1] + red[2] + red[3];
+  if (host_flag) {
+    *host_flag = *(const int32_t *)(scal + S_SYM);
+    __threadfence_system();
+  }
+}
+
+template <typename T>
+hipError_t launch_dense_check(const T *R, int64_t ldr, int64_t n, double *scal, int32_t *host_flag,
+                              hipStream_t st) {
+  // tile traces in the scratch tail of the scalar block (4096 doubles)
+  const int64_t nb = (n + 63) / 64;
+  if (n < 1 || nb > 4096) return hipErrorInvalidValue;
+  double *tmp = scal + 4096;
+  dense_check_kernel<T><<<(unsigned)(nb * (nb + 1) / 2), 256, 0, st>>>(R, ldr, n, tmp, (int32_t *)(scal + S_SYM));
+  dense_check_finish_kernel<<<1, 256, 0, st>>>(tmp, (int32_t)nb, scal, host_flag);
+  return hipGetLastError();
+}
+template hipError_t launch_dense_check<double>(const double *, int64_t, int64_t, double *, int32_t *, hipStream_t);
+template hipError_t launch_dense_check<float>(const float *, int64_t, int64_t, double *, int32_t *, hipStream_t);
+
 // CSR: diagonal entries found by a scan of each row, L lanes per row (L by
 // the mean row length, as in the power-method product) so that a row's
 // column indices are read together; per-block partials are combined by the
@@ -730,7 +800,7 @@ hipError_t launch_reduce_moments(const double *part, int32_t nslot, int32_t ntil
 // h_j and the mean/standard error.  Chebyshev: h_j = -sum_{k=0}^m alpha_k d_kj
 // (Clenshaw schedule: from g^T y_0, g^T y_2 and g^T g, see FINAL_CLENSHAW).
 // Taylor: h_j = ln(1/u) + u sum_{k=1}^m e_kj / k  (e_kj = g^T (R/u) C^k g).
-__device__ __forceinline__ void final_body(const double *__restrict__ d, double *__restrict__ scal,
+__device__ __forceinline__ void final_body(double *__restrict__ d, double *__restrict__ scal,
                                            int32_t method, int32_t m, int32_t s,
                                            double *__restrict__ h) {
   __shared__ double red[4];
@@ -745,6 +815,23 @@ __device__ __forceinline__ void final_body(const double *__restrict__ d, double 
       const double gg = d[(int64_t)(m + 1) * s + j];
       const double y2 = m >= 2 ? d[(int64_t)2 * s + j] : 0.0;
       v = -0.5 * (scal[S_ALPHA] * gg + d[j] - y2);
+    } else if (method == FINAL_CHEB_PAIRS) {
+      // d_w = 2 (half sum of slot w) - d_{w mod 2}, written back; eight slots
+      // loaded at a time, before the stores that would order later loads
+      const double d0 = d[j], d1 = d[(int64_t)s + j];
+      v = -(scal[S_ALPHA] * d0 + scal[S_ALPHA + 1] * d1);
+      for (int k = 2; k <= m; k += 8) {
+        double r[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r[e] = k + e <= m ? d[(int64_t)(k + e) * s + j] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (k + e > m) break;
+          const double dw = 2.0 * r[e] - ((e & 1) ? d1 : d0);
+          d[(int64_t)(k + e) * s + j] = dw;
+          v -= scal[S_ALPHA + k + e] * dw;
+        }
+      }
     } else if (method == 1) {
       v = 0.0;
       for (int k = 0; k <= m; ++k) v -= scal[S_ALPHA + k] * d[(int64_t)k * s + j];
@@ -776,12 +863,12 @@ __device__ __forceinline__ void final_body(const double *__restrict__ d, double 
   }
 }
 
-__global__ void final_kernel(const double *__restrict__ d, double *__restrict__ scal, int32_t method,
+__global__ void final_kernel(double *__restrict__ d, double *__restrict__ scal, int32_t method,
                              int32_t m, int32_t s, double *__restrict__ h) {
   final_body(d, scal, method, m, s, h);
 }
 
-hipError_t launch_final(const double *d, double *scal, int32_t method, int32_t m, int32_t s,
+hipError_t launch_final(double *d, double *scal, int32_t method, int32_t m, int32_t s,
                         double *h, hipStream_t st) {
   final_kernel<<<1, 256, 0, st>>>(d, scal, method, m, s, h);
   return hipGetLastError();
@@ -1014,13 +1101,13 @@ hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double
   return hipGetLastError();
 }
 
-__global__ void batch_final_kernel(const BatchMat *__restrict__ mats, const double *d,
+__global__ void batch_final_kernel(const BatchMat *__restrict__ mats, double *d,
                                    int32_t method, int32_t m, int32_t s, double *h) {
   const BatchMat &M = mats[blockIdx.x];
   final_body(d + M.doff, M.scal, method, m, s, h + M.hoff);
 }
 
-hipError_t launch_batch_final(const BatchMat *mats, int32_t count, const double *d, int32_t method,
+hipError_t launch_batch_final(const BatchMat *mats, int32_t count, double *d, int32_t method,
                               int32_t m, int32_t s, double *h, hipStream_t st) {
   batch_final_kernel<<<(unsigned)count, 256, 0, st>>>(mats, d, method, m, s, h);
   return hipGetLastError();
