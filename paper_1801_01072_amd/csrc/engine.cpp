@@ -96,12 +96,12 @@ bool step_pairs_enabled(const char *name) {
   return !(e && e[0] == '0');
 }
 
-// Recurrence steps per tridiagonal launch: ENT_TRI_FUSE (1 = one step per
-// launch, at most kTriMaxFuse), else the most.
-constexpr int32_t kTriFuseDefault = ent::kTriMaxFuse;
-int32_t tri_fuse_steps() {
+// Recurrence steps (moments) per tridiagonal launch: ENT_TRI_FUSE (1 = one
+// product per launch, at most kTriMaxFuse), else as many as kTriMaxFuse
+// products give (two each with dots in pairs).
+int32_t tri_fuse_steps(bool pairs) {
   const char *e = std::getenv("ENT_TRI_FUSE");
-  if (!e || !*e) return kTriFuseDefault;
+  if (!e || !*e) return (pairs ? 2 : 1) * ent::kTriMaxFuse;
   const int v = std::atoi(e);
   return v < 1 ? 1 : (v > ent::kTriMaxFuse ? ent::kTriMaxFuse : v);
 }
@@ -671,21 +671,29 @@ ent_status enqueue_power_split(const uint16_t *hi, const uint16_t *lo, int64_t n
 // Validate a CSR structure on the device before any kernel dereferences its
 // indices (one synchronisation).  Uses the first 256 bytes of the workspace.
 // With hbw non-null, also measures the half-bandwidth max |col - row| (after
-// the structure check, in the same synchronisation).
+// the structure check, in the same synchronisation).  short_rows: also
+// whether R differs from its transpose (*asym; see launch_validate_csr_rows).
 ent_status check_csr(const ent_matrix *R, void *scratch, hipStream_t st, int32_t *hbw = nullptr,
-                     bool short_rows = false) {
+                     bool short_rows = false, int32_t *asym = nullptr) {
   if (R->layout != ENT_CSR) return ENT_OK;
   int32_t *flag = (int32_t *)scratch;
-  int32_t h[2] = {0, 0};
-  HIP_TRY(ent::launch_zero(flag, 2 * sizeof(int32_t), st));
+  int32_t h[3] = {0, 0, 0};
+  HIP_TRY(ent::launch_zero(flag, 3 * sizeof(int32_t), st));
   if (hbw && short_rows) {
-    // a few entries per row: the check and the half-bandwidth in one pass
-    HIP_TRY(ent::launch_validate_csr_rows(R->row_ptr, R->col_idx, R->n, R->nnz, flag, st));
-    HIP_TRY(hipMemcpyAsync(h, flag, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    // a few entries per row: the check, the half-bandwidth and the comparison
+    // with the transpose in one pass
+    if (R->dtype == ENT_STORE_F64)
+      HIP_TRY(ent::launch_validate_csr_rows<double>(R->row_ptr, R->col_idx, asym ? (const double *)R->values : nullptr,
+                                                    R->n, R->nnz, flag, st));
+    else
+      HIP_TRY(ent::launch_validate_csr_rows<float>(R->row_ptr, R->col_idx, asym ? (const float *)R->values : nullptr,
+                                                   R->n, R->nnz, flag, st));
+    HIP_TRY(hipMemcpyAsync(h, flag, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (h[0]) return fail(ENT_EINVAL, "invalid CSR structure (row_ptr must start at 0, be non-decreasing "
                                       "and end at nnz; column indices must lie in [0, n))");
     *hbw = h[1];
+    if (asym) *asym = h[2];
     return ENT_OK;
   }
   HIP_TRY(ent::launch_validate_csr(R->row_ptr, R->col_idx, R->n, R->nnz, flag, st));
@@ -769,6 +777,14 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     if (r0 != ENT_OK) return r0;
   }
 
+  // Clenshaw (Algorithm 5): slots 0..m hold g^T y_k, slot m+1 holds g^T g
+  const bool clenshaw = method == ENT_CHEBYSHEV && (o.flags & ENT_FLAG_CLENSHAW);
+  // dots in pairs halve the products, for a symmetric R only; whether R is
+  // one is known below (tridiagonal: with the structure check; else from a
+  // pass over R whose answer is read before the recurrence)
+  bool pairs = !clenshaw && (!dense || n <= kDenseCheckMaxN) &&
+               recurrence_products(method, m, true) < recurrence_products(method, m, false);
+
   // CSR: validate the structure, and serve a matrix whose entries all lie
   // within one of the diagonal with the tridiagonal step kernel, within 16
   // with the banded step kernel
@@ -786,9 +802,11 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     // at most three entries per row (duplicates aside) may be tridiagonal
     const bool maybe_tri = !(o.flags & (ENT_FLAG_CSR_GENERAL | ENT_FLAG_CSR_BANDED)) && R->nnz <= 3 * n;
     int32_t hbw = 0;
-    rc0 = check_csr(R, ws.ptr(), st, (want || maybe_tri) ? &hbw : nullptr, maybe_tri);
+    int32_t differs = 0;
+    rc0 = check_csr(R, ws.ptr(), st, (want || maybe_tri) ? &hbw : nullptr, maybe_tri, pairs ? &differs : nullptr);
     if (rc0 != ENT_OK) return rc0;
     tri = maybe_tri && hbw <= 1;
+    if (tri) pairs = pairs && differs == 0;
     if (want && !tri) hp = ent::band_half_width_padded(hbw);
     if (hp > 0 && (double)(16 + 2 * hp) * sizeof(T) > csr_row && !forced) hp = 0;
   }
@@ -807,8 +825,6 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   // per-probe dot partials: one per row tile (64 rows), or per 16 rows when
   // the split-K epilogue forms them
   const int32_t npart = ksplit > 1 ? (int32_t)(n_pad / 16) : ntile;
-  // Clenshaw (Algorithm 5): slots 0..m hold g^T y_k, slot m+1 holds g^T g
-  const bool clenshaw = method == ENT_CHEBYSHEV && (o.flags & ENT_FLAG_CLENSHAW);
   const int32_t nslot = m + 1 + (clenshaw ? 1 : 0);
   const bool rad = o.probe_dist == ENT_RADEMACHER;
   const bool use_power = !(o.u_fixed > 0);
@@ -825,11 +841,11 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   DegreeStages *stg = (hook && hook->stages && hook->stages->count > 0 && method == ENT_CHEBYSHEV && !clenshaw)
                           ? hook->stages : nullptr;
   bool band_pairs = banded && sizeof(T) == 4 && nsteps_all >= 2 && !stg && step_pairs_enabled("ENT_BAND_PAIRS");
-  // tridiagonal R: up to kTriMaxFuse steps per launch (both precisions)
-  const int32_t tri_nf = tri ? tri_fuse_steps() : 1;
+  // tridiagonal R: up to kTriMaxFuse products per launch (both precisions)
+  const int32_t tri_nf = tri ? tri_fuse_steps(pairs) : 1;
   bool tri_fused = tri && nsteps_all >= 2 && tri_nf >= 2 && !stg;
-  // all steps in one launch from the probe block: its two outputs are the
-  // only V blocks (Clenshaw starts from two zero blocks)
+  // all steps in one launch from the probe block: nothing is stored
+  // (Clenshaw starts from two zero blocks)
   const bool tri_one_launch = tri_fused && !clenshaw && nsteps_all <= tri_nf;
   T *VC = nullptr, *VD = nullptr, *tprep = nullptr;
   double *ttmp = nullptr;
@@ -856,8 +872,10 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     if (need_copy) cv.add(&Rc, (size_t)n * ldc);
     if (dense || !rad) cv.add(&G, (size_t)n_pad * ldb);
     if (!dense && rad) cv.add(&signs, (size_t)n_pad * (ldv / 32));
-    cv.add(&VA, (size_t)n_pad * ldb);
-    cv.add(&VB, (size_t)n_pad * ldb);
+    if (!(tri_fused && tri_one_launch)) {
+      cv.add(&VA, (size_t)n_pad * ldb);
+      cv.add(&VB, (size_t)n_pad * ldb);
+    }
     if (band_pairs || (tri_fused && !tri_one_launch)) {
       cv.add(&VC, (size_t)n_pad * ldb);
       cv.add(&VD, (size_t)n_pad * ldb);
@@ -892,13 +910,10 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   // trace check (or the trace that normalises R)
   const bool normalize = (o.flags & ENT_FLAG_NORMALIZE) != 0;
   const bool check_trace = !(o.flags & ENT_FLAG_SKIP_TRACE_CHECK) && !normalize;
-  // dots in pairs halve the products, for a symmetric R only: whether R is
-  // one comes with the trace, from one pass over R
-  bool pairs = dense && !clenshaw && n <= kDenseCheckMaxN &&
-               recurrence_products(method, m, true) < recurrence_products(method, m, false);
   DeviceAnswer asym;
-  if (pairs) {
-    asym.attach(ws, scal + ent::S_SYM);
+  const bool ask = pairs && !tri;
+  if (ask) asym.attach(ws, scal + ent::S_SYM);
+  if (pairs && dense) {  // with the trace, from one pass over R
     if (R->dtype == ENT_STORE_F64)
       HIP_TRY(ent::launch_dense_check<double>((const double *)R->values, R->ld, n, scal, asym.word, st));
     else
@@ -934,13 +949,23 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     Rt = Rc;
     ldr = ldc;
   }
-  if (banded)
+  if (banded) {
     HIP_TRY(ent::launch_band_pack<T>(R->row_ptr, R->col_idx, (const T *)R->values, n, hp, band, st));
-  else if (tri)
+    if (ask) HIP_TRY(ent::launch_band_check<T>(band, n, hp, (int32_t *)(scal + ent::S_SYM), asym.word, st));
+  } else if (tri)
     HIP_TRY(ent::launch_tri_pack<T>(R->row_ptr, R->col_idx, (const T *)R->values, n, trid, ttmp,
                                     (check_trace || normalize) ? scal + ent::S_TRACE : nullptr, st));
-  else if (!dense)
+  else if (!dense) {
     HIP_TRY(ent::launch_csr_chunk_window(R->row_ptr, R->col_idx, n, ch, cwin, st));
+    if (ask)
+      HIP_TRY(ent::launch_csr_check<T>(R->row_ptr, R->col_idx, (const T *)R->values, n,
+                                       (int32_t *)(scal + ent::S_SYM), (int64_t *)(scal + ent::S_SYM_NET), asym.word,
+                                       st));
+  }
+  if (ask && !dense) {
+    rc = asym.mark(st);
+    if (rc != ENT_OK) return rc;
+  }
   // probes
   if (dense || !rad)
     HIP_TRY(ent::launch_probe_gen<T>(G, nullptr, op.probe_rows > 0 ? op.probe_rows : n, n_pad, s, ldb,
@@ -963,7 +988,7 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   if (tprep) HIP_TRY(ent::launch_tri_prepare<T>(trid, scal, n, tprep, st));
 
   // recurrence
-  if (pairs) {
+  if (ask) {
     int32_t differs = 0;
     rc = asym.read(st, &differs);
     if (rc != ENT_OK) return rc;
@@ -1004,15 +1029,25 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     prev_mark = e;
   };
   if (band_pairs || tri_fused) {
-    // banded: steps k, k + 1 in one launch, the last step of an odd count
-    // alone; tridiagonal: launches of up to tri_nf steps
+    // products of each launch.  Banded: steps k, k + 1 together, the last of
+    // an odd count alone.  Tridiagonal: the moments are dealt to launches of up
+    // to tri_nf, and a launch runs the products its moments still lack (with
+    // dots in pairs one product gives two).
     std::vector<int32_t> sizes;
     if (tri_fused) {
-      sizes = fuse_split(nsteps, tri_nf);
+      const std::vector<int32_t> moments = fuse_split(nsteps_all, tri_nf);
+      pe.steps_fused = moments[0];
+      int32_t upto = 0, done = 0;
+      for (const int32_t len : moments) {
+        upto += len;
+        const int32_t products = pairs ? (upto + 1) / 2 : upto;
+        if (products > done) sizes.push_back(products - done);
+        done = products;
+      }
     } else {
       for (int32_t k = 0; k < nsteps; k += 2) sizes.push_back(k + 1 < nsteps ? 2 : 1);
+      pe.steps_fused = sizes[0];
     }
-    pe.steps_fused = sizes[0];
     T *pool[4] = {VA, VB, VC, VD};
     auto free_buf = [&](const void *x, const void *y, const void *z) -> T * {
       for (T *b : pool)
@@ -1027,19 +1062,21 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
         StepScalars qs[ent::kTriMaxFuse];
         for (int32_t j = 0; j < len; ++j) qs[j] = step_scalars(k + j);
         const bool last_write = qs[len - 1].write;
-        T *outA = free_buf(Vk, Vkm1, nullptr);
-        T *outB = free_buf(Vk, Vkm1, outA);
+        // the last launch's results are read by nothing
+        T *outA = last_write ? free_buf(Vk, Vkm1, nullptr) : nullptr;
+        T *outB = last_write ? free_buf(Vk, Vkm1, outA) : nullptr;
         const int e0 = pe.mark();
         if (tri_fused) {
           ent::TriFusedArgs ta{};
           ta.diag = trid; ta.prep = tprep; ta.n = n; ta.ldv = ldv; ta.ldb = ldb; ta.s = s;
           ta.Vk = Vk; ta.Vkm1 = q.cw != 0.0 ? Vkm1 : nullptr;
-          ta.VoutA = outA; ta.VoutB = last_write ? outB : nullptr;
+          ta.VoutA = outA; ta.VoutB = outB; ta.pair = pairs;
           ta.signs = rad ? signs : nullptr; ta.G = rad ? nullptr : G;
           ta.scal = scal; ta.part = part; ta.nblk = ntile; ta.slot_gg = q.slot_gg;
           for (int32_t j = 0; j < len; ++j) {
             ta.c1[j] = qs[j].c1; ta.c2[j] = qs[j].c2; ta.cw[j] = qs[j].cw;
-            ta.dot_y[j] = qs[j].dot_y; ta.slot[j] = qs[j].slot; ta.cg[j] = qs[j].cg;
+            ta.dot_y[j] = qs[j].dot_y; ta.slot[j] = qs[j].slot; ta.slot_b[j] = qs[j].slot_b;
+            ta.cg[j] = qs[j].cg;
           }
           HIP_TRY(ent::launch_tri_fused<T>(ta, len, st));
         } else {
@@ -1050,10 +1087,10 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
           pa.scal = scal; pa.part = part; pa.nwave = ntile; pa.slot_gg = q.slot_gg;
           for (int32_t j = 0; j < 2; ++j) {
             pa.c1[j] = qs[j].c1; pa.c2[j] = qs[j].c2; pa.cw[j] = qs[j].cw;
-            pa.dot_y[j] = qs[j].dot_y; pa.slot[j] = qs[j].slot; pa.cg[j] = qs[j].cg;
+            pa.dot_y[j] = qs[j].dot_y; pa.slot[j] = qs[j].slot; pa.slot_b[j] = qs[j].slot_b;
+            pa.cg[j] = qs[j].cg;
           }
-          pa.VoutA = outA;
-          pa.VoutB = last_write ? outB : nullptr;
+          pa.VoutA = outA; pa.VoutB = outB; pa.pair = pairs;
           HIP_TRY(ent::launch_band_pair(pa, hp, st));
         }
         const int e1 = pe.mark();
@@ -1069,7 +1106,10 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
         a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
         a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nblk = ntile; a.cg = q.cg;
+        a.pair = pairs; a.slot_b = q.slot_b;
         HIP_TRY(ent::launch_tri_step<T>(a, st));
+        Vkm1 = Vk;
+        Vk = (T *)a.Vkp1;
         k += 1;
       } else {
         ent::BandStepArgs a{};
@@ -1079,6 +1119,7 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
         a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
         a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nwave = ntile; a.cg = q.cg;
+        a.pair = pairs; a.slot_b = q.slot_b;
         HIP_TRY(ent::launch_band_step<T>(a, hp, st));
         k += 1;
       }
@@ -1118,7 +1159,7 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
         a.Vk = Vk; a.Vkm1 = Vm; a.Vkp1 = Vw;
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
         a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
-        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nwave = ntile; a.cg = q.cg;
+        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nwave = ntile; a.cg = q.cg; a.pair = pairs; a.slot_b = q.slot_b;
         HIP_TRY(ent::launch_band_step<T>(a, hp, st));
       } else if (tri) {
         ent::TriStepArgs a{};
@@ -1126,7 +1167,7 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
         a.Vk = Vk; a.Vkm1 = Vm; a.Vkp1 = Vw;
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
         a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
-        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nblk = ntile; a.cg = q.cg;
+        a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nblk = ntile; a.cg = q.cg; a.pair = pairs; a.slot_b = q.slot_b;
         HIP_TRY(ent::launch_tri_step<T>(a, st));
       } else {
         ent::CsrStepArgs a{};
@@ -1135,7 +1176,7 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
         a.signs = rad ? signs : nullptr; a.G = rad ? nullptr : G;
         a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
         a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.nblk = ntile; a.win = cwin;
-        a.cg = q.cg; a.s = s;
+        a.cg = q.cg; a.pair = pairs; a.slot_b = q.slot_b; a.s = s;
         HIP_TRY(ent::launch_csr_step<T>(a, st));
       }
       if (clenshaw || method == ENT_CHEBYSHEV) Vkm1 = Vk;

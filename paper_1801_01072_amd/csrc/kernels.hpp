@@ -24,6 +24,7 @@ enum ScalarSlot {
   S_ENT = 8,    // estimate
   S_SE = 9,     // standard error
   S_SYM = 10,   // int32: nonzero if R differs from its transpose somewhere
+  S_SYM_NET = 11,  // int64 scratch of the CSR comparison
   S_ALPHA = 16  // alpha_0 .. alpha_m (Chebyshev) follow
 };
 
@@ -96,6 +97,7 @@ struct CsrStepArgs {
   const double *cg;     // device scalar: z += (*cg) g (Clenshaw's alpha_k term); null: none
   int32_t s;            // probes in use (<= ldv): columns past s are neither read
                         // nor written, and their dot partials are zero; 0: ldv
+  int32_t pair, slot_b; // dots in pairs, as in DenseStepArgs (no g, no cg)
 };
 
 // Per-matrix descriptor of a batch (device resident).  Offsets are in
@@ -186,8 +188,23 @@ hipError_t launch_validate_csr(const int64_t *rp, const int32_t *ci, int64_t n, 
 // The same check and the half-bandwidth max |col - row| (into flag[1], which
 // must start at 0; meaningful only if flag[0] stays 0) in one pass, one row
 // per thread: for short rows (at most a few entries each on average).
-hipError_t launch_validate_csr_rows(const int64_t *rp, const int32_t *ci, int64_t n, int64_t nnz,
+// val non-null: flag[2] (must start at 0) is set unless every off-diagonal
+// entry (r, c) has exactly one entry (c, r) of the same value; rows of more
+// than 64 entries are not searched and set it.
+template <typename T>
+hipError_t launch_validate_csr_rows(const int64_t *rp, const int32_t *ci, const T *val, int64_t n, int64_t nnz,
                                     int32_t *flag, hipStream_t st);
+// Whether a validated CSR R with strictly ascending columns in every row
+// equals its transpose: *asym (must start at 0) is set where it does not, or
+// where a row's columns do not ascend.  count (one int64, must start at 0) is
+// scratch.  host_flag (pinned host memory, may be null) receives *asym.
+template <typename T>
+hipError_t launch_csr_check(const int64_t *rp, const int32_t *ci, const T *val, int64_t n, int32_t *asym,
+                            int64_t *count, int32_t *host_flag, hipStream_t st);
+
+// *flag |= (*count != 0) (count may be null), then *host_flag = *flag (pinned
+// host memory; null: not stored).
+hipError_t launch_publish_flag(int32_t *flag, const int64_t *count, int32_t *host_flag, hipStream_t st);
 
 // ---- conversion --------------------------------------------------------------
 template <typename Tin, typename Tout>
@@ -250,14 +267,15 @@ struct TriStepArgs {
   double *part;        // partials [slot][block][ldv]
   int32_t nblk;        // workgroups of the grid (partial stride), from tri_step_blocks
   const double *cg;    // device scalar: z += (*cg) g (Clenshaw's alpha_k term); null: none
+  int32_t pair, slot_b; // dots in pairs, as in DenseStepArgs (no g, no cg)
 };
 int32_t tri_step_blocks(int64_t n, int32_t s, int32_t fp64);
 // nf consecutive recurrence steps in one pass (2 <= nf <= kTriMaxFuse).
 // Step 0 reads V_k (null: sign block) and V_{k-1} (null with cw[0] != 0:
-// sign block); only the results of steps nf - 2 (VoutA) and nf - 1 (VoutB;
-// null: no write) are stored; the outputs may not alias the inputs; row
+// sign block); only the results of steps nf - 2 (VoutA) and nf - 1 (VoutB)
+// are stored (null: no write); the outputs may not alias the inputs; row
 // strides as in TriStepArgs; per-step scalars indexed by step, slot_gg for
-// step 0.
+// step 0; pair as in DenseStepArgs (slot_b[j] < 0: none).
 constexpr int kTriMaxFuse = 10;
 struct TriFusedArgs {
   const void *diag;
@@ -274,6 +292,8 @@ struct TriFusedArgs {
   double c1[kTriMaxFuse], c2[kTriMaxFuse], cw[kTriMaxFuse];
   int32_t dot_y[kTriMaxFuse];
   int32_t slot[kTriMaxFuse];
+  int32_t slot_b[kTriMaxFuse];
+  int32_t pair;
   int32_t slot_gg;
   const double *cg[kTriMaxFuse];
   double *part;
@@ -305,8 +325,9 @@ hipError_t launch_tri_step(const TriStepArgs &a, hipStream_t st);
 
 // ---- banded CSR (every entry within HP of the diagonal) -----------------------
 // Half-bandwidth max |col - row| of a validated CSR matrix into out[0] (which
-// must start at 0); the padded half-bandwidth (4, 8 or 16) the banded step
-// serves it with, or 0 if it is wider.
+// must start at 0; beyond 16, where the banded kernels end, some value past
+// 16); the padded half-bandwidth (4, 8 or 16) the banded step serves it with,
+// or 0 if it is wider.
 hipError_t launch_csr_half_bandwidth(const int64_t *rp, const int32_t *ci, int64_t n, int32_t *out,
                                      hipStream_t st);
 int32_t band_half_width_padded(int32_t hbw);
@@ -315,6 +336,11 @@ size_t band_pack_elems(int64_t n, int32_t hp);
 template <typename T>
 hipError_t launch_band_pack(const int64_t *rp, const int32_t *ci, const T *val, int64_t n, int32_t hp,
                             T *band, hipStream_t st);
+// Whether the slabs hold a matrix equal to its transpose: *asym (must start at
+// 0) is set where they do not; host_flag as in launch_csr_check.
+template <typename T>
+hipError_t launch_band_check(const T *band, int64_t n, int32_t hp, int32_t *asym, int32_t *host_flag,
+                             hipStream_t st);
 struct BandStepArgs {
   const void *band;    // slabs (launch_band_pack), element type T
   int64_t n;
@@ -332,6 +358,7 @@ struct BandStepArgs {
   double *part;        // partials [slot][wave][ldv]
   int32_t nwave;       // waves of the grid (partial stride), from band_step_waves
   const double *cg;    // device scalar: z += (*cg) g (Clenshaw's alpha_k term); null: none
+  int32_t pair, slot_b; // dots in pairs, as in DenseStepArgs (no g, no cg)
 };
 int32_t band_step_waves(int64_t n, int32_t hp, int32_t fp64);
 // Two consecutive recurrence steps in one pass (FP32): step A reads V_k
@@ -360,6 +387,7 @@ struct BandPairArgs {
   const double *cg[2];
   double *part;        // partials [slot][wave][ldv]
   int32_t nwave;       // waves of the grid (partial stride), from band_step_waves
+  int32_t pair, slot_b[2];
 };
 hipError_t launch_band_pair(const BandPairArgs &a, int32_t hp, hipStream_t st);
 // Power-method product on the slabs: the contract of launch_power_spmv, with

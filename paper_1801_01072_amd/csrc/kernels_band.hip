@@ -100,6 +100,8 @@ __global__ __launch_bounds__(256) void csr_half_bandwidth_kernel(const int64_t *
   const int64_t nb = (n + 15) / 16;
   int64_t m = 0;
   for (int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); b < nb; b += (int64_t)gridDim.x * 4) {
+    // wider than any banded kernel serves: no need to know by how much
+    if (__any(m > 16)) break;
     int64_t bnd[17];
     block_bounds(rp, 16 * b, n, lane, bnd);
     for (int64_t e = bnd[0] + lane; e < bnd[16]; e += 64) {
@@ -114,7 +116,10 @@ __global__ __launch_bounds__(256) void csr_half_bandwidth_kernel(const int64_t *
     const int32_t o = __shfl_xor(m32, off, 64);
     m32 = o > m32 ? o : m32;
   }
-  if (lane == 0 && m32 > 0) atomicMax(out, m32);
+  // the waves meet at one address (n = 200000: 12500 of them): only those that
+  // would raise it go there (an out-of-date value read here costs one of them
+  // its trip, never the maximum)
+  if (lane == 0 && m32 > *(volatile int32_t *)out) atomicMax(out, m32);
 }
 
 hipError_t launch_csr_half_bandwidth(const int64_t *rp, const int32_t *ci, int64_t n, int32_t *out,
@@ -200,6 +205,61 @@ template hipError_t launch_band_pack<float>(const int64_t *, const int32_t *, co
                                             float *, hipStream_t);
 template hipError_t launch_band_pack<double>(const int64_t *, const int32_t *, const double *, int64_t, int32_t,
                                              double *, hipStream_t);
+
+// ---------------------------------------------------------------------------
+// R = R^T on the slabs.  A workgroup takes four blocks (64 rows) and the block
+// behind them, copied into LDS as rows of K values (the block's lanes
+// hold them in MFMA order), and compares every entry right of the diagonal
+// with its mirror.  Reads each slab once (plus the overlap): HBM-bound.
+// ---------------------------------------------------------------------------
+template <typename T, int KS>
+__global__ __launch_bounds__(256) void band_check_kernel(const T *__restrict__ band, int64_t n,
+                                                         int32_t *__restrict__ asym) {
+  constexpr int HP = BandShape<KS>::HP, K = BandShape<KS>::K;
+  constexpr int NBK = 4;                 // blocks checked per workgroup pass
+  constexpr int ROWS = 16 * (NBK + 1);   // HP <= 16: one more block holds every mirror
+  __shared__ T rows[ROWS][K + 1];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t nb = (n + 15) / 16;
+  bool bad = false;
+  for (int64_t b0 = (int64_t)blockIdx.x * NBK; b0 < nb; b0 += (int64_t)gridDim.x * NBK) {
+    __syncthreads();
+    for (int i = w; i < NBK + 1; i += 4) {
+      const int64_t b = b0 + i;
+      T a[KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) a[k] = b < nb ? band[(64 * b + lane) * KS + k] : T(0);
+#pragma unroll
+      for (int k = 0; k < KS; ++k) rows[16 * i + (lane & 15)][4 * k + (lane >> 4)] = a[k];
+    }
+    __syncthreads();
+    // entry (r, r + d), d = 1..HP: column HP + i + d of row i of its block;
+    // its mirror (r + d, r): column HP + (r - 16 (block of r + d))
+    for (int t = threadIdx.x; t < 16 * NBK * HP; t += 256) {
+      const int r = t / HP, d = t % HP + 1;
+      const int rm = r + d;
+      const T x = rows[r][HP + (r & 15) + d], y = rows[rm][HP + r - (rm & ~15)];
+      if (!(x == y)) bad = true;
+    }
+  }
+  if (__any(bad) && lane == 0) atomicOr(asym, 1);
+}
+
+template <typename T>
+hipError_t launch_band_check(const T *band, int64_t n, int32_t hp, int32_t *asym, int32_t *host_flag,
+                             hipStream_t st) {
+  const int64_t nb = (n + 15) / 16, want = (nb + 3) / 4;
+  const unsigned blocks = (unsigned)(want < 4096 ? want : 4096);
+  switch (hp) {
+    case 4: band_check_kernel<T, 6><<<blocks, 256, 0, st>>>(band, n, asym); break;
+    case 8: band_check_kernel<T, 8><<<blocks, 256, 0, st>>>(band, n, asym); break;
+    case 16: band_check_kernel<T, 12><<<blocks, 256, 0, st>>>(band, n, asym); break;
+    default: return hipErrorInvalidValue;
+  }
+  return launch_publish_flag(asym, nullptr, host_flag, st);
+}
+template hipError_t launch_band_check<float>(const float *, int64_t, int32_t, int32_t *, int32_t *, hipStream_t);
+template hipError_t launch_band_check<double>(const double *, int64_t, int32_t, int32_t *, int32_t *, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Row pieces: lane (q, c) of a 64-probe chunk handles probes 4c .. 4c+3.
@@ -479,11 +539,15 @@ template hipError_t launch_power_band_fused<double>(const double *, int32_t, int
                                                     const double *, double *, double *, int32_t, int32_t,
                                                     hipStream_t);
 
+// Probe rows of a banded step: the Gaussian block, the sign bits, or none
+// (dots in pairs are taken with V_k).
+enum BandProbes { kProbeBlock = 0, kProbeSigns = 1, kProbePairs = 2 };
+
 // VKS: V_k is the sign block.  M1: no V_{k-1} term (0), V_{k-1} stored (1)
-// or the sign block (2).  GS: the probe rows come from the sign bits.  All
+// or the sign block (2).  PK: the probe rows' source (BandProbes).  All
 // three are compile-time choices, so a block's row loads issue together
 // rather than one branch and wait each.
-template <typename T, int KS, bool VKS, int M1, bool GS>
+template <typename T, int KS, bool VKS, int M1, int PK>
 __global__ __launch_bounds__(64 * kBandWaves) void band_step_kernel(BandStepArgs a) {
   typedef Mfma16<T> M;
   typedef typename M::v4 v4;
@@ -510,7 +574,7 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_step_kernel(BandStepArgs
   constexpr bool vk_signs = VKS;
   constexpr int m1 = M1;
   const bool gg = a.slot_gg >= 0;
-  constexpr bool g_signs = GS;
+  constexpr bool pair = PK == kProbePairs;
   const bool dot_y = a.dot_y != 0;
   const T ta = (T)a.scal[S_A];
   const T tb = (T)(a.c2 * a.scal[S_B]);
@@ -518,7 +582,7 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_step_kernel(BandStepArgs
   const bool use_cg = a.cg != nullptr;
   const T tcg = use_cg ? (T)a.cg[0] : T(0);
 
-  double ds[4] = {0.0, 0.0, 0.0, 0.0}, gs[4] = {0.0, 0.0, 0.0, 0.0};
+  double ds[4] = {0.0, 0.0, 0.0, 0.0}, gs[4] = {0.0, 0.0, 0.0, 0.0}, bs[4] = {0.0, 0.0, 0.0, 0.0};
   T win[WF][4];  // window fragments: V_k rows 4f + q, probes 4c .. 4c+3; the block's are 0 .. KS-1
   T an[KS];      // slab values of the next block
   if (b_beg < b_end) {
@@ -564,9 +628,9 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_step_kernel(BandStepArgs
 #pragma unroll
           for (int t = 0; t < 4; ++t) vm[r][t] = T(0);
         }
-        if constexpr (g_signs)
+        if constexpr (PK == kProbeSigns)
           sign4<T>(signs, row, nw, chunk0, c, gv[r]);
-        else
+        else if constexpr (PK == kProbeBlock)
           load4<T>(G, row, ldv, chunk0, c, gv[r]);
       }
       // Y_b = slab_b x window, one 16-probe tile per probe of the lane's four
@@ -594,11 +658,13 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_step_kernel(BandStepArgs
           const T y = ta * acc[t][r];
           T zz = tc1 * y + tb * xr[r][t];
           if (m1 != 0) zz += tcw * vm[r][t];
-          if (use_cg) zz += tcg * gv[r][t];
+          if (!pair && use_cg) zz += tcg * gv[r][t];
           z[t] = zz;
           if (live) {
-            ds[t] += (double)gv[r][t] * (double)(dot_y ? y : zz);
-            if (gg) gs[t] += (double)gv[r][t] * (double)gv[r][t];
+            const double g = (double)(pair ? xr[r][t] : gv[r][t]), dq = (double)(dot_y ? y : zz);
+            ds[t] += g * dq;
+            if (gg) gs[t] += g * g;
+            if (pair) bs[t] += (double)zz * dq;
           }
         }
         if (live && Vkp1) store4<T>(Vkp1, row, ldv, chunk0, c, z);
@@ -612,11 +678,16 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_step_kernel(BandStepArgs
     ds[t] += __shfl_xor(ds[t], 32, 64);
     gs[t] += __shfl_xor(gs[t], 16, 64);
     gs[t] += __shfl_xor(gs[t], 32, 64);
+    if (pair) {
+      bs[t] += __shfl_xor(bs[t], 16, 64);
+      bs[t] += __shfl_xor(bs[t], 32, 64);
+    }
   }
   if (q == 0) {
     const int64_t bidx = wv * ldv + chunk0 + 4 * c;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
+      if (pair && a.slot_b >= 0) a.part[(int64_t)a.slot_b * a.nwave * ldv + bidx + t] = bs[t];
       a.part[(int64_t)a.slot * a.nwave * ldv + bidx + t] = ds[t];
       if (gg) a.part[(int64_t)a.slot_gg * a.nwave * ldv + bidx + t] = gs[t];
     }
@@ -698,10 +769,10 @@ __device__ __forceinline__ void pair_own(const float *f0, const float *f1, const
 }
 
 // NP: probes per lane (4: 64-probe chunks; 2: 32-probe chunks, half the
-// per-lane state, the slabs read once per chunk).  GS: the probe rows come
-// from the sign bits (Rademacher), else from G; a compile-time choice, so the
-// four rows' loads of a block issue together instead of one branch each.
-template <int KS, int NP, bool VK_SIGNS, int M1A, bool GG, bool GS>
+// per-lane state, the slabs read once per chunk).  PK: the probe rows' source
+// (BandProbes); a compile-time choice, so the four rows' loads of a block
+// issue together instead of one branch each.
+template <int KS, int NP, bool VK_SIGNS, int M1A, bool GG, int PK>
 __global__ __launch_bounds__(64 * kBandWaves) void band_pair_kernel(BandPairArgs a) {
   typedef float T;
   typedef Mfma16<T> M;
@@ -727,16 +798,16 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_pair_kernel(BandPairArgs
   const uint32_t *__restrict__ signs = a.signs;
   T *__restrict__ VoutA = (T *)a.VoutA;
   T *__restrict__ VoutB = (T *)a.VoutB;
-  constexpr bool g_signs = GS;
+  constexpr bool pair = PK == kProbePairs;
   const T ta = (T)a.scal[S_A];
   const T tbA = (T)(a.c2[0] * a.scal[S_B]), tbB = (T)(a.c2[1] * a.scal[S_B]);
   const T c1A = (T)a.c1[0], c1B = (T)a.c1[1], cwA = (T)a.cw[0], cwB = (T)a.cw[1];
   const T cgA = a.cg[0] ? (T)a.cg[0][0] : T(0), cgB = a.cg[1] ? (T)a.cg[1][0] : T(0);
   const bool dyA = a.dot_y[0] != 0, dyB = a.dot_y[1] != 0;
 
-  double dA[NP], dB[NP], gs[NP];
+  double dA[NP], dB[NP], gs[NP], eA[NP], eB[NP];  // eA, eB: the second dots of a pair
 #pragma unroll
-  for (int t = 0; t < NP; ++t) dA[t] = dB[t] = gs[t] = 0.0;
+  for (int t = 0; t < NP; ++t) dA[t] = dB[t] = gs[t] = eA[t] = eB[t] = 0.0;
   if (b_beg < b_end) {
     const int64_t a_beg = b_beg - 1, a_end = b_end + 1;  // step A blocks [a_beg, a_end)
     T win[WF][NP];   // V_k fragments of step A's current block
@@ -800,9 +871,9 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_pair_kernel(BandPairArgs
           pair_load<NP>(Vkm1, rr, ldv, col0, vm[r]);
         else if (M1A == 2)
           pair_signs<NP>(signs, rr, nw, col0, vm[r]);
-        if constexpr (g_signs)
+        if constexpr (PK == kProbeSigns)
           pair_signs<NP>(signs, rr, nw, col0, gv[r]);
-        else
+        else if constexpr (PK == kProbeBlock)
           pair_load<NP>(G, rr, ldv, col0, gv[r]);
         // a row outside [0, n) keeps the (finite) values of row rr: its
         // results are zeroed below and it adds to no dot product
@@ -835,14 +906,16 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_pair_kernel(BandPairArgs
           const T y = ta * acc[t][r];
           T z = c1A * y + tbA * xr[r][t];
           if (M1A != 0) z += cwA * vm[r][t];
-          z += cgA * gv[r][t];
+          if (!pair) z += cgA * gv[r][t];
           za[r][t] = in ? z : T(0);
           if (own && in) {
-            dA[t] += (double)gv[r][t] * (double)(dyA ? y : z);
-            if (GG) gs[t] += (double)gv[r][t] * (double)gv[r][t];
+            const double g = (double)(pair ? xr[r][t] : gv[r][t]), dq = (double)(dyA ? y : z);
+            dA[t] += g * dq;
+            if (GG) gs[t] += g * g;
+            if (pair) eA[t] += (double)z * dq;
           }
         }
-        if (own && in) pair_store<NP>(VoutA, row, ldv, col0, za[r]);
+        if (own && in && VoutA) pair_store<NP>(VoutA, row, ldv, col0, za[r]);
       }
       // V_{k+1} of block b into the step-B window (fragment order)
 #pragma unroll
@@ -879,9 +952,13 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_pair_kernel(BandPairArgs
             const T y = ta * bcc[t][r];
             T z = c1B * y + tbB * zp[r][t];
             z += cwB * xp[r][t];
-            z += cgB * gp[r][t];
+            if (!pair) z += cgB * gp[r][t];
             z4[t] = z;
-            if (in) dB[t] += (double)gp[r][t] * (double)(dyB ? y : z);
+            if (in) {
+              const double dq = (double)(dyB ? y : z);
+              dB[t] += (double)(pair ? zp[r][t] : gp[r][t]) * dq;
+              if (pair) eB[t] += (double)z * dq;
+            }
           }
           if (in && VoutB) pair_store<NP>(VoutB, row, ldv, col0, z4);
         }
@@ -895,7 +972,7 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_pair_kernel(BandPairArgs
         for (int t = 0; t < NP; ++t) {
           zp[r][t] = za[r][t];
           xp[r][t] = xr[r][t];
-          gp[r][t] = gv[r][t];
+          if (!pair) gp[r][t] = gv[r][t];
         }
     }
   }
@@ -910,11 +987,19 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_pair_kernel(BandPairArgs
       gs[t] += __shfl_xor(gs[t], 16, 64);
       gs[t] += __shfl_xor(gs[t], 32, 64);
     }
+    if (pair) {
+      eA[t] += __shfl_xor(eA[t], 16, 64);
+      eA[t] += __shfl_xor(eA[t], 32, 64);
+      eB[t] += __shfl_xor(eB[t], 16, 64);
+      eB[t] += __shfl_xor(eB[t], 32, 64);
+    }
   }
   if (q == 0) {
     const int64_t bidx = wv * ldv + col0;
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
+      if (pair && a.slot_b[0] >= 0) a.part[(int64_t)a.slot_b[0] * a.nwave * ldv + bidx + t] = eA[t];
+      if (pair && a.slot_b[1] >= 0) a.part[(int64_t)a.slot_b[1] * a.nwave * ldv + bidx + t] = eB[t];
       a.part[(int64_t)a.slot[0] * a.nwave * ldv + bidx + t] = dA[t];
       a.part[(int64_t)a.slot[1] * a.nwave * ldv + bidx + t] = dB[t];
       if (GG) a.part[(int64_t)a.slot_gg * a.nwave * ldv + bidx + t] = gs[t];
@@ -926,10 +1011,12 @@ template <int KS, bool VK_SIGNS, int M1A, bool GG>
 static void band_pair_launch(const BandPairArgs &a, hipStream_t st) {
   constexpr int NP = kBandPairProbes;
   dim3 grid((unsigned)(a.nwave / kBandWaves), (unsigned)(a.ldv / (16 * NP)));
-  if (a.signs != nullptr && a.G == nullptr)
-    band_pair_kernel<KS, NP, VK_SIGNS, M1A, GG, true><<<grid, 64 * kBandWaves, 0, st>>>(a);
+  if (a.pair)
+    band_pair_kernel<KS, NP, VK_SIGNS, M1A, GG, kProbePairs><<<grid, 64 * kBandWaves, 0, st>>>(a);
+  else if (a.signs != nullptr && a.G == nullptr)
+    band_pair_kernel<KS, NP, VK_SIGNS, M1A, GG, kProbeSigns><<<grid, 64 * kBandWaves, 0, st>>>(a);
   else
-    band_pair_kernel<KS, NP, VK_SIGNS, M1A, GG, false><<<grid, 64 * kBandWaves, 0, st>>>(a);
+    band_pair_kernel<KS, NP, VK_SIGNS, M1A, GG, kProbeBlock><<<grid, 64 * kBandWaves, 0, st>>>(a);
 }
 
 template <int KS>
@@ -959,7 +1046,8 @@ static hipError_t band_pair_dispatch(const BandPairArgs &a, hipStream_t st) {
 }
 
 hipError_t launch_band_pair(const BandPairArgs &a, int32_t hp, hipStream_t st) {
-  if (a.nwave <= 0 || a.nwave % kBandWaves != 0 || a.ldv % 64 != 0 || !a.VoutA) return hipErrorInvalidValue;
+  if (a.nwave <= 0 || a.nwave % kBandWaves != 0 || a.ldv % 64 != 0 || (!a.VoutA && a.VoutB)) return hipErrorInvalidValue;
+  if (a.pair && (a.cg[0] || a.cg[1])) return hipErrorInvalidValue;
   if ((a.Vk == nullptr || (a.cw[0] != 0.0 && a.Vkm1 == nullptr)) && !a.signs) return hipErrorInvalidValue;
   if (a.G == nullptr && a.signs == nullptr) return hipErrorInvalidValue;
   // outputs must not alias the inputs (other waves read the input rows next
@@ -986,7 +1074,7 @@ static int32_t band_resident_blocks() {
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)band_step_kernel<T, KS, false, 1, true>,
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)band_step_kernel<T, KS, false, 1, kProbeSigns>,
                                                    64 * kBandWaves, 0) != hipSuccess || per_cu < 1)
     per_cu = 1;
   const int32_t r = (int32_t)(cus * per_cu);
@@ -1013,10 +1101,12 @@ int32_t band_step_waves(int64_t n, int32_t hp, int32_t fp64) {
 
 template <typename T, int KS, bool VKS, int M1>
 static hipError_t band_step_launch(const BandStepArgs &a, dim3 grid, hipStream_t st) {
-  if (a.signs != nullptr && a.G == nullptr)
-    band_step_kernel<T, KS, VKS, M1, true><<<grid, 64 * kBandWaves, 0, st>>>(a);
+  if (a.pair)
+    band_step_kernel<T, KS, VKS, M1, kProbePairs><<<grid, 64 * kBandWaves, 0, st>>>(a);
+  else if (a.signs != nullptr && a.G == nullptr)
+    band_step_kernel<T, KS, VKS, M1, kProbeSigns><<<grid, 64 * kBandWaves, 0, st>>>(a);
   else
-    band_step_kernel<T, KS, VKS, M1, false><<<grid, 64 * kBandWaves, 0, st>>>(a);
+    band_step_kernel<T, KS, VKS, M1, kProbeBlock><<<grid, 64 * kBandWaves, 0, st>>>(a);
   return hipGetLastError();
 }
 
@@ -1038,6 +1128,7 @@ hipError_t launch_band_step(const BandStepArgs &a, int32_t hp, hipStream_t st) {
   if (a.nwave <= 0 || a.nwave % kBandWaves != 0 || a.ldv % 64 != 0) return hipErrorInvalidValue;
   if ((a.Vk == nullptr || (a.cw != 0.0 && a.Vkm1 == nullptr)) && !a.signs) return hipErrorInvalidValue;
   if (a.G == nullptr && a.signs == nullptr) return hipErrorInvalidValue;
+  if (a.pair && a.cg) return hipErrorInvalidValue;
   dim3 grid((unsigned)(a.nwave / kBandWaves), (unsigned)(a.ldv / 64));
   switch (hp) {
     case 4: return band_step_dispatch<T, 6>(a, grid, st);

@@ -169,7 +169,8 @@ __device__ __forceinline__ T shfl_t(T v, int src) {
 
 // VK_SIGNS: V_k is the sign block.  M1: no V_{k-1} term (0), V_{k-1} stored
 // (1) or the sign block (2).  GG: also accumulate g.g (first Chebyshev step).
-template <typename T, bool VK_SIGNS, int M1, bool GG>
+// PAIR: dots in pairs (with V_k, and of the result: no probe rows are read).
+template <typename T, bool VK_SIGNS, int M1, bool GG, bool PAIR>
 __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a) {
   typedef CsrLanes<T> C;
   constexpr int P = C::P, L = C::L, RPW = C::RPW, CH = C::CH, ROWB = C::ROWB;
@@ -177,7 +178,7 @@ __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a)
   constexpr int JM = 10;  // rounds whose entries are loaded together
   constexpr bool use_win = !VK_SIGNS;  // a window of the sign block is not needed
   __shared__ __attribute__((aligned(16))) uint8_t wbuf[use_win ? 2 : 1][use_win ? C::WBYTES : 16];
-  __shared__ double red[2][kCsrWaves][64];
+  __shared__ double red[3][kCsrWaves][64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane / L;       // row of the wave's group
@@ -236,7 +237,9 @@ __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a)
     }
   };
 
-  double ds[P], gs[GG ? P : 1];
+  double ds[P], gs[GG ? P : 1], bs[PAIR ? P : 1];
+#pragma unroll
+  for (int e = 0; e < (PAIR ? P : 1); ++e) bs[e] = 0.0;
 #pragma unroll
   for (int e = 0; e < P; ++e) ds[e] = 0.0;
 #pragma unroll
@@ -293,10 +296,12 @@ __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a)
 #pragma unroll
       for (int e = 0; e < P; ++e) vm[e] = T(0);
     }
-    if (signs)
-      load_row<T, true>(nullptr, signs, rr, ldv, nw, chunk0, o, gv, pv);
-    else
-      load_row<T, false>(G, nullptr, rr, ldv, nw, chunk0, o, gv, pv);
+    if constexpr (!PAIR) {
+      if (signs)
+        load_row<T, true>(nullptr, signs, rr, ldv, nw, chunk0, o, gv, pv);
+      else
+        load_row<T, false>(G, nullptr, rr, ldv, nw, chunk0, o, gv, pv);
+    }
     // longest row of the wave: the number of gather rounds
     int mlen = len;
 #pragma unroll
@@ -351,10 +356,12 @@ __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a)
         const T y = ta * acc[e];
         T z = tc1 * y + tb * xr[e];
         if (use_m1) z += tcw * vm[e];
-        if (use_cg) z += tcg * gv[e];
+        if (!PAIR && use_cg) z += tcg * gv[e];
         zs[e] = z;
-        ds[e] += (double)gv[e] * (double)(a.dot_y ? y : z);
-        if (GG) gs[GG ? e : 0] += (double)gv[e] * (double)gv[e];
+        const double g = (double)(PAIR ? xr[e] : gv[e]), q = (double)(a.dot_y ? y : z);
+        ds[e] += g * q;
+        if (GG) gs[GG ? e : 0] += g * g;
+        if (PAIR) bs[PAIR ? e : 0] += (double)z * q;
       }
       zrow = r;
     }
@@ -368,6 +375,7 @@ __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a)
     if (!pv[e / VEC]) {
       ds[e] = 0.0;
       if (GG) gs[GG ? e : 0] = 0.0;
+      if (PAIR) bs[PAIR ? e : 0] = 0.0;
     }
   // per probe: sum over the wave's rows (lanes o, o+L, ...), then over waves
 #pragma unroll
@@ -376,6 +384,7 @@ __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a)
     for (int off = L; off < 64; off <<= 1) {
       ds[e] += __shfl_xor(ds[e], off, 64);
       if (GG) gs[GG ? e : 0] += __shfl_xor(gs[GG ? e : 0], off, 64);
+      if (PAIR) bs[PAIR ? e : 0] += __shfl_xor(bs[PAIR ? e : 0], off, 64);
     }
   }
   if (lane < L) {
@@ -383,6 +392,7 @@ __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a)
     for (int e = 0; e < P; ++e) {
       red[0][w][probe_of<T>(lane, e)] = ds[e];
       red[1][w][probe_of<T>(lane, e)] = GG ? gs[GG ? e : 0] : 0.0;
+      if (PAIR) red[2][w][probe_of<T>(lane, e)] = bs[PAIR ? e : 0];
     }
   }
   __syncthreads();
@@ -396,6 +406,12 @@ __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a)
     const int64_t bidx = (int64_t)blockIdx.x * ldv + chunk0 + lane;
     a.part[(int64_t)a.slot * a.nblk * ldv + bidx] = t0;
     if (GG) a.part[(int64_t)a.slot_gg * a.nblk * ldv + bidx] = t1;
+    if (PAIR && a.slot_b >= 0) {
+      double t2 = 0.0;
+#pragma unroll
+      for (int q = 0; q < kCsrWaves; ++q) t2 += red[2][q][lane];
+      a.part[(int64_t)a.slot_b * a.nblk * ldv + bidx] = t2;
+    }
   }
 }
 
@@ -406,7 +422,7 @@ __global__ __launch_bounds__(64 * kCsrWaves) void csr_step_kernel(CsrStepArgs a)
 // Each instance is launched with its own count; the partial-sum stride is
 // the largest count of any instance (csr_step_blocks), and the partials of
 // workgroups an instance does not launch stay zero.
-template <typename T, bool VK_SIGNS, int M1, bool GG>
+template <typename T, bool VK_SIGNS, int M1, bool GG, bool PAIR>
 static int32_t csr_instance_blocks() {
   static int32_t cache[64] = {};
   int dev = 0;
@@ -416,7 +432,7 @@ static int32_t csr_instance_blocks() {
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)csr_step_kernel<T, VK_SIGNS, M1, GG>,
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)csr_step_kernel<T, VK_SIGNS, M1, GG, PAIR>,
                                                    64 * kCsrWaves, 0) != hipSuccess || per_cu < 1)
     per_cu = 1;
   const int32_t r = (int32_t)(cus * per_cu);
@@ -426,9 +442,12 @@ static int32_t csr_instance_blocks() {
 
 template <typename T>
 static int32_t csr_resident_blocks() {
-  const int32_t c[] = {csr_instance_blocks<T, true, 0, true>(), csr_instance_blocks<T, false, 0, true>(),
-                       csr_instance_blocks<T, true, 0, false>(), csr_instance_blocks<T, false, 0, false>(),
-                       csr_instance_blocks<T, false, 1, false>(), csr_instance_blocks<T, false, 2, false>()};
+  const int32_t c[] = {csr_instance_blocks<T, true, 0, true, false>(), csr_instance_blocks<T, false, 0, true, false>(),
+                       csr_instance_blocks<T, true, 0, false, false>(), csr_instance_blocks<T, false, 0, false, false>(),
+                       csr_instance_blocks<T, false, 1, false, false>(), csr_instance_blocks<T, false, 2, false, false>(),
+                       csr_instance_blocks<T, true, 0, true, true>(), csr_instance_blocks<T, false, 0, true, true>(),
+                       csr_instance_blocks<T, true, 0, false, true>(), csr_instance_blocks<T, false, 0, false, true>(),
+                       csr_instance_blocks<T, false, 1, false, true>(), csr_instance_blocks<T, false, 2, false, true>()};
   int32_t r = 1;
   for (int32_t v : c) r = v > r ? v : r;
   return r;
@@ -442,11 +461,18 @@ int32_t csr_step_blocks(int64_t n, int32_t fp64) {
   return (int32_t)(groups < cap ? groups : cap);
 }
 
+template <typename T, bool VK_SIGNS, int M1, bool GG, bool PAIR>
+static void csr_step_launch_as(const CsrStepArgs &a, hipStream_t st) {
+  const int32_t inst = csr_instance_blocks<T, VK_SIGNS, M1, GG, PAIR>();
+  dim3 grid((unsigned)(a.nblk < inst ? a.nblk : inst), (unsigned)(a.ldv / 64));
+  csr_step_kernel<T, VK_SIGNS, M1, GG, PAIR><<<grid, 64 * kCsrWaves, 0, st>>>(a);
+}
 template <typename T, bool VK_SIGNS, int M1, bool GG>
 static void csr_step_launch(const CsrStepArgs &a, hipStream_t st) {
-  const int32_t inst = csr_instance_blocks<T, VK_SIGNS, M1, GG>();
-  dim3 grid((unsigned)(a.nblk < inst ? a.nblk : inst), (unsigned)(a.ldv / 64));
-  csr_step_kernel<T, VK_SIGNS, M1, GG><<<grid, 64 * kCsrWaves, 0, st>>>(a);
+  if (a.pair)
+    csr_step_launch_as<T, VK_SIGNS, M1, GG, true>(a, st);
+  else
+    csr_step_launch_as<T, VK_SIGNS, M1, GG, false>(a, st);
 }
 
 // The partial slots written by a launch must be zero beyond its grid (the
@@ -457,6 +483,7 @@ hipError_t launch_csr_step(const CsrStepArgs &a, hipStream_t st) {
   const int m1 = a.cw == 0.0 ? 0 : (a.Vkm1 == nullptr ? 2 : 1);
   const bool gg = a.slot_gg >= 0;
   if ((vk_signs || m1 == 2) && !a.signs) return hipErrorInvalidValue;
+  if (a.pair && a.cg) return hipErrorInvalidValue;
   if (gg) {
     if (m1 != 0) return hipErrorInvalidValue;  // g.g is taken on the first step only
     if (vk_signs)

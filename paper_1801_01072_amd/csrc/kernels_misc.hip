@@ -639,10 +639,22 @@ hipError_t launch_validate_csr(const int64_t *rp, const int32_t *ci, int64_t n, 
 // 0 <= rp[r] <= rp[r+1] <= nnz) hold for every row exactly when row_ptr is
 // valid, and a row's column indices are read only if its range lies in
 // [0, nnz), so the entries of a valid structure are each checked once.
+//
+// With val, also whether R equals its transpose: each off-diagonal entry
+// (r, c) needs exactly one entry (c, r) of the same value.  Row c is searched
+// from its first entry (short rows: a tridiagonal row has three, adjacent in
+// memory to the row's own); its range is checked before it is read, as row_ptr
+// is validated in the same pass.  A row c of more than kSymScan entries is not
+// searched (one long row met by every other would cost n^2 reads): the matrix
+// then counts as not symmetric.
+constexpr int64_t kSymScan = 64;
+
+template <typename T>
 __global__ __launch_bounds__(256) void validate_csr_rows_kernel(const int64_t *__restrict__ rp,
-                                                                const int32_t *__restrict__ ci, int64_t n,
+                                                                const int32_t *__restrict__ ci,
+                                                                const T *__restrict__ val, int64_t n,
                                                                 int64_t nnz, int32_t *__restrict__ flag) {
-  bool bad = false;
+  bool bad = false, asym = false;
   int64_t hb = 0;
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
     const int64_t a = rp[r], b = rp[r + 1];
@@ -657,10 +669,20 @@ __global__ __launch_bounds__(256) void validate_csr_rows_kernel(const int64_t *_
       } else {
         const int64_t d = c > r ? c - r : r - c;
         hb = d > hb ? d : hb;
+        if (val && d != 0 && !asym) {
+          const int64_t a2 = rp[c], b2 = rp[c + 1];
+          int found = 0;
+          if (a2 >= 0 && b2 <= nnz && b2 - a2 <= kSymScan) {
+            for (int64_t f = a2; f < b2; ++f)
+              if (ci[f] == r) found += val[f] == val[e] ? 1 : 2;
+          }
+          asym = found != 1;
+        }
       }
     }
   }
   if (bad) atomicOr(flag, 1);
+  if (__any(asym) && (threadIdx.x & 63) == 0) atomicOr(flag + 2, 1);
   // n < 2^31 (int32 column indices), so the half-bandwidth fits
   int32_t h = (int32_t)hb;
   for (int off = 32; off > 0; off >>= 1) {
@@ -670,13 +692,94 @@ __global__ __launch_bounds__(256) void validate_csr_rows_kernel(const int64_t *_
   if ((threadIdx.x & 63) == 0 && h > 0) atomicMax(flag + 1, h);
 }
 
-hipError_t launch_validate_csr_rows(const int64_t *rp, const int32_t *ci, int64_t n, int64_t nnz,
+template <typename T>
+hipError_t launch_validate_csr_rows(const int64_t *rp, const int32_t *ci, const T *val, int64_t n, int64_t nnz,
                                     int32_t *flag, hipStream_t st) {
   if (n < 1) return hipErrorInvalidValue;
   const int64_t b = (n + 255) / 256;
-  validate_csr_rows_kernel<<<(unsigned)(b < 4096 ? b : 4096), 256, 0, st>>>(rp, ci, n, nnz, flag);
+  validate_csr_rows_kernel<T><<<(unsigned)(b < 4096 ? b : 4096), 256, 0, st>>>(rp, ci, val, n, nnz, flag);
   return hipGetLastError();
 }
+template hipError_t launch_validate_csr_rows<double>(const int64_t *, const int32_t *, const double *, int64_t,
+                                                     int64_t, int32_t *, hipStream_t);
+template hipError_t launch_validate_csr_rows<float>(const int64_t *, const int32_t *, const float *, int64_t,
+                                                    int64_t, int32_t *, hipStream_t);
+
+// R = R^T for a validated CSR matrix whose rows ascend strictly in column
+// (checked here; other rows count as not symmetric).  Each entry right of the
+// diagonal is looked up in its mirror row by bisection (about log2 of the row
+// length dependent loads, mostly from L2); the entries left of the diagonal
+// are then all mirrors exactly when there are as many of them.  Lanes share a
+// row as in the power-method product.
+template <typename T, int L>
+__global__ __launch_bounds__(256) void csr_check_kernel(const int64_t *__restrict__ rp,
+                                                        const int32_t *__restrict__ ci,
+                                                        const T *__restrict__ val, int64_t n,
+                                                        int32_t *__restrict__ asym, int64_t *__restrict__ count) {
+  constexpr int RPB = 256 / L;
+  const int sub = threadIdx.x % L;
+  bool bad = false;
+  int64_t net = 0;  // entries right of the diagonal minus entries left of it
+  for (int64_t base = (int64_t)blockIdx.x * RPB; base < n && !__any(bad); base += (int64_t)gridDim.x * RPB) {
+    const int64_t row = base + threadIdx.x / L;
+    if (row >= n) continue;
+    const int64_t e1 = rp[row + 1];
+    for (int64_t e = rp[row] + sub; e < e1; e += L) {
+      const int64_t c = ci[e];
+      if (e + 1 < e1 && ci[e + 1] <= c) bad = true;
+      if (c < row) --net;
+      if (c <= row) continue;
+      ++net;
+      int64_t lo = rp[c], hi = rp[c + 1];
+      const int64_t end = hi;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (ci[mid] < row)
+          lo = mid + 1;
+        else
+          hi = mid;
+      }
+      if (!(lo < end && ci[lo] == row && val[lo] == val[e])) bad = true;
+    }
+  }
+  // one addition per workgroup: they meet at one address
+  __shared__ int64_t nets[4];
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) net += __shfl_xor(net, off, 64);
+  if ((threadIdx.x & 63) == 0) nets[threadIdx.x >> 6] = net;
+  if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(asym, 1);
+  __syncthreads();
+  if (threadIdx.x == 0)
+    atomicAdd((unsigned long long *)count, (unsigned long long)(nets[0] + nets[1] + nets[2] + nets[3]));
+}
+
+__global__ void publish_flag_kernel(int32_t *__restrict__ flag, const int64_t *__restrict__ count,
+                                    int32_t *__restrict__ host_flag) {
+  if (threadIdx.x != 0) return;
+  int32_t v = *flag;
+  if (count && *count != 0) *flag = v = v | 1;
+  if (host_flag) {
+    *host_flag = v;
+    __threadfence_system();
+  }
+}
+
+hipError_t launch_publish_flag(int32_t *flag, const int64_t *count, int32_t *host_flag, hipStream_t st) {
+  publish_flag_kernel<<<1, 64, 0, st>>>(flag, count, host_flag);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_csr_check(const int64_t *rp, const int32_t *ci, const T *val, int64_t n, int32_t *asym,
+                            int64_t *count, int32_t *host_flag, hipStream_t st) {
+  const int64_t b = (n + 31) / 32;
+  csr_check_kernel<T, 8><<<(unsigned)(b < 2048 ? b : 2048), 256, 0, st>>>(rp, ci, val, n, asym, count);
+  return launch_publish_flag(asym, count, host_flag, st);
+}
+template hipError_t launch_csr_check<double>(const int64_t *, const int32_t *, const double *, int64_t, int32_t *,
+                                             int64_t *, int32_t *, hipStream_t);
+template hipError_t launch_csr_check<float>(const int64_t *, const int32_t *, const float *, int64_t, int32_t *,
+                                            int64_t *, int32_t *, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Conversion copies

@@ -293,7 +293,7 @@ __global__ __launch_bounds__(64 * kTriWaves) void tri_step_kernel(TriStepArgs a)
   constexpr int NSW = 64 / LS;          // streams per wave
   constexpr int SPB = NSW * kTriWaves;  // streams per workgroup
   constexpr int PP = 4 * LS;            // probes per pass
-  __shared__ double red[2][kTriWaves][PP];
+  __shared__ double red[3][kTriWaves][PP];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = tid >> 6, q = lane / LS, p = lane % LS;
   const int64_t n = a.n, ldb = a.ldb, ldv = a.ldv;
@@ -317,6 +317,7 @@ __global__ __launch_bounds__(64 * kTriWaves) void tri_step_kernel(TriStepArgs a)
   const T tc1 = (T)a.c1, tcw = (T)a.cw;
   const bool use_cg = a.cg != nullptr;
   const T tcg = use_cg ? (T)a.cg[0] : T(0);
+  const bool pair = a.pair != 0;
 
   // this stream's rows [r_beg, r_end): equal shares, a multiple of kTriRows
   const int64_t nstream = (int64_t)gridDim.x * SPB;
@@ -354,7 +355,7 @@ __global__ __launch_bounds__(64 * kTriWaves) void tri_step_kernel(TriStepArgs a)
     return x;
   };
 
-  double ds[4] = {0.0, 0.0, 0.0, 0.0}, gs[4] = {0.0, 0.0, 0.0, 0.0};
+  double ds[4] = {0.0, 0.0, 0.0, 0.0}, gs[4] = {0.0, 0.0, 0.0, 0.0}, bs[4] = {0.0, 0.0, 0.0, 0.0};
   auto row = [&](int64_t r, const v4 &vp, const v4 &vc, const v4 &vn, const v4 &vm, const v4 &gv, const v4 &dd) {
     v4 z;
 #pragma unroll
@@ -364,8 +365,10 @@ __global__ __launch_bounds__(64 * kTriWaves) void tri_step_kernel(TriStepArgs a)
       if (M1 != 0) ze += tcw * vm[e];
       if (use_cg) ze += tcg * gv[e];
       z[e] = ze;
-      ds[e] += (double)gv[e] * (double)(a.dot_y ? y : ze);
-      if (GG) gs[e] += (double)gv[e] * (double)gv[e];
+      const double g = (double)(pair ? vc[e] : gv[e]), dq = (double)(a.dot_y ? y : ze);
+      ds[e] += g * dq;
+      if (GG) gs[e] += g * g;
+      if (pair) bs[e] += (double)ze * dq;
     }
     if (Vkp1 && pv) *(v4 *)(Vkp1 + r * ldb + col) = z;
   };
@@ -375,7 +378,11 @@ __global__ __launch_bounds__(64 * kTriWaves) void tri_step_kernel(TriStepArgs a)
     for (int64_t r = r_beg; r < r_end; r += kTriRows) {
       const v4 n1 = vk_row(r + 1), n2 = vk_row(r + 2);
       const v4 m0 = vm_row(r), m1 = vm_row(r + 1);
-      const v4 g0 = g_row(r), g1 = g_row(r + 1);
+      v4 g0 = {T(0), T(0), T(0), T(0)}, g1 = g0;  // dots in pairs read no probe rows
+      if (!pair) {
+        g0 = g_row(r);
+        g1 = g_row(r + 1);
+      }
       const v4 d0 = d_row(r), d1 = d_row(r + 1);
       row(r, vp, vc, n1, m0, g0, d0);
       if (r + 1 < r_end) row(r + 1, vc, n1, n2, m1, g1, d1);
@@ -391,6 +398,7 @@ __global__ __launch_bounds__(64 * kTriWaves) void tri_step_kernel(TriStepArgs a)
     for (int off = LS; off < 64; off <<= 1) {
       ds[e] += __shfl_xor(ds[e], off, 64);
       if (GG) gs[e] += __shfl_xor(gs[e], off, 64);
+      bs[e] += __shfl_xor(bs[e], off, 64);
     }
   }
   if (lane < LS) {
@@ -398,20 +406,23 @@ __global__ __launch_bounds__(64 * kTriWaves) void tri_step_kernel(TriStepArgs a)
     for (int e = 0; e < 4; ++e) {
       red[0][w][4 * p + e] = ds[e];
       red[1][w][4 * p + e] = GG ? gs[e] : 0.0;
+      red[2][w][4 * p + e] = bs[e];
     }
   }
   __syncthreads();
   for (int t = tid; t < PP; t += 64 * kTriWaves) {
-    double t0 = 0.0, t1 = 0.0;
+    double t0 = 0.0, t1 = 0.0, t2 = 0.0;
 #pragma unroll
     for (int k = 0; k < kTriWaves; ++k) {
       t0 += red[0][k][t];
       t1 += red[1][k][t];
+      t2 += red[2][k][t];
     }
     if (chunk0 + t < ldv) {
       const int64_t bidx = (int64_t)blockIdx.x * ldv + chunk0 + t;
       a.part[(int64_t)a.slot * a.nblk * ldv + bidx] = t0;
       if (GG) a.part[(int64_t)a.slot_gg * a.nblk * ldv + bidx] = t1;
+      if (pair && a.slot_b >= 0) a.part[(int64_t)a.slot_b * a.nblk * ldv + bidx] = t2;
     }
   }
 }
@@ -472,6 +483,7 @@ hipError_t launch_tri_step(const TriStepArgs &a, hipStream_t st) {
   const bool vk_signs = a.Vk == nullptr;
   const int m1 = a.cw == 0.0 ? 0 : (a.Vkm1 == nullptr ? 2 : 1);
   if ((vk_signs || m1 == 2) && !a.signs) return hipErrorInvalidValue;
+  if (a.pair && a.cg) return hipErrorInvalidValue;
   const int32_t s_use = a.s > 0 ? a.s : (int32_t)a.ldv;
   // V rows of ldb >= s values (a multiple of 4: 16- or 32-byte pieces stay
   // aligned); partials and sign words in rows of ldv, a multiple of 64

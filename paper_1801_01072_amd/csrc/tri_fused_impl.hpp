@@ -13,7 +13,8 @@
 // side, step j one row behind step j - 1, from the last three rows of step
 // j - 1 held in registers (step j's V_{k-1} term is step j - 2's row; step
 // 1's is V_k's).  Only the last two steps' rows are stored (the next launch
-// needs V_{k+NF-1} and V_{k+NF}): a launch reads V_k, V_{k-1}, the probes and
+// needs V_{k+NF-1} and V_{k+NF}; the last launch of an estimate stores
+// nothing): a launch reads V_k, V_{k-1}, the probes and
 // the diagonals once and writes two V blocks, four V row passes for NF steps
 // instead of 3 NF.  Two probes per lane keep about a dozen registers per
 // step, so ten steps fit.  Chebyshev and Clenshaw steps read the prepared
@@ -41,8 +42,9 @@ inline int tri_fused_lanes(int32_t s) { return s <= 32 ? 16 : (s <= 64 ? 32 : 64
 // is the sign block.  M1: step 0 has a V_{k-1} term (read from Vkm1).  GG:
 // accumulate g.g (step 0).  DY: the dot products are of the product R V
 // (Taylor), else of the step's result.  CG: a g term with a per-step device
-// coefficient (Clenshaw's alpha_k).
-template <typename T, int LS, int NF, bool RAD, bool VKS, bool M1, bool GG, bool DY, bool CG>
+// coefficient (Clenshaw's alpha_k).  PR: dots in pairs (with the step's input,
+// and of its result: no probe rows are read beyond V_k itself).
+template <typename T, int LS, int NF, bool RAD, bool VKS, bool M1, bool GG, bool DY, bool CG, bool PR>
 __global__ __launch_bounds__(64 * kFusedWaves) void tri_fused_kernel(TriFusedArgs a) {
   typedef T v2 __attribute__((ext_vector_type(2)));
   typedef T v4 __attribute__((ext_vector_type(4)));
@@ -123,9 +125,11 @@ __global__ __launch_bounds__(64 * kFusedWaves) void tri_fused_kernel(TriFusedArg
       return h;
   };
 
-  double dots[NF][2], gs[2] = {0.0, 0.0};
+  double dots[NF][2], dotb[PR ? NF : 1][2], gs[2] = {0.0, 0.0};
 #pragma unroll
   for (int j = 0; j < NF; ++j) dots[j][0] = dots[j][1] = 0.0;
+#pragma unroll
+  for (int j = 0; j < (PR ? NF : 1); ++j) dotb[j][0] = dotb[j][1] = 0.0;
   if (r_beg < r_end) {
     const v2 zero = {T(0), T(0)};
     const int64_t r0 = r_beg - (NF - 1), r1 = r_end + NF - 2;
@@ -156,12 +160,14 @@ __global__ __launch_bounds__(64 * kFusedWaves) void tri_fused_kernel(TriFusedArg
       v4 dx[NF];
 #pragma unroll
       for (int j = 0; j < NF; ++j) dx[j] = ldd(EDGE ? clampr(r - j) : r - j);
+      if constexpr (!PR) {
 #pragma unroll
-      for (int j = NF - 1; j > 0; --j) gh[j] = gh[j - 1];
-      if constexpr (RAD)
-        gh[0] = masks(rc);
-      else
-        gh[0] = ld2(G, rc);
+        for (int j = NF - 1; j > 0; --j) gh[j] = gh[j - 1];
+        if constexpr (RAD)
+          gh[0] = masks(rc);
+        else
+          gh[0] = ld2(G, rc);
+      }
 #pragma unroll
       for (int j = 0; j < NF; ++j) {
         const int64_t x = r - j;
@@ -184,12 +190,19 @@ __global__ __launch_bounds__(64 * kFusedWaves) void tri_fused_kernel(TriFusedArg
           if (CG) ze += cg[j] * g_of(gh[j])[e];
           z[e] = in ? ze : T(0);
           if (own) {
-            dots[j][e] += gdot(gh[j], e, DY ? yt : ze);
-            if (GG && j == 0) gs[e] += (double)g_of(gh[j])[e] * (double)g_of(gh[j])[e];
+            if constexpr (PR) {
+              const double dq = (double)(DY ? yt : ze), dv = (double)mid[e];
+              dots[j][e] += dv * dq;
+              dotb[PR ? j : 0][e] += (double)ze * dq;
+              if (GG && j == 0) gs[e] += dv * dv;
+            } else {
+              dots[j][e] += gdot(gh[j], e, DY ? yt : ze);
+              if (GG && j == 0) gs[e] += (double)g_of(gh[j])[e] * (double)g_of(gh[j])[e];
+            }
           }
         }
         if (own && pv) {
-          if (j == NF - 2) *(v2 *)(VoutA + x * ldb + col) = z;
+          if (j == NF - 2 && VoutA) *(v2 *)(VoutA + x * ldb + col) = z;
           if (j == NF - 1 && VoutB) *(v2 *)(VoutB + x * ldb + col) = z;
         }
         ow[j][0] = ow[j][1];
@@ -217,14 +230,22 @@ __global__ __launch_bounds__(64 * kFusedWaves) void tri_fused_kernel(TriFusedArg
     for (int j = 0; j < NF; ++j) {
       dots[j][0] *= ta;
       dots[j][1] *= ta;
+      if (PR) {
+        dotb[PR ? j : 0][0] *= ta;
+        dotb[PR ? j : 0][1] *= ta;
+      }
     }
   }
   // streams of a wave, then waves, in a fixed order; one slot at a time
   const int64_t bbase = (int64_t)blockIdx.x * ldv + chunk0;
+  constexpr int NSLOT = PR ? 2 * NF + 1 : NF + 1;  // main dots, (second dots,) g.g
 #pragma unroll
-  for (int j = 0; j <= NF; ++j) {
-    if (j == NF && !GG) break;
-    double v0 = j < NF ? dots[j][0] : gs[0], v1 = j < NF ? dots[j][1] : gs[1];
+  for (int j = 0; j < NSLOT; ++j) {
+    if (j == NSLOT - 1 && !GG) break;
+    const int jb = PR && j >= NF && j < 2 * NF ? j - NF : 0;
+    if (PR && j >= NF && j < 2 * NF && a.slot_b[jb] < 0) continue;
+    double v0 = j < NF ? dots[j < NF ? j : 0][0] : (j == NSLOT - 1 ? gs[0] : dotb[jb][0]);
+    double v1 = j < NF ? dots[j < NF ? j : 0][1] : (j == NSLOT - 1 ? gs[1] : dotb[jb][1]);
 #pragma unroll
     for (int off = LS; off < 64; off <<= 1) {
       v0 += __shfl_xor(v0, off, 64);
@@ -235,7 +256,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void tri_fused_kernel(TriFusedArg
       red[w][2 * p + 1] = v1;
     }
     __syncthreads();
-    const int32_t slot = j < NF ? a.slot[j] : a.slot_gg;
+    const int32_t slot = j < NF ? a.slot[j < NF ? j : 0] : (j == NSLOT - 1 ? a.slot_gg : a.slot_b[jb]);
     for (int t = tid; t < PP; t += 64 * kFusedWaves) {
       if (chunk0 + t < ldv) {
         double acc = 0.0;
@@ -251,7 +272,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void tri_fused_kernel(TriFusedArg
 namespace {
 // Workgroups of one instance resident at once (the grid of one pass, so no
 // workgroup waits for a second round), at most the partial stride.
-template <typename T, int LS, int NF, bool RAD, bool VKS, bool M1, bool GG, bool DY, bool CG>
+template <typename T, int LS, int NF, bool RAD, bool VKS, bool M1, bool GG, bool DY, bool CG, bool PR>
 int32_t tri_fused_grid(int32_t nblk) {
   static int32_t cap = 0;
   if (cap == 0) {
@@ -260,7 +281,7 @@ int32_t tri_fused_grid(int32_t nblk) {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
       cus = 256;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, (const void *)tri_fused_kernel<T, LS, NF, RAD, VKS, M1, GG, DY, CG>, 64 * kFusedWaves, 0) !=
+            &per_cu, (const void *)tri_fused_kernel<T, LS, NF, RAD, VKS, M1, GG, DY, CG, PR>, 64 * kFusedWaves, 0) !=
             hipSuccess ||
         per_cu < 1)
       per_cu = 1;
@@ -269,11 +290,11 @@ int32_t tri_fused_grid(int32_t nblk) {
   return nblk < cap ? nblk : cap;
 }
 
-template <typename T, int LS, int NF, bool RAD, bool VKS, bool M1, bool GG, bool DY, bool CG>
+template <typename T, int LS, int NF, bool RAD, bool VKS, bool M1, bool GG, bool DY, bool CG, bool PR = false>
 hipError_t tri_fused_launch(const TriFusedArgs &a, int32_t s_use, hipStream_t st) {
-  dim3 grid((unsigned)tri_fused_grid<T, LS, NF, RAD, VKS, M1, GG, DY, CG>(a.nblk),
+  dim3 grid((unsigned)tri_fused_grid<T, LS, NF, RAD, VKS, M1, GG, DY, CG, PR>(a.nblk),
             (unsigned)((s_use + 2 * LS - 1) / (2 * LS)));
-  tri_fused_kernel<T, LS, NF, RAD, VKS, M1, GG, DY, CG><<<grid, 64 * kFusedWaves, 0, st>>>(a);
+  tri_fused_kernel<T, LS, NF, RAD, VKS, M1, GG, DY, CG, PR><<<grid, 64 * kFusedWaves, 0, st>>>(a);
   return hipGetLastError();
 }
 
@@ -284,6 +305,19 @@ hipError_t tri_fused_launch(const TriFusedArgs &a, int32_t s_use, hipStream_t st
 template <typename T, int LS, int NF>
 hipError_t tri_fused_dispatch(const TriFusedArgs &a, int32_t s_use, hipStream_t st, bool rad, bool vks, bool m1,
                               bool gg, bool dy, bool cg) {
+  if (a.pair) {
+    // the probes are read only as the first launch's V_k: a stored block, or
+    // expanded from the sign bits
+    const int pc = (vks ? 8 : 0) | (m1 ? 4 : 0) | (gg ? 2 : 0) | (dy ? 1 : 0);
+    switch (pc) {
+      case 8 | 1: return tri_fused_launch<T, LS, NF, true, true, false, false, true, false, true>(a, s_use, st);
+      case 1: return tri_fused_launch<T, LS, NF, false, false, false, false, true, false, true>(a, s_use, st);
+      case 8 | 2: return tri_fused_launch<T, LS, NF, true, true, false, true, false, false, true>(a, s_use, st);
+      case 2: return tri_fused_launch<T, LS, NF, false, false, false, true, false, false, true>(a, s_use, st);
+      case 4: return tri_fused_launch<T, LS, NF, false, false, true, false, false, false, true>(a, s_use, st);
+      default: return hipErrorInvalidValue;
+    }
+  }
   const int code = (rad ? 32 : 0) | (vks ? 16 : 0) | (m1 ? 8 : 0) | (gg ? 4 : 0) | (dy ? 2 : 0) | (cg ? 1 : 0);
   switch (code) {
     // Taylor
@@ -339,7 +373,7 @@ hipError_t launch_tri_fused(const TriFusedArgs &a, int32_t nf, hipStream_t st) {
   }
   const int32_t s_use = a.s > 0 ? a.s : (int32_t)a.ldv;
   if (a.n < 1 || a.nblk < 1 || a.ldv % 64 != 0 || a.ldb % 4 != 0 || a.ldb < s_use || a.ldv < s_use ||
-      a.ldb > a.ldv || !a.VoutA || !a.scal || !a.part || !a.diag || (!vks && !a.Vk))
+      a.ldb > a.ldv || (!a.VoutA && a.VoutB) || (a.pair && cg) || !a.scal || !a.part || !a.diag || (!vks && !a.Vk))
     return hipErrorInvalidValue;
   const void *outs[2] = {a.VoutA, a.VoutB};
   for (const void *o : outs)

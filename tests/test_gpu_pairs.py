@@ -94,3 +94,83 @@ def test_dense_strided_storage(orc):
         big[:, 1:n + 1] = torch.from_numpy(A).to(DEV)
         A64 = A.astype(np.float64)
         check(orc, big[:, 1:n + 1], lambda V, A=A64: A @ V, n, "chebyshev", m, s, 4, 0, "f64", f"strided {off}")
+
+
+def sparse_csr(A, order=None):
+    """int64/int32 CSR arrays of a scipy matrix; order: reverses the entries of every row."""
+    A = A.tocsr()
+    A.sort_indices()
+    rp, ci, val = A.indptr.astype(np.int64), A.indices.astype(np.int32), A.data.copy()
+    if order == "reversed":
+        for i in range(A.shape[0]):
+            ci[rp[i]:rp[i + 1]] = ci[rp[i]:rp[i + 1]][::-1].copy()
+            val[rp[i]:rp[i + 1]] = val[rp[i]:rp[i + 1]][::-1].copy()
+    return rp, ci, val, A.shape[0]
+
+
+def to_dev(csr, dtype):
+    return (torch.from_numpy(csr[0]).to(DEV), torch.from_numpy(csr[1]).to(DEV),
+            torch.from_numpy(csr[2].astype(dtype)).to(DEV), csr[3])
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("kind,n,s,m", [("tri", 1, 1, 2), ("tri", 2, 3, 3), ("tri", 65, 100, 4), ("tri", 1000, 130, 21),
+                                        ("band", 17, 33, 2), ("band", 300, 64, 5), ("band", 1030, 65, 8),
+                                        ("wide", 700, 50, 3), ("wide", 900, 66, 6), ("arrow", 500, 40, 4)])
+def test_sparse(orc, kind, n, s, m, dtype):
+    """Every sparse form, each with R as it is, with one value or one entry of
+    one triangle changed, and with rows whose columns do not ascend (the
+    general kernels then keep one moment per product)."""
+    import scipy.sparse as sp
+
+    rng = np.random.default_rng(n + m)
+    if kind == "tri":
+        off = rng.uniform(-1, 1, max(n - 1, 0))
+        A = sp.diags([off, rng.uniform(2, 3, n), off], [-1, 0, 1], shape=(n, n))
+    elif kind == "band":
+        rp, ci, val, _ = W.banded_density_csr(n, 6, seed=n)
+        A = sp.csr_matrix((val, ci, rp), shape=(n, n))
+    elif kind == "wide":
+        B = sp.random(n, n, density=5.0 / n, random_state=rng, format="csr") + sp.eye(n, format="csr")
+        A = B @ B.T
+    else:  # one long row and column: at most three entries per row on average
+        v = rng.uniform(-0.02, 0.02, n - 1)
+        A = sp.lil_matrix((n, n))
+        A[0, 1:], A[1:, 0] = v, v.reshape(-1, 1)
+        A.setdiag(rng.uniform(0.5, 1.0, n))
+    A = (A * (0.8 / abs(A).sum(axis=1).max())).astype(dtype).astype(np.float64).tocsr()
+    A.sort_indices()
+    cases = [("symmetric", A, None, 0)]
+    if n > 1:
+        V = A.copy()
+        V.data[V.indptr[n - 1]] *= 1.5     # last row, leftmost entry
+        D = A.tolil()
+        row = np.flatnonzero(D[0].toarray().ravel())
+        D[0, row[-1]] = 0.0                # first row, rightmost entry
+        D = D.tocsr()
+        D.eliminate_zeros()
+        cases += [("value changed", V, None, 0), ("entry dropped", D, None, 0), ("reversed rows", A, "reversed", 0),
+                  ("general", A, None, ent.FLAG_CSR_GENERAL), ("general, changed", V, None, ent.FLAG_CSR_GENERAL)]
+    for label, M, order, flags in cases:
+        Rd = to_dev(sparse_csr(M, order), dtype)
+        for method in ("chebyshev", "taylor"):
+            for dist in (0, 1):
+                check(orc, Rd, lambda V, M=M: M @ V, n, method, m, s, 7 + n, dist,
+                      "f64" if dtype == np.float64 else "f32", f"{kind} {label} {dist}", flags=flags)
+
+
+@pytest.mark.parametrize("fuse", ["2", "3", "7"])
+def test_tridiagonal_launch_splits(orc, monkeypatch, fuse):
+    # the moments dealt to several launches, some of one product
+    import scipy.sparse as sp
+
+    n, s = 517, 70
+    rng = np.random.default_rng(1)
+    off = rng.uniform(-1, 1, n - 1)
+    A = (sp.diags([off, rng.uniform(2, 3, n), off], [-1, 0, 1]) * 0.15).tocsr()
+    monkeypatch.setenv("ENT_TRI_FUSE", fuse)
+    for m in (2, 3, 9, 10, 23):
+        for method in ("chebyshev", "taylor"):
+            for dist in (0, 1):
+                check(orc, to_dev(sparse_csr(A), np.float64), lambda V: A @ V, n, method, m, s, 5, dist, "f64",
+                      f"tri fuse {fuse}")
