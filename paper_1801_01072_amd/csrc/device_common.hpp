@@ -202,7 +202,8 @@ __device__ __forceinline__ int sched_next(const SchedArgs &s, int *sh) {
     const int seg = s.seg_of_xcc[xcc_id()];
     if (seg >= 0) {
       const int q = __hip_atomic_fetch_add(s.head + seg, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (q < s.seg_off[seg + 1] - s.seg_off[seg] &&
+      const int end = s.tail && *s.tail == 0 ? s.seg_mid[seg] : s.seg_off[seg + 1];
+      if (q < end - s.seg_off[seg] &&
           __hip_atomic_fetch_add(s.err, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
         i = s.seg_off[seg] + q;
     }
@@ -240,22 +241,24 @@ __device__ __forceinline__ void sched_release(const SchedArgs &s, int b) {
   if (threadIdx.x == 0) __hip_atomic_fetch_add(s.done + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Recurrence of step k (the host's per-step launches use the same rule):
-// Chebyshev forward: V_1 = Y_0 - V_0 (dot slot 1, g.g in slot 0), then
-// V_{k+1} = 2 Y_k - 2 V_k - V_{k-1} written over V_{k-1}; Taylor: W_{k+1} =
-// W_k - Y_k into alternating buffers, dots with Y_k in slot k, the last step
-// writes nothing.  V_0 is the probe block.
+// Recurrence of step k of a batch: Chebyshev forward: V_1 = Y_0 - V_0 (g.g in
+// slot 0), then V_{k+1} = 2 Y_k - 2 V_k - V_{k-1} written over V_{k-1}; Taylor:
+// W_{k+1} = W_k - Y_k into alternating buffers, dots with Y_k; the last step
+// writes nothing.  V_0 is the probe block.  Dots: slot k + 1 (Taylor: k), or in
+// pairs slots 2k + 1 and 2k + 2 (2k and 2k + 1).
 struct StepRule {
   double c1, c2, cw;
-  int32_t dot_y, slot, slot_gg;
+  int32_t dot_y, slot, slot_gg, slot_b;
   int vk, vkm1, vout;  // buffer ids: 0 = probe block, 1 = VA, 2 = VB, -1 = none
 };
-__device__ __forceinline__ StepRule step_rule(int32_t method, int32_t k, int32_t nsteps) {
+__device__ __forceinline__ StepRule step_rule(int32_t method, int32_t m, int32_t k, int32_t nsteps, bool pair) {
   StepRule r;
   const int out = 1 + (k & 1), prev = 1 + ((k - 1) & 1);
+  const int32_t last = (pair ? (nsteps + 1) / 2 : nsteps) - 1;
   if (method == 1) {  // Chebyshev
     r.dot_y = 0;
-    r.slot = k + 1;
+    r.slot = pair ? 2 * k + 1 : k + 1;
+    r.slot_b = pair && 2 * k + 2 <= m ? 2 * k + 2 : -1;
     if (k == 0) {
       r.c1 = 1.0; r.c2 = -1.0; r.cw = 0.0; r.slot_gg = 0;
       r.vk = 0; r.vkm1 = -1;
@@ -263,15 +266,19 @@ __device__ __forceinline__ StepRule step_rule(int32_t method, int32_t k, int32_t
       r.c1 = 2.0; r.c2 = -2.0; r.cw = -1.0; r.slot_gg = -1;
       r.vk = prev; r.vkm1 = k == 1 ? 0 : out;
     }
-    r.vout = out;
   } else {  // Taylor
     r.c1 = -1.0; r.c2 = 1.0; r.cw = 0.0;
-    r.dot_y = 1; r.slot = k; r.slot_gg = -1;
+    r.dot_y = 1; r.slot_gg = -1;
+    r.slot = pair ? 2 * k : k;
+    r.slot_b = pair && 2 * k + 1 <= m ? 2 * k + 1 : -1;
     r.vk = k == 0 ? 0 : prev;
     r.vkm1 = -1;
-    r.vout = k < nsteps - 1 ? out : -1;
   }
+  r.vout = k < last ? out : -1;
   return r;
 }
+
+// A matrix's dots come in pairs if it equals its transpose.
+__device__ __forceinline__ bool batch_pairs(const BatchMat &M) { return *(const int32_t *)(M.scal + S_SYM) == 0; }
 
 }  // namespace ent

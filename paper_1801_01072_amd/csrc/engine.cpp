@@ -1966,6 +1966,7 @@ struct ent_graph_s {
   int32_t grid_p = 0, nitems = 0, spin_limit = 1 << 20;
   int32_t nseg = 0;                            // 0: XCDs not probed yet
   int32_t seg_off[ent::kMaxXcc + 1] = {};      // items of segment s: [seg_off[s], seg_off[s + 1])
+  int32_t seg_mid[ent::kMaxXcc] = {};          // first of them that only matrices R != R^T have
   int32_t seg_of_xcc[ent::kMaxXcc];            // hardware XCC id -> segment, -1: no workgroups
   int32_t seg_wgs[ent::kMaxXcc] = {};          // workgroups of the grid on each segment's XCD
   int4 *items_d = nullptr;
@@ -1973,6 +1974,7 @@ struct ent_graph_s {
   // [0, kMaxXcc) next item of each segment, [kMaxXcc] error flag,
   // [kMaxXcc + 1 + b] finished tiles of matrix b
   int32_t *sched = nullptr;
+  int32_t *tail_d = nullptr;  // nonzero: some matrix differs from its transpose
 };
 
 constexpr int32_t kXccProbe = 4096;
@@ -1981,117 +1983,13 @@ constexpr int32_t kSchedDone = ent::kMaxXcc + 1;
 
 namespace {
 
-// The m recurrence steps of an FP32 / FP64 batch as one grouped launch per
-// step (every row tile of every matrix).
-template <typename T>
-ent_status enqueue_steps_grouped(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
-  const int32_t nsteps = (g->method == ENT_CHEBYSHEV) ? g->m : g->m + 1;
-  const T *Vk = (const T *)g->G, *Vkm1 = nullptr;
-  T *bufs[2] = {(T *)g->VA, (T *)g->VB};
-  if (pe) pe->steps_begin = pe->mark();
-  for (int32_t k = 0; k < nsteps; ++k) {
-    T *Vout = bufs[k & 1];
-    ent::BatchStepArgs ba{};
-    ent::DenseStepArgs &a = ba.base;
-    a.ldv = g->ldv;
-    a.Vk = Vk;
-    a.G = g->G;
-    a.part = g->part;
-    a.bn = 64;
-    if (g->method == ENT_CHEBYSHEV) {
-      a.dot_y = 0;
-      a.slot = k + 1;
-      if (k == 0) {
-        a.c1 = 1.0; a.c2 = -1.0; a.cw = 0.0;
-        a.slot_gg = 0;
-      } else {
-        a.c1 = 2.0; a.c2 = -2.0; a.cw = -1.0;
-        a.slot_gg = -1;
-      }
-      a.Vkm1 = Vkm1;
-      a.Vkp1 = Vout;
-    } else {
-      a.c1 = -1.0; a.c2 = 1.0; a.cw = 0.0;
-      a.dot_y = 1;
-      a.slot = k;
-      a.slot_gg = -1;
-      a.Vkp1 = (k < nsteps - 1) ? Vout : nullptr;
-    }
-    ba.mats = g->mats_d;
-    ba.tiles = g->wr == 2 ? g->tiles2_d : g->tiles1_d;
-    HIP_TRY(ent::launch_batch_dense_step<T>(ba, g->wr == 2 ? g->ntiles2 : g->ntiles1, g->wr, st));
-    if (g->method == ENT_CHEBYSHEV) Vkm1 = Vk;
-    Vk = Vout;
-    if (pe) {
-      const int e = pe->mark();
-      if (k == nsteps - 1) pe->steps_end = e;
-    }
-  }
-  return ENT_OK;
-}
-
-// The m recurrence steps of a BF16x3 batch as one grouped launch per step.
-ent_status enqueue_steps_grouped_bf16(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
-  const int32_t nsteps = (g->method == ENT_CHEBYSHEV) ? g->m : g->m + 1;
-  const float *Vk = (const float *)g->G, *Vkm1 = nullptr;
-  float *bufs[2] = {(float *)g->VA, (float *)g->VB};
-  if (pe) pe->steps_begin = pe->mark();
-  for (int32_t k = 0; k < nsteps; ++k) {
-    float *Vout = bufs[k & 1];
-    ent::Bf16EpiArgs ea{};
-    bool write = true;
-    if (g->method == ENT_CHEBYSHEV) {
-      ea.dot_y = 0;
-      ea.slot = k + 1;
-      if (k == 0) {
-        ea.c1 = 1.0; ea.c2 = -1.0; ea.cw = 0.0;
-        ea.slot_gg = 0;
-      } else {
-        ea.c1 = 2.0; ea.c2 = -2.0; ea.cw = -1.0;
-        ea.slot_gg = -1;
-      }
-    } else {
-      ea.c1 = -1.0; ea.c2 = 1.0; ea.cw = 0.0;
-      ea.dot_y = 1;
-      ea.slot = k;
-      ea.slot_gg = -1;
-      write = k < nsteps - 1;
-    }
-    // fused step: product + epilogue; V_k hi/lo in set k % 2, V_{k+1} hi/lo to the other
-    ea.Vk = Vk;
-    ea.Vkm1 = (g->method == ENT_CHEBYSHEV && k > 0) ? Vkm1 : nullptr;
-    ea.Vkp1 = write ? Vout : nullptr; ea.V_hi = g->Vhi[(k + 1) & 1]; ea.V_lo = g->Vlo[(k + 1) & 1];
-    ea.G = (const float *)g->G; ea.scale_y = 1; ea.part = g->part; ea.ldv = g->ldv;
-    HIP_TRY(ent::launch_batch_bf16x3_step(ea, g->mats_d, g->tiles2_d, g->ntiles2, g->Ahi, g->Alo,
-                                          g->Vhi[k & 1], g->Vlo[k & 1], st));
-    if (pe) {
-      const int e = pe->mark();
-      if (k == nsteps - 1) pe->steps_end = e;
-    }
-    if (g->method == ENT_CHEBYSHEV) Vkm1 = Vk;
-    Vk = Vout;
-  }
-  return ENT_OK;
-}
-
-// The m recurrence steps as one persistent launch over the batch's schedule
-// (counters cleared by a kernel first, so the sequence can be captured).
-ent_status enqueue_steps_persistent(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
-  const int32_t nsteps = (g->method == ENT_CHEBYSHEV) ? g->m : g->m + 1;
-  HIP_TRY(ent::launch_zero(g->sched, sizeof(int32_t) * (kSchedDone + (size_t)g->count), st));
+// Buffers and recurrence of the batch's steps.
+ent::BatchPersistArgs batch_step_args(ent_graph_s *g) {
   ent::BatchPersistArgs pa{};
-  pa.sched.items = g->items_d;
-  pa.sched.nitems = g->nitems;
-  pa.sched.spin_limit = g->spin_limit;
-  pa.sched.nseg = g->nseg;
-  for (int q = 0; q <= ent::kMaxXcc; ++q) pa.sched.seg_off[q] = g->seg_off[q];
-  for (int q = 0; q < ent::kMaxXcc; ++q) pa.sched.seg_of_xcc[q] = g->seg_of_xcc[q];
-  pa.sched.head = g->sched;
-  pa.sched.err = g->sched + kSchedErr;
-  pa.sched.done = g->sched + kSchedDone;
   pa.mats = g->mats_d;
   pa.method = g->method;
-  pa.nsteps = nsteps;
+  pa.m = g->m;
+  pa.nsteps = recurrence_products(g->method, g->m, false);
   pa.ldv = g->ldv;
   pa.G = g->G;
   pa.VA = g->VA;
@@ -2103,6 +2001,47 @@ ent_status enqueue_steps_persistent(ent_graph_s *g, hipStream_t st, PhaseEvents 
     pa.Vhi[q] = g->Vhi[q];
     pa.Vlo[q] = g->Vlo[q];
   }
+  return pa;
+}
+
+// The recurrence steps of a batch as one grouped launch per step (every row
+// tile of every matrix; tiles of matrices without that step end at once).
+ent_status enqueue_steps_grouped(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
+  const ent::BatchPersistArgs pa = batch_step_args(g);
+  const int2 *tiles = g->bf16 || g->wr == 2 ? g->tiles2_d : g->tiles1_d;
+  const int32_t nt = g->bf16 || g->wr == 2 ? g->ntiles2 : g->ntiles1;
+  if (pe) pe->steps_begin = pe->mark();
+  for (int32_t k = 0; k < pa.nsteps; ++k) {
+    if (g->bf16)
+      HIP_TRY(ent::launch_batch_bf16x3_step(pa, k, tiles, nt, st));
+    else if (g->comp_f64)
+      HIP_TRY(ent::launch_batch_dense_step<double>(pa, k, tiles, nt, g->wr, st));
+    else
+      HIP_TRY(ent::launch_batch_dense_step<float>(pa, k, tiles, nt, g->wr, st));
+    if (pe) {
+      const int e = pe->mark();
+      if (k == pa.nsteps - 1) pe->steps_end = e;
+    }
+  }
+  return ENT_OK;
+}
+
+// The m recurrence steps as one persistent launch over the batch's schedule
+// (counters cleared by a kernel first, so the sequence can be captured).
+ent_status enqueue_steps_persistent(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
+  HIP_TRY(ent::launch_zero(g->sched, sizeof(int32_t) * (kSchedDone + (size_t)g->count), st));
+  ent::BatchPersistArgs pa = batch_step_args(g);
+  pa.sched.items = g->items_d;
+  pa.sched.nitems = g->nitems;
+  pa.sched.spin_limit = g->spin_limit;
+  pa.sched.nseg = g->nseg;
+  for (int q = 0; q <= ent::kMaxXcc; ++q) pa.sched.seg_off[q] = g->seg_off[q];
+  for (int q = 0; q < ent::kMaxXcc; ++q) pa.sched.seg_of_xcc[q] = g->seg_of_xcc[q];
+  for (int q = 0; q < ent::kMaxXcc; ++q) pa.sched.seg_mid[q] = g->seg_mid[q];
+  pa.sched.head = g->sched;
+  pa.sched.err = g->sched + kSchedErr;
+  pa.sched.done = g->sched + kSchedDone;
+  pa.sched.tail = g->tail_d;
   if (pe) pe->steps_begin = pe->mark();
   if (g->bf16)
     HIP_TRY(ent::launch_batch_bf16x3_persistent(pa, g->grid_p, st));
@@ -2113,15 +2052,13 @@ ent_status enqueue_steps_persistent(ent_graph_s *g, hipStream_t st, PhaseEvents 
   HIP_TRY(ent::launch_sched_check(pa.sched, st));  // a segment no workgroup reached is an error
   if (pe) {
     pe->steps_end = pe->mark();
-    pe->logical_steps = nsteps;
+    pe->logical_steps = pa.nsteps;
   }
   return ENT_OK;
 }
 
 ent_status batch_enqueue_steps(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
-  if (g->window > 0) return enqueue_steps_persistent(g, st, pe);
-  if (g->bf16) return enqueue_steps_grouped_bf16(g, st, pe);
-  return g->comp_f64 ? enqueue_steps_grouped<double>(g, st, pe) : enqueue_steps_grouped<float>(g, st, pe);
+  return g->window > 0 ? enqueue_steps_persistent(g, st, pe) : enqueue_steps_grouped(g, st, pe);
 }
 
 template <typename T>
@@ -2135,6 +2072,8 @@ ent_status enqueue_batch(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
     HIP_TRY((ent::launch_batch_convert<float, T>(g->mats_d, count, g->max_elems, st)));
   if (!(o.flags & ENT_FLAG_SKIP_TRACE_CHECK) || (o.flags & ENT_FLAG_NORMALIZE))
     HIP_TRY(ent::launch_batch_trace<T>(g->mats_d, count, st));
+  HIP_TRY(ent::launch_zero(g->tail_d, sizeof(int32_t), st));
+  HIP_TRY(ent::launch_batch_check<T>(g->mats_d, count, g->max_n, g->tail_d, st));
   HIP_TRY(ent::launch_batch_probes<T>(g->mats_d, count, g->max_npad, (T *)g->G, g->s, g->ldv,
                                       o.probe_dist, st));
   if (!(o.u_fixed > 0)) {
@@ -2179,6 +2118,11 @@ ent_status enqueue_batch_bf16(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
     else
       HIP_TRY(ent::launch_batch_trace<float>(g->mats_d, count, st));
   }
+  HIP_TRY(ent::launch_zero(g->tail_d, sizeof(int32_t), st));
+  if (g->src_f64)
+    HIP_TRY(ent::launch_batch_check<double>(g->mats_d, count, g->max_n, g->tail_d, st));
+  else
+    HIP_TRY(ent::launch_batch_check<float>(g->mats_d, count, g->max_n, g->tail_d, st));
   if (g->src_f64)
     HIP_TRY(ent::launch_batch_split<double>(g->mats_d, g->tiles2_d, g->ntiles2, g->Ahi, g->Alo, st));
   else
@@ -2236,10 +2180,10 @@ size_t batch_matrix_bytes(const ent_graph_s *g, const ent::BatchMat &M) {
 // round emits the next step of each matrix in the window, all its row tiles,
 // so a matrix's data is reused across its steps while it stays cached, and a
 // step's items come one round after those of the step before.  A matrix
-// leaves the window after its last step.
+// leaves the window after its last step.  Steps [k0, k1).
 void batch_schedule_segment(const ent_graph_s *g, std::vector<int32_t> order, size_t window,
-                            int32_t tile_rows, std::vector<int4> &items) {
-  const int32_t nsteps = (g->method == ENT_CHEBYSHEV) ? g->m : g->m + 1;
+                            int32_t tile_rows, int32_t k0, int32_t k1, std::vector<int4> &items) {
+  if (k0 >= k1) return;
   std::stable_sort(order.begin(), order.end(),
                    [&](int32_t a, int32_t b) { return g->mats[a].n > g->mats[b].n; });
   struct Active {
@@ -2251,7 +2195,7 @@ void batch_schedule_segment(const ent_graph_s *g, std::vector<int32_t> order, si
     while (next < order.size()) {
       const size_t mb = batch_matrix_bytes(g, g->mats[order[next]]);
       if (!act.empty() && bytes + mb > window) break;
-      act.push_back({order[next], 0});
+      act.push_back({order[next], k0});
       bytes += mb;
       ++next;
     }
@@ -2262,7 +2206,7 @@ void batch_schedule_segment(const ent_graph_s *g, std::vector<int32_t> order, si
     }
     std::vector<Active> keep;
     for (auto &a : act) {
-      if (a.k < nsteps)
+      if (a.k < k1)
         keep.push_back(a);
       else
         bytes -= batch_matrix_bytes(g, g->mats[a.b]);
@@ -2304,7 +2248,12 @@ std::vector<int4> batch_schedule(ent_graph_s *g, size_t window, int32_t tile_row
   for (int32_t q = 0; q < ns; ++q) {
     g->seg_off[q] = (int32_t)items.size();
     const size_t share = (size_t)((double)window * g->seg_wgs[q] / (double)wgs);
-    batch_schedule_segment(g, members[q], share, tile_rows, items);
+    // first the steps every matrix has, then those that only a matrix
+    // unequal to its transpose has (one moment per product)
+    const int32_t all = recurrence_products(g->method, g->m, false), both = recurrence_products(g->method, g->m, true);
+    batch_schedule_segment(g, members[q], share, tile_rows, 0, both, items);
+    g->seg_mid[q] = (int32_t)items.size();
+    batch_schedule_segment(g, members[q], share, tile_rows, both, all, items);
   }
   for (int32_t q = ns; q <= ent::kMaxXcc; ++q) g->seg_off[q] = (int32_t)items.size();
   return items;
@@ -2587,6 +2536,7 @@ ent_status batch_create(const ent_matrix *Rs, int32_t count, int32_t method, int
     cv.add(&g->items_d, items);
     cv.add(&g->xcc_d, (size_t)kXccProbe);
     cv.add(&g->sched, kSchedDone + (size_t)count);
+    cv.add(&g->tail_d, 1);
   }
   g->ws_bytes = cv.total();
   if (g_ws_limit && g->ws_bytes > g_ws_limit)

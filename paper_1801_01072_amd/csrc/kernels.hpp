@@ -122,12 +122,6 @@ struct BatchMat {
   int64_t aoff;    // BF16x3: bf16 hi/lo split of R (n_pad x n_pad, fragment-major)
 };
 
-struct BatchStepArgs {
-  DenseStepArgs base;  // V/G/part are batch base pointers; R, n, ntile, scal per matrix
-  const BatchMat *mats;
-  const int2 *tiles;   // (matrix, row tile) per workgroup
-};
-
 // ---- probes ----------------------------------------------------------------
 // G[i][j] (row-major, ld = ldv) for i < n_pad, j < ldv; zero outside n x s.
 // Rademacher also writes the sign words signs[i][w] (w < ldv/32) if non-null.
@@ -488,6 +482,9 @@ struct SchedArgs {
   int32_t spin_limit;
   int32_t nseg;                  // segments (XCDs that hold workgroups)
   int32_t seg_off[kMaxXcc + 1];  // segment s: items [seg_off[s], seg_off[s + 1])
+  int32_t seg_mid[kMaxXcc];      // ... of which those from seg_mid[s] on are the steps
+                                 // that only a matrix unequal to its transpose has
+  const int32_t *tail;           // 0: no matrix of the batch is one (null: all items run)
   int32_t seg_of_xcc[kMaxXcc];   // hardware XCC id -> segment (-1: none)
   int32_t *head;   // [nseg] next item of each segment (zeroed before the launch)
   int32_t *done;   // per-matrix finished tiles (zeroed before the launch)
@@ -498,11 +495,14 @@ hipError_t launch_xcc_probe(int32_t *ids, int32_t grid, hipStream_t st);
 // After a persistent launch: sets bit 1 of *err when a segment's items were
 // not all taken (no workgroup of the launch ran on its XCD).
 hipError_t launch_sched_check(const SchedArgs &s, hipStream_t st);
-// Buffers and recurrence of the batched steps, common to every item.
+// Buffers and recurrence of the batched steps, common to every item.  A
+// matrix equal to its transpose (its scal[S_SYM] is 0) takes two moments per
+// step and has none from step (nsteps + 1) / 2 on.
 struct BatchPersistArgs {
-  SchedArgs sched;
+  SchedArgs sched;   // persistent launches only
   const BatchMat *mats;
   int32_t method;    // ENT_TAYLOR / ENT_CHEBYSHEV
+  int32_t m;         // degree
   int32_t nsteps;    // m (Chebyshev) or m + 1 (Taylor)
   int64_t ldv;
   const void *G;     // probe block (batch base; FP32 probe-major for BF16x3)
@@ -521,14 +521,18 @@ hipError_t launch_batch_dense_persistent(const BatchPersistArgs &pa, int32_t wr,
                                          hipStream_t st);
 hipError_t launch_batch_bf16x3_persistent(const BatchPersistArgs &pa, int32_t grid, hipStream_t st);
 
-hipError_t launch_batch_bf16x3_step(const Bf16EpiArgs &base, const BatchMat *mats, const int2 *tiles,
-                                    int32_t ntiles, const uint16_t *Ahi, const uint16_t *Alo,
-                                    const uint16_t *vin_hi, const uint16_t *vin_lo, hipStream_t st);
+// Step k of every matrix (tiles: (matrix, row tile) per workgroup).
+hipError_t launch_batch_bf16x3_step(const BatchPersistArgs &pa, int32_t k, const int2 *tiles, int32_t ntiles,
+                                    hipStream_t st);
 
 // ---- batches of dense matrices (one launch per phase over all matrices) ------
 template <typename T>
-hipError_t launch_batch_dense_step(const BatchStepArgs &ba, int32_t ntiles, int32_t wr,
-                                   hipStream_t st);
+hipError_t launch_batch_dense_step(const BatchPersistArgs &pa, int32_t k, const int2 *tiles, int32_t ntiles,
+                                   int32_t wr, hipStream_t st);
+// Sets scal[S_SYM] of every matrix that differs from its transpose, and
+// *tail (must start at 0) if any does.  T: the type of M.R.
+template <typename T>
+hipError_t launch_batch_check(const BatchMat *mats, int32_t count, int64_t max_n, int32_t *tail, hipStream_t st);
 hipError_t launch_fill(double *p, int64_t count, double v, hipStream_t st);
 // Zero `bytes` bytes at p (kernel stores, no memset node).
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);

@@ -416,9 +416,10 @@ __device__ __forceinline__ void bf16x3_gemm_tile(const uint16_t *__restrict__ A_
   const float c1 = (float)e.c1, c2b = (float)(e.c2 * e.scal[S_B]), cw = (float)e.cw;
   const bool use_m1 = e.Vkm1 && e.cw != 0.0;
 
-  double ds[S::WCB], gs[S::WCB];
+  const bool pair = e.pair != 0;
+  double ds[S::WCB], gs[S::WCB], bs[S::WCB];
 #pragma unroll
-  for (int c = 0; c < S::WCB; ++c) ds[c] = gs[c] = 0.0;
+  for (int c = 0; c < S::WCB; ++c) ds[c] = gs[c] = bs[c] = 0.0;
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
     const int64_t rbase = row0 + 32 * (2 * wr + r) + 4 * kh;
@@ -429,7 +430,8 @@ __device__ __forceinline__ void bf16x3_gemm_tile(const uint16_t *__restrict__ A_
       for (int g = 0; g < 4; ++g) {
         const int64_t off = col * npad + rbase + 8 * g;
         const f32x4 vk = *(const f32x4 *)(e.Vk + off);
-        const f32x4 gv = *(const f32x4 *)(e.G + off);
+        f32x4 gv = vk;  // dots in pairs are taken with V_k
+        if (!pair) gv = *(const f32x4 *)(e.G + off);
         f32x4 vm = {0.f, 0.f, 0.f, 0.f};
         if (use_m1) vm = *(const f32x4 *)(e.Vkm1 + off);
         f32x4 z;
@@ -440,8 +442,10 @@ __device__ __forceinline__ void bf16x3_gemm_tile(const uint16_t *__restrict__ A_
           z[q] = c1 * y + c2b * vk[q] + cw * vm[q];
           zh[q] = bf16_rne(z[q]);
           zl[q] = bf16_rne(z[q] - bf16_to_f32(zh[q]));
-          ds[c] += (double)gv[q] * (double)(e.dot_y ? y : z[q]);
+          const double dq = (double)(e.dot_y ? y : z[q]);
+          ds[c] += (double)gv[q] * dq;
           gs[c] += (double)gv[q] * (double)gv[q];
+          bs[c] += (double)z[q] * dq;
         }
         if (e.Vkp1) {
           *(f32x4 *)(e.Vkp1 + off) = z;
@@ -455,24 +459,28 @@ __device__ __forceinline__ void bf16x3_gemm_tile(const uint16_t *__restrict__ A_
   if (e.slot < 0) return;
   // per probe: the two lane halves, then the WM waves of a probe column
   __syncthreads();  // every wave is done with the operand stages
-  double *red = (double *)lds;  // [2][WM][BN]
+  double *red = (double *)lds;  // [3][WM][BN]
 #pragma unroll
   for (int c = 0; c < S::WCB; ++c) {
     ds[c] += __shfl_xor(ds[c], 32, 64);
     gs[c] += __shfl_xor(gs[c], 32, 64);
+    bs[c] += __shfl_xor(bs[c], 32, 64);
     if (kh == 0) {
       const int pc = 32 * (S::WCB * wc + c) + m32;
       red[(0 * WM + wr) * BN + pc] = ds[c];
       red[(1 * WM + wr) * BN + pc] = gs[c];
+      red[(2 * WM + wr) * BN + pc] = bs[c];
     }
   }
   __syncthreads();
   for (int pc = threadIdx.x; pc < BN; pc += blockDim.x) {
-    double t0 = 0.0, t1 = 0.0;
+    double t0 = 0.0, t1 = 0.0, t2 = 0.0;
     for (int q = 0; q < WM; ++q) {
       t0 += red[(0 * WM + q) * BN + pc];
       t1 += red[(1 * WM + q) * BN + pc];
+      t2 += red[(2 * WM + q) * BN + pc];
     }
+    if (pair && e.slot_b >= 0) e.part[((int64_t)e.slot_b * e.nblk + ptile) * e.ldv + col0 + pc] = t2;
     e.part[((int64_t)e.slot * e.nblk + ptile) * e.ldv + col0 + pc] = t0;
     if (e.slot_gg >= 0) e.part[((int64_t)e.slot_gg * e.nblk + ptile) * e.ldv + col0 + pc] = t1;
   }
@@ -493,38 +501,55 @@ __global__ __launch_bounds__(128 * WM) void bf16x3_gemm_kernel(Bf16GemmArgs a) {
                                   (int64_t)rt * S::BM, (int64_t)ct * BN, nullptr, 0);
 }
 
+// Step k of a batch's matrix as epilogue arguments (bf16 V sets by step
+// parity: a step reads set k % 2 and writes the other); false: the matrix has
+// no step k.
+__device__ __forceinline__ bool batch_bf16x3_args(const BatchPersistArgs &pa, const BatchMat &M, int k,
+                                                  Bf16EpiArgs &e) {
+  const bool pair = batch_pairs(M);
+  if (pair && k >= (pa.nsteps + 1) / 2) return false;
+  const StepRule r = step_rule(pa.method, pa.m, k, pa.nsteps, pair);
+  const float *bufs[3] = {(const float *)pa.G + M.voff, (const float *)pa.VA + M.voff,
+                          (const float *)pa.VB + M.voff};
+  e.part_y = nullptr;
+  e.splits = 1;
+  e.Vk = bufs[r.vk];
+  e.Vkm1 = r.vkm1 >= 0 ? bufs[r.vkm1] : nullptr;
+  e.Vkp1 = r.vout >= 0 ? (float *)bufs[r.vout] : nullptr;
+  const int pout = (k + 1) & 1;
+  e.V_hi = pa.Vhi[pout] + M.voff;
+  e.V_lo = pa.Vlo[pout] + M.voff;
+  e.G = bufs[0];
+  e.scal = M.scal;
+  e.c1 = r.c1; e.c2 = r.c2; e.cw = r.cw;
+  e.dot_y = r.dot_y; e.slot = r.slot; e.slot_gg = r.slot_gg;
+  e.pair = pair; e.slot_b = r.slot_b;
+  e.scale_y = 1;
+  e.part = pa.part + M.poff;
+  e.nblk = M.ntile;
+  e.n_pad = M.n_pad;
+  e.ldv = pa.ldv;
+  e.cg = nullptr;
+  return true;
+}
+
 // Batch step: one workgroup per (matrix, 128-row tile) over the matrix's full
 // K, with the epilogue fused (the matrix's probe block is one tile of BN =
-// ldv probes).  The step reads V_k hi/lo and writes V_{k+1} hi/lo, so the
-// two live in separate buffers (vin / vout, alternating by step).  The
-// pointers of `base` are batch-wide and offset by the matrix's regions.
+// ldv probes).
 template <int BN>
-__global__ __launch_bounds__(256) void batch_bf16x3_step_kernel(Bf16EpiArgs base,
-                                                                const BatchMat *__restrict__ mats,
-                                                                const int2 *__restrict__ tiles,
-                                                                const uint16_t *Ahi, const uint16_t *Alo,
-                                                                const uint16_t *vin_hi,
-                                                                const uint16_t *vin_lo) {
+__global__ __launch_bounds__(256) void batch_bf16x3_step_kernel(BatchPersistArgs pa, int k, const int2 *tiles) {
   const int2 t = tiles[blockIdx.x];
-  const BatchMat &M = mats[t.x];
-  Bf16EpiArgs e = base;
-  e.Vk = base.Vk + M.voff;
-  e.Vkm1 = base.Vkm1 ? base.Vkm1 + M.voff : nullptr;
-  e.Vkp1 = base.Vkp1 ? base.Vkp1 + M.voff : nullptr;
-  e.V_hi = base.V_hi + M.voff;
-  e.V_lo = base.V_lo + M.voff;
-  e.G = base.G + M.voff;
-  e.scal = M.scal;
-  e.part = base.part + M.poff;
-  e.nblk = M.ntile;
-  bf16x3_gemm_tile<BN, 2, true>(Ahi + M.aoff, Alo + M.aoff, vin_hi + M.voff, vin_lo + M.voff, nullptr,
-                                M.n_pad, 0, (int)(M.n_pad / kBK), (int64_t)t.y * 128, 0, &e, t.y);
+  const BatchMat &M = pa.mats[t.x];
+  Bf16EpiArgs e{};
+  if (!batch_bf16x3_args(pa, M, k, e)) return;
+  bf16x3_gemm_tile<BN, 2, true>(pa.Ahi + M.aoff, pa.Alo + M.aoff, pa.Vhi[k & 1] + M.voff, pa.Vlo[k & 1] + M.voff,
+                                nullptr, M.n_pad, 0, (int)(M.n_pad / kBK), (int64_t)t.y * 128, 0, &e, t.y);
 }
 
 // Persistent batch steps (BF16x3): each workgroup takes (matrix, 128-row
 // tile, step) items in schedule order, waits for the matrix's previous step,
 // runs the fused GEMM + epilogue tile of the grouped kernel with that step's
-// recurrence (bf16 V sets by step parity), publishes it.
+// recurrence, publishes it.
 template <int BN>
 __global__ __launch_bounds__(256) void batch_bf16x3_persistent_kernel(BatchPersistArgs pa) {
   __shared__ int sh;
@@ -533,29 +558,10 @@ __global__ __launch_bounds__(256) void batch_bf16x3_persistent_kernel(BatchPersi
     if (i < 0) return;
     const int4 it = pa.sched.items[i];
     const BatchMat &M = pa.mats[it.x];
-    if (!sched_wait(pa.sched, it.x, it.z * M.ntile, &sh)) return;
-    const StepRule r = step_rule(pa.method, it.z, pa.nsteps);
-    const float *bufs[3] = {(const float *)pa.G + M.voff, (const float *)pa.VA + M.voff,
-                            (const float *)pa.VB + M.voff};
     Bf16EpiArgs e{};
-    e.part_y = nullptr;
-    e.splits = 1;
-    e.Vk = bufs[r.vk];
-    e.Vkm1 = r.vkm1 >= 0 ? bufs[r.vkm1] : nullptr;
-    e.Vkp1 = r.vout >= 0 ? (float *)bufs[r.vout] : nullptr;
-    const int pin = it.z & 1, pout = (it.z + 1) & 1;
-    e.V_hi = pa.Vhi[pout] + M.voff;
-    e.V_lo = pa.Vlo[pout] + M.voff;
-    e.G = bufs[0];
-    e.scal = M.scal;
-    e.c1 = r.c1; e.c2 = r.c2; e.cw = r.cw;
-    e.dot_y = r.dot_y; e.slot = r.slot; e.slot_gg = r.slot_gg;
-    e.scale_y = 1;
-    e.part = pa.part + M.poff;
-    e.nblk = M.ntile;
-    e.n_pad = M.n_pad;
-    e.ldv = pa.ldv;
-    e.cg = nullptr;
+    if (!batch_bf16x3_args(pa, M, it.z, e)) continue;  // nor has the matrix any later step
+    if (!sched_wait(pa.sched, it.x, it.z * M.ntile, &sh)) return;
+    const int pin = it.z & 1;
     bf16x3_gemm_tile<BN, 2, true>(pa.Ahi + M.aoff, pa.Alo + M.aoff, pa.Vhi[pin] + M.voff,
                                   pa.Vlo[pin] + M.voff, nullptr, M.n_pad, 0, (int)(M.n_pad / kBK),
                                   (int64_t)it.y * 128, 0, &e, it.y);
@@ -589,13 +595,12 @@ int32_t bf16x3_persistent_grid(int64_t ldv) {
   return cus * (per > 0 ? per : 1);
 }
 
-hipError_t launch_batch_bf16x3_step(const Bf16EpiArgs &base, const BatchMat *mats, const int2 *tiles,
-                                    int32_t ntiles, const uint16_t *Ahi, const uint16_t *Alo,
-                                    const uint16_t *vin_hi, const uint16_t *vin_lo, hipStream_t st) {
-  switch (base.ldv) {
-    case 64: batch_bf16x3_step_kernel<64><<<(unsigned)ntiles, 256, 0, st>>>(base, mats, tiles, Ahi, Alo, vin_hi, vin_lo); break;
-    case 128: batch_bf16x3_step_kernel<128><<<(unsigned)ntiles, 256, 0, st>>>(base, mats, tiles, Ahi, Alo, vin_hi, vin_lo); break;
-    case 256: batch_bf16x3_step_kernel<256><<<(unsigned)ntiles, 256, 0, st>>>(base, mats, tiles, Ahi, Alo, vin_hi, vin_lo); break;
+hipError_t launch_batch_bf16x3_step(const BatchPersistArgs &pa, int32_t k, const int2 *tiles, int32_t ntiles,
+                                    hipStream_t st) {
+  switch (pa.ldv) {
+    case 64: batch_bf16x3_step_kernel<64><<<(unsigned)ntiles, 256, 0, st>>>(pa, k, tiles); break;
+    case 128: batch_bf16x3_step_kernel<128><<<(unsigned)ntiles, 256, 0, st>>>(pa, k, tiles); break;
+    case 256: batch_bf16x3_step_kernel<256><<<(unsigned)ntiles, 256, 0, st>>>(pa, k, tiles); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -475,24 +475,41 @@ int32_t dense_step_splits(int64_t n, int32_t ntile, int64_t ldv, int32_t bn) {
   return ks;
 }
 
-// Grouped step over a batch: block -> (matrix, row tile) from the tile table;
-// the batch base pointers are offset by the matrix's region.
-template <typename T, int BN, int WR>
-__global__ __launch_bounds__(256) void batch_dense_step_kernel(BatchStepArgs ba) {
-  const int2 tl = ba.tiles[blockIdx.x];
-  const BatchMat &M = ba.mats[tl.x];
-  DenseStepArgs a = ba.base;
+// Step k of a batch's matrix as arguments of the tile body; false: the matrix
+// has no step k.
+template <typename T>
+__device__ __forceinline__ bool batch_dense_args(const BatchPersistArgs &pa, const BatchMat &M, int k,
+                                                 DenseStepArgs &a) {
+  const bool pair = batch_pairs(M);
+  if (pair && k >= (pa.nsteps + 1) / 2) return false;
+  const StepRule r = step_rule(pa.method, pa.m, k, pa.nsteps, pair);
+  const T *bufs[3] = {(const T *)pa.G + M.voff, (const T *)pa.VA + M.voff, (const T *)pa.VB + M.voff};
   a.R = M.R;
   a.ldr = M.ldr;
   a.n = M.n;
-  a.Vk = (const T *)ba.base.Vk + M.voff;
-  if (ba.base.Vkm1) a.Vkm1 = (const T *)ba.base.Vkm1 + M.voff;
-  if (ba.base.Vkp1) a.Vkp1 = (T *)ba.base.Vkp1 + M.voff;
-  a.G = (const T *)ba.base.G + M.voff;
-  a.part = ba.base.part + M.poff;
-  a.ntile = M.ntile;
+  a.ldv = pa.ldv;
+  a.Vk = bufs[r.vk];
+  a.Vkm1 = r.vkm1 >= 0 ? bufs[r.vkm1] : nullptr;
+  a.Vkp1 = r.vout >= 0 ? (void *)bufs[r.vout] : nullptr;
+  a.G = bufs[0];
   a.scal = M.scal;
-  dense_step_tile<T, BN, WR, kBatchCols>(a, tl.y, 0, 0, a.n, nullptr);
+  a.c1 = r.c1; a.c2 = r.c2; a.cw = r.cw;
+  a.dot_y = r.dot_y; a.slot = r.slot; a.slot_gg = r.slot_gg;
+  a.pair = pair; a.slot_b = r.slot_b;
+  a.part = pa.part + M.poff;
+  a.ntile = M.ntile;
+  a.bn = 64;
+  return true;
+}
+
+// Grouped step over a batch: block -> (matrix, row tile) from the tile table
+// (x) and 64 probes (y).
+template <typename T, int WR>
+__global__ __launch_bounds__(256) void batch_dense_step_kernel(BatchPersistArgs pa, int k, const int2 *tiles) {
+  const int2 tl = tiles[blockIdx.x];
+  DenseStepArgs a{};
+  if (!batch_dense_args<T>(pa, pa.mats[tl.x], k, a)) return;
+  dense_step_tile<T, 64, WR, kBatchCols>(a, tl.y, (int)blockIdx.y, 0, a.n, nullptr);
 }
 
 // Persistent batch steps: each workgroup takes (matrix, row tile, step)
@@ -506,24 +523,9 @@ __global__ __launch_bounds__(256) void batch_dense_persistent_kernel(BatchPersis
     if (i < 0) return;
     const int4 it = pa.sched.items[i];
     const BatchMat &M = pa.mats[it.x];
-    if (!sched_wait(pa.sched, it.x, it.z * M.ntile, &sh)) return;
-    const StepRule r = step_rule(pa.method, it.z, pa.nsteps);
-    const T *bufs[3] = {(const T *)pa.G + M.voff, (const T *)pa.VA + M.voff, (const T *)pa.VB + M.voff};
     DenseStepArgs a{};
-    a.R = M.R;
-    a.ldr = M.ldr;
-    a.n = M.n;
-    a.ldv = pa.ldv;
-    a.Vk = bufs[r.vk];
-    a.Vkm1 = r.vkm1 >= 0 ? bufs[r.vkm1] : nullptr;
-    a.Vkp1 = r.vout >= 0 ? (void *)bufs[r.vout] : nullptr;
-    a.G = bufs[0];
-    a.scal = M.scal;
-    a.c1 = r.c1; a.c2 = r.c2; a.cw = r.cw;
-    a.dot_y = r.dot_y; a.slot = r.slot; a.slot_gg = r.slot_gg;
-    a.part = pa.part + M.poff;
-    a.ntile = M.ntile;
-    a.bn = 64;
+    if (!batch_dense_args<T>(pa, M, it.z, a)) continue;  // nor has the matrix any later step
+    if (!sched_wait(pa.sched, it.x, it.z * M.ntile, &sh)) return;
     dense_step_tile<T, 64, WR, kBatchCols>(a, it.y, 0, 0, a.n, nullptr);
     sched_release(pa.sched, it.x);
   }
@@ -602,19 +604,22 @@ hipError_t launch_dense_step(const DenseStepArgs &a, hipStream_t st, bool epilog
 }
 
 template <typename T>
-hipError_t launch_batch_dense_step(const BatchStepArgs &ba, int32_t ntiles, int32_t wr,
-                                   hipStream_t st) {
-  if (ba.base.bn != 64) return hipErrorInvalidValue;
+hipError_t launch_batch_dense_step(const BatchPersistArgs &pa, int32_t k, const int2 *tiles, int32_t ntiles,
+                                   int32_t wr, hipStream_t st) {
+  if (pa.ldv % 64 != 0 || ntiles < 1) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)ntiles, (unsigned)(pa.ldv / 64));
   if (wr == 1)
-    batch_dense_step_kernel<T, 64, 1><<<(unsigned)ntiles, 256, 0, st>>>(ba);
+    batch_dense_step_kernel<T, 1><<<grid, 256, 0, st>>>(pa, k, tiles);
   else if (wr == 2)
-    batch_dense_step_kernel<T, 64, 2><<<(unsigned)ntiles, 256, 0, st>>>(ba);
+    batch_dense_step_kernel<T, 2><<<grid, 256, 0, st>>>(pa, k, tiles);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
-template hipError_t launch_batch_dense_step<double>(const BatchStepArgs &, int32_t, int32_t, hipStream_t);
-template hipError_t launch_batch_dense_step<float>(const BatchStepArgs &, int32_t, int32_t, hipStream_t);
+template hipError_t launch_batch_dense_step<double>(const BatchPersistArgs &, int32_t, const int2 *, int32_t, int32_t,
+                                                     hipStream_t);
+template hipError_t launch_batch_dense_step<float>(const BatchPersistArgs &, int32_t, const int2 *, int32_t, int32_t,
+                                                    hipStream_t);
 template hipError_t launch_dense_step<double>(const DenseStepArgs &, hipStream_t, bool);
 template hipError_t launch_dense_step<float>(const DenseStepArgs &, hipStream_t, bool);
 

@@ -473,10 +473,8 @@ template hipError_t launch_trace_dense<float>(const float *, int64_t, int64_t, d
 // bank conflicts down a column).  Diagonal tiles leave their part of the
 // trace in tmp[bi].
 template <typename T>
-__global__ __launch_bounds__(256) void dense_check_kernel(const T *__restrict__ R, int64_t ldr, int64_t n,
-                                                          double *__restrict__ tmp, int32_t *__restrict__ asym) {
-  __shared__ T tile[64][65];
-  const int64_t t = blockIdx.x;
+__device__ __forceinline__ bool dense_check_tile(const T *__restrict__ R, int64_t ldr, int64_t n, int64_t t,
+                                                 T (*tile)[65], double *__restrict__ tmp) {
   int64_t bj = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
   while (bj * (bj + 1) / 2 > t) --bj;
   while ((bj + 1) * (bj + 2) / 2 <= t) ++bj;
@@ -498,12 +496,47 @@ __global__ __launch_bounds__(256) void dense_check_kernel(const T *__restrict__ 
 #pragma unroll
   for (int i = 0; i < 16; ++i)
     if (!(tile[lane][16 * w + i] == y[i])) bad = true;  // also where either is NaN
-  if (__any(bad) && lane == 0) atomicOr(asym, 1);
-  if (bi == bj && w == 0) {
+  if (tmp && bi == bj && w == 0) {
     const double d = wave_sum((double)tile[lane][lane]);
     if (lane == 0) tmp[bi] = d;
   }
+  return __any(bad) != 0;
 }
+
+template <typename T>
+__global__ __launch_bounds__(256) void dense_check_kernel(const T *__restrict__ R, int64_t ldr, int64_t n,
+                                                          double *__restrict__ tmp, int32_t *__restrict__ asym) {
+  __shared__ T tile[64][65];
+  if (dense_check_tile<T>(R, ldr, n, blockIdx.x, tile, tmp) && (threadIdx.x & 63) == 0) atomicOr(asym, 1);
+}
+
+// Batch: the tiles of matrix blockIdx.y dealt to the workgroups of its row of
+// the grid; a mismatch marks the matrix and the batch.
+template <typename T>
+__global__ __launch_bounds__(256) void batch_check_kernel(const BatchMat *__restrict__ mats, int32_t *tail) {
+  __shared__ T tile[64][65];
+  const BatchMat &M = mats[blockIdx.y];
+  const int64_t nb = (M.n + 63) / 64, nt = nb * (nb + 1) / 2;
+  bool bad = false;
+  for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+    __syncthreads();
+    if (dense_check_tile<T>((const T *)M.R, M.ldr, M.n, t, tile, nullptr)) bad = true;
+  }
+  if (bad && (threadIdx.x & 63) == 0) {
+    atomicOr((int32_t *)(M.scal + S_SYM), 1);
+    atomicOr(tail, 1);
+  }
+}
+
+template <typename T>
+hipError_t launch_batch_check(const BatchMat *mats, int32_t count, int64_t max_n, int32_t *tail, hipStream_t st) {
+  const int64_t nb = (max_n + 63) / 64, nt = nb * (nb + 1) / 2;
+  dim3 grid((unsigned)(nt < 128 ? nt : 128), (unsigned)count);
+  batch_check_kernel<T><<<grid, 256, 0, st>>>(mats, tail);
+  return hipGetLastError();
+}
+template hipError_t launch_batch_check<double>(const BatchMat *, int32_t, int64_t, int32_t *, hipStream_t);
+template hipError_t launch_batch_check<float>(const BatchMat *, int32_t, int64_t, int32_t *, hipStream_t);
 
 __global__ __launch_bounds__(256) void dense_check_finish_kernel(const double *__restrict__ tmp, int32_t cnt,
                                                                  double *__restrict__ scal,
@@ -1018,7 +1051,7 @@ hipError_t launch_xcc_probe(int32_t *ids, int32_t grid, hipStream_t st) {
 __global__ void sched_check_kernel(SchedArgs s) {
   const int q = (int)threadIdx.x;
   if (q < s.nseg) {
-    const int len = s.seg_off[q + 1] - s.seg_off[q];
+    const int len = (s.tail && *s.tail == 0 ? s.seg_mid[q] : s.seg_off[q + 1]) - s.seg_off[q];
     if (len > 0 && __hip_atomic_load(s.head + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < len)
       __hip_atomic_fetch_or(s.err, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -1207,7 +1240,7 @@ hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double
 __global__ void batch_final_kernel(const BatchMat *__restrict__ mats, double *d,
                                    int32_t method, int32_t m, int32_t s, double *h) {
   const BatchMat &M = mats[blockIdx.x];
-  final_body(d + M.doff, M.scal, method, m, s, h + M.hoff);
+  final_body(d + M.doff, M.scal, method == 1 && batch_pairs(M) ? FINAL_CHEB_PAIRS : method, m, s, h + M.hoff);
 }
 
 hipError_t launch_batch_final(const BatchMat *mats, int32_t count, double *d, int32_t method,

@@ -174,3 +174,34 @@ def test_tridiagonal_launch_splits(orc, monkeypatch, fuse):
             for dist in (0, 1):
                 check(orc, to_dev(sparse_csr(A), np.float64), lambda V: A @ V, n, method, m, s, 5, dist, "f64",
                       f"tri fuse {fuse}")
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32", "bf16x3"])
+@pytest.mark.parametrize("flags", [0, ent.FLAG_BATCH_STEPWISE])
+@pytest.mark.parametrize("changed", [(), (1, 4), (0, 1, 2, 3, 4)])
+def test_batch(orc, precision, flags, changed):
+    """Each matrix of a batch decides for itself, in every replay: none, some
+    or all of them unequal to their transpose (the values are changed in place
+    between replays of one graph, and back)."""
+    ns, s, seed = [33, 64, 65, 200, 300], 40, 11
+    host = [W.dense_density(W.spectrum_exp(n, n / 5.0), 50 + n) for n in ns]
+    mats = [torch.from_numpy(R).to(DEV) for R in host]
+    for method, m in (("chebyshev", 7), ("taylor", 6)):
+        g = ent.Graph(mats, method, m, s, seed, precision=precision, probe_dist="gaussian", u_fixed=0.9, flags=flags)
+        for touch in ((), changed, ()):
+            for b in touch:
+                mats[b][ns[b] - 1, 0] += 0.05
+            torch.cuda.synchronize()
+            g.launch()
+            per = g.per_probe()
+            for b in touch:
+                mats[b].copy_(torch.from_numpy(host[b]))
+            for b, R in enumerate(host):
+                A = R.copy()
+                if b in touch:
+                    A[ns[b] - 1, 0] += 0.05
+                _, ref = reference(orc, lambda V, A=A: A @ V, ns[b], method, m, s, seed + b, 1, 0.9)
+                e = float(np.max(np.abs(per[b] - ref)) / max(np.mean(np.abs(ref)), 1.0))
+                print(f"[pairs batch {precision} {flags} {method} changed {touch}] b={b} per-probe {e:.2e}", flush=True)
+                assert e <= tol_for(precision)
+        g.destroy()
