@@ -905,108 +905,146 @@ __device__ __forceinline__ void reduce_moments_body(const double *__restrict__ p
 }
 
 // One estimate's moments: workgroup = (slot, 64 probes); wave w sums the
-// tiles of its contiguous quarter in order, then the quarters are added in
-// order (fixed, so repeated runs agree bit for bit).
-__global__ __launch_bounds__(256) void reduce_moments_kernel(const double *__restrict__ part, int32_t nslot,
+// tiles of its contiguous sixteenth in order, then the sixteenths are added in
+// order (fixed, so repeated runs agree bit for bit).  Bound by latency: the
+// workgroups are few (slots x probes / 64), so each takes 16 waves and eight
+// loads in flight (n = 200000 CSR, 31 slots: 107 -> 14 us; n = 8192 dense, 51
+// slots x 256 probes: 57 -> 13 us).
+constexpr int kReduceWaves = 16;
+__global__ __launch_bounds__(64 * kReduceWaves) void reduce_moments_kernel(const double *__restrict__ part, int32_t nslot,
                                                              int32_t ntile, int64_t ldv, int32_t s,
                                                              double *__restrict__ d) {
-  __shared__ double q[4][64];
+  __shared__ double q[kReduceWaves][64];
   const int k = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int j = blockIdx.y * 64 + lane;
-  const int32_t per = (ntile + 3) / 4;
+  const int32_t per = (ntile + kReduceWaves - 1) / kReduceWaves;
   const int32_t i0 = w * per, i1 = i0 + per < ntile ? i0 + per : ntile;
   double acc = 0.0;
   if (j < s) {
     const double *p = part + (int64_t)k * ntile * ldv + j;
+#pragma unroll 8
     for (int32_t i = i0; i < i1; ++i) acc += p[(int64_t)i * ldv];
   }
   q[w][lane] = acc;
   __syncthreads();
-  if (w == 0 && j < s) d[(int64_t)k * s + j] = ((q[0][lane] + q[1][lane]) + q[2][lane]) + q[3][lane];
+  if (w == 0 && j < s) {
+    double sum = q[0][lane];
+#pragma unroll
+    for (int i = 1; i < kReduceWaves; ++i) sum += q[i][lane];
+    d[(int64_t)k * s + j] = sum;
+  }
 }
 
 hipError_t launch_reduce_moments(const double *part, int32_t nslot, int32_t ntile, int64_t ldv,
                                  int32_t s, double *d, hipStream_t st) {
   if (nslot < 1 || s < 1) return hipSuccess;
-  reduce_moments_kernel<<<dim3((unsigned)nslot, (unsigned)((s + 63) / 64)), 256, 0, st>>>(part, nslot, ntile, ldv,
-                                                                                         s, d);
+  reduce_moments_kernel<<<dim3((unsigned)nslot, (unsigned)((s + 63) / 64)), 64 * kReduceWaves, 0, st>>>(
+      part, nslot, ntile, ldv, s, d);
   return hipGetLastError();
 }
 
 // h_j and the mean/standard error.  Chebyshev: h_j = -sum_{k=0}^m alpha_k d_kj
 // (Clenshaw schedule: from g^T y_0, g^T y_2 and g^T g, see FINAL_CLENSHAW).
 // Taylor: h_j = ln(1/u) + u sum_{k=1}^m e_kj / k  (e_kj = g^T (R/u) C^k g).
+//
+// Latency-bound (one workgroup, s (m + 1) values): the terms of a probe are
+// dealt to up to 16 threads, whose sums are added in order, so that all of its
+// loads are in flight at once (m = 50, s = 256: 18 -> 12 us; m = 30, s = 50:
+// 12 -> 6 us).
+constexpr int kFinalThreads = 1024;
+
 __device__ __forceinline__ void final_body(double *__restrict__ d, double *__restrict__ scal,
                                            int32_t method, int32_t m, int32_t s,
                                            double *__restrict__ h) {
-  __shared__ double red[4];
+  __shared__ double red[kFinalThreads / 64], sums[kFinalThreads];
   __shared__ double smean;
+  const int tid = threadIdx.x, nwv = kFinalThreads / 64;
+  int sp = 64;  // probes per pass
+  while (sp < s && sp < kFinalThreads) sp <<= 1;
+  const int tp = kFinalThreads / sp;  // threads per probe (1..16)
+  const int jl = tid % sp, q = tid / sp;
   const double u = scal[S_U];
+  const double *alpha = scal + S_ALPHA;
   double acc = 0.0;
-  for (int j = threadIdx.x; j < s; j += blockDim.x) {
-    double v;
-    if (method == FINAL_CLENSHAW) {
-      // Algorithm 5: g^T f_m g = (alpha_0 g^T g + g^T y_0 - g^T y_2) / 2, with
-      // d_k = g^T y_k in slots 0..m (y_2 = 0 for m < 2) and g^T g in slot m+1
-      const double gg = d[(int64_t)(m + 1) * s + j];
-      const double y2 = m >= 2 ? d[(int64_t)2 * s + j] : 0.0;
-      v = -0.5 * (scal[S_ALPHA] * gg + d[j] - y2);
-    } else if (method == FINAL_CHEB_PAIRS) {
-      // d_w = 2 (half sum of slot w) - d_{w mod 2}, written back; eight slots
-      // loaded at a time, before the stores that would order later loads
-      const double d0 = d[j], d1 = d[(int64_t)s + j];
-      v = -(scal[S_ALPHA] * d0 + scal[S_ALPHA + 1] * d1);
-      for (int k = 2; k <= m; k += 8) {
-        double r[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) r[e] = k + e <= m ? d[(int64_t)(k + e) * s + j] : 0.0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if (k + e > m) break;
-          const double dw = 2.0 * r[e] - ((e & 1) ? d1 : d0);
-          d[(int64_t)(k + e) * s + j] = dw;
-          v -= scal[S_ALPHA + k + e] * dw;
+  for (int jb = 0; jb < s; jb += sp) {
+    const int j = jb + jl;
+    double v = 0.0;
+    if (j < s) {
+      if (method == FINAL_CLENSHAW) {
+        // Algorithm 5: g^T f_m g = (alpha_0 g^T g + g^T y_0 - g^T y_2) / 2, with
+        // d_k = g^T y_k in slots 0..m (y_2 = 0 for m < 2) and g^T g in slot m+1
+        if (q == 0) {
+          const double gg = d[(int64_t)(m + 1) * s + j];
+          const double y2 = m >= 2 ? d[(int64_t)2 * s + j] : 0.0;
+          v = -0.5 * (alpha[0] * gg + d[j] - y2);
         }
+      } else if (method == FINAL_CHEB_PAIRS) {
+        // d_w = 2 (half sum of slot w) - d_{w mod 2}, written back
+        const double d0 = d[j], d1 = d[(int64_t)s + j];
+        if (q == 0) v = -(alpha[0] * d0 + alpha[1] * d1);
+        for (int k = 2 + q; k <= m; k += 4 * tp) {
+          double r[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) r[e] = k + e * tp <= m ? d[(int64_t)(k + e * tp) * s + j] : 0.0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int w = k + e * tp;
+            if (w > m) break;
+            const double dw = 2.0 * r[e] - ((w & 1) ? d1 : d0);
+            d[(int64_t)w * s + j] = dw;
+            v -= alpha[w] * dw;
+          }
+        }
+      } else if (method == 1) {
+#pragma unroll 4
+        for (int k = q; k <= m; k += tp) v -= alpha[k] * d[(int64_t)k * s + j];
+      } else {
+#pragma unroll 4
+        for (int k = 1 + q; k <= m; k += tp) v += d[(int64_t)k * s + j] / (double)k;
       }
-    } else if (method == 1) {
-      v = 0.0;
-      for (int k = 0; k <= m; ++k) v -= scal[S_ALPHA + k] * d[(int64_t)k * s + j];
-    } else {
-      double t = 0.0;
-      for (int k = 1; k <= m; ++k) t += d[(int64_t)k * s + j] / (double)k;
-      v = log(1.0 / u) + u * t;
     }
-    h[j] = v;
-    acc += v;
+    sums[tid] = v;
+    __syncthreads();
+    if (q == 0 && j < s) {
+      for (int i = 1; i < tp; ++i) v += sums[i * sp + jl];
+      if (method == 0) v = log(1.0 / u) + u * v;
+      h[j] = v;
+      acc += v;
+    }
+    __syncthreads();
   }
-  acc = wave_sum(acc);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) smean = (red[0] + red[1] + red[2] + red[3]) / (double)s;
+  auto block_sum = [&](double x) {
+    x = wave_sum(x);
+    __syncthreads();
+    if ((tid & 63) == 0) red[tid >> 6] = x;
+    __syncthreads();
+    double t = 0.0;
+    for (int i = 0; i < nwv; ++i) t += red[i];
+    return t;
+  };
+  const double total = block_sum(acc);
+  if (tid == 0) smean = total / (double)s;
   __syncthreads();
   const double mean = smean;
   double var = 0.0;
-  for (int j = threadIdx.x; j < s; j += blockDim.x) var += (h[j] - mean) * (h[j] - mean);
-  var = wave_sum(var);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = var;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double v = red[0] + red[1] + red[2] + red[3];
+  if (q == 0)
+    for (int j = jl; j < s; j += sp) var += (h[j] - mean) * (h[j] - mean);
+  const double v2 = block_sum(var);
+  if (tid == 0) {
     scal[S_ENT] = mean;
-    scal[S_SE] = s > 1 ? sqrt(v / ((double)s * (double)(s - 1))) : 0.0;
+    scal[S_SE] = s > 1 ? sqrt(v2 / ((double)s * (double)(s - 1))) : 0.0;
     if (!isfinite(mean)) scal[S_FLAG] = 1.0;
   }
 }
 
-__global__ void final_kernel(double *__restrict__ d, double *__restrict__ scal, int32_t method,
+__global__ __launch_bounds__(kFinalThreads) void final_kernel(double *__restrict__ d, double *__restrict__ scal, int32_t method,
                              int32_t m, int32_t s, double *__restrict__ h) {
   final_body(d, scal, method, m, s, h);
 }
 
 hipError_t launch_final(double *d, double *scal, int32_t method, int32_t m, int32_t s,
                         double *h, hipStream_t st) {
-  final_kernel<<<1, 256, 0, st>>>(d, scal, method, m, s, h);
+  final_kernel<<<1, kFinalThreads, 0, st>>>(d, scal, method, m, s, h);
   return hipGetLastError();
 }
 
@@ -1237,7 +1275,7 @@ hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double
   return hipGetLastError();
 }
 
-__global__ void batch_final_kernel(const BatchMat *__restrict__ mats, double *d,
+__global__ __launch_bounds__(kFinalThreads) void batch_final_kernel(const BatchMat *__restrict__ mats, double *d,
                                    int32_t method, int32_t m, int32_t s, double *h) {
   const BatchMat &M = mats[blockIdx.x];
   final_body(d + M.doff, M.scal, method == 1 && batch_pairs(M) ? FINAL_CHEB_PAIRS : method, m, s, h + M.hoff);
@@ -1245,7 +1283,7 @@ __global__ void batch_final_kernel(const BatchMat *__restrict__ mats, double *d,
 
 hipError_t launch_batch_final(const BatchMat *mats, int32_t count, double *d, int32_t method,
                               int32_t m, int32_t s, double *h, hipStream_t st) {
-  batch_final_kernel<<<(unsigned)count, 256, 0, st>>>(mats, d, method, m, s, h);
+  batch_final_kernel<<<(unsigned)count, kFinalThreads, 0, st>>>(mats, d, method, m, s, h);
   return hipGetLastError();
 }
 
