@@ -150,6 +150,24 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
   return (b & 7) * (nb >> 3) + (b >> 3);
 }
 
+// ||x||^2 of the previous product from its block triples, on every thread (all
+// threads of a block of 256 or 1024 call it; the order of power_reduce_body).
+// Called behind the product, so the loads are the only cost.
+__device__ __forceinline__ double power_prev_norm(const double *__restrict__ part, int32_t nblk) {
+  __shared__ double red[16];
+  double a = 0.0;
+  if (threadIdx.x < 256)
+    for (int i = threadIdx.x; i < nblk; i += 256) a += part[3 * i];
+  a = wave_sum(a);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+  __syncthreads();
+  return red[0] + red[1] + red[2] + red[3];
+}
+__device__ __forceinline__ double power_scale(const PowerPrev &p) {
+  if (p.part) return 1.0 / sqrt(power_prev_norm(p.part, p.nblk));
+  return p.norm ? 1.0 / sqrt(p.norm[0]) : 1.0;
+}
+
 // Block sums of y^2, xs.y, xs^2 over the rows a block produced (fixed order).
 __device__ __forceinline__ void block_power_partials(double yy, double xy, double xx,
                                                      double *part3, int64_t blk) {

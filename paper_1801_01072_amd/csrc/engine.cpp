@@ -247,6 +247,10 @@ StagingBuffer *staging_for(int dev) {
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 constexpr int kScalarDoubles = 8192;
+// Scratch tail of the scalar block for the power method's triples (behind the
+// tile traces of every R with so few triples).
+constexpr int kScalarPowerTail = 5120;
+static_assert(kScalarDoubles - kScalarPowerTail >= 3 * ent::kPowerSelfSum, "one product's triples");
 
 // Largest dense n whose symmetry is checked: the check keeps the traces of its
 // 64-row tiles in 4096 scratch scalars (an FP32 R of this order has 275 GB).
@@ -581,6 +585,34 @@ ent_status validate_options(const ent_options &o) {
 // ---------------------------------------------------------------------------
 // Power method on the device (Algorithm 4).  Leaves p~1 in scal[S_P1].
 // ---------------------------------------------------------------------------
+// The trials of a dense power method: start(trial) fills x0, product(it, prev,
+// part, &nblk) multiplies (x0 and x1 alternating) and leaves its block triples
+// in part.  With at most kPowerSelfSum triples (pblk, the most of a product)
+// the next product sums them itself, and those of consecutive products
+// alternate between part3 and the tail of the scalar block; else a kernel
+// sums them.
+template <typename Start, typename Product>
+hipError_t power_trials(int32_t t, int32_t q, int32_t pblk, double *part3, double *norm, double *scal, hipStream_t st,
+                        Start start, Product product) {
+  const bool self = pblk <= ent::kPowerSelfSum;
+  for (int32_t trial = 0; trial < q; ++trial) {
+    hipError_t e = start(trial);
+    ent::PowerPrev prev{};
+    double *part = part3;
+    int32_t nblk = 0;
+    for (int32_t it = 0; it <= t && e == hipSuccess; ++it) {  // t iterations + the Rayleigh product
+      part = self && (it & 1) ? scal + kScalarPowerTail : part3;
+      e = product(it, prev, part, &nblk);
+      if (e == hipSuccess && !self) e = ent::launch_power_reduce(part, nblk, norm, st);
+      prev = self ? ent::PowerPrev{nullptr, part, nblk} : ent::PowerPrev{norm, nullptr, 0};
+    }
+    if (e == hipSuccess)
+      e = self ? ent::launch_power_rq_sum(scal, part, nblk, trial, st) : ent::launch_power_rq(scal, norm, trial, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 template <typename T>
 ent_status enqueue_power(const ent_matrix *R, const T *Rc, int64_t ldr, int32_t t, int32_t q,
                          uint64_t seed, double *x0, double *x1, double *part3, double *norm,
@@ -596,6 +628,15 @@ ent_status enqueue_power(const ent_matrix *R, const T *Rc, int64_t ldr, int32_t 
     pf = pf < 1 ? 1 : (pf > ent::kPowerMaxFuse ? ent::kPowerMaxFuse : pf);
   }
   int32_t nl = 0;
+  if (R->layout == ENT_DENSE) {
+    HIP_TRY(power_trials(t, q, ent::power_blocks_dense(n), part3, norm, scal, st, [&](int32_t trial) {
+      return ent::launch_power_start(x0, n, seed, trial, st);
+    }, [&](int32_t it, const ent::PowerPrev &prev, double *part, int32_t *nblk) {
+      return ent::launch_power_gemv<T>(Rc, ldr, n, it & 1 ? x1 : x0, prev, it & 1 ? x0 : x1, part, nblk, st);
+    }));
+    if (launches) *launches = q * (t + 1);
+    return ENT_OK;
+  }
   for (int32_t trial = 0; trial < q; ++trial) {
     HIP_TRY(ent::launch_power_start(x0, n, seed, trial, st));
     double *xin = x0, *xout = x1;
@@ -622,9 +663,7 @@ ent_status enqueue_power(const ent_matrix *R, const T *Rc, int64_t ldr, int32_t 
         continue;
       }
       ++it;
-      if (R->layout == ENT_DENSE) {
-        HIP_TRY(ent::launch_power_gemv<T>(Rc, ldr, n, xin, in_norm, xout, part3, &nblk, st));
-      } else if (band) {
+      if (band) {
         // banded CSR: the same product on the slabs of the step kernel
         nblk = ent::power_blocks_csr(n);
         HIP_TRY(ent::launch_power_band<T>(band, hp, n, xin, in_norm, xout, part3, nblk, st));
@@ -652,19 +691,12 @@ ent_status enqueue_power_split(const uint16_t *hi, const uint16_t *lo, int64_t n
   // the split is zero beyond n, and so must be the vectors it multiplies
   HIP_TRY(ent::launch_fill(x0, n_pad, 0.0, st));
   HIP_TRY(ent::launch_fill(x1, n_pad, 0.0, st));
-  for (int32_t trial = 0; trial < q; ++trial) {
-    HIP_TRY(ent::launch_power_start(x0, n, seed, trial, st));
-    double *xin = x0, *xout = x1;
-    const double *in_norm = nullptr;
-    for (int32_t it = 0; it <= t; ++it) {
-      int32_t nblk = 0;
-      HIP_TRY(ent::launch_power_gemv_split(hi, lo, n_pad, n, xin, in_norm, xout, part3, ypart, &nblk, st));
-      HIP_TRY(ent::launch_power_reduce(part3, nblk, norm, st));
-      std::swap(xin, xout);
-      in_norm = norm;
-    }
-    HIP_TRY(ent::launch_power_rq(scal, norm, trial, st));
-  }
+  HIP_TRY(power_trials(t, q, ent::power_blocks_split(n_pad), part3, norm, scal, st, [&](int32_t trial) {
+    return ent::launch_power_start(x0, n, seed, trial, st);
+  }, [&](int32_t it, const ent::PowerPrev &prev, double *part, int32_t *nblk) {
+    return ent::launch_power_gemv_split(hi, lo, n_pad, n, it & 1 ? x1 : x0, prev, it & 1 ? x0 : x1, part, ypart, nblk,
+                                        st);
+  }));
   return ENT_OK;
 }
 
@@ -1949,7 +1981,7 @@ struct ent_graph_s {
   void *ws = nullptr;
   size_t ws_bytes = 0;
   char *Rc = nullptr, *G = nullptr, *VA = nullptr, *VB = nullptr;
-  double *x0 = nullptr, *x1 = nullptr, *p0 = nullptr, *norm = nullptr;
+  double *x0 = nullptr, *x1 = nullptr, *p0 = nullptr;
   double *part = nullptr, *d = nullptr, *h = nullptr, *scal = nullptr;
   double *host_scal = nullptr;
   // BF16x3 batches: split of every R, bf16 probe blocks, FP32 products
@@ -2080,16 +2112,15 @@ ent_status enqueue_batch(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
     if (pe) pe->power_begin = pe->mark();
     for (int32_t trial = 0; trial < o.power_trials; ++trial) {
       HIP_TRY(ent::launch_batch_power_start(g->mats_d, count, g->max_n, g->x0, trial, st));
-      double *xin = g->x0, *xout = g->x1;
-      const double *in_norm = nullptr;
+      double *xin = g->x0, *xout = g->x1, *pout = g->p0;
+      const double *pprev = nullptr;
       for (int32_t it = 0; it <= o.power_iters; ++it) {
-        HIP_TRY(ent::launch_batch_power_gemv<T>(g->mats_d, g->ptiles_d, g->nptiles, xin, in_norm,
-                                                xout, g->p0, st));
-        HIP_TRY(ent::launch_batch_power_reduce(g->mats_d, count, g->p0, g->norm, st));
+        pout = it & 1 ? g->part : g->p0;  // the steps' partials are not in use yet
+        HIP_TRY(ent::launch_batch_power_gemv<T>(g->mats_d, g->ptiles_d, g->nptiles, xin, pprev, xout, pout, st));
         std::swap(xin, xout);
-        in_norm = g->norm;
+        pprev = pout;
       }
-      HIP_TRY(ent::launch_batch_power_rq(g->mats_d, count, g->norm, trial, st));
+      HIP_TRY(ent::launch_batch_power_rq(g->mats_d, count, pout, trial, st));
     }
     if (pe) {
       pe->power_end = pe->mark();
@@ -2136,16 +2167,16 @@ ent_status enqueue_batch_bf16(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
     HIP_TRY(ent::launch_fill(g->x1, g->xlen, 0.0, st));
     for (int32_t trial = 0; trial < o.power_trials; ++trial) {
       HIP_TRY(ent::launch_batch_power_start(g->mats_d, count, g->max_n, g->x0, trial, st));
-      double *xin = g->x0, *xout = g->x1;
-      const double *in_norm = nullptr;
+      double *xin = g->x0, *xout = g->x1, *pout = g->p0;
+      const double *pprev = nullptr;
       for (int32_t it = 0; it <= o.power_iters; ++it) {
+        pout = it & 1 ? g->part : g->p0;  // the steps' partials are not in use yet
         HIP_TRY(ent::launch_batch_power_split(g->mats_d, g->ptiles_d, g->nptiles, g->Ahi, g->Alo, xin,
-                                              in_norm, xout, g->p0, st));
-        HIP_TRY(ent::launch_batch_power_reduce(g->mats_d, count, g->p0, g->norm, st));
+                                              pprev, xout, pout, st));
         std::swap(xin, xout);
-        in_norm = g->norm;
+        pprev = pout;
       }
-      HIP_TRY(ent::launch_batch_power_rq(g->mats_d, count, g->norm, trial, st));
+      HIP_TRY(ent::launch_batch_power_rq(g->mats_d, count, pout, trial, st));
     }
     if (pe) {
       pe->power_end = pe->mark();
@@ -2480,6 +2511,7 @@ ent_status batch_create(const ent_matrix *Rs, int32_t count, int32_t method, int
       roff += n * M.ldr;
     }
     voff += M.n_pad * g->ldv;
+    // (in all no less than the triples of a product, 3 pblk <= n_pad each)
     poff += (int64_t)g->nslot * M.ntile * g->ldv;
     xoff += M.n_pad;
     pboff += 3 * (int64_t)M.pblk;
@@ -2523,7 +2555,6 @@ ent_status batch_create(const ent_matrix *Rs, int32_t count, int32_t method, int
   cv.add(&g->x0, (size_t)xoff);
   cv.add(&g->x1, (size_t)xoff);
   cv.add(&g->p0, (size_t)pboff);
-  cv.add(&g->norm, (size_t)4 * count);
   cv.add(&g->part, (size_t)poff);
   cv.add(&g->d, (size_t)count * g->nslot * s);
   cv.add(&g->h, (size_t)count * s);

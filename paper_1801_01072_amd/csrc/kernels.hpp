@@ -133,6 +133,16 @@ hipError_t launch_sign_gen(uint32_t *signs, int64_t n, int32_t s, int64_t ldv, u
 
 // ---- power method (Algorithm 4) ------------------------------------------
 hipError_t launch_power_start(double *x, int64_t n, uint64_t seed, int32_t trial, hipStream_t st);
+// The previous product's norm: where a product has few workgroups, each of
+// the next product's sums the previous triples itself (PowerPrev::part), which
+// saves a launch per product; else launch_power_reduce sums them into norm
+// (PowerPrev::norm).  Both null: no scaling.
+struct PowerPrev {
+  const double *norm;  // ||x||^2 at norm[0]
+  const double *part;  // nblk block triples
+  int32_t nblk;
+};
+constexpr int32_t kPowerSelfSum = 1024;  // most triples summed by every workgroup
 // y = (R x) / ||x_prev||, ||x_prev||^2 = in_norm[0] (in_norm null: scale 1);
 // part3[3*b + {0,1,2}] = per-block sums of y^2, xs.y, xs^2, xs = x/||x_prev||.
 // *nblk receives the number of blocks.
@@ -140,7 +150,7 @@ int32_t power_blocks_dense(int64_t n);
 int32_t power_blocks_csr(int64_t n);
 template <typename T>
 hipError_t launch_power_gemv(const T *R, int64_t ldr, int64_t n, const double *x,
-                             const double *in_norm, double *y, double *part3, int32_t *nblk,
+                             const PowerPrev &prev, double *y, double *part3, int32_t *nblk,
                              hipStream_t st);
 template <typename T>
 // (nnz only picks the lanes per row: 1, 2, 4 or 8 by the mean row length)
@@ -152,6 +162,8 @@ hipError_t launch_power_reduce(const double *part3, int32_t nblk, double *norm3,
 // p~ of trial = norm3[1]/norm3[2] of its final product; scal[S_P1] keeps the
 // maximum over trials (trial 0 overwrites).
 hipError_t launch_power_rq(double *scal, const double *norm3, int32_t trial, hipStream_t st);
+// The same from the block triples of that product.
+hipError_t launch_power_rq_sum(double *scal, const double *part3, int32_t nblk, int32_t trial, hipStream_t st);
 // u = u_fixed > 0 ? u_fixed : min(1, c p~1); interval scalars and, for
 // Chebyshev, alpha_0..alpha_m (closed form of Lemma 3 when lo = 0,
 // interpolant at m+1 Chebyshev points otherwise).
@@ -448,7 +460,7 @@ hipError_t launch_bf16x3_gemm(const Bf16GemmArgs &a, hipStream_t st);
 int32_t power_blocks_split(int64_t n_pad);
 int32_t power_split_parts(int64_t n_pad);
 hipError_t launch_power_gemv_split(const uint16_t *hi, const uint16_t *lo, int64_t n_pad, int64_t n,
-                                   const double *x, const double *in_norm, double *y, double *part3,
+                                   const double *x, const PowerPrev &prev, double *y, double *part3,
                                    double *ypart, int32_t *nblk, hipStream_t st);
 hipError_t launch_bf16x3_epilogue(const Bf16EpiArgs &a, hipStream_t st);
 int32_t bf16x3_epilogue_blocks(int64_t n_pad);
@@ -465,7 +477,7 @@ hipError_t launch_batch_probe_t(const BatchMat *mats, const int2 *tiles, int32_t
                                 hipStream_t st);
 hipError_t launch_batch_power_split(const BatchMat *mats, const int2 *ptiles, int32_t nptiles,
                                     const uint16_t *Ahi, const uint16_t *Alo, const double *x,
-                                    const double *norm, double *y, double *pout, hipStream_t st);
+                                    const double *pprev, double *y, double *pout, hipStream_t st);
 // ---- persistent batch steps: one launch walks a schedule of work items ------
 // Item (matrix b, row tile t, step k, 0).  Every matrix belongs to one XCD and
 // its items form part of that XCD's segment of the schedule, which only the
@@ -547,14 +559,13 @@ hipError_t launch_batch_probes(const BatchMat *mats, int32_t count, int64_t max_
                                int32_t s, int64_t ldv, int32_t dist, hipStream_t st);
 hipError_t launch_batch_power_start(const BatchMat *mats, int32_t count, int64_t max_n, double *x,
                                     int32_t trial, hipStream_t st);
-// norm holds 4 doubles per matrix (reduced triple of the previous product).
+// pprev: the triples of the previous product (null: none); pout: this one's
+// (another buffer).
 template <typename T>
 hipError_t launch_batch_power_gemv(const BatchMat *mats, const int2 *ptiles, int32_t nptiles,
-                                   const double *x, const double *norm, double *y, double *pout,
+                                   const double *x, const double *pprev, double *y, double *pout,
                                    hipStream_t st);
-hipError_t launch_batch_power_reduce(const BatchMat *mats, int32_t count, const double *p,
-                                     double *norm, hipStream_t st);
-hipError_t launch_batch_power_rq(const BatchMat *mats, int32_t count, const double *norm,
+hipError_t launch_batch_power_rq(const BatchMat *mats, int32_t count, const double *p,
                                  int32_t trial, hipStream_t st);
 hipError_t launch_batch_setup(const BatchMat *mats, int32_t count, int32_t method, int32_t m,
                               double c, double u_fixed, double lo, hipStream_t st,

@@ -616,11 +616,10 @@ template <int W>
 __device__ __forceinline__ void power_split_band(const uint16_t *__restrict__ hi,
                                                  const uint16_t *__restrict__ lo, int64_t n_pad,
                                                  int64_t n, const double *__restrict__ x,
-                                                 const double *__restrict__ in_norm,
+                                                 const PowerPrev &prev,
                                                  double *__restrict__ y, double *__restrict__ part3,
                                                  int64_t band) {
   __shared__ double red[W][32];
-  const double sc = in_norm ? 1.0 / sqrt(in_norm[0]) : 1.0;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t nkb = n_pad / 16;
   const uint16_t *H = hi + band * nkb * 512 + 8 * lane;
@@ -647,6 +646,7 @@ __device__ __forceinline__ void power_split_band(const uint16_t *__restrict__ hi
   acc += acc2;
   acc += __shfl_xor(acc, 32, 64);  // the two 8-column halves of a row
   if (lane < 32) red[w][lane] = acc;
+  const double sc = power_scale(prev);
   __syncthreads();
   double yy = 0.0, xy = 0.0, xx = 0.0;
   if (w == 0 && lane < 32) {
@@ -667,11 +667,10 @@ __device__ __forceinline__ void power_split_band(const uint16_t *__restrict__ hi
 __global__ __launch_bounds__(1024) void power_gemv_split_kernel(const uint16_t *__restrict__ hi,
                                                                const uint16_t *__restrict__ lo,
                                                                int64_t n_pad, int64_t n,
-                                                               const double *__restrict__ x,
-                                                               const double *__restrict__ in_norm,
+                                                               const double *__restrict__ x, PowerPrev prev,
                                                                double *__restrict__ y,
                                                                double *__restrict__ part3) {
-  power_split_band<16>(hi, lo, n_pad, n, x, in_norm, y, part3, blockIdx.x);
+  power_split_band<16>(hi, lo, n_pad, n, x, prev, y, part3, blockIdx.x);
 }
 
 // Batch: one workgroup of 4 waves per (matrix, 32-row band) (the matrices are
@@ -680,18 +679,19 @@ __global__ __launch_bounds__(256) void batch_power_split_kernel(const BatchMat *
                                                                 const int2 *__restrict__ ptiles,
                                                                 const uint16_t *Ahi,
                                                                 const uint16_t *Alo, const double *x,
-                                                                const double *norm, double *y,
+                                                                const double *pprev, double *y,
                                                                 double *pout) {
   const int2 t = ptiles[blockIdx.x];
   const BatchMat &M = mats[t.x];
-  power_split_band<4>(Ahi + M.aoff, Alo + M.aoff, M.n_pad, M.n, x + M.xoff, norm ? norm + 4 * t.x : nullptr,
-                      y + M.xoff, pout + M.pboff, t.y);
+  const PowerPrev prev = {nullptr, pprev ? pprev + M.pboff : nullptr, M.pblk};
+  power_split_band<4>(Ahi + M.aoff, Alo + M.aoff, M.n_pad, M.n, x + M.xoff, prev, y + M.xoff, pout + M.pboff, t.y);
 }
 
 hipError_t launch_batch_power_split(const BatchMat *mats, const int2 *ptiles, int32_t nptiles,
                                     const uint16_t *Ahi, const uint16_t *Alo, const double *x,
-                                    const double *norm, double *y, double *pout, hipStream_t st) {
-  batch_power_split_kernel<<<(unsigned)nptiles, 256, 0, st>>>(mats, ptiles, Ahi, Alo, x, norm, y, pout);
+                                    const double *pprev, double *y, double *pout, hipStream_t st) {
+  if (pprev == pout) return hipErrorInvalidValue;
+  batch_power_split_kernel<<<(unsigned)nptiles, 256, 0, st>>>(mats, ptiles, Ahi, Alo, x, pprev, y, pout);
   return hipGetLastError();
 }
 
@@ -755,11 +755,10 @@ __global__ __launch_bounds__(256) void power_split_part_kernel(const uint16_t *_
 
 __global__ __launch_bounds__(256) void power_split_combine_kernel(const double *__restrict__ ypart,
                                                                   int32_t nparts, int64_t n_pad, int64_t n,
-                                                                  const double *__restrict__ x,
-                                                                  const double *__restrict__ in_norm,
+                                                                  const double *__restrict__ x, PowerPrev prev,
                                                                   double *__restrict__ y,
                                                                   double *__restrict__ part3) {
-  const double sc = in_norm ? 1.0 / sqrt(in_norm[0]) : 1.0;
+  const double sc = power_scale(prev);
   const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
   double yy = 0.0, xy = 0.0, xx = 0.0;
   if (r < n) {
@@ -775,8 +774,9 @@ __global__ __launch_bounds__(256) void power_split_combine_kernel(const double *
 }
 
 hipError_t launch_power_gemv_split(const uint16_t *hi, const uint16_t *lo, int64_t n_pad, int64_t n,
-                                   const double *x, const double *in_norm, double *y, double *part3,
+                                   const double *x, const PowerPrev &prev, double *y, double *part3,
                                    double *ypart, int32_t *nblk, hipStream_t st) {
+  if (prev.part == part3) return hipErrorInvalidValue;  // read while this product's are written
   const int32_t parts = power_split_parts(n_pad);
   if (parts > 1) {
     if (!ypart) return hipErrorInvalidValue;
@@ -784,12 +784,12 @@ hipError_t launch_power_gemv_split(const uint16_t *hi, const uint16_t *lo, int64
                                                                                           parts);
     const int32_t blocks = (int32_t)((n_pad + 255) / 256);
     *nblk = blocks;
-    power_split_combine_kernel<<<(unsigned)blocks, 256, 0, st>>>(ypart, parts, n_pad, n, x, in_norm, y, part3);
+    power_split_combine_kernel<<<(unsigned)blocks, 256, 0, st>>>(ypart, parts, n_pad, n, x, prev, y, part3);
     return hipGetLastError();
   }
   const int32_t blocks = power_blocks_split(n_pad);
   *nblk = blocks;
-  power_gemv_split_kernel<<<(unsigned)blocks, 1024, 0, st>>>(hi, lo, n_pad, n, x, in_norm, y, part3);
+  power_gemv_split_kernel<<<(unsigned)blocks, 1024, 0, st>>>(hi, lo, n_pad, n, x, prev, y, part3);
   return hipGetLastError();
 }
 

@@ -108,16 +108,14 @@ hipError_t launch_power_start(double *x, int64_t n, uint64_t seed, int32_t trial
   return hipGetLastError();
 }
 
-// Dense y = (R x)/||x_prev|| (||x_prev||^2 = in_norm[0]; null: no scaling).
+// Dense y = (R x)/||x_prev||.
 // Each wave owns 2 consecutive rows; lanes stride over 16-byte vectors of
 // both rows, two vectors in flight per row (FP64 accumulation).
 template <typename T>
 __device__ __forceinline__ void power_gemv_body(const T *__restrict__ R, int64_t ldr, int64_t n,
-                                                const double *__restrict__ x,
-                                                const double *__restrict__ in_norm,
+                                                const double *__restrict__ x, const PowerPrev &prev,
                                                 double *__restrict__ y, double *__restrict__ part3,
                                                 int64_t blk) {
-  const double sc = in_norm ? 1.0 / sqrt(in_norm[0]) : 1.0;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   constexpr int VEC = 16 / sizeof(T);
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
@@ -164,6 +162,7 @@ __device__ __forceinline__ void power_gemv_body(const T *__restrict__ R, int64_t
     if (ok1) a1 += (double)R1[k] * x[k];
   }
   const double s0 = wave_sum(a0 + b0), s1 = wave_sum(a1 + b1);
+  const double sc = power_scale(prev);
   double yy = 0.0, xy = 0.0, xx = 0.0;
   if (lane == 0) {
     if (ok0) {
@@ -187,10 +186,9 @@ __device__ __forceinline__ void power_gemv_body(const T *__restrict__ R, int64_t
 template <typename T>
 __global__ __launch_bounds__(256) void power_gemv_kernel(const T *__restrict__ R, int64_t ldr,
                                                          int64_t n, const double *__restrict__ x,
-                                                         const double *__restrict__ in_norm,
-                                                         double *__restrict__ y,
+                                                         PowerPrev prev, double *__restrict__ y,
                                                          double *__restrict__ part3) {
-  power_gemv_body<T>(R, ldr, n, x, in_norm, y, part3, blockIdx.x);
+  power_gemv_body<T>(R, ldr, n, x, prev, y, part3, blockIdx.x);
 }
 
 int32_t power_blocks_dense(int64_t n) { return (int32_t)((n + 7) / 8); }
@@ -201,18 +199,19 @@ int32_t power_blocks_csr(int64_t n) {
 
 template <typename T>
 hipError_t launch_power_gemv(const T *R, int64_t ldr, int64_t n, const double *x,
-                             const double *in_norm, double *y, double *part3, int32_t *nblk,
+                             const PowerPrev &prev, double *y, double *part3, int32_t *nblk,
                              hipStream_t st) {
+  if (prev.part == part3) return hipErrorInvalidValue;  // read while this product's are written
   const int32_t blocks = power_blocks_dense(n);
   *nblk = blocks;
-  power_gemv_kernel<T><<<(unsigned)blocks, 256, 0, st>>>(R, ldr, n, x, in_norm, y, part3);
+  power_gemv_kernel<T><<<(unsigned)blocks, 256, 0, st>>>(R, ldr, n, x, prev, y, part3);
   return hipGetLastError();
 }
 template hipError_t launch_power_gemv<double>(const double *, int64_t, int64_t, const double *,
-                                              const double *, double *, double *, int32_t *,
+                                              const PowerPrev &, double *, double *, int32_t *,
                                               hipStream_t);
 template hipError_t launch_power_gemv<float>(const float *, int64_t, int64_t, const double *,
-                                             const double *, double *, double *, int32_t *,
+                                             const PowerPrev &, double *, double *, int32_t *,
                                              hipStream_t);
 
 // CSR: L lanes per row (L = 1, 2, 4 or 8 by the mean row length), 256 / L
@@ -325,6 +324,19 @@ __device__ __forceinline__ void power_rq_body(double *__restrict__ scal,
 __global__ void power_rq_kernel(double *__restrict__ scal, const double *__restrict__ norm3,
                                 int32_t trial) {
   power_rq_body(scal, norm3, trial);
+}
+
+__global__ __launch_bounds__(256) void power_rq_sum_kernel(double *__restrict__ scal,
+                                                           const double *__restrict__ part3, int32_t nblk,
+                                                           int32_t trial) {
+  __shared__ double norm3[3];
+  power_reduce_body(part3, nblk, norm3);
+  power_rq_body(scal, norm3, trial);  // by the thread that wrote norm3
+}
+
+hipError_t launch_power_rq_sum(double *scal, const double *part3, int32_t nblk, int32_t trial, hipStream_t st) {
+  power_rq_sum_kernel<<<1, 256, 0, st>>>(scal, part3, nblk, trial);
+  return hipGetLastError();
 }
 
 hipError_t launch_power_rq(double *scal, const double *norm3, int32_t trial, hipStream_t st) {
@@ -1202,19 +1214,20 @@ hipError_t launch_batch_power_start(const BatchMat *mats, int32_t count, int64_t
 template <typename T>
 __global__ __launch_bounds__(256) void batch_power_gemv_kernel(const BatchMat *__restrict__ mats,
                                                                const int2 *__restrict__ ptiles,
-                                                               const double *x, const double *norm,
+                                                               const double *x, const double *pprev,
                                                                double *y, double *pout) {
   const int2 t = ptiles[blockIdx.x];
   const BatchMat &M = mats[t.x];
-  power_gemv_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, norm ? norm + 4 * t.x : nullptr,
-                     y + M.xoff, pout + M.pboff, t.y);
+  const PowerPrev prev = {nullptr, pprev ? pprev + M.pboff : nullptr, M.pblk};
+  power_gemv_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, prev, y + M.xoff, pout + M.pboff, t.y);
 }
 
 template <typename T>
 hipError_t launch_batch_power_gemv(const BatchMat *mats, const int2 *ptiles, int32_t nptiles,
-                                   const double *x, const double *norm, double *y, double *pout,
+                                   const double *x, const double *pprev, double *y, double *pout,
                                    hipStream_t st) {
-  batch_power_gemv_kernel<T><<<(unsigned)nptiles, 256, 0, st>>>(mats, ptiles, x, norm, y, pout);
+  if (pprev == pout) return hipErrorInvalidValue;
+  batch_power_gemv_kernel<T><<<(unsigned)nptiles, 256, 0, st>>>(mats, ptiles, x, pprev, y, pout);
   return hipGetLastError();
 }
 template hipError_t launch_batch_power_gemv<double>(const BatchMat *, const int2 *, int32_t,
@@ -1224,27 +1237,18 @@ template hipError_t launch_batch_power_gemv<float>(const BatchMat *, const int2 
                                                    const double *, const double *, double *, double *,
                                                    hipStream_t);
 
-// One block per matrix: reduce its block triples into norm[4*b .. 4*b+2].
-__global__ __launch_bounds__(256) void batch_power_reduce_kernel(const BatchMat *__restrict__ mats,
-                                                                 const double *p, double *norm) {
+// One block per matrix: its final product's triples and Rayleigh quotient.
+__global__ __launch_bounds__(256) void batch_power_rq_kernel(const BatchMat *__restrict__ mats, const double *p,
+                                                             int32_t trial) {
+  __shared__ double norm3[3];
   const BatchMat &M = mats[blockIdx.x];
-  power_reduce_body(p + M.pboff, M.pblk, norm + 4 * blockIdx.x);
+  power_reduce_body(p + M.pboff, M.pblk, norm3);
+  power_rq_body(M.scal, norm3, trial);
 }
 
-hipError_t launch_batch_power_reduce(const BatchMat *mats, int32_t count, const double *p,
-                                     double *norm, hipStream_t st) {
-  batch_power_reduce_kernel<<<(unsigned)count, 256, 0, st>>>(mats, p, norm);
-  return hipGetLastError();
-}
-
-__global__ void batch_power_rq_kernel(const BatchMat *__restrict__ mats, const double *norm,
-                                      int32_t trial) {
-  power_rq_body(mats[blockIdx.x].scal, norm + 4 * blockIdx.x, trial);
-}
-
-hipError_t launch_batch_power_rq(const BatchMat *mats, int32_t count, const double *norm,
+hipError_t launch_batch_power_rq(const BatchMat *mats, int32_t count, const double *p,
                                  int32_t trial, hipStream_t st) {
-  batch_power_rq_kernel<<<(unsigned)count, 64, 0, st>>>(mats, norm, trial);
+  batch_power_rq_kernel<<<(unsigned)count, 256, 0, st>>>(mats, p, trial);
   return hipGetLastError();
 }
 
