@@ -852,11 +852,12 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
                                      : (banded ? ent::band_step_waves(n, hp, sizeof(T) == 8)
                                                : ent::csr_step_blocks(n, sizeof(T) == 8)));
   // dense steps whose tile grid is smaller than the chip split K
+  const int32_t direct = dense ? ent::dense_direct_tiles(n, s) : 0;
   const int32_t ksplit = dense ? ent::dense_step_splits(n, ntile, ldv, bn) : 1;
   const int64_t kper = round_up((n + ksplit - 1) / ksplit, 32);
   // per-probe dot partials: one per row tile (64 rows), or per 16 rows when
-  // the split-K epilogue forms them
-  const int32_t npart = ksplit > 1 ? (int32_t)(n_pad / 16) : ntile;
+  // the split-K epilogue or the small-problem kernel forms them
+  const int32_t npart = ksplit > 1 || direct ? (int32_t)(n_pad / 16) : ntile;
   const int32_t nslot = m + 1 + (clenshaw ? 1 : 0);
   const bool rad = o.probe_dist == ENT_RADEMACHER;
   const bool use_power = !(o.u_fixed > 0);
@@ -912,6 +913,8 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
       cv.add(&VC, (size_t)n_pad * ldb);
       cv.add(&VD, (size_t)n_pad * ldb);
     }
+    // (also where the small-problem kernel needs none: what the workspace limit
+    // refuses does not depend on the kernel)
     if (ksplit > 1) cv.add(&party, (size_t)ksplit * n_pad * ldv);
     cv.add(&part, (size_t)nslot * npart * ldv);
     cv.add(&d, (size_t)nslot * s);
@@ -1182,8 +1185,8 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
         a.Vk = Vk; a.Vkm1 = Vm; a.Vkp1 = Vw; a.G = G;
         a.scal = scal; a.c1 = q.c1; a.c2 = q.c2; a.cw = q.cw; a.dot_y = q.dot_y;
         a.slot = q.slot; a.slot_gg = q.slot_gg; a.part = part; a.ntile = ntile; a.bn = bn;
-        a.pair = pairs; a.slot_b = q.slot_b; a.cg = q.cg;
-        a.ksplit = ksplit; a.kper = kper; a.party = party; a.nptile = npart;
+        a.pair = pairs; a.slot_b = q.slot_b; a.cg = q.cg; a.direct = direct; a.s = s;
+        a.ksplit = direct ? 1 : ksplit; a.kper = kper; a.party = party; a.nptile = npart;
         HIP_TRY(dense_step(a));
       } else if (banded) {
         ent::BandStepArgs a{};

@@ -73,6 +73,10 @@ struct DenseStepArgs {
   int64_t kper;       // multiple of 32
   void *party;
   int32_t nptile;     // split-K: 16-row partial tiles (part is [slot][nptile][ldv])
+  // direct > 0: the small-problem kernel with 16 * direct probes per workgroup
+  // (dense_direct_tiles; part as with split-K); s: probes in use
+  int32_t direct;
+  int32_t s;
 };
 
 struct CsrStepArgs {
@@ -235,6 +239,9 @@ hipError_t launch_dense_split_epilogue(const DenseStepArgs &a, hipStream_t st);
 // 512 workgroups (two per CU): a power of two up to 16 while every split
 // keeps >= 256 columns.
 int32_t dense_step_splits(int64_t n, int32_t ntile, int64_t ldv, int32_t bn);
+// 16-probe tiles per workgroup of the small-problem step kernel (1, 2 or 4),
+// or 0 where the tiled kernel is the faster one.
+int32_t dense_direct_tiles(int64_t n, int32_t s);
 template <typename T>
 hipError_t launch_csr_step(const CsrStepArgs &a, hipStream_t st);
 int32_t csr_step_blocks(int64_t n, int32_t fp64);

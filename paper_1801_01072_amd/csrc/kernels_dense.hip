@@ -468,6 +468,193 @@ __global__ __launch_bounds__(256) void dense_split_epilogue_kernel(DenseStepArgs
   }
 }
 
+// ---------------------------------------------------------------------------
+// Small problems: one step in one launch of short workgroups.  The tiled kernel
+// above walks K chunk by chunk through LDS, a memory latency per chunk, with
+// few workgroups when n is small (n = 512, 50 probes: 16), and a second launch
+// adds its K-splits.  Here a workgroup owns 16 rows x 16 NS probes and its
+// kDirectWaves waves share out K in chunks of 32 columns; a wave loads its
+// operands from memory (L2 at these sizes) straight into MFMA order, two
+// chunks' loads in flight together, the waves' sums meet in LDS, and the
+// epilogue's operands were loaded before the products began.  What is left is
+// about three memory latencies per step.  R is read once per probe group and
+// V_k once per row tile, from L2; see dense_direct_tiles for where that stops
+// paying.
+//
+// Lane (m, q) of a wave holds R[row m][k0 + VEC (4 h + q) ..] in piece h, so
+// the four lanes of a row read 64 contiguous bytes; MFMA k-slot q of call
+// (h, e) is column k0 + VEC (4 h + q) + e, for V_k likewise.
+// ---------------------------------------------------------------------------
+namespace {
+constexpr int kDirectWaves = 8;
+}  // namespace
+
+template <typename T, int NS>
+__global__ __launch_bounds__(64 * kDirectWaves) void dense_direct_kernel(DenseStepArgs a) {
+  using M = Mfma16<T>;
+  using v4 = typename M::v4;
+  constexpr int W = kDirectWaves, VEC = 16 / (int)sizeof(T), KC = 32, H = KC / (4 * VEC);
+  constexpr int PAIRS = 4 * NS;               // (register, probe tile) pairs
+  constexpr int PPW = (PAIRS + W - 1) / W;    // pairs finished per wave
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  __shared__ T sums[W][NS][4][64];
+  __shared__ double red[3][NS][4][16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m16 = lane & 15, kq = lane >> 4;
+  const int nct = (a.s + 16 * NS - 1) / (16 * NS);
+  const int blk = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+  const int tp = blk / nct;                   // 16-row tile
+  const int64_t col0 = (int64_t)(blk % nct) * 16 * NS;
+  const int64_t n = a.n, ldv = a.ldv;
+  const T *__restrict__ R = (const T *)a.R;
+  const T *__restrict__ Vk = (const T *)a.Vk;
+  const T *Vkm1 = (const T *)a.Vkm1;
+  const T *__restrict__ G = (const T *)a.G;
+  T *Vkp1 = (T *)a.Vkp1;
+  const bool use_m1 = (a.cw != 0.0) && Vkm1;
+  const bool pair = a.pair != 0, want_gg = a.slot_gg >= 0, want_b = pair && a.slot_b >= 0;
+  const bool use_cg = a.cg != nullptr, use_g = use_cg || !pair;
+  // epilogue operands of this wave's pairs: (tile c, register r)
+  T vk[PPW], vm[PPW], gv[PPW];
+#pragma unroll
+  for (int i = 0; i < PPW; ++i) {
+    const int q = w + W * i;
+    if (q < PAIRS) {
+      const int64_t off = ((int64_t)tp * 16 + M::drow(kq, q & 3)) * ldv + col0 + 16 * (q >> 2) + m16;
+      vk[i] = Vk[off];
+      vm[i] = use_m1 ? Vkm1[off] : T(0);
+      gv[i] = use_g ? G[off] : vk[i];
+    }
+  }
+  const int64_t arow = (int64_t)tp * 16 + m16;
+  const T *__restrict__ Ar = R + (arow < n ? arow : n - 1) * a.ldr;
+  const T *__restrict__ Vc = Vk + col0 + m16;
+  v4 acc[NS];
+#pragma unroll
+  for (int c = 0; c < NS; ++c) acc[c] = v4{0, 0, 0, 0};
+  struct Chunk {
+    vec_t av[H];
+    T bv[H][VEC][NS];
+  };
+  auto load = [&](Chunk &f, int64_t k0) {
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int64_t k = k0 + VEC * (4 * h + kq);
+      if (k + VEC <= n) {
+        f.av[h] = *(const vec_t *)(Ar + k);
+      } else {
+        // V_k is zero in rows >= n, R's padding is not ours to read
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) f.av[h][e] = k + e < n ? Ar[k + e] : T(0);
+      }
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+#pragma unroll
+        for (int c = 0; c < NS; ++c) f.bv[h][e][c] = Vc[(k + e) * ldv + 16 * c];
+    }
+  };
+  auto mul = [&](const Chunk &f) {
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+#pragma unroll
+        for (int c = 0; c < NS; ++c) acc[c] = M::mma(f.av[h][e], f.bv[h][e][c], acc[c]);
+  };
+  // chunks w, w + W, ... (rows of V_k exist up to n rounded up to 64)
+  const int nch = (int)((n + KC - 1) / KC);
+  Chunk f0, f1;
+  for (int c = w; c < nch; c += 2 * W) {
+    load(f0, (int64_t)c * KC);
+    const bool two = c + W < nch;
+    if (two) load(f1, (int64_t)(c + W) * KC);
+    mul(f0);
+    if (two) mul(f1);
+  }
+#pragma unroll
+  for (int c = 0; c < NS; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sums[w][c][r][lane] = acc[c][r];
+  __syncthreads();
+  const T ta = (T)a.scal[S_A];
+  const T tb = (T)(a.c2 * a.scal[S_B]);
+  const T tc1 = (T)a.c1, tcw = (T)a.cw;
+  const T tcg = use_cg ? (T)a.cg[0] : T(0);
+#pragma unroll
+  for (int i = 0; i < PPW; ++i) {
+    const int q = w + W * i;
+    if (q >= PAIRS) break;
+    const int r = q & 3, c = q >> 2;
+    const int64_t row = (int64_t)tp * 16 + M::drow(kq, r);
+    T sum = sums[0][c][r][lane];
+#pragma unroll
+    for (int x = 1; x < W; ++x) sum += sums[x][c][r][lane];
+    const T y = row < n ? ta * sum : T(0);
+    T z = tc1 * y + tb * vk[i];
+    if (use_m1) z += tcw * vm[i];
+    if (use_cg) z += tcg * gv[i];
+    if (Vkp1) Vkp1[row * ldv + col0 + 16 * c + m16] = z;
+    const double g = (double)(pair ? vk[i] : gv[i]);
+    const double dq = (double)(a.dot_y ? y : z);
+    double ds = g * dq, gs = g * g, bs = (double)z * dq;
+    ds += __shfl_xor(ds, 16, 64);
+    ds += __shfl_xor(ds, 32, 64);
+    gs += __shfl_xor(gs, 16, 64);
+    gs += __shfl_xor(gs, 32, 64);
+    bs += __shfl_xor(bs, 16, 64);
+    bs += __shfl_xor(bs, 32, 64);
+    if (kq == 0) {
+      red[0][c][r][m16] = ds;
+      red[1][c][r][m16] = gs;
+      red[2][c][r][m16] = bs;
+    }
+  }
+  __syncthreads();
+  if (tid < 16 * NS * 3) {
+    const int k = tid / (16 * NS), col = tid % (16 * NS);
+    const int32_t slot = k == 0 ? a.slot : (k == 1 ? a.slot_gg : a.slot_b);
+    if (k == 0 || (k == 1 ? want_gg : want_b)) {
+      const double(*x)[16] = red[k][col >> 4];
+      const int m = col & 15;
+      a.part[((int64_t)slot * a.nptile + tp) * ldv + col0 + col] = x[0][m] + x[1][m] + x[2][m] + x[3][m];
+    }
+  }
+}
+
+template <typename T>
+static hipError_t launch_dense_direct(const DenseStepArgs &a, hipStream_t st) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  if (a.slot < 0 || a.s < 1 || a.s > a.ldv || a.nptile != a.ntile * 4 || a.ldr % VEC != 0 ||
+      ((uintptr_t)a.R % 16) != 0 || (a.s + 16 * a.direct - 1) / (16 * a.direct) * (16 * a.direct) > a.ldv)
+    return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)(a.nptile * ((a.s + 16 * a.direct - 1) / (16 * a.direct)));
+  switch (a.direct) {
+    case 1: dense_direct_kernel<T, 1><<<grid, 64 * kDirectWaves, 0, st>>>(a); break;
+    case 2: dense_direct_kernel<T, 2><<<grid, 64 * kDirectWaves, 0, st>>>(a); break;
+    case 4: dense_direct_kernel<T, 4><<<grid, 64 * kDirectWaves, 0, st>>>(a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// One round of workgroups, as narrow as that allows (narrow ones are the
+// quicker: at n = 512, 50 probes, FP64 6.6 us a step with 16 probes each, 7.9
+// with 32, 12.3 with 64; past one round a second one costs as much as the
+// first: n = 1400, 50 probes 16.7 us with 352 workgroups, 15.6 with 176), and
+// up to 4.2e8 elements n^2 s, where the tiled kernel's reuse of R and V_k from
+// LDS overtakes.  Both sides, us a step, direct against tiled, FP64 (FP32 alike):
+// n = 96, 32 probes 4 / 10; 512, 50: 6.6 / 15.8; 1024, 128: 13.3 / 27.6;
+// 1800, 128 (4.1e8): 30.7 / 44.0; 2048, 128 (5.4e8): 35.3 / 31.3; 1400, 256
+// (5.0e8): 39.4 / 37.3; 3000, 50 (5.8e8): 42.7 / 36.9.
+int32_t dense_direct_tiles(int64_t n, int32_t s) {
+  const int64_t rows = (n + 63) / 64 * 4, probes = (s + 15) / 16;
+  if ((double)n * (double)n * 16.0 * (double)probes > 4.2e8) return 0;
+  for (int32_t ns = 1; ns <= 4; ns *= 2)
+    if (rows * ((probes + ns - 1) / ns) <= 256) return ns;
+  return 0;
+}
+
 int32_t dense_step_splits(int64_t n, int32_t ntile, int64_t ldv, int32_t bn) {
   const int64_t tiles = (int64_t)ntile * (ldv / bn);
   int32_t ks = 1;
@@ -575,6 +762,7 @@ template hipError_t launch_dense_split_epilogue<float>(const DenseStepArgs &, hi
 
 template <typename T>
 hipError_t launch_dense_step(const DenseStepArgs &a, hipStream_t st, bool epilogue) {
+  if (a.direct > 0) return launch_dense_direct<T>(a, st);
   const int ntn = (int)(a.ldv / a.bn);
   if (a.ksplit > 1 && (!a.party || a.kper % 32 != 0 || (int64_t)a.ksplit * a.kper < a.n ||
                        a.nptile != a.ntile * 4))

@@ -61,8 +61,13 @@ def check(orc, R, mul, n, method, m, s, seed, dist, precision, label, **kw):
 
 @pytest.mark.parametrize("precision", ["f64", "f32", "bf16x3"])
 @pytest.mark.parametrize("n,s,m", [(1, 1, 2), (2, 3, 1), (63, 17, 2), (64, 64, 3), (65, 65, 4), (130, 128, 9),
-                                   (300, 129, 8), (2048, 8, 5), (3000, 20, 6)])
+                                   (300, 129, 8), (2048, 8, 5), (3000, 20, 6), (300, 1500, 4), (1500, 300, 4),
+                                   (2100, 130, 5)])
 def test_dense(orc, precision, n, s, m):
+    # sizes on both sides of the lines between the step kernels: 16, 32 and 64
+    # probes per workgroup of the small-problem kernel (130 x 128, 3000 x 20,
+    # 300 x 129), the tiled kernel whole (300 x 1500) and with K split (1500 x
+    # 300, 2100 x 130)
     R = W.dense_density(W.spectrum_exp(n, max(n / 5.0, 1.0)), 100 + n)
     cases = [("symmetric", R)]
     if n > 1:
@@ -84,7 +89,8 @@ def test_dense(orc, precision, n, s, m):
 
 
 def test_dense_strided_storage(orc):
-    # the check reads R as it is stored: odd leading dimension, FP32 storage
+    # the check reads R as it is stored (odd leading dimension, FP32 storage);
+    # n is no multiple of the 32 columns a wave takes at a time
     n, m, s = 200, 7, 33
     R = W.dense_density(W.spectrum_exp(n, 40.0), 5).astype(np.float32)
     for off in (0.0, 0.05):
