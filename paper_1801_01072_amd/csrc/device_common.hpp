@@ -113,6 +113,12 @@ __device__ __forceinline__ double wave_sum(double v) {
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
+// Per column of a 16 x 16 MFMA result: the four lanes l, l + 16, l + 32, l + 48.
+__device__ __forceinline__ double column_sum(double v) {
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  return v;
+}
 
 // ---------------------------------------------------------------------------
 // MFMA 16x16x4 for FP64 and FP32.  Operand layout (per lane l of the wave):

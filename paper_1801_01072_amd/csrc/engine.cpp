@@ -628,6 +628,11 @@ ent_status enqueue_power(const ent_matrix *R, const T *Rc, int64_t ldr, int32_t 
     pf = pf < 1 ? 1 : (pf > ent::kPowerMaxFuse ? ent::kPowerMaxFuse : pf);
   }
   int32_t nl = 0;
+  if (R->layout == ENT_DENSE && n <= ent::kDenseResidentMax) {
+    HIP_TRY(ent::launch_power_resident<T>(Rc, ldr, n, t, q, seed, scal, st));
+    if (launches) *launches = 1;
+    return ENT_OK;
+  }
   if (R->layout == ENT_DENSE) {
     HIP_TRY(power_trials(t, q, ent::power_blocks_dense(n), part3, norm, scal, st, [&](int32_t trial) {
       return ent::launch_power_start(x0, n, seed, trial, st);
@@ -852,12 +857,15 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
                                      : (banded ? ent::band_step_waves(n, hp, sizeof(T) == 8)
                                                : ent::csr_step_blocks(n, sizeof(T) == 8)));
   // dense steps whose tile grid is smaller than the chip split K
-  const int32_t direct = dense ? ent::dense_direct_tiles(n, s) : 0;
+  // small problems: the whole recurrence in one launch (R in the registers of a
+  // workgroup; not where the degree may be extended), or a short launch per step
+  bool resident = dense && n <= ent::kDenseResidentMax && !(hook && hook->stages);
+  int32_t direct = dense && !resident ? ent::dense_direct_tiles(n, s) : 0;
   const int32_t ksplit = dense ? ent::dense_step_splits(n, ntile, ldv, bn) : 1;
   const int64_t kper = round_up((n + ksplit - 1) / ksplit, 32);
   // per-probe dot partials: one per row tile (64 rows), or per 16 rows when
-  // the split-K epilogue or the small-problem kernel forms them
-  const int32_t npart = ksplit > 1 || direct ? (int32_t)(n_pad / 16) : ntile;
+  // the split-K epilogue or a small-problem kernel forms them
+  int32_t npart = resident ? ent::dense_resident_tiles(n) : ksplit > 1 || direct ? (int32_t)(n_pad / 16) : ntile;
   const int32_t nslot = m + 1 + (clenshaw ? 1 : 0);
   const bool rad = o.probe_dist == ENT_RADEMACHER;
   const bool use_power = !(o.u_fixed > 0);
@@ -927,6 +935,15 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     // the multi-step launches need two more V blocks: without room for
     // them, one step per launch
     band_pairs = tri_fused = false;
+    cv = Carve();
+    plan(cv);
+    rc = ws.ensure(cv.total());
+  }
+  if (rc == ENT_ENOMEM && (direct || resident) && ksplit == 1) {
+    // their dot partials are four times those of the tiled kernel
+    direct = 0;
+    resident = false;
+    npart = ntile;
     cv = Carve();
     plan(cv);
     rc = ws.ensure(cv.total());
@@ -1037,7 +1054,7 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   const T *Vk = dense || !rad ? G : nullptr;  // null: expand the sign block
   const T *Vkm1 = nullptr;
   T *bufs[2] = {VA, VB};
-  if (clenshaw) {
+  if (clenshaw && !resident) {
     // y_{m+1} = y_{m+2} = 0; y_k = alpha_k g + 2X y_{k+1} - y_{k+2}, k = m..0,
     // each y_k written over y_{k+2} (same element, same thread)
     HIP_TRY(ent::launch_zero(VA, sizeof(T) * (size_t)n_pad * ldb, st));
@@ -1161,7 +1178,15 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     }
     pe.steps_end = pe.mark();
   }
-  int32_t k_begin = (band_pairs || tri_fused) ? nsteps : 0;
+  if (resident) {
+    ent::DenseResidentArgs ra{};
+    ra.R = Rt; ra.ldr = ldr; ra.n = n; ra.ldv = ldv; ra.G = G; ra.scal = scal; ra.part = part; ra.s = s;
+    ra.method = clenshaw ? ent::FINAL_CLENSHAW : method; ra.m = m; ra.nsteps = nsteps; ra.pair = pairs;
+    HIP_TRY(ent::launch_dense_resident<T>(ra, st));
+    pe.steps_end = pe.mark();
+    pe.logical_steps = nsteps;
+  }
+  int32_t k_begin = (band_pairs || tri_fused || resident) ? nsteps : 0;
   const int32_t final_code = clenshaw ? ent::FINAL_CLENSHAW
                              : pairs && method == ENT_CHEBYSHEV ? ent::FINAL_CHEB_PAIRS : method;
   int32_t m_run = stg ? stg->deg[0] : m;  // degree of the estimate

@@ -179,6 +179,31 @@ hipError_t launch_setup_interval(double *scal, int32_t method, int32_t m, double
 // S_NORM alone (random projection: singular values scaled by it).
 hipError_t launch_set_norm(double *scal, double norm_div, hipStream_t st);
 
+// ---- matrices that fit in the registers of one workgroup --------------------
+// Largest n of the kernels below (R's rows in registers; 256 would spill at the
+// 128 registers of a full workgroup), and their 16-row tiles: n padded to 32.
+constexpr int64_t kDenseResidentMax = 192;
+inline int32_t dense_resident_tiles(int64_t n) { return (int32_t)((n + 31) / 32 * 2); }
+// Every trial of the power method (Algorithm 4) in one launch of one
+// workgroup: scal[S_P1] as launch_power_start .. launch_power_rq leave it.
+template <typename T>
+hipError_t launch_power_resident(const T *R, int64_t ldr, int64_t n, int32_t t, int32_t q, uint64_t seed,
+                                 double *scal, hipStream_t st);
+// Every step of the recurrence in one launch, 16 probes per workgroup: the
+// forward schedule of nsteps products (pair: dots in pairs), or Clenshaw's
+// m + 1 (method 2).  G: n rounded up to 32 rows of ldv, zero outside n x s.
+// part: [slot][dense_resident_tiles(n)][ldv], every slot up to s written.
+struct DenseResidentArgs {
+  const void *R;
+  int64_t ldr, n, ldv;
+  const void *G;
+  const double *scal;
+  double *part;
+  int32_t s, method, m, nsteps, pair;
+};
+template <typename T>
+hipError_t launch_dense_resident(const DenseResidentArgs &a, hipStream_t st);
+
 // ---- trace check -----------------------------------------------------------
 template <typename T>
 hipError_t launch_trace_dense(const T *R, int64_t ldr, int64_t n, double *scal, hipStream_t st);

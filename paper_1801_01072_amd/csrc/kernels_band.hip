@@ -388,8 +388,7 @@ __global__ __launch_bounds__(256) void power_band_kernel(const T *__restrict__ b
       const double xv = (col >= 0 && col < n) ? x[col] : 0.0;
       acc += (double)a[k] * xv;
     }
-    acc += __shfl_xor(acc, 16, 64);
-    acc += __shfl_xor(acc, 32, 64);
+    acc = column_sum(acc);
     const int64_t row = 16 * b + (lane & 15);
     if (q == 0 && row < n) {
       const double yv = sc * acc;
@@ -475,8 +474,7 @@ __global__ __launch_bounds__(256) void power_band_fused_kernel(const T *__restri
             xv = ring[w][j - 1][(col >> 4) & 3][col & 15];
           acc += (double)a[k] * xv;
         }
-        acc += __shfl_xor(acc, 16, 64);
-        acc += __shfl_xor(acc, 32, 64);
+        acc = column_sum(acc);
         const int64_t row = 16 * bb + c;
         double v = acc;
         if (j == 0) v *= sc0;
@@ -674,13 +672,10 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_step_kernel(BandStepArgs
   // per probe: the four row groups (lanes c, c+16, c+32, c+48), fixed order
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    ds[t] += __shfl_xor(ds[t], 16, 64);
-    ds[t] += __shfl_xor(ds[t], 32, 64);
-    gs[t] += __shfl_xor(gs[t], 16, 64);
-    gs[t] += __shfl_xor(gs[t], 32, 64);
+    ds[t] = column_sum(ds[t]);
+    gs[t] = column_sum(gs[t]);
     if (pair) {
-      bs[t] += __shfl_xor(bs[t], 16, 64);
-      bs[t] += __shfl_xor(bs[t], 32, 64);
+      bs[t] = column_sum(bs[t]);
     }
   }
   if (q == 0) {
@@ -979,19 +974,14 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_pair_kernel(BandPairArgs
   // per probe: the four row groups (lanes c, c+16, c+32, c+48), fixed order
 #pragma unroll
   for (int t = 0; t < NP; ++t) {
-    dA[t] += __shfl_xor(dA[t], 16, 64);
-    dA[t] += __shfl_xor(dA[t], 32, 64);
-    dB[t] += __shfl_xor(dB[t], 16, 64);
-    dB[t] += __shfl_xor(dB[t], 32, 64);
+    dA[t] = column_sum(dA[t]);
+    dB[t] = column_sum(dB[t]);
     if (GG) {
-      gs[t] += __shfl_xor(gs[t], 16, 64);
-      gs[t] += __shfl_xor(gs[t], 32, 64);
+      gs[t] = column_sum(gs[t]);
     }
     if (pair) {
-      eA[t] += __shfl_xor(eA[t], 16, 64);
-      eA[t] += __shfl_xor(eA[t], 32, 64);
-      eB[t] += __shfl_xor(eB[t], 16, 64);
-      eB[t] += __shfl_xor(eB[t], 32, 64);
+      eA[t] = column_sum(eA[t]);
+      eB[t] = column_sum(eB[t]);
     }
   }
   if (q == 0) {

@@ -337,12 +337,9 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
             if (want_b) bs += (double)z * q;
           }
         }
-      ds += __shfl_xor(ds, 16, 64);
-      ds += __shfl_xor(ds, 32, 64);
-      gs += __shfl_xor(gs, 16, 64);
-      gs += __shfl_xor(gs, 32, 64);
-      bs += __shfl_xor(bs, 16, 64);
-      bs += __shfl_xor(bs, 32, 64);
+      ds = column_sum(ds);
+      gs = column_sum(gs);
+      bs = column_sum(bs);
       if (kq == 0) {
         red[0][w][16 * c + m16] = ds;
         red[1][w][16 * c + m16] = gs;
@@ -598,12 +595,9 @@ __global__ __launch_bounds__(64 * kDirectWaves) void dense_direct_kernel(DenseSt
     const double g = (double)(pair ? vk[i] : gv[i]);
     const double dq = (double)(a.dot_y ? y : z);
     double ds = g * dq, gs = g * g, bs = (double)z * dq;
-    ds += __shfl_xor(ds, 16, 64);
-    ds += __shfl_xor(ds, 32, 64);
-    gs += __shfl_xor(gs, 16, 64);
-    gs += __shfl_xor(gs, 32, 64);
-    bs += __shfl_xor(bs, 16, 64);
-    bs += __shfl_xor(bs, 32, 64);
+    ds = column_sum(ds);
+    gs = column_sum(gs);
+    bs = column_sum(bs);
     if (kq == 0) {
       red[0][c][r][m16] = ds;
       red[1][c][r][m16] = gs;
@@ -621,6 +615,190 @@ __global__ __launch_bounds__(64 * kDirectWaves) void dense_direct_kernel(DenseSt
     }
   }
 }
+
+// ---------------------------------------------------------------------------
+// Matrices that fit in the registers of one workgroup (n <= 192): a launch per step or per power product costs more than its work
+// (n = 96 in FP64: 3.7 us and 4.2 us a launch, and about 1 us between two).
+// The probes are independent, so a workgroup runs the whole recurrence of 16
+// of them with no exchange beyond its own barrier, R held in MFMA order in the
+// registers of its waves (wave w: rows 16 w .., n padded to 32), V_k in LDS, V_{k-1} and the
+// wave's own rows of V_k in registers; one barrier per step.  One workgroup
+// likewise runs the whole power method, a few threads to a row.
+// ---------------------------------------------------------------------------
+template <typename T, int NP>
+__global__ __launch_bounds__(4 * NP) void dense_resident_kernel(DenseResidentArgs a) {
+  using M = Mfma16<T>;
+  using v4 = typename M::v4;
+  constexpr int NT = NP / 4;  // k-steps of four columns
+  __shared__ T V[2][NP * 16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m16 = lane & 15, kq = lane >> 4;
+  const int64_t n = a.n, ldv = a.ldv, col = (int64_t)blockIdx.x * 16 + m16;
+  const int row0 = 16 * w;
+  T ra[NT];
+  {
+    const int64_t r = row0 + m16;
+    const T *Rr = (const T *)a.R + (r < n ? r : 0) * a.ldr;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) ra[t] = r < n && 4 * t + kq < n ? Rr[4 * t + kq] : T(0);
+  }
+  const bool clen = a.method == FINAL_CLENSHAW, pair = a.pair != 0;
+  T g[4], vk[4], vm[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    g[r] = ((const T *)a.G)[(int64_t)(row0 + M::drow(kq, r)) * ldv + col];
+    vk[r] = clen ? T(0) : g[r];
+    vm[r] = T(0);
+    V[0][(row0 + M::drow(kq, r)) * 16 + m16] = vk[r];
+  }
+  const double sa = a.scal[S_A], sb = a.scal[S_B];
+  const T ta = (T)sa;
+  __syncthreads();
+  // column sums of a value over the wave's 16 rows, into the wave's tile of a slot
+  auto put = [&](int32_t slot, double x) {
+    x = column_sum(x);
+    if (kq == 0) a.part[((int64_t)slot * (NP / 16) + w) * ldv + col] = x;
+  };
+  for (int k = 0; k < a.nsteps; ++k) {
+    StepRule q{};
+    T cg = T(0);
+    if (clen) {
+      q.c1 = 2.0; q.c2 = -2.0; q.cw = -1.0;  // y_{m+2} = 0 on the first step
+      q.slot = a.m - k;
+      q.slot_gg = k == 0 ? a.m + 1 : -1;
+      q.slot_b = -1;
+      cg = (T)a.scal[S_ALPHA + a.m - k];
+    } else {
+      q = step_rule(a.method, a.m, k, pair ? 2 * a.nsteps : a.nsteps, pair);
+    }
+    const T *Vb = V[k & 1];
+    v4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+#pragma unroll
+    for (int t = 0; t < NT; t += 2) {
+      acc0 = M::mma(ra[t], Vb[(4 * t + kq) * 16 + m16], acc0);
+      acc1 = M::mma(ra[t + 1], Vb[(4 * t + 4 + kq) * 16 + m16], acc1);
+    }
+    const T c1 = (T)q.c1, tb = (T)(q.c2 * sb), cw = (T)q.cw;
+    double ds = 0.0, gs = 0.0, bs = 0.0;
+    T *Vo = V[(k + 1) & 1];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const T y = ta * (acc0[r] + acc1[r]);
+      T z = c1 * y + tb * vk[r];
+      z += cw * vm[r];
+      if (clen) z += cg * g[r];
+      const double p = (double)(pair ? vk[r] : g[r]), dq = (double)(q.dot_y ? y : z);
+      ds += p * dq;
+      gs += p * p;
+      bs += (double)z * dq;
+      Vo[(row0 + M::drow(kq, r)) * 16 + m16] = z;
+      vm[r] = vk[r];
+      vk[r] = z;
+    }
+    put(q.slot, ds);
+    if (q.slot_gg >= 0) put(q.slot_gg, gs);
+    if (q.slot_b >= 0) put(q.slot_b, bs);
+    __syncthreads();
+  }
+}
+
+template <typename T>
+hipError_t launch_dense_resident(const DenseResidentArgs &a, hipStream_t st) {
+  if (a.n < 1 || a.n > kDenseResidentMax || a.s < 1 || (a.s + 15) / 16 * 16 > a.ldv ||
+      a.nsteps < 1 || (a.pair && a.method == FINAL_CLENSHAW))
+    return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)((a.s + 15) / 16);
+  switch (dense_resident_tiles(a.n)) {
+    case 2: dense_resident_kernel<T, 32><<<grid, 128, 0, st>>>(a); break;
+    case 4: dense_resident_kernel<T, 64><<<grid, 256, 0, st>>>(a); break;
+    case 6: dense_resident_kernel<T, 96><<<grid, 384, 0, st>>>(a); break;
+    case 8: dense_resident_kernel<T, 128><<<grid, 512, 0, st>>>(a); break;
+    case 10: dense_resident_kernel<T, 160><<<grid, 640, 0, st>>>(a); break;
+    default: dense_resident_kernel<T, 192><<<grid, 768, 0, st>>>(a); break;
+  }
+  return hipGetLastError();
+}
+template hipError_t launch_dense_resident<double>(const DenseResidentArgs &, hipStream_t);
+template hipError_t launch_dense_resident<float>(const DenseResidentArgs &, hipStream_t);
+
+// TPR threads per row of R, columns sub, sub + TPR, ... each.  The iterate of
+// product k is scaled by the norm of product k - 1, as in the launches per
+// product; the products of a trial follow each other over one barrier.
+template <typename T, int NP, int TPR>
+__global__ __launch_bounds__(NP * TPR) void power_resident_kernel(const T *__restrict__ R, int64_t ldr, int64_t n,
+                                                                  int32_t t, int32_t q, uint64_t seed,
+                                                                  double *__restrict__ scal) {
+  constexpr int C = NP / TPR, NW = NP * TPR / 64;
+  __shared__ double xs[2][NP], red[2][NW], fin[2][NW];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int row = tid / TPR, sub = tid % TPR;
+  T r[C];
+#pragma unroll
+  for (int i = 0; i < C; ++i) r[i] = row < n && sub + TPR * i < n ? R[row * ldr + sub + TPR * i] : T(0);
+  for (int32_t trial = 0; trial < q; ++trial) {
+    __syncthreads();
+    if (sub == 0) xs[0][row] = row < n ? rademacher(seed, 1u, row, trial) : 0.0;
+    __syncthreads();
+    double sc = 1.0;
+    for (int32_t it = 0; it <= t; ++it) {
+      const double *x = xs[it & 1];
+      double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+      for (int i = 0; i < C; i += 2) {
+        a0 += (double)r[i] * x[sub + TPR * i];
+        a1 += (double)r[i + 1] * x[sub + TPR * (i + 1)];
+      }
+      double s0 = a0 + a1;
+#pragma unroll
+      for (int off = 1; off < TPR; off <<= 1) s0 += __shfl_xor(s0, off, 64);
+      const double yv = sub == 0 ? sc * s0 : 0.0;
+      const double yy = wave_sum(yv * yv);
+      if (lane == 0) red[it & 1][w] = yy;
+      if (sub == 0) xs[(it + 1) & 1][row] = yv;
+      if (it == t) {
+        const double xv = sub == 0 ? sc * x[row] : 0.0;
+        const double xy = wave_sum(xv * yv), xx = wave_sum(xv * xv);
+        if (lane == 0) {
+          fin[0][w] = xy;
+          fin[1][w] = xx;
+        }
+      }
+      __syncthreads();
+      double nn = 0.0;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) nn += red[it & 1][i];
+      sc = 1.0 / sqrt(nn);
+    }
+    if (tid == 0) {
+      double xy = 0.0, xx = 0.0;
+      for (int i = 0; i < NW; ++i) {
+        xy += fin[0][i];
+        xx += fin[1][i];
+      }
+      const double rq = xy / xx;
+      if (trial == 0 || rq > scal[S_P1]) scal[S_P1] = rq;
+    }
+  }
+}
+
+template <typename T>
+hipError_t launch_power_resident(const T *R, int64_t ldr, int64_t n, int32_t t, int32_t q, uint64_t seed,
+                                 double *scal, hipStream_t st) {
+  const int64_t np = (n + 63) / 64 * 64;
+  if (n < 1 || n > kDenseResidentMax || q < 1 || t < 0) return hipErrorInvalidValue;
+  if (np == 64)
+    power_resident_kernel<T, 64, 16><<<1, 1024, 0, st>>>(R, ldr, n, t, q, seed, scal);
+  else if (np == 128)
+    power_resident_kernel<T, 128, 8><<<1, 1024, 0, st>>>(R, ldr, n, t, q, seed, scal);
+  else
+    power_resident_kernel<T, 192, 4><<<1, 768, 0, st>>>(R, ldr, n, t, q, seed, scal);
+  return hipGetLastError();
+}
+template hipError_t launch_power_resident<double>(const double *, int64_t, int64_t, int32_t, int32_t, uint64_t,
+                                                  double *, hipStream_t);
+template hipError_t launch_power_resident<float>(const float *, int64_t, int64_t, int32_t, int32_t, uint64_t,
+                                                 double *, hipStream_t);
 
 template <typename T>
 static hipError_t launch_dense_direct(const DenseStepArgs &a, hipStream_t st) {

@@ -62,11 +62,11 @@ def check(orc, R, mul, n, method, m, s, seed, dist, precision, label, **kw):
 @pytest.mark.parametrize("precision", ["f64", "f32", "bf16x3"])
 @pytest.mark.parametrize("n,s,m", [(1, 1, 2), (2, 3, 1), (63, 17, 2), (64, 64, 3), (65, 65, 4), (130, 128, 9),
                                    (300, 129, 8), (2048, 8, 5), (3000, 20, 6), (300, 1500, 4), (1500, 300, 4),
-                                   (2100, 130, 5)])
+                                   (2100, 130, 5), (128, 16, 31), (129, 33, 6), (192, 40, 7), (193, 40, 7)])
 def test_dense(orc, precision, n, s, m):
-    # sizes on both sides of the lines between the step kernels: 16, 32 and 64
-    # probes per workgroup of the small-problem kernel (130 x 128, 3000 x 20,
-    # 300 x 129), the tiled kernel whole (300 x 1500) and with K split (1500 x
+    # sizes on both sides of the lines between the step kernels: R in registers
+    # (up to 192, padded to 64), 16, 32 and 64 probes per workgroup of the
+    # small-problem kernel (193 x 40, 3000 x 20, 300 x 129), the tiled kernel whole (300 x 1500) and with K split (1500 x
     # 300, 2100 x 130)
     R = W.dense_density(W.spectrum_exp(n, max(n / 5.0, 1.0)), 100 + n)
     cases = [("symmetric", R)]
@@ -86,6 +86,47 @@ def test_dense(orc, precision, n, s, m):
     with pytest.raises(ent.EntropyError) as e:
         ent.entropy_estimate(torch.from_numpy(A).to(DEV), "chebyshev", m, s, 1, precision=precision, u_fixed=0.9)
     assert e.value.status in (ent.ENOTDENSITY, ent.ENUMERIC)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 150, 192, 193])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_small_power_method_and_clenshaw(orc, n, dtype):
+    # one launch for every trial and product, and for Clenshaw's schedule
+    R = W.dense_density(W.spectrum_exp(n, max(n / 3.0, 1.0)), 7 + n).astype(dtype)
+    Rd = torch.from_numpy(R).to(DEV)
+    for t, q in ((0, 1), (1, 2), (20, 3)):
+        assert ent.power_method(Rd, t, q, 5) == pytest.approx(orc.power_method(R, t, q, 5), rel=1e-12)
+    prec = "f64" if dtype == np.float64 else "f32"
+    for m, s in ((1, 5), (2, 16), (9, 17)):
+        _, per, mom = ent.entropy_estimate_detail(Rd, "chebyshev", m, s, 3, precision=prec, probe_dist="gaussian",
+                                                  flags=ent.FLAG_CLENSHAW, trace_tol=1e-4)
+        ref = orc.estimate(R, 1, m, s, 3, dist=1)
+        e = float(np.max(np.abs(per - ref.per_probe)) / max(np.mean(np.abs(ref.per_probe)), 1.0))
+        print(f"[small clenshaw {prec} n={n} m={m} s={s}] per-probe {e:.2e}", flush=True)
+        assert e <= tol_for(prec)
+
+
+def test_small_problem_within_the_workspace_limit():
+    """The small-problem kernels need more partial sums than the tiled one: a
+    limit that held the estimate before still holds it (on the tiled kernel)."""
+    n, m, s = 300, 400, 64
+    R = torch.from_numpy(W.dense_density(W.spectrum_exp(n, 60.0), 3)).to(DEV)
+    free = ent.entropy_estimate_detail(R, "chebyshev", m, s, 2)
+    blocks = 3 * 320 * 64 * 8                # G and two V blocks
+    part = (m + 1) * 64 * 8                  # one tile's partials
+    ent.release_workspace()
+    try:
+        ent.set_workspace_limit(blocks + 5 * part + (m + 1) * s * 8 + 200_000)
+        held = ent.entropy_estimate_detail(R, "chebyshev", m, s, 2)
+        ent.set_workspace_limit(blocks + 5 * part)
+        with pytest.raises(ent.EntropyError) as e:
+            ent.entropy_estimate(R, "chebyshev", m, s, 2)
+        assert e.value.status == ent.ENOMEM
+    finally:
+        ent.set_workspace_limit(0)
+        ent.release_workspace()
+    assert held[0].entropy == pytest.approx(free[0].entropy, rel=1e-12)
+    assert np.max(np.abs(held[2] - free[2])) <= 1e-10 * float(np.max(free[2]))
 
 
 def test_dense_strided_storage(orc):
