@@ -106,17 +106,43 @@ __device__ __forceinline__ double srht_entry(uint64_t seed, int64_t j, int64_t t
 }
 
 // ---------------------------------------------------------------------------
-// wave64 reductions (fixed butterfly order: deterministic)
+// wave64 reductions (fixed butterfly order: deterministic).  The exchanges are
+// register moves (lane-group swaps between the rows of 16 lanes, DPP rotations
+// within one) rather than trips through the LDS crossbar.  The order is that of
+// the butterfly xor 32, 16, 8, 4, 2, 1: once the sums repeat every 2 k lanes, a
+// rotation by k is the exchange with lane xor k.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// The sum of the two rows of 16 lanes of each half (xor 16), then of the two
+// halves (xor 32).
+__device__ __forceinline__ double sum_xor16(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return __longlong_as_double(((long long)h[0] << 32) | l[0]) + __longlong_as_double(((long long)h[1] << 32) | l[1]);
+}
+__device__ __forceinline__ double sum_xor32(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return __longlong_as_double(((long long)h[0] << 32) | l[0]) + __longlong_as_double(((long long)h[1] << 32) | l[1]);
 }
 // Per column of a 16 x 16 MFMA result: the four lanes l, l + 16, l + 32, l + 48.
-__device__ __forceinline__ double column_sum(double v) {
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
+__device__ __forceinline__ double column_sum(double v) { return sum_xor32(sum_xor16(v)); }
+__device__ __forceinline__ double wave_sum(double v) {
+  v = sum_xor16(sum_xor32(v));
+  v += dpp_move<0x128>(v);  // row_ror:8
+  v += dpp_move<0x124>(v);  // row_ror:4
+  v += dpp_move<0x122>(v);  // row_ror:2
+  v += dpp_move<0x121>(v);  // row_ror:1
   return v;
 }
 
