@@ -147,7 +147,14 @@ struct DeviceWorkspace {
   // behind it (made on first use, released with the workspace).
   int32_t *word = nullptr;
   hipEvent_t word_ready = nullptr;
+  // Pinned memory that the last kernel of an estimate stores its results to
+  // (kResultDoubles; made on first use, released with the workspace).
+  double *results = nullptr;
 };
+
+// Results up to this size (1 MiB) reach the host through pinned memory; larger
+// ones, where a copy's fixed cost no longer counts, by copies.
+constexpr size_t kResultDoubles = 131072;
 
 std::mutex g_ws_mu;
 std::map<int, DeviceWorkspace *> g_ws;
@@ -466,6 +473,17 @@ struct WsLease {
     }
     return ws->word;
   }
+  // Pinned memory for `count` doubles of results, or null (too many, the
+  // no-allocation entry point, no pinned memory left): they are then copied.
+  double *result_block(size_t count) {
+    if (fixed || count > kResultDoubles) return nullptr;
+    if (!ws->results &&
+        hipHostMalloc((void **)&ws->results, kResultDoubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      ws->results = nullptr;
+    }
+    return ws->results;
+  }
   ent_status ensure(size_t need) {
     if (fixed) {
       if (need > ent::kNoAllocScratchBytes)
@@ -504,6 +522,34 @@ struct DeviceAnswer {
     HIP_TRY(hipMemcpyAsync(v, dev, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     return ENT_OK;
+  }
+};
+
+// An estimate's results on their way to the caller: head (the scalar block's
+// first 16), alpha_0..m, h and, if wanted, the moments, either through the
+// pinned block the last kernel stored them to or by copies.
+struct Results {
+  const double *host = nullptr;  // pinned block of launch_final, or null
+  double head[16];
+  // Enqueues what is still to be copied; take() after the stream is idle.
+  ent_status fetch(const double *scal, const double *h, const double *d, int32_t m, int32_t s, double *per_probe,
+                   double *moments, double *alpha, hipStream_t st) {
+    if (host) return ENT_OK;
+    if (alpha)
+      HIP_TRY(hipMemcpyAsync(alpha, scal + ent::S_ALPHA, sizeof(double) * (m + 1), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(head, scal, sizeof(head), hipMemcpyDeviceToHost, st));
+    if (per_probe) HIP_TRY(hipMemcpyAsync(per_probe, h, sizeof(double) * s, hipMemcpyDeviceToHost, st));
+    if (moments)
+      HIP_TRY(hipMemcpyAsync(moments, d, sizeof(double) * (size_t)(m + 1) * s, hipMemcpyDeviceToHost, st));
+    return ENT_OK;
+  }
+  void take(int32_t m, int32_t s, double *per_probe, double *moments, double *alpha) {
+    if (!host) return;
+    const double *hp = host + ent::S_ALPHA + m + 1;
+    std::memcpy(head, host, sizeof(head));
+    if (alpha) std::memcpy(alpha, host + ent::S_ALPHA, sizeof(double) * (m + 1));
+    if (per_probe) std::memcpy(per_probe, hp, sizeof(double) * s);
+    if (moments) std::memcpy(moments, hp + s, sizeof(double) * (size_t)(m + 1) * s);
   }
 };
 
@@ -1190,6 +1236,7 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   const int32_t final_code = clenshaw ? ent::FINAL_CLENSHAW
                              : pairs && method == ENT_CHEBYSHEV ? ent::FINAL_CHEB_PAIRS : method;
   int32_t m_run = stg ? stg->deg[0] : m;  // degree of the estimate
+  Results res;
   int32_t stage = 0;
   for (;;) {
     const int32_t k_end = stg ? recurrence_products(method, m_run, pairs) : nsteps;
@@ -1246,14 +1293,16 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
       end_step(e);
     }
     HIP_TRY(ent::launch_reduce_moments(part, stg ? m_run + 1 : nslot, npart, ldv, s, d, st));
-    HIP_TRY(ent::launch_final(d, scal, final_code, m_run, s, h, st));
+    double *hb = ws.result_block(ent::S_ALPHA + (size_t)m_run + 1 + s + (size_t)(m_run + 1) * s);
+    HIP_TRY(ent::launch_final(d, scal, final_code, m_run, s, h, st, hb, moments || stg));
+    res.host = hb;
     if (!stg) break;
     // the check on the host; on rejection the recurrence continues from V_k, V_{k-1}
     std::vector<double> smom((size_t)(m_run + 1) * s), salpha(m_run + 1);
-    HIP_TRY(hipMemcpyAsync(smom.data(), d, sizeof(double) * smom.size(), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(salpha.data(), scal + ent::S_ALPHA, sizeof(double) * salpha.size(),
-                           hipMemcpyDeviceToHost, st));
+    rc = res.fetch(scal, h, d, m_run, s, nullptr, smom.data(), salpha.data(), st);
+    if (rc != ENT_OK) return rc;
     HIP_TRY(hipStreamSynchronize(st));
+    res.take(m_run, s, nullptr, smom.data(), salpha.data());
     const int outcome = stg->check(smom, salpha, m_run, s);
     stg->passed = outcome == 1 ? 1 : 0;
     stg->used = m_run;
@@ -1268,17 +1317,13 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     if (hook->feat_host)
       HIP_TRY(hipMemcpyAsync(hook->feat_host, hook->feat_dev, 16 * sizeof(float), hipMemcpyDeviceToHost, st));
   }
-  if (hook && hook->alpha_host)
-    HIP_TRY(hipMemcpyAsync(hook->alpha_host, scal + ent::S_ALPHA, sizeof(double) * (m_run + 1),
-                           hipMemcpyDeviceToHost, st));
-
-  double hs[16];
-  HIP_TRY(hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, st));
-  if (per_probe) HIP_TRY(hipMemcpyAsync(per_probe, h, sizeof(double) * s, hipMemcpyDeviceToHost, st));
-  if (moments)
-    HIP_TRY(hipMemcpyAsync(moments, d, sizeof(double) * (m_run + 1) * s, hipMemcpyDeviceToHost, st));
+  double *alpha_out = hook ? hook->alpha_host : nullptr;
+  rc = res.fetch(scal, h, d, m_run, s, per_probe, moments, alpha_out, st);
+  if (rc != ENT_OK) return rc;
   pe.mark();
   HIP_TRY(hipStreamSynchronize(st));
+  res.take(m_run, s, per_probe, moments, alpha_out);
+  const double *hs = res.head;
   pe.finish();
 
   if (check_trace) {
@@ -1464,20 +1509,20 @@ ent_status run_bf16x3(const ent_matrix *R, int32_t method, int32_t m, int32_t s,
   }
   pe.steps_end = pe.mark();
   HIP_TRY(ent::launch_reduce_moments(part, nslot, nblk, ldv, s, d, st));
+  Results res;
+  double *hb = ws.result_block(ent::S_ALPHA + (size_t)m + 1 + s + (size_t)(m + 1) * s);
   HIP_TRY(ent::launch_final(d, scal,
                             clenshaw ? ent::FINAL_CLENSHAW
                             : pairs && method == ENT_CHEBYSHEV ? ent::FINAL_CHEB_PAIRS : method,
-                            m, s, h, st));
-  if (hook && hook->alpha_host)
-    HIP_TRY(hipMemcpyAsync(hook->alpha_host, scal + ent::S_ALPHA, sizeof(double) * (m + 1),
-                           hipMemcpyDeviceToHost, st));
-  double hs[16];
-  HIP_TRY(hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, st));
-  if (per_probe) HIP_TRY(hipMemcpyAsync(per_probe, h, sizeof(double) * s, hipMemcpyDeviceToHost, st));
-  if (moments)
-    HIP_TRY(hipMemcpyAsync(moments, d, sizeof(double) * (m + 1) * s, hipMemcpyDeviceToHost, st));
+                            m, s, h, st, hb, moments != nullptr));
+  res.host = hb;
+  double *alpha_out = hook ? hook->alpha_host : nullptr;
+  rc = res.fetch(scal, h, d, m, s, per_probe, moments, alpha_out, st);
+  if (rc != ENT_OK) return rc;
   pe.mark();
   HIP_TRY(hipStreamSynchronize(st));
+  res.take(m, s, per_probe, moments, alpha_out);
+  const double *hs = res.head;
   pe.finish();
   if (check_trace) {
     double tol = o.trace_tol > 0 ? o.trace_tol : (f64 ? 1e-10 : 1e-4);
@@ -2794,17 +2839,21 @@ ent_status free_buffers(std::mutex &map_mu, std::map<int, Buf *> &bufs) {
   return rc;
 }
 
-// The workspaces' answer words and events (nothing is in flight between calls).
-void free_answer_words() {
+// The workspaces' pinned memory and events (nothing is in flight between calls).
+void free_pinned() {
   std::lock_guard<std::mutex> lk(g_ws_mu);
   for (auto &kv : g_ws) {
-    std::lock_guard<std::mutex> l2(kv.second->mu);
-    if (!kv.second->word) continue;
+    DeviceWorkspace *w = kv.second;
+    std::lock_guard<std::mutex> l2(w->mu);
     (void)hipSetDevice(kv.first);
-    (void)hipEventDestroy(kv.second->word_ready);
-    (void)hipHostFree(kv.second->word);
-    kv.second->word = nullptr;
-    kv.second->word_ready = nullptr;
+    if (w->word) {
+      (void)hipEventDestroy(w->word_ready);
+      (void)hipHostFree(w->word);
+      w->word = nullptr;
+      w->word_ready = nullptr;
+    }
+    if (w->results) (void)hipHostFree(w->results);
+    w->results = nullptr;
   }
 }
 
@@ -3281,7 +3330,7 @@ ent_status ent_release_workspace(void) {
   int cur = 0;
   HIP_TRY(hipGetDevice(&cur));
   const ent_status r1 = free_buffers(g_ws_mu, g_ws);
-  free_answer_words();
+  free_pinned();
   const ent_status r2 = free_buffers(g_rf_mu, g_rf);
   const ent_status r3 = free_buffers(g_stage_mu, g_stage);
   const hipError_t e = hipSetDevice(cur);

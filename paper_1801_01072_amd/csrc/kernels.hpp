@@ -647,8 +647,10 @@ hipError_t launch_selector_features(const double *scal, const double *d, int32_t
 hipError_t launch_reduce_moments(const double *part, int32_t nslot, int32_t ntile, int64_t ldv,
                                  int32_t s, double *d, hipStream_t st);
 // Per-probe values and the estimate (Algorithms 1-2 output line).
+// host (pinned memory the kernel stores to; null: none) receives scal[0 ..
+// S_ALPHA + m], then h (s values), then with host_moments d's (m + 1) s.
 hipError_t launch_final(double *d, double *scal, int32_t method, int32_t m, int32_t s,
-                        double *h, hipStream_t st);
+                        double *h, hipStream_t st, double *host = nullptr, bool host_moments = false);
 
 // ---- fixed scratch of the no-allocation entry point ---------------------------
 // Size of the per-device scratch array (ENT_NOALLOC_SCRATCH_BYTES).

@@ -1049,14 +1049,28 @@ __device__ __forceinline__ void final_body(double *__restrict__ d, double *__res
   }
 }
 
+// The results go to pinned host memory with the last stores of the estimate
+// (three copies behind it cost 10 to 20 us together).
 __global__ __launch_bounds__(kFinalThreads) void final_kernel(double *__restrict__ d, double *__restrict__ scal, int32_t method,
-                             int32_t m, int32_t s, double *__restrict__ h) {
+                             int32_t m, int32_t s, double *__restrict__ h, double *__restrict__ host,
+                             int32_t host_moments) {
   final_body(d, scal, method, m, s, h);
+  if (!host) return;
+  __syncthreads();  // the block's own stores to scal, h and d
+  const int head = S_ALPHA + m + 1;
+  for (int i = threadIdx.x; i < head; i += kFinalThreads) host[i] = scal[i];
+  for (int j = threadIdx.x; j < s; j += kFinalThreads) host[head + j] = h[j];
+  if (host_moments) {
+    const int64_t cnt = (int64_t)(m + 1) * s;
+#pragma unroll 4
+    for (int64_t i = threadIdx.x; i < cnt; i += kFinalThreads) host[head + s + i] = d[i];
+  }
+  __threadfence_system();
 }
 
 hipError_t launch_final(double *d, double *scal, int32_t method, int32_t m, int32_t s,
-                        double *h, hipStream_t st) {
-  final_kernel<<<1, kFinalThreads, 0, st>>>(d, scal, method, m, s, h);
+                        double *h, hipStream_t st, double *host, bool host_moments) {
+  final_kernel<<<1, kFinalThreads, 0, st>>>(d, scal, method, m, s, h, host, host_moments);
   return hipGetLastError();
 }
 
