@@ -1000,7 +1000,15 @@ __global__ __launch_bounds__(64 * kBandWaves) void band_pair_kernel(BandPairArgs
 template <int KS, bool VK_SIGNS, int M1A, bool GG>
 static void band_pair_launch(const BandPairArgs &a, hipStream_t st) {
   constexpr int NP = kBandPairProbes;
-  dim3 grid((unsigned)(a.nwave / kBandWaves), (unsigned)(a.ldv / (16 * NP)));
+  // The probe chunks of one range of rows run at the same time (and, with the
+  // ranges a multiple of 8, on the same XCD), so that the slabs one of them
+  // reads are still cached for the others; with every resident workgroup on
+  // the first chunk the next one read them from HBM again.  The partials of
+  // waves without a range stay zero.
+  const unsigned chunks = (unsigned)(a.ldv / (16 * NP));
+  unsigned ranges = (unsigned)(a.nwave / kBandWaves);
+  if (ranges >= 8 * chunks) ranges = ranges / chunks / 8 * 8;
+  dim3 grid(ranges, chunks);
   if (a.pair)
     band_pair_kernel<KS, NP, VK_SIGNS, M1A, GG, kProbePairs><<<grid, 64 * kBandWaves, 0, st>>>(a);
   else if (a.signs != nullptr && a.G == nullptr)
