@@ -1027,7 +1027,7 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
         else
           HIP_TRY(ent::launch_trace_dense<float>((const float *)R->values, R->ld, n, scal, st));
       }
-    } else if (!tri) {  // the tridiagonal pack below sums the diagonal itself
+    } else if (!tri && !(banded && ask)) {  // the tridiagonal pack and the slabs' check sum the diagonal themselves
       if (R->dtype == ENT_STORE_F64)
         HIP_TRY(ent::launch_trace_csr<double>(R->row_ptr, R->col_idx, (const double *)R->values, n, R->nnz,
                                               scal, st));
@@ -1049,7 +1049,7 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   }
   if (banded) {
     HIP_TRY(ent::launch_band_pack<T>(R->row_ptr, R->col_idx, (const T *)R->values, n, hp, band, st));
-    if (ask) HIP_TRY(ent::launch_band_check<T>(band, n, hp, (int32_t *)(scal + ent::S_SYM), asym.word, st));
+    if (ask) HIP_TRY(ent::launch_band_check<T>(band, n, hp, scal, asym.word, st));
   } else if (tri)
     HIP_TRY(ent::launch_tri_pack<T>(R->row_ptr, R->col_idx, (const T *)R->values, n, trid, ttmp,
                                     (check_trace || normalize) ? scal + ent::S_TRACE : nullptr, st));

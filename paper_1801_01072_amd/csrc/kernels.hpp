@@ -210,6 +210,8 @@ hipError_t launch_trace_dense(const T *R, int64_t ldr, int64_t n, double *scal, 
 // The trace and, in the same pass over R, whether R equals its transpose: a
 // mismatch sets the int32 at scal[S_SYM] (which must start at 0).  host_flag
 // (pinned host memory, may be null) receives that int32 too.
+// (its last part: the trace from cnt partial sums, and the flag to the host)
+hipError_t launch_check_finish(const double *tmp, int32_t cnt, double *scal, int32_t *host_flag, hipStream_t st);
 template <typename T>
 hipError_t launch_dense_check(const T *R, int64_t ldr, int64_t n, double *scal, int32_t *host_flag,
                               hipStream_t st);
@@ -374,10 +376,10 @@ size_t band_pack_elems(int64_t n, int32_t hp);
 template <typename T>
 hipError_t launch_band_pack(const int64_t *rp, const int32_t *ci, const T *val, int64_t n, int32_t hp,
                             T *band, hipStream_t st);
-// Whether the slabs hold a matrix equal to its transpose: *asym (must start at
-// 0) is set where they do not; host_flag as in launch_csr_check.
+// Trace of the slabs' matrix and whether it equals its transpose, as
+// launch_dense_check leaves them.
 template <typename T>
-hipError_t launch_band_check(const T *band, int64_t n, int32_t hp, int32_t *asym, int32_t *host_flag,
+hipError_t launch_band_check(const T *band, int64_t n, int32_t hp, double *scal, int32_t *host_flag,
                              hipStream_t st);
 struct BandStepArgs {
   const void *band;    // slabs (launch_band_pack), element type T

@@ -63,28 +63,32 @@ size_t band_pack_elems(int64_t n, int32_t hp) {
 }
 
 // ---------------------------------------------------------------------------
-// Row of entry e among the 16 rows r0 .. r0+15 whose row pointers are bnd[0..16]
-// (wave-uniform): the number of row starts after r0 at or before e.
+// Row of entry e (counted from the block's first) among 16 rows whose starts,
+// counted alike, are bnd[0..16] (wave-uniform): the number of row starts after
+// the first at or before e.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int row_in_block(int64_t e, const int64_t *bnd) {
+__device__ __forceinline__ int row_in_block(int32_t e, const int32_t *bnd) {
   int i = 0;
 #pragma unroll
   for (int k = 1; k < 16; ++k) i += e >= bnd[k] ? 1 : 0;
   return i;
 }
 
-// The row pointers rp[r0 .. r0+16] (clamped at n) of one 16-row block, as
-// wave-uniform values.
-__device__ __forceinline__ void block_bounds(const int64_t *__restrict__ rp, int64_t r0, int64_t n, int lane,
-                                             int64_t *bnd) {
+// The row starts of rows r0 .. r0+16 (clamped at n) of one 16-row block,
+// relative to the first (32 bits: half the compares of 64-bit ones), as
+// wave-uniform values; returns rp[r0].  A block of 2^31 entries or more has
+// bnd[16] = -1.
+__device__ __forceinline__ int64_t block_bounds(const int64_t *__restrict__ rp, int64_t r0, int64_t n, int lane,
+                                                int32_t *bnd) {
   const int64_t r = r0 + (lane < 16 ? lane : 16);
   const int64_t v = rp[r < n ? r : n];
+  const int lo0 = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v & 0xffffffffu), 0);
+  const int hi0 = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), 0);
+  const int64_t first = (int64_t)(((uint64_t)(uint32_t)hi0 << 32) | (uint64_t)(uint32_t)lo0);
+  const int32_t rel = v - first > INT32_MAX ? -1 : (int32_t)(v - first);
 #pragma unroll
-  for (int k = 0; k <= 16; ++k) {
-    const int lo = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v & 0xffffffffu), k);
-    const int hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), k);
-    bnd[k] = (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
-  }
+  for (int k = 0; k <= 16; ++k) bnd[k] = __builtin_amdgcn_readlane(rel, k);
+  return first;
 }
 
 // ---------------------------------------------------------------------------
@@ -102,10 +106,14 @@ __global__ __launch_bounds__(256) void csr_half_bandwidth_kernel(const int64_t *
   for (int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); b < nb; b += (int64_t)gridDim.x * 4) {
     // wider than any banded kernel serves: no need to know by how much
     if (__any(m > 16)) break;
-    int64_t bnd[17];
-    block_bounds(rp, 16 * b, n, lane, bnd);
-    for (int64_t e = bnd[0] + lane; e < bnd[16]; e += 64) {
-      const int64_t d = (int64_t)ci[e] - (16 * b + row_in_block(e, bnd));
+    int32_t bnd[17];
+    const int64_t first = block_bounds(rp, 16 * b, n, lane, bnd);
+    if (bnd[16] < 0) {  // far more entries than a band of 16 holds
+      m = 17;
+      break;
+    }
+    for (int32_t e = lane; e < bnd[16]; e += 64) {
+      const int64_t d = (int64_t)ci[first + e] - (16 * b + row_in_block(e, bnd));
       const int64_t ad = d < 0 ? -d : d;
       m = ad > m ? ad : m;
     }
@@ -131,56 +139,65 @@ hipError_t launch_csr_half_bandwidth(const int64_t *rp, const int32_t *ci, int64
 }
 
 // ---------------------------------------------------------------------------
-// Packing: one wave per 16-row block.  The block's entries are copied into
-// LDS with contiguous loads (when they fit), then lane l gathers the KS slab
-// values of row l%16 and k-slot l/16 by walking that row's entries in order
-// (duplicate entries are summed in entry order).  Requires |col - row| <= HP
-// for every entry.
+// Packing: one wave per 16-row block.  The block's entries are read with
+// contiguous loads and put at their place in a dense copy of the slab in LDS,
+// which the lanes then read in MFMA order: bound by its bytes
+// (n = 1e7, 33 entries a row, FP32: 2.39 ms when every lane searched its row,
+// 1.36 ms this way).  That
+// needs distinct places, which a row with strictly ascending columns has; a
+// block with any other row is gathered by lane l walking the entries of row
+// l%16 in order and keeping those of k-slot l/16 (duplicate entries are summed
+// in entry order).  Requires |col - row| <= HP for every entry.
 // ---------------------------------------------------------------------------
 template <typename T, int KS>
 __global__ __launch_bounds__(256) void band_pack_kernel(const int64_t *__restrict__ rp,
                                                         const int32_t *__restrict__ ci,
                                                         const T *__restrict__ val, int64_t n,
                                                         T *__restrict__ band) {
-  constexpr int HP = BandShape<KS>::HP;
-  constexpr int CAP = 1024;  // entries of a block staged in LDS
-  __shared__ int32_t scol[4][CAP];
-  __shared__ T sval[4][CAP];
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, q = l >> 4;
+  constexpr int HP = BandShape<KS>::HP, K = BandShape<KS>::K;
+  __shared__ T slab[4][16][K + 1];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, q = l >> 4, i = l & 15;
   const int64_t nb = (n + 15) / 16;
   const int64_t b = (int64_t)blockIdx.x * 4 + w;
-  const bool live = b < nb;
-  int64_t bnd[17];
-  bool staged = false;
-  if (live) {
-    block_bounds(rp, 16 * b, n, l, bnd);
-    staged = bnd[16] - bnd[0] <= CAP;
-    if (staged) {
-      for (int64_t e = bnd[0] + l; e < bnd[16]; e += 64) {
-        scol[w][e - bnd[0]] = ci[e];
-        sval[w][e - bnd[0]] = val[e];
-      }
+  if (b >= nb) return;  // waves work alone: no barrier below
+  int32_t bnd[17];
+  const int64_t first = block_bounds(rp, 16 * b, n, l, bnd);
+  const int64_t base = 16 * b - HP;
+#pragma unroll
+  for (int k = 0; k < KS; ++k) slab[w][i][4 * k + q] = T(0);
+  bool ascending = bnd[16] >= 0;
+  if (ascending) {
+    for (int32_t e = l; e < bnd[16]; e += 64) {
+      const int32_t c = ci[first + e];
+      const int r = row_in_block(e, bnd);
+      // the entry before, unless this is its row's first
+      bool start = e == 0;
+#pragma unroll
+      for (int k = 1; k < 16; ++k) start = start || e == bnd[k];
+      if (!start && ci[first + e - 1] >= c) ascending = false;
+      slab[w][r][c - base] = val[first + e];
     }
   }
-  __syncthreads();
-  if (!live) return;
-  const int i = l & 15;
-  const int64_t row = 16 * b + i;
-  const int64_t base = 16 * b - HP;
   T out[KS];
+  if (__all(ascending)) {
+    __builtin_amdgcn_wave_barrier();  // LDS accesses of a wave complete in order
 #pragma unroll
-  for (int k = 0; k < KS; ++k) out[k] = T(0);
-  if (row < n) {
-    const int64_t e1 = rp[row + 1];
-    for (int64_t e = rp[row]; e < e1; ++e) {
-      const int32_t col = staged ? scol[w][e - bnd[0]] : ci[e];
-      const int64_t j = (int64_t)col - base - q;  // slab column minus this lane's k-slot
-      if (j < 0 || (j & 3) != 0) continue;
-      const int64_t kk = j >> 2;
-      const T v = staged ? sval[w][e - bnd[0]] : val[e];
+    for (int k = 0; k < KS; ++k) out[k] = slab[w][i][4 * k + q];
+  } else {
 #pragma unroll
-      for (int k = 0; k < KS; ++k)
-        if (k == kk) out[k] += v;
+    for (int k = 0; k < KS; ++k) out[k] = T(0);
+    const int64_t row = 16 * b + i;
+    if (row < n) {
+      const int64_t e1 = rp[row + 1];
+      for (int64_t e = rp[row]; e < e1; ++e) {
+        const int64_t j = (int64_t)ci[e] - base - q;  // slab column minus this lane's k-slot
+        if (j < 0 || (j & 3) != 0) continue;
+        const int64_t kk = j >> 2;
+        const T v = val[e];
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+          if (k == kk) out[k] += v;
+      }
     }
   }
   T *dst = band + (64 * b + l) * KS;
@@ -210,11 +227,13 @@ template hipError_t launch_band_pack<double>(const int64_t *, const int32_t *, c
 // R = R^T on the slabs.  A workgroup takes four blocks (64 rows) and the block
 // behind them, copied into LDS as rows of K values (the block's lanes
 // hold them in MFMA order), and compares every entry right of the diagonal
-// with its mirror.  Reads each slab once (plus the overlap): HBM-bound.
+// with its mirror.  Reads each slab once (plus the overlap): HBM-bound.  The
+// trace comes with it (tmp: one partial sum per workgroup), where the CSR
+// kernel would look for the diagonal in the column indices (n = 1e7: 1.05 ms).
 // ---------------------------------------------------------------------------
 template <typename T, int KS>
 __global__ __launch_bounds__(256) void band_check_kernel(const T *__restrict__ band, int64_t n,
-                                                         int32_t *__restrict__ asym) {
+                                                         int32_t *__restrict__ asym, double *__restrict__ tmp) {
   constexpr int HP = BandShape<KS>::HP, K = BandShape<KS>::K;
   constexpr int NBK = 4;                 // blocks checked per workgroup pass
   constexpr int ROWS = 16 * (NBK + 1);   // HP <= 16: one more block holds every mirror
@@ -222,6 +241,7 @@ __global__ __launch_bounds__(256) void band_check_kernel(const T *__restrict__ b
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t nb = (n + 15) / 16;
   bool bad = false;
+  double tr = 0.0;  // wave 0: rows lane, lane + 64, ... of the workgroup's
   for (int64_t b0 = (int64_t)blockIdx.x * NBK; b0 < nb; b0 += (int64_t)gridDim.x * NBK) {
     __syncthreads();
     for (int i = w; i < NBK + 1; i += 4) {
@@ -241,25 +261,32 @@ __global__ __launch_bounds__(256) void band_check_kernel(const T *__restrict__ b
       const T x = rows[r][HP + (r & 15) + d], y = rows[rm][HP + r - (rm & ~15)];
       if (!(x == y)) bad = true;
     }
+    if (w == 0) tr += (double)rows[lane][HP + (lane & 15)];
   }
   if (__any(bad) && lane == 0) atomicOr(asym, 1);
+  if (w == 0) {
+    tr = wave_sum(tr);
+    if (lane == 0) tmp[blockIdx.x] = tr;
+  }
 }
 
 template <typename T>
-hipError_t launch_band_check(const T *band, int64_t n, int32_t hp, int32_t *asym, int32_t *host_flag,
+hipError_t launch_band_check(const T *band, int64_t n, int32_t hp, double *scal, int32_t *host_flag,
                              hipStream_t st) {
+  int32_t *asym = (int32_t *)(scal + S_SYM);
+  double *tmp = scal + 4096;
   const int64_t nb = (n + 15) / 16, want = (nb + 3) / 4;
   const unsigned blocks = (unsigned)(want < 4096 ? want : 4096);
   switch (hp) {
-    case 4: band_check_kernel<T, 6><<<blocks, 256, 0, st>>>(band, n, asym); break;
-    case 8: band_check_kernel<T, 8><<<blocks, 256, 0, st>>>(band, n, asym); break;
-    case 16: band_check_kernel<T, 12><<<blocks, 256, 0, st>>>(band, n, asym); break;
+    case 4: band_check_kernel<T, 6><<<blocks, 256, 0, st>>>(band, n, asym, tmp); break;
+    case 8: band_check_kernel<T, 8><<<blocks, 256, 0, st>>>(band, n, asym, tmp); break;
+    case 16: band_check_kernel<T, 12><<<blocks, 256, 0, st>>>(band, n, asym, tmp); break;
     default: return hipErrorInvalidValue;
   }
-  return launch_publish_flag(asym, nullptr, host_flag, st);
+  return launch_check_finish(tmp, (int32_t)blocks, scal, host_flag, st);
 }
-template hipError_t launch_band_check<float>(const float *, int64_t, int32_t, int32_t *, int32_t *, hipStream_t);
-template hipError_t launch_band_check<double>(const double *, int64_t, int32_t, int32_t *, int32_t *, hipStream_t);
+template hipError_t launch_band_check<float>(const float *, int64_t, int32_t, double *, int32_t *, hipStream_t);
+template hipError_t launch_band_check<double>(const double *, int64_t, int32_t, double *, int32_t *, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Row pieces: lane (q, c) of a 64-probe chunk handles probes 4c .. 4c+3.
@@ -424,9 +451,12 @@ template hipError_t launch_power_band<double>(const double *, int32_t, int64_t, 
 // 16-row blocks; product j runs one block behind product j - 1 (a block's
 // stencil reaches at most 16 rows, one block, to each side) and reads product
 // j - 1's values of the three blocks around its own from a four-block ring in
-// LDS, private to the wave.  Each product reads its block's slab: from HBM for
-// product 0, from the caches for the products a few blocks behind.  Scaling
-// and the triple as launch_power_tri_fused.
+// LDS, private to the wave.  A block's slab is read once and passed on in
+// registers from product to product (SR; up to 128 registers of them, loaded one
+// block ahead): read again by every product, from the caches, each product
+// waited for its loads behind the one before (n = 1e7, hp = 16, FP32, ten
+// products: 2.67 ms, 1.35 ms this way).  Longer slabs are read by every product.  Scaling and the
+// triple as launch_power_tri_fused.
 template <typename T, int KS, int K>
 __global__ __launch_bounds__(256) void power_band_fused_kernel(const T *__restrict__ band, int64_t n,
                                                                const double *__restrict__ x,
@@ -451,17 +481,41 @@ __global__ __launch_bounds__(256) void power_band_fused_kernel(const T *__restri
   double yy = 0.0, xy = 0.0, xx = 0.0;
   if (b_beg < b_end) {
     for (int i = lane; i < K * 64; i += 64) (&ring[w][0][0][0])[i] = 0.0;
+    constexpr bool SR = (K + 1) * KS * (int)sizeof(T) / 4 <= 132;
+    T sl[SR ? K + 1 : 1][KS];  // slabs of blocks beta + 1 (next), beta, .. beta - K + 1
+    auto slab_at = [&](int64_t bb, T *a) {  // a block outside the matrix is zero
+      if (bb >= 0 && bb < nb) {
+        load_slab<T, KS>(band, bb, lane, a);
+      } else {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) a[k] = T(0);
+      }
+    };
+    if constexpr (SR) {
+#pragma unroll
+      for (int j = 1; j <= K; ++j)
+#pragma unroll
+        for (int k = 0; k < KS; ++k) sl[j][k] = T(0);
+      slab_at(b_beg - (K - 1), sl[0]);
+    }
     for (int64_t beta = b_beg - (K - 1); beta - (K - 1) < b_end; ++beta) {
+      if constexpr (SR) {
+#pragma unroll
+        for (int j = K; j > 0; --j)
+#pragma unroll
+          for (int k = 0; k < KS; ++k) sl[j][k] = sl[j - 1][k];
+        slab_at(beta + 1, sl[0]);
+      }
 #pragma unroll
       for (int j = 0; j < K; ++j) {
         const int64_t bb = beta - j;
         const bool blk_in = bb >= 0 && bb < nb;
         T a[KS];
-        if (blk_in) {
-          load_slab<T, KS>(band, bb, lane, a);
-        } else {
+        if constexpr (SR) {
 #pragma unroll
-          for (int k = 0; k < KS; ++k) a[k] = T(0);
+          for (int k = 0; k < KS; ++k) a[k] = sl[j + 1][k];
+        } else {
+          slab_at(bb, a);
         }
         double acc = 0.0;
 #pragma unroll

@@ -550,7 +550,7 @@ hipError_t launch_batch_check(const BatchMat *mats, int32_t count, int64_t max_n
 template hipError_t launch_batch_check<double>(const BatchMat *, int32_t, int64_t, int32_t *, hipStream_t);
 template hipError_t launch_batch_check<float>(const BatchMat *, int32_t, int64_t, int32_t *, hipStream_t);
 
-__global__ __launch_bounds__(256) void dense_check_finish_kernel(const double *__restrict__ tmp, int32_t cnt,
+__global__ __launch_bounds__(256) void check_finish_kernel(const double *__restrict__ tmp, int32_t cnt,
                                                                  double *__restrict__ scal,
                                                                  int32_t *__restrict__ host_flag) {
   __shared__ double red[4];
@@ -567,6 +567,11 @@ __global__ __launch_bounds__(256) void dense_check_finish_kernel(const double *_
   }
 }
 
+hipError_t launch_check_finish(const double *tmp, int32_t cnt, double *scal, int32_t *host_flag, hipStream_t st) {
+  check_finish_kernel<<<1, 256, 0, st>>>(tmp, cnt, scal, host_flag);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_dense_check(const T *R, int64_t ldr, int64_t n, double *scal, int32_t *host_flag,
                               hipStream_t st) {
@@ -575,8 +580,7 @@ hipError_t launch_dense_check(const T *R, int64_t ldr, int64_t n, double *scal, 
   if (n < 1 || nb > 4096) return hipErrorInvalidValue;
   double *tmp = scal + 4096;
   dense_check_kernel<T><<<(unsigned)(nb * (nb + 1) / 2), 256, 0, st>>>(R, ldr, n, tmp, (int32_t *)(scal + S_SYM));
-  dense_check_finish_kernel<<<1, 256, 0, st>>>(tmp, (int32_t)nb, scal, host_flag);
-  return hipGetLastError();
+  return launch_check_finish(tmp, (int32_t)nb, scal, host_flag, st);
 }
 template hipError_t launch_dense_check<double>(const double *, int64_t, int64_t, double *, int32_t *, hipStream_t);
 template hipError_t launch_dense_check<float>(const float *, int64_t, int64_t, double *, int32_t *, hipStream_t);
