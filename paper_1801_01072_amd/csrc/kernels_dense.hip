@@ -414,13 +414,6 @@ __global__ __launch_bounds__(256) void dense_split_epilogue_kernel(DenseStepArgs
     off[i] = ((int64_t)tp * 16 + rq * 4 + i) * ldv + col;
     acc[i] = T(0);
   }
-  for (int ks = 0; ks < a.ksplit; ++ks) {
-    T pv[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) pv[i] = P[ks * pstride + off[i]];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] += pv[i];
-  }
   const bool use_g = use_cg || (want_dot && !pair);
   double ds = 0.0, gs = 0.0, bs = 0.0;
   // operands of every row before the first store (V_{k+1} may overwrite V_{k-1})
@@ -430,6 +423,21 @@ __global__ __launch_bounds__(256) void dense_split_epilogue_kernel(DenseStepArgs
     vk[i] = Vk[off[i]];
     vm[i] = use_m1 ? Vkm1[off[i]] : T(0);
     gv[i] = use_g ? G[off[i]] : vk[i];
+  }
+  // the partials of four splits in flight together: one round trip in place of
+  // four (n = 3001, 100 probes, FP32, 5 splits: 7.3 us a step, now 5.0)
+  for (int ks = 0; ks < a.ksplit; ks += 4) {
+    T pv[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (ks + j < a.ksplit)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pv[j][i] = P[(ks + j) * pstride + off[i]];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (ks + j < a.ksplit)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += pv[j][i];
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -833,10 +841,31 @@ int32_t dense_direct_tiles(int64_t n, int32_t s) {
   return 0;
 }
 
+// Workgroups run in rounds of one per compute unit, so a split is paid by its
+// rounds times its rows (16 more for filling the pipeline and storing the
+// partials), and the last of an odd number of rounds, alone on its compute
+// unit, an eighth more (n = 8192, 256 probes FP64: 623 us a step in one round,
+// 550 in two); each split adds its partials to the epilogue's reads.  Of the
+// splits up to the smallest power of two that gives the chip 512 workgroups the
+// cheapest one.  Power of two against this rule, us a step, FP32 and FP64:
+// n = 2200, 128 probes 31.9 / 24.3 and 51.2 / 36.7 (8 and 7 splits); 2500, 200:
+// 47.7 / 42.2 and 80.6 / 73.4 (8, 6); 3001, 100: 38.2 / 33.4 and 63.5 / 56.4
+// (8, 5); 4500, 256: 132.8 / 114.0 and 246 / 210 (4, 3); 7000, 100: 139 / 129
+// and 254 / 244 (8, 4); 4096, 64 and 8192, 256 stay.
 int32_t dense_step_splits(int64_t n, int32_t ntile, int64_t ldv, int32_t bn) {
   const int64_t tiles = (int64_t)ntile * (ldv / bn);
-  int32_t ks = 1;
-  while (tiles * ks < 512 && ks < 16 && n / (2 * ks) >= 256) ks *= 2;
+  int32_t most = 1;
+  while (tiles * most < 512 && most < 16 && n / (2 * most) >= 256) most *= 2;
+  int32_t ks = most;
+  int64_t least = INT64_MAX;
+  for (int32_t k = most > 1 ? 2 : 1; k <= most; ++k) {
+    const int64_t kper = ((n + k - 1) / k + 31) / 32 * 32, rounds = (tiles * k + 255) / 256;
+    const int64_t cost = (8 * rounds + rounds % 2) * (kper + 16) + 32 * k;
+    if (cost < least) {
+      least = cost;
+      ks = k;
+    }
+  }
   return ks;
 }
 
