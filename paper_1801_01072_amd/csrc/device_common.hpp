@@ -245,22 +245,58 @@ __device__ __forceinline__ int xcc_id() {
 
 // Next item index of this workgroup, or -1 when its XCD's segment is
 // exhausted or a wait has failed.  sh: a __shared__ int of the calling kernel.
-__device__ __forceinline__ int sched_next(const SchedArgs &s, int *sh) {
-  __syncthreads();  // every wave is done with the previous item (and with sh)
+// In two parts: sched_reserve (thread 0's value counts) takes the place in the
+// queue without waiting for it, sched_item waits and gives it to the workgroup.
+// The loops around these begin with a convergent operation and branch on scalar
+// values: a loop that began with thread 0's branch would let the compiler send
+// the other lanes straight to the barrier behind it.
+__device__ __forceinline__ int sched_reserve(const SchedArgs &s) {
+  __builtin_amdgcn_wave_barrier();
+  int q = 0;
+  if (threadIdx.x == 0) {
+    const int seg = s.seg_of_xcc[xcc_id()];
+    // the address as a vector value: for one that the compiler knows to be
+    // uniform it combines lanes, which waits for the result here
+    int v = seg;
+    asm("" : "+v"(v));
+    if (seg >= 0) q = __hip_atomic_fetch_add(s.head + v, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __builtin_amdgcn_wave_barrier();
+  return q;
+}
+__device__ __forceinline__ int sched_item(const SchedArgs &s, int q, int *sh) {
+  __builtin_amdgcn_wave_barrier();
   if (threadIdx.x == 0) {
     int i = -1;
     const int seg = s.seg_of_xcc[xcc_id()];
+    const int err = __hip_atomic_load(s.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (seg >= 0) {
-      const int q = __hip_atomic_fetch_add(s.head + seg, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int end = s.tail && *s.tail == 0 ? s.seg_mid[seg] : s.seg_off[seg + 1];
-      if (q < end - s.seg_off[seg] &&
-          __hip_atomic_fetch_add(s.err, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
-        i = s.seg_off[seg] + q;
+      if (q < end - s.seg_off[seg] && err == 0) i = s.seg_off[seg] + q;
     }
     *sh = i;
   }
   __syncthreads();
-  return *sh;
+  return __builtin_amdgcn_readfirstlane(*sh);
+}
+__device__ __forceinline__ int sched_next(const SchedArgs &s, int *sh) {
+  __syncthreads();  // every wave is done with the previous item (and with sh)
+  return sched_item(s, sched_reserve(s), sh);
+}
+
+// A value of global memory that is the same for every lane, in scalar registers:
+// behind stores of the same kernel the compiler loads through vector registers
+// and takes every branch and address made from it for divergent.
+template <typename T>
+__device__ __forceinline__ T uniform_load(const T *p) {
+  static_assert(sizeof(T) % 4 == 0, "whole dwords");
+  T v = *p;
+  int w[sizeof(T) / 4];
+  __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
 }
 
 // Waits until done[b] >= need; false (and *err set) after spin_limit polls.
@@ -268,8 +304,8 @@ __device__ __forceinline__ bool sched_wait(const SchedArgs &s, int b, int need, 
   if (threadIdx.x == 0) {
     int ok = 1;
     int polls = 0;
-    while (__hip_atomic_fetch_add(s.done + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
-      if (__hip_atomic_fetch_add(s.err, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
+    while (__hip_atomic_load(s.done + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
+      if (__hip_atomic_load(s.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
           polls++ >= s.spin_limit) {
         __hip_atomic_fetch_or(s.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         ok = 0;
@@ -281,7 +317,7 @@ __device__ __forceinline__ bool sched_wait(const SchedArgs &s, int b, int need, 
   }
   __syncthreads();
   asm volatile("buffer_inv sc1" ::: "memory");  // L1 of this CU (device scope: a group-scope invalidate may keep it)
-  return *sh != 0;
+  return __builtin_amdgcn_readfirstlane(*sh) != 0;
 }
 
 // Publishes one finished tile of matrix b.
@@ -329,6 +365,8 @@ __device__ __forceinline__ StepRule step_rule(int32_t method, int32_t m, int32_t
 }
 
 // A matrix's dots come in pairs if it equals its transpose.
-__device__ __forceinline__ bool batch_pairs(const BatchMat &M) { return *(const int32_t *)(M.scal + S_SYM) == 0; }
+__device__ __forceinline__ bool batch_pairs(const BatchMat &M) {
+  return __builtin_amdgcn_readfirstlane(*(const int32_t *)(M.scal + S_SYM)) == 0;  // one matrix per wave
+}
 
 }  // namespace ent

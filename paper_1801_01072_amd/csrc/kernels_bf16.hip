@@ -552,15 +552,15 @@ __global__ __launch_bounds__(256) void batch_bf16x3_step_kernel(BatchPersistArgs
 // recurrence, publishes it.
 template <int BN>
 __global__ __launch_bounds__(256) void batch_bf16x3_persistent_kernel(BatchPersistArgs pa) {
-  __shared__ int sh;
+  __shared__ int sh[2];
   for (;;) {
-    const int i = sched_next(pa.sched, &sh);
+    const int i = sched_next(pa.sched, sh);
     if (i < 0) return;
-    const int4 it = pa.sched.items[i];
-    const BatchMat &M = pa.mats[it.x];
+    const int4 it = uniform_load(pa.sched.items + i);
+    const BatchMat M = uniform_load(pa.mats + it.x);
     Bf16EpiArgs e{};
     if (!batch_bf16x3_args(pa, M, it.z, e)) continue;  // nor has the matrix any later step
-    if (!sched_wait(pa.sched, it.x, it.z * M.ntile, &sh)) return;
+    if (!sched_wait(pa.sched, it.x, it.z * M.ntile, sh + 1)) return;
     const int pin = it.z & 1;
     bf16x3_gemm_tile<BN, 2, true>(pa.Ahi + M.aoff, pa.Alo + M.aoff, pa.Vhi[pin] + M.voff,
                                   pa.Vlo[pin] + M.voff, nullptr, M.n_pad, 0, (int)(M.n_pad / kBK),

@@ -36,14 +36,20 @@ __device__ __forceinline__ void dense_wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
 }
 
+// LDS of a tile's stages: two workgroups on a CU; the grouped FP32 batch step
+// takes half of it and 16-column chunks, four workgroups on a CU hide each
+// other's prologue and epilogue (64 matrices, n <= 2048, 64 probes: 160 us a
+// step with 32-column chunks, 136 with 16; n = 1024: 115 and 96; n = 2048, where
+// the chunks alone count, 362 and 357; FP64 lacks the registers for it).
+constexpr int kChunkLds = 61440, kGroupedLds = 30720;
+
 // Chunk geometry of the dense step: BK columns of R per chunk (32, 16 or 8),
-// KPL = BK/4 of them per lane; one stage holds the chunk's V_k rows (BK x BN,
+// KPL = BK/4 of them per lane in APL pieces of VEC; one stage holds the chunk's V_k rows (BK x BN,
 // shared by the 4 waves) and each wave's A values (WR 16-row slabs x BK); the
-// NST stages take at most 60 KB, so two workgroups fit on a CU.
-template <typename T, int BN, int WR>
+// NST stages take at most BUDGET bytes.
+template <typename T, int BN, int WR, int BUDGET = kChunkLds>
 struct DenseChunk {
   static constexpr int NST = 3;                      // stages (prefetch distance NST - 1)
-  static constexpr int BUDGET = 61440;
   static_assert(NST >= 3 && NST <= 4, "the waits cover three or four stages");
   static constexpr int ES = (int)sizeof(T);
   static constexpr int VEC = 16 / ES;                // elements per 16-byte piece
@@ -62,20 +68,39 @@ struct DenseChunk {
   static_assert((BK * G) % 256 == 0, "V pieces must split over the 4 waves");
   static_assert(4 * ES <= G, "V rows too short for the swizzle");
   // V row r sits at r * RB bytes, its 16-byte groups XOR-swizzled so that
-  // the four 16-lane groups of an MFMA B-operand read (rows t, KPL+t, 2KPL+t,
-  // 3KPL+t, 16 consecutive probes each) fall on disjoint banks
-  __device__ static constexpr int swz(int r) { return ((r / KPL) & 3) * ES; }
+  // the four 16-lane groups of an MFMA B-operand read (rows t, VEC+t, 2VEC+t,
+  // 3VEC+t of a piece, 16 consecutive probes each) fall on disjoint banks
+  __device__ static constexpr int swz(int r) { return ((r / VEC) & 3) * ES; }
+  // chunk column of MFMA call t in lane group q
+  __device__ static constexpr int kcol(int q, int t) { return (t / VEC * 4 + q) * VEC + t % VEC; }
   __device__ static int voff(int r, int col) {
     return r * RB + (((col / VEC) ^ swz(r)) << 4) + (col % VEC) * ES;
   }
 };
 
 namespace {
-// Column groups whose epilogue operands a batch tile loads together: the
-// workgroups of a batch hide each other's latency, and more operands in
-// registers cost it (64 matrices, n <= 2048, FP32: 10.89 ms with 1, 10.93
-// with 2, 11.03 with 4).
-constexpr int kBatchCols = 1;
+// Column groups whose epilogue operands a batch tile loads together: all of a
+// 64-row tile; a 128-row one has no registers left for more than one.
+template <int WR>
+constexpr int kBatchCols = WR == 1 ? 4 : 1;
+
+// What a persistent kernel does inside a tile: ready() once R's first loads are
+// out and before anything of the step before is read (false: give up, the tile
+// returns false), products_done() before the epilogue.
+struct DenseNoHook {
+  static constexpr bool on = false;
+  __device__ bool ready() { return true; }
+  __device__ void products_done() {}
+};
+struct BatchHook {
+  static constexpr bool on = true;
+  const SchedArgs &s;
+  int b, need;
+  int *sh;
+  int *next;
+  __device__ bool ready() { return sched_wait(s, b, need, sh); }
+  __device__ void products_done() { *next = sched_reserve(s); }
+};
 }  // namespace
 
 // Body of one tile: rows [64*WR*tm, +64*WR) (wave w owns WR 16-row slabs),
@@ -88,18 +113,21 @@ constexpr int kBatchCols = 1;
 // and each wave's A values go from global memory straight into LDS (direct
 // loads, no registers), two chunks ahead of the MFMAs that read them; every
 // wait on them is explicit (vmcnt), one barrier per chunk.  Lane (m, q) of a
-// wave loads R[row m][k0 + KPL q .. + KPL) of each of its slabs, which it
-// reads back from its own 16-byte slots: MFMA k-slot q of call t is column
-// KPL q + t (the k order inside a chunk is permuted consistently for A and
-// B).  A ragged last chunk (n not a multiple of BK) reads A into registers,
-// column min(k, n - 1) element by element: V_k is zero in rows k >= n, so
-// those products vanish.
-template <typename T, int BN, int WR, int EC>
-__device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, int tn, int64_t kbeg,
-                                                int64_t kend, T *yout) {
+// wave loads 16-byte pieces of R[row m] of each of its slabs, piece h at chunk
+// column (4 h + q) VEC, so that the four lanes of a row take 64 consecutive
+// bytes with each load (pieces of one lane side by side touched every 64 bytes
+// twice: n = 5000, 64 probes, FP32 42.1 us a step, now 39.9; n = 8192, bound by
+// the products, unchanged), and reads them back from its own 16-byte slots:
+// MFMA k-slot q of call t is column kcol(q, t) (the k order inside a chunk is
+// permuted consistently for A and B).  A ragged last chunk (n not a multiple of
+// BK) reads A into registers at the start, column min(k, n - 1) element by
+// element: V_k is zero in rows k >= n, so those products vanish.
+template <typename T, int BN, int WR, int EC, int BUDGET = kChunkLds, bool PRE = false, typename H = DenseNoHook>
+__device__ __forceinline__ bool dense_step_tile(const DenseStepArgs &a, int tm, int tn, int64_t kbeg,
+                                                int64_t kend, T *yout, H hook = H{}) {
   using M = Mfma16<T>;
   using v4 = typename M::v4;
-  using C = DenseChunk<T, BN, WR>;
+  using C = DenseChunk<T, BN, WR, BUDGET>;
   constexpr int BM = 64 * WR, BK = C::BK, KPL = C::KPL, VEC = C::VEC;
   constexpr int NSUB = BN / 16;
   constexpr int NVL = C::NVL, NAL = C::NAL, APL = C::APL;
@@ -129,7 +157,7 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
 #pragma unroll
   for (int f = 0; f < WR; ++f) {
     const int64_t arow = wrow0 + 16 * f + m16;
-    Arow[f] = R + (arow < n ? arow : n - 1) * a.ldr + KPL * kq;
+    Arow[f] = R + (arow < n ? arow : n - 1) * a.ldr + VEC * kq;
   }
   // V piece q = (i*4 + w)*64 + lane of a chunk: row q / G, swizzled group q % G
   int64_t vsrc[NVL];
@@ -150,15 +178,19 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
     for (int i = 0; i < NVL; ++i)
       __builtin_amdgcn_global_load_lds((const void *)(vb + vsrc[i]), (LdsPtr)(st + (i * 4 + w) * 1024), 16, 0, 0);
   };
-  auto issue = [&](int c, unsigned char *st) {
-    issue_v(c, st);
+  auto issue_a = [&](int c, unsigned char *st) {
     const int64_t kc = kbeg + (int64_t)c * BK;
 #pragma unroll
     for (int f = 0; f < WR; ++f)
 #pragma unroll
       for (int h = 0; h < APL; ++h)
-        __builtin_amdgcn_global_load_lds((const void *)(Arow[f] + kc + h * VEC),
+        __builtin_amdgcn_global_load_lds((const void *)(Arow[f] + kc + h * 4 * VEC),
                                          (LdsPtr)(st + C::VBYTES + ((w * WR + f) * APL + h) * 1024), 16, 0, 0);
+  };
+
+  auto issue = [&](int c, unsigned char *st) {
+    issue_v(c, st);
+    issue_a(c, st);
   };
 
   v4 acc[WR][NSUB];
@@ -182,7 +214,7 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
 #pragma unroll
     for (int t = 0; t < KPL; ++t)
 #pragma unroll
-      for (int c2 = 0; c2 < NSUB; ++c2) fr.b[t][c2] = *(const T *)(st + C::voff(KPL * kq + t, 16 * c2 + m16));
+      for (int c2 = 0; c2 < NSUB; ++c2) fr.b[t][c2] = *(const T *)(st + C::voff(C::kcol(kq, t), 16 * c2 + m16));
   };
   auto mfma_frag = [&](const Frag &fr) {
 #pragma unroll
@@ -199,10 +231,58 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
   // landed and its reads of chunk c have returned, barrier (every wave's part
   // of chunk c + 1 landed; every wave done reading chunk c, whose stage chunk
   // c + NST now takes), issue chunk c + NST, read chunk c + 1, multiply chunk c.
+  // A ragged chunk follows as chunk nfull, its A values loaded into registers
+  // at the start, its V rows directly when its stage is free (fewer loads than
+  // PER: the waits below, which count full chunks only, then wait for more).
   constexpr int PER = NVL + NAL;  // direct loads per wave per chunk
-  for (int c = 0; c < NST; ++c)
-    if (c < nfull) issue(c, lds + c * STAGE);
-  Frag fx, fy;
+  Frag fx, fy, fr;
+  auto load_ragged = [&] {
+    const int64_t k0 = kbeg + (int64_t)nfull * BK;
+#pragma unroll
+    for (int f = 0; f < WR; ++f)
+#pragma unroll
+      for (int t = 0; t < KPL; ++t) {
+        const int64_t k = k0 + C::kcol(kq, t);
+        fr.a[f][t / VEC][t % VEC] = (Arow[f] - VEC * kq)[k < n ? k : n - 1];
+      }
+  };
+  // operands of the epilogue, loaded here and not after the products
+  const bool use_m1 = (a.cw != 0.0) && a.Vkm1;
+  T pk[PRE ? NSUB : 1][WR][4], pm[PRE ? NSUB : 1][WR][4];
+  auto load_epilogue = [&] {
+#pragma unroll
+    for (int c = 0; c < (PRE ? NSUB : 0); ++c)
+#pragma unroll
+      for (int f = 0; f < WR; ++f)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int64_t off = (wrow0 + 16 * f + M::drow(kq, r)) * ldv + col0 + 16 * c + m16;
+          pk[c][f][r] = Vk[off];
+          pm[c][f][r] = use_m1 ? ((const T *)a.Vkm1)[off] : T(0);
+        }
+  };
+  if constexpr (H::on) {
+    // R does not depend on the step before: its loads go out ahead of the wait
+    if (ragged) load_ragged();
+    for (int c = 0; c < NST; ++c)
+      if (c < nfull) issue_a(c, lds + c * STAGE);
+    if (!hook.ready()) {
+      dense_wait_vm<0>();
+      return false;
+    }
+    load_epilogue();
+    for (int c = 0; c < NST; ++c)
+      if (c < nfull + (ragged ? 1 : 0)) issue_v(c, lds + c * STAGE);
+  } else {
+    if (ragged) load_ragged();
+    load_epilogue();
+    for (int c = 0; c < NST; ++c) {
+      if (c < nfull)
+        issue(c, lds + c * STAGE);
+      else if (c == nfull && ragged)
+        issue_v(c, lds + c * STAGE);
+    }
+  }
   // wait until at most k chunks' loads of this wave are in flight (k < NST)
   auto wait_chunks = [&](int k) {
     if (NST >= 4 && k >= 3)
@@ -214,19 +294,38 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
     else
       dense_wait_vm<0>();
   };
+  // the same for the first chunks behind a hook, of which only the V loads came last
+  auto wait_first = [&](int k) {
+    if (k >= 2)
+      dense_wait_vm<2 * NVL>();
+    else if (k >= 1)
+      dense_wait_vm<NVL>();
+    else
+      dense_wait_vm<0>();
+  };
   auto step = [&](int c, int s0, Frag &cur, Frag &nxt) {
     // chunks issued after chunk c + 1: c + 2 .. min(c + NST - 1, nfull - 1)
     const int ahead = nfull - 2 - c < NST - 2 ? nfull - 2 - c : NST - 2;
-    wait_chunks(ahead);
+    if (H::on && c == 0)
+      wait_first(ahead);
+    else
+      wait_chunks(ahead);
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's reads of chunk c returned
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    if (c + NST < nfull) issue(c + NST, lds + s0 * STAGE);
+    if (c + NST < nfull)
+      issue(c + NST, lds + s0 * STAGE);
+    else if (c + NST == nfull && ragged)
+      issue_v(nfull, lds + s0 * STAGE);
     if (c + 1 < nfull) read_frag(nxt, lds + (s0 == NST - 1 ? 0 : s0 + 1) * STAGE);
     mfma_frag(cur);
   };
   if (nfull > 0) {
-    wait_chunks(nfull - 1 < NST - 1 ? nfull - 1 : NST - 1);  // chunk 0 landed
+    const int ahead = nfull - 1 < NST - 1 ? nfull - 1 : NST - 1;  // chunk 0 landed
+    if (H::on)
+      wait_first(ahead);
+    else
+      wait_chunks(ahead);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     read_frag(fx, lds);
@@ -243,31 +342,18 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
     s0 = s0 == NST - 1 ? 0 : s0 + 1;
   }
   if (ragged) {
-    // the stage this chunk takes (s0) was last read at step nfull - NST - 1,
-    // before barriers every wave has passed; its A values come into
-    // registers element by element, column min(k, n - 1)
     unsigned char *st = lds + s0 * STAGE;
-    dense_wait_vm<0>();
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    issue_v(nfull, st);
-    const int64_t k0 = kbeg + (int64_t)nfull * BK + KPL * kq;
-    Frag fr;
-#pragma unroll
-    for (int f = 0; f < WR; ++f)
-#pragma unroll
-      for (int t = 0; t < KPL; ++t) fr.a[f][t / VEC][t % VEC] = (Arow[f] - KPL * kq)[k0 + t < n ? k0 + t : n - 1];
     dense_wait_vm<0>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < KPL; ++t)
 #pragma unroll
-      for (int c2 = 0; c2 < NSUB; ++c2) fr.b[t][c2] = *(const T *)(st + C::voff(KPL * kq + t, 16 * c2 + m16));
+      for (int c2 = 0; c2 < NSUB; ++c2) fr.b[t][c2] = *(const T *)(st + C::voff(C::kcol(kq, t), 16 * c2 + m16));
     mfma_frag(fr);
   }
   __syncthreads();
+  if constexpr (H::on) hook.products_done();
 
   if (yout) {
 #pragma unroll
@@ -279,7 +365,7 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
           const int64_t row = wrow0 + 16 * f + M::drow(kq, r);
           yout[row * ldv + col0 + 16 * c + m16] = row < n ? acc[f][c][r] : T(0);
         }
-    return;
+    return true;
   }
   // ---- epilogue ----
   const T ta = (T)a.scal[S_A];
@@ -288,7 +374,6 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
   const T *Vkm1 = (const T *)a.Vkm1;
   const T *__restrict__ G = (const T *)a.G;
   T *Vkp1 = (T *)a.Vkp1;
-  const bool use_m1 = (a.cw != 0.0) && Vkm1;
   const bool want_dot = a.slot >= 0;
   const bool want_gg = a.slot_gg >= 0;
   const bool pair = a.pair != 0;
@@ -311,8 +396,8 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int64_t off = (wrow0 + 16 * f + M::drow(kq, r)) * ldv + col0 + 16 * (cb + e) + m16;
-          vk[e][f][r] = Vk[off];
-          vm[e][f][r] = use_m1 ? Vkm1[off] : T(0);
+          vk[e][f][r] = PRE ? pk[PRE ? cb + e : 0][f][r] : Vk[off];
+          vm[e][f][r] = PRE ? pm[PRE ? cb + e : 0][f][r] : use_m1 ? Vkm1[off] : T(0);
           gv[e][f][r] = use_g ? G[off] : vk[e][f][r];
         }
 #pragma unroll
@@ -347,7 +432,7 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
       }
     }
   }
-  if (!want_dot) return;
+  if (!want_dot) return true;
   __syncthreads();
   for (int col = tid; col < BN; col += 256) {
     const double s = red[0][0][col] + red[0][1][col] + red[0][2][col] + red[0][3][col];
@@ -361,6 +446,7 @@ __device__ __forceinline__ void dense_step_tile(const DenseStepArgs &a, int tm, 
       a.part[((int64_t)a.slot_b * a.ntile + tm) * ldv + col0 + col] = b2;
     }
   }
+  return true;
 }
 
 template <typename T, int BN, int WR>
@@ -903,24 +989,40 @@ __global__ __launch_bounds__(256) void batch_dense_step_kernel(BatchPersistArgs 
   const int2 tl = tiles[blockIdx.x];
   DenseStepArgs a{};
   if (!batch_dense_args<T>(pa, pa.mats[tl.x], k, a)) return;
-  dense_step_tile<T, 64, WR, kBatchCols>(a, tl.y, (int)blockIdx.y, 0, a.n, nullptr);
+  dense_step_tile<T, 64, WR, kBatchCols<WR>, sizeof(T) == 4 ? kGroupedLds : kChunkLds>(a, tl.y, (int)blockIdx.y, 0, a.n, nullptr);
 }
 
 // Persistent batch steps: each workgroup takes (matrix, row tile, step)
 // items in schedule order, waits for the matrix's previous step, runs the
 // tile body of the grouped kernel with that step's recurrence, publishes it.
+// An item is short (64 rows of n <= 2048: 30 us of products), so what stands
+// around its products counted as much again: 6 us for the next item, 4 for the
+// first chunk, 3 for a ragged last one, 13 in the epilogue.  The next item is
+// reserved before the epilogue, R's first chunks and the ragged chunk's values
+// are on their way during the wait, FP32 tiles hold the epilogue's V_k and
+// V_{k-1} in registers from the start (FP64 has none left), and the matrix's
+// description is in scalar registers.  64 matrices, n <= 2048, 64 probes, FP32:
+// 160 -> 127 us a step (two workgroups on a CU; three of 16-column chunks: 193,
+// an XCD has 126 tiles a step and they wait for each other).
 template <typename T, int WR>
-__global__ __launch_bounds__(256) void batch_dense_persistent_kernel(BatchPersistArgs pa) {
-  __shared__ int sh;
+__global__ __launch_bounds__(256, 2) void batch_dense_persistent_kernel(BatchPersistArgs pa) {
+  __shared__ int sh[2];
+  int next = sched_reserve(pa.sched);
   for (;;) {
-    const int i = sched_next(pa.sched, &sh);
+    const int i = sched_item(pa.sched, next, sh);
     if (i < 0) return;
-    const int4 it = pa.sched.items[i];
-    const BatchMat &M = pa.mats[it.x];
+    const int4 it = uniform_load(pa.sched.items + i);
+    const BatchMat M = uniform_load(pa.mats + it.x);
     DenseStepArgs a{};
-    if (!batch_dense_args<T>(pa, M, it.z, a)) continue;  // nor has the matrix any later step
-    if (!sched_wait(pa.sched, it.x, it.z * M.ntile, &sh)) return;
-    dense_step_tile<T, 64, WR, kBatchCols>(a, it.y, 0, 0, a.n, nullptr);
+    if (!batch_dense_args<T>(pa, M, it.z, a)) {  // nor has the matrix any later step
+      next = sched_reserve(pa.sched);
+      __syncthreads();  // every wave has read sh[0]
+      continue;
+    }
+    a.ldv = 64;
+    BatchHook hook{pa.sched, it.x, it.z * M.ntile, sh + 1, &next};
+    if (!dense_step_tile<T, 64, WR, kBatchCols<WR>, kChunkLds, sizeof(T) == 4 && WR == 1, BatchHook>(a, it.y, 0, 0, a.n, nullptr, hook))
+      return;
     sched_release(pa.sched, it.x);
   }
 }

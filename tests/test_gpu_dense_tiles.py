@@ -1,0 +1,58 @@
+"""Tiles of the dense step at the edges of their chunks and K-splits.
+
+Batches: matrices whose products are fewer, as many or more chunks than a tile
+keeps in flight, with and without a ragged last one, in the persistent schedule
+(reserved items, R's loads ahead of the wait) and in grouped launches.  Single
+matrices: sizes whose K-split is not a power of two, with a ragged last split.
+The reference is the plain recurrence in FP64 numpy on the library's own
+probes; FP64 bar 1e-10 relative as in the other parity tests, FP32 TOL_F32.
+"""
+import numpy as np
+import pytest
+
+from test_gpu_pairs import check, reference
+from tolerances import tol_for
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_1801_01072_amd as ent  # noqa: E402
+
+DEV = "cuda:0"
+
+
+def symmetric(n, seed):
+    """Eigenvalues within [0.2, 0.6] for large n, within [0, 0.9] for small n."""
+    X = np.random.default_rng(seed).standard_normal((n, n))
+    X = X + X.T
+    return 0.4 * np.eye(n) + X * (0.2 / max(2.9 * np.sqrt(n), np.linalg.norm(X, 2) if n < 300 else 0.0))
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("flags", [0, ent.FLAG_BATCH_STEPWISE])
+@pytest.mark.parametrize("method,m", [("chebyshev", 6), ("taylor", 5)])
+def test_batch_chunk_edges(orc, precision, flags, method, m):
+    ns, s, seed = [1, 7, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65, 95, 96, 97, 127, 128, 129, 161, 257], 33, 3
+    host = [symmetric(n, n) for n in ns]
+    for i in (5, 12, 19):
+        host[i][0, ns[i] - 1] += 0.03  # one moment per product
+    g = ent.Graph([torch.from_numpy(R).to(DEV) for R in host], method, m, s, seed, precision=precision,
+                  probe_dist="gaussian", u_fixed=0.9, flags=flags | ent.FLAG_SKIP_TRACE_CHECK)
+    for _ in range(3):
+        g.launch()
+        per = g.per_probe()
+        for b, R in enumerate(host):
+            _, ref = reference(orc, lambda V, R=R: R @ V, ns[b], method, m, s, seed + b, 1, 0.9)
+            e = float(np.max(np.abs(per[b] - ref)) / max(np.mean(np.abs(ref)), 1.0))
+            assert e <= tol_for(precision), (ns[b], e)
+    g.destroy()
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("n,s", [(2200, 128), (2500, 200), (3001, 100), (4500, 256), (2111, 130)])
+def test_split_counts(orc, precision, n, s):
+    R = symmetric(n, n)
+    check(orc, torch.from_numpy(R).to(DEV), lambda V: R @ V, n, "chebyshev", 4, s, 7, 1, precision, "splits")
