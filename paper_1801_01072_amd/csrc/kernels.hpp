@@ -206,7 +206,8 @@ hipError_t launch_dense_resident(const DenseResidentArgs &a, hipStream_t st);
 
 // ---- trace check -----------------------------------------------------------
 template <typename T>
-hipError_t launch_trace_dense(const T *R, int64_t ldr, int64_t n, double *scal, hipStream_t st);
+hipError_t launch_trace_dense(const T *R, int64_t ldr, int64_t n, double *scal, hipStream_t st,
+                              double *tmp = nullptr, int64_t room = 0);
 // The trace and, in the same pass over R, whether R equals its transpose: a
 // mismatch sets the int32 at scal[S_SYM] (which must start at 0).  host_flag
 // (pinned host memory, may be null) receives that int32 too.
