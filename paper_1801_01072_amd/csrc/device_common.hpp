@@ -200,6 +200,34 @@ __device__ __forceinline__ double power_scale(const PowerPrev &p) {
   return p.norm ? 1.0 / sqrt(p.norm[0]) : 1.0;
 }
 
+// Tiles of a product with a symmetric R (128 x 128, 256 threads): tile t of the
+// lower triangle, row by row (cb <= rb).
+constexpr int kSymTile = 128;
+__device__ __forceinline__ void sym_tile(int64_t t, int64_t &rb, int64_t &cb) {
+  rb = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
+  while (rb * (rb + 1) / 2 > t) --rb;
+  while ((rb + 1) * (rb + 2) / 2 <= t) ++rb;
+  cb = t - rb * (rb + 1) / 2;
+}
+// Sums of 16 values a lane over each of a wave's H lane groups (64 / H lanes),
+// through LDS in place of 16 sums of six cross-lane steps: sum r is value r / H
+// of group r % H, returned on the 4 / H lanes from r * 4 / H on.
+template <int H>
+__device__ __forceinline__ double sym_sums(const double (&val)[16], double (*buf)[65], int lane) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) buf[i][lane] = val[i];
+  __builtin_amdgcn_wave_barrier();
+  constexpr int LP = 4 / H;  // lanes that share a sum
+  const int r = lane / LP, p = lane % LP;
+  double s = 0.0;
+#pragma unroll
+  for (int c = 0; c < 16; ++c) s += buf[r / H][(r % H) * (64 / H) + c * LP + p];
+  s += dpp_move<0xB1>(s);
+  if (LP == 4) s += dpp_move<0x4E>(s);
+  __builtin_amdgcn_wave_barrier();
+  return s;
+}
+
 // Block sums of y^2, xs.y, xs^2 over the rows a block produced (fixed order).
 __device__ __forceinline__ void block_power_partials(double yy, double xy, double xx,
                                                      double *part3, int64_t blk) {

@@ -659,11 +659,22 @@ hipError_t power_trials(int32_t t, int32_t q, int32_t pblk, double *part3, doubl
   return hipSuccess;
 }
 
+// Whether a dense power method reads half of a symmetric R per product: from 64
+// MB of R on (24 MB in BF16x3, whose product at most sizes has two launches
+// either way), given room for the partial sums.  Whole against half, us a
+// product: FP64 n = 2500 10.5 / 10.5, 3001 13.9 / 12.8, 4096 27.9 / 17.7, 8192
+// 104 / 50; FP32 3840 11.3 / 11.0, 4000 11.7 / 12.4, 4096 13.1 / 11.4, 8192 47 /
+// 28; BF16x3 2048 8.5 / 9.2, 2500 10.2 / 8.6, 5000 21.1 / 15.2, 8192 41 / 27.
+bool power_sym_pays(int64_t n, size_t elem, bool split, size_t room) {
+  return (size_t)ent::power_sym_parts(n) * (size_t)n * sizeof(double) <= room &&
+         (size_t)n * (size_t)n * elem >= ((size_t)(split ? 24 : 64) << 20);
+}
+
 template <typename T>
 ent_status enqueue_power(const ent_matrix *R, const T *Rc, int64_t ldr, int32_t t, int32_t q,
                          uint64_t seed, double *x0, double *x1, double *part3, double *norm,
                          double *scal, hipStream_t st, const T *band = nullptr, int32_t hp = 0,
-                         const T *trid = nullptr, int32_t *launches = nullptr) {
+                         const T *trid = nullptr, int32_t *launches = nullptr, double *sym_part = nullptr) {
   const int64_t n = R->n;
   // tridiagonal and banded R: after the first product, the products of a
   // trial in launches of up to pf (ENT_POWER_FUSE, 1 = one per launch)
@@ -677,6 +688,16 @@ ent_status enqueue_power(const ent_matrix *R, const T *Rc, int64_t ldr, int32_t 
   if (R->layout == ENT_DENSE && n <= ent::kDenseResidentMax) {
     HIP_TRY(ent::launch_power_resident<T>(Rc, ldr, n, t, q, seed, scal, st));
     if (launches) *launches = 1;
+    return ENT_OK;
+  }
+  if (R->layout == ENT_DENSE && sym_part) {
+    HIP_TRY(power_trials(t, q, ent::power_blocks_sym(n), part3, norm, scal, st, [&](int32_t trial) {
+      return ent::launch_power_start(x0, n, seed, trial, st);
+    }, [&](int32_t it, const ent::PowerPrev &prev, double *part, int32_t *nblk) {
+      return ent::launch_power_sym<T>(Rc, ldr, n, it & 1 ? x1 : x0, prev, it & 1 ? x0 : x1, part, sym_part, nblk,
+                                      st);
+    }));
+    if (launches) *launches = q * (t + 1);
     return ENT_OK;
   }
   if (R->layout == ENT_DENSE) {
@@ -738,10 +759,20 @@ ent_status enqueue_power(const ent_matrix *R, const T *Rc, int64_t ldr, int32_t 
 // The same power method on the bf16 hi/lo split of a dense R.
 ent_status enqueue_power_split(const uint16_t *hi, const uint16_t *lo, int64_t n, int64_t n_pad,
                                int32_t t, int32_t q, uint64_t seed, double *x0, double *x1,
-                               double *part3, double *norm, double *scal, double *ypart, hipStream_t st) {
+                               double *part3, double *norm, double *scal, double *ypart, hipStream_t st,
+                               double *sym_part = nullptr) {
   // the split is zero beyond n, and so must be the vectors it multiplies
   HIP_TRY(ent::launch_fill(x0, n_pad, 0.0, st));
   HIP_TRY(ent::launch_fill(x1, n_pad, 0.0, st));
+  if (sym_part) {
+    HIP_TRY(power_trials(t, q, ent::power_blocks_sym(n), part3, norm, scal, st, [&](int32_t trial) {
+      return ent::launch_power_start(x0, n, seed, trial, st);
+    }, [&](int32_t it, const ent::PowerPrev &prev, double *part, int32_t *nblk) {
+      return ent::launch_power_sym_split(hi, lo, n_pad, n, it & 1 ? x1 : x0, prev, it & 1 ? x0 : x1, part,
+                                         sym_part, nblk, st);
+    }));
+    return ENT_OK;
+  }
   HIP_TRY(power_trials(t, q, ent::power_blocks_split(n_pad), part3, norm, scal, st, [&](int32_t trial) {
     return ent::launch_power_start(x0, n, seed, trial, st);
   }, [&](int32_t it, const ent::PowerPrev &prev, double *part, int32_t *nblk) {
@@ -1071,11 +1102,20 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
   else
     HIP_TRY(ent::launch_sign_gen(signs, n, s, ldv, seed, st));
   // power method and interval
+  int32_t differs = -1;  // not read yet
   if (use_power) {
     pe.power_begin = pe.mark();
     int32_t pl = 0;
+    // the answer first where the power method can use it (probes are generated
+    // meanwhile), with a V block, free until the recurrence starts, for the sums
+    double *sym_part = nullptr;
+    if (dense && ask && power_sym_pays(n, sizeof(T), false, (size_t)n_pad * ldv * sizeof(T))) {
+      rc = asym.read(st, &differs);
+      if (rc != ENT_OK) return rc;
+      if (differs == 0) sym_part = (double *)VA;
+    }
     rc = enqueue_power<T>(R, Rt, ldr, o.power_iters, o.power_trials, seed, x0, x1, p0, p1, scal, st, band, hp,
-                          trid, &pl);
+                          trid, &pl, sym_part);
     if (rc != ENT_OK) return rc;
     pe.power_end = pe.mark();
     pe.power_launches = pl;
@@ -1087,9 +1127,10 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
 
   // recurrence
   if (ask) {
-    int32_t differs = 0;
-    rc = asym.read(st, &differs);
-    if (rc != ENT_OK) return rc;
+    if (differs < 0) {
+      rc = asym.read(st, &differs);
+      if (rc != ENT_OK) return rc;
+    }
     pairs = differs == 0;
   }
   const int32_t nsteps = clenshaw ? m + 1 : recurrence_products(method, m, pairs);
@@ -1452,10 +1493,17 @@ ent_status run_bf16x3(const ent_matrix *R, int32_t method, int32_t m, int32_t s,
     HIP_TRY(ent::launch_split_matrix<double>((const double *)R->values, R->ld, n, n_pad, nullptr, Ahi, Alo, st));
   else
     HIP_TRY(ent::launch_split_matrix<float>((const float *)R->values, R->ld, n, n_pad, nullptr, Ahi, Alo, st));
+  int32_t differs = -1;  // not read yet
   if (use_power) {
     pe.power_begin = pe.mark();
+    double *sym_part = nullptr;
+    if (pairs && power_sym_pays(n_pad, 4, true, (size_t)n_pad * ldv * sizeof(float))) {
+      rc = asym.read(st, &differs);
+      if (rc != ENT_OK) return rc;
+      if (differs == 0) sym_part = (double *)VA;
+    }
     rc = enqueue_power_split(Ahi, Alo, n, n_pad, o.power_iters, o.power_trials, seed, x0, x1, p0, p1,
-                             scal, ypart, st);
+                             scal, ypart, st, sym_part);
     if (rc != ENT_OK) return rc;
     pe.power_end = pe.mark();
     pe.power_launches = o.power_trials * (o.power_iters + 1);
@@ -1464,9 +1512,10 @@ ent_status run_bf16x3(const ent_matrix *R, int32_t method, int32_t m, int32_t s,
                                      normalize ? op.trace_div : 0.0));
 
   if (pairs) {
-    int32_t differs = 0;
-    rc = asym.read(st, &differs);
-    if (rc != ENT_OK) return rc;
+    if (differs < 0) {
+      rc = asym.read(st, &differs);
+      if (rc != ENT_OK) return rc;
+    }
     pairs = differs == 0;
   }
   const int32_t nsteps = clenshaw ? m + 1 : recurrence_products(method, m, pairs);

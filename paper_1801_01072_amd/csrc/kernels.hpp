@@ -152,6 +152,15 @@ constexpr int32_t kPowerSelfSum = 1024;  // most triples summed by every workgro
 // *nblk receives the number of blocks.
 int32_t power_blocks_dense(int64_t n);
 int32_t power_blocks_csr(int64_t n);
+// The same product reading half of an R that equals its transpose; part holds
+// power_sym_parts(n) * n doubles, nblk is power_blocks_sym(n).
+int32_t power_blocks_sym(int64_t n);
+int64_t power_sym_parts(int64_t n);
+template <typename T>
+hipError_t launch_power_sym(const T *R, int64_t ldr, int64_t n, const double *x, const PowerPrev &prev, double *y,
+                            double *part3, double *part, int32_t *nblk, hipStream_t st);
+hipError_t launch_power_sym_combine(const double *part, int64_t nparts, int64_t stride, int64_t n, const double *x,
+                                    const PowerPrev &prev, double *y, double *part3, int32_t *nblk, hipStream_t st);
 template <typename T>
 hipError_t launch_power_gemv(const T *R, int64_t ldr, int64_t n, const double *x,
                              const PowerPrev &prev, double *y, double *part3, int32_t *nblk,
@@ -494,6 +503,9 @@ hipError_t launch_bf16x3_gemm(const Bf16GemmArgs &a, hipStream_t st);
 // doubles).
 int32_t power_blocks_split(int64_t n_pad);
 int32_t power_split_parts(int64_t n_pad);
+hipError_t launch_power_sym_split(const uint16_t *hi, const uint16_t *lo, int64_t n_pad, int64_t n,
+                                  const double *x, const PowerPrev &prev, double *y, double *part3,
+                                  double *part, int32_t *nblk, hipStream_t st);
 hipError_t launch_power_gemv_split(const uint16_t *hi, const uint16_t *lo, int64_t n_pad, int64_t n,
                                    const double *x, const PowerPrev &prev, double *y, double *part3,
                                    double *ypart, int32_t *nblk, hipStream_t st);

@@ -773,6 +773,76 @@ __global__ __launch_bounds__(256) void power_split_combine_kernel(const double *
   block_power_partials(yy, xy, xx, part3, blockIdx.x);
 }
 
+// The product from half of a symmetric R, on the split: see
+// power_sym_part_kernel.  n = 8192: 41 -> 27 us a product.  A wave takes 32 columns (two blocks of 16) of the
+// tile's four 32-row bands; lane l holds row l & 31 and 8 columns of a block.
+__global__ __launch_bounds__(256) void power_sym_split_kernel(const uint16_t *__restrict__ hi,
+                                                              const uint16_t *__restrict__ lo, int64_t n_pad,
+                                                              const double *__restrict__ x,
+                                                              double *__restrict__ part) {
+  __shared__ double buf[4][16][65];
+  __shared__ double rows[4][kSymTile];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int64_t nkb = n_pad / 16;
+  int64_t rb, cb;
+  sym_tile(blockIdx.x, rb, cb);
+  const int64_t kb = cb * 8 + 2 * w;
+  double xr[4], racc[4], xc[16], cacc[16];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    xr[b] = x[rb * kSymTile + 32 * b + (lane & 31)];
+    racc[b] = 0.0;
+  }
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    xc[c] = x[(kb + c / 8) * 16 + 8 * (lane >> 5) + c % 8];
+    cacc[c] = 0.0;
+  }
+  u16x8 h[4][2], l[4][2];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int64_t at = ((rb * 4 + b) * nkb + kb + k) * 512 + 8 * lane;
+      h[b][k] = *(const u16x8 *)(hi + at);
+      l[b][k] = *(const u16x8 *)(lo + at);
+    }
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double v = (double)(bf16_to_f32(h[b][k][e]) + bf16_to_f32(l[b][k][e]));
+        racc[b] += v * xc[8 * k + e];
+        cacc[8 * k + e] += v * xr[b];
+      }
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const double s = racc[b] + __shfl_xor(racc[b], 32, 64);
+    if (lane < 32) rows[w][32 * b + lane] = s;
+  }
+  if (rb != cb) {
+    // sum r of sym_sums: value r / 2 (block r / 16, column r / 2 % 8) of half r % 2
+    const double s = sym_sums<2>(cacc, buf[w], lane);
+    const int r = lane / 2;
+    if (lane % 2 == 0) part[rb * n_pad + (kb + r / 16) * 16 + 8 * (r % 2) + r / 2 % 8] = s;
+  }
+  __syncthreads();
+  if (tid < kSymTile)
+    part[cb * n_pad + rb * kSymTile + tid] = rows[0][tid] + rows[1][tid] + rows[2][tid] + rows[3][tid];
+}
+
+hipError_t launch_power_sym_split(const uint16_t *hi, const uint16_t *lo, int64_t n_pad, int64_t n,
+                                  const double *x, const PowerPrev &prev, double *y, double *part3,
+                                  double *part, int32_t *nblk, hipStream_t st) {
+  if (n_pad % kSymTile != 0) return hipErrorInvalidValue;
+  const int64_t nb = n_pad / kSymTile;
+  power_sym_split_kernel<<<(unsigned)(nb * (nb + 1) / 2), 256, 0, st>>>(hi, lo, n_pad, x, part);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_power_sym_combine(part, nb, n_pad, n, x, prev, y, part3, nblk, st);
+}
+
 hipError_t launch_power_gemv_split(const uint16_t *hi, const uint16_t *lo, int64_t n_pad, int64_t n,
                                    const double *x, const PowerPrev &prev, double *y, double *part3,
                                    double *ypart, int32_t *nblk, hipStream_t st) {

@@ -191,6 +191,150 @@ __global__ __launch_bounds__(256) void power_gemv_kernel(const T *__restrict__ R
   power_gemv_body<T>(R, ldr, n, x, prev, y, part3, blockIdx.x);
 }
 
+// The same product from half of an R that equals its transpose: a workgroup
+// reads a 128 x 128 tile on or below the diagonal once and leaves its row sums
+// A x_J in part[J][rows of I] and its column sums A^T x_I in part[I][columns of
+// J]; power_sym_combine_kernel adds the n / 128 parts of a row in order.
+// Consecutive workgroups take consecutive tiles of a row of tiles.  Bound by
+// HBM (the combination adds 4 us): n = 8192, FP64 103 -> 50 us a product, FP32
+// 48 -> 28; more at power_sym_pays.
+template <typename T>
+__global__ __launch_bounds__(256) void power_sym_part_kernel(const T *__restrict__ R, int64_t ldr, int64_t n,
+                                                             const double *__restrict__ x,
+                                                             double *__restrict__ part) {
+  constexpr int VEC = 16 / sizeof(T), LPR = kSymTile / VEC, H = 64 / LPR;  // lanes per row, rows at a time
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  __shared__ double buf[4][16][65];
+  __shared__ double xr[kSymTile];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int half = lane / LPR, cl = (lane % LPR) * VEC;
+  int64_t rb, cb;
+  sym_tile(blockIdx.x, rb, cb);
+  const int64_t c0 = cb * kSymTile + cl, w0 = rb * kSymTile + 32 * w;
+  if (tid < kSymTile) xr[tid] = rb * kSymTile + tid < n ? x[rb * kSymTile + tid] : 0.0;
+  __syncthreads();
+  double xc[VEC], cacc[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    xc[e] = c0 + e < n ? x[c0 + e] : 0.0;
+    cacc[e] = 0.0;
+  }
+  // a tile that reaches beyond n reads row n - 1 and column 0 there (x is zero
+  // in xr and xc, the row sums are not stored), and a vector across n one by one
+  const bool inside = rb * kSymTile + kSymTile <= n && cb * kSymTile + kSymTile <= n;
+  const bool whole = c0 + VEC <= n;
+#pragma unroll 1
+  for (int ch = 0; ch < 2 / H; ++ch) {  // 16 H rows at a time
+    const int row0 = 32 * w + ch * 16 * H + half;
+    const T *Rr = R + (rb * kSymTile + row0) * ldr + c0;
+    double racc[16];
+#pragma unroll
+    for (int i0 = 0; i0 < 16; i0 += 8) {
+      vec_t v[8];
+      if (inside) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = *(const vec_t *)(Rr + (int64_t)(i0 + i) * H * ldr);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int64_t r = rb * kSymTile + row0 + (i0 + i) * H;
+          v[i] = *(const vec_t *)(R + (r < n ? r : n - 1) * ldr + (whole ? c0 : 0));
+        }
+        if (!whole && c0 < n) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const int64_t r = rb * kSymTile + row0 + (i0 + i) * H;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e)
+              if (c0 + e < n) v[i][e] = R[(r < n ? r : n - 1) * ldr + c0 + e];
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const double xv = xr[row0 + (i0 + i) * H];
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          s += (double)v[i][e] * xc[e];
+          cacc[e] += (double)v[i][e] * xv;
+        }
+        racc[i0 + i] = s;
+      }
+    }
+    const double s = sym_sums<H>(racc, buf[w], lane);
+    const int64_t r = w0 + ch * 16 * H + lane / (4 / H);
+    if (lane % (4 / H) == 0 && r < n) part[cb * n + r] = s;
+  }
+  if (rb != cb) {
+    double(*cs)[kSymTile] = (double(*)[kSymTile])buf;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      double s = cacc[e];
+      if (H == 2) s += __shfl_xor(s, 32, 64);
+      if (half == 0) cs[w][cl + e] = s;
+    }
+    __syncthreads();
+    if (tid < kSymTile && cb * kSymTile + tid < n)
+      part[rb * n + cb * kSymTile + tid] = cs[0][tid] + cs[1][tid] + cs[2][tid] + cs[3][tid];
+  }
+}
+
+// y = sum of the parts (stride rows apart), scaled; 64 rows a workgroup, each
+// wave a quarter of the parts.
+__global__ __launch_bounds__(256) void power_sym_combine_kernel(const double *__restrict__ part, int32_t nparts,
+                                                                int64_t stride, int64_t n,
+                                                                const double *__restrict__ x, PowerPrev prev,
+                                                                double *__restrict__ y,
+                                                                double *__restrict__ part3) {
+  __shared__ double sums[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t r = (int64_t)blockIdx.x * 64 + lane;
+  const int32_t p0 = nparts * w / 4, p1 = nparts * (w + 1) / 4;
+  double s = 0.0;
+  if (r < n) {
+#pragma unroll 8
+    for (int32_t p = p0; p < p1; ++p) s += part[p * stride + r];
+  }
+  sums[w][lane] = s;
+  const double sc = power_scale(prev);
+  __syncthreads();
+  double yy = 0.0, xy = 0.0, xx = 0.0;
+  if (w == 0 && r < n) {
+    const double yv = sc * (sums[0][lane] + sums[1][lane] + sums[2][lane] + sums[3][lane]), xs = sc * x[r];
+    y[r] = yv;
+    yy = yv * yv;
+    xy = xs * yv;
+    xx = xs * xs;
+  }
+  block_power_partials(yy, xy, xx, part3, blockIdx.x);
+}
+
+int32_t power_blocks_sym(int64_t n) { return (int32_t)((n + 63) / 64); }
+int64_t power_sym_parts(int64_t n) { return (n + kSymTile - 1) / kSymTile; }
+
+hipError_t launch_power_sym_combine(const double *part, int64_t nparts, int64_t stride, int64_t n, const double *x,
+                                    const PowerPrev &prev, double *y, double *part3, int32_t *nblk, hipStream_t st) {
+  if (prev.part == part3) return hipErrorInvalidValue;  // read while this product's are written
+  *nblk = power_blocks_sym(n);
+  power_sym_combine_kernel<<<(unsigned)*nblk, 256, 0, st>>>(part, (int32_t)nparts, stride, n, x, prev, y, part3);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_power_sym(const T *R, int64_t ldr, int64_t n, const double *x, const PowerPrev &prev, double *y,
+                            double *part3, double *part, int32_t *nblk, hipStream_t st) {
+  const int64_t nb = power_sym_parts(n);
+  power_sym_part_kernel<T><<<(unsigned)(nb * (nb + 1) / 2), 256, 0, st>>>(R, ldr, n, x, part);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_power_sym_combine(part, nb, n, n, x, prev, y, part3, nblk, st);
+}
+template hipError_t launch_power_sym<double>(const double *, int64_t, int64_t, const double *, const PowerPrev &,
+                                             double *, double *, double *, int32_t *, hipStream_t);
+template hipError_t launch_power_sym<float>(const float *, int64_t, int64_t, const double *, const PowerPrev &,
+                                            double *, double *, double *, int32_t *, hipStream_t);
+
 int32_t power_blocks_dense(int64_t n) { return (int32_t)((n + 7) / 8); }
 int32_t power_blocks_csr(int64_t n) {
   const int64_t b = (n + 31) / 32;

@@ -56,3 +56,22 @@ def test_batch_chunk_edges(orc, precision, flags, method, m):
 def test_split_counts(orc, precision, n, s):
     R = symmetric(n, n)
     check(orc, torch.from_numpy(R).to(DEV), lambda V: R @ V, n, "chebyshev", 4, s, 7, 1, precision, "splits")
+
+
+@pytest.mark.parametrize("precision,n", [("f64", 2897), ("f64", 3001), ("f64", 3072), ("f32", 4097), ("f32", 4162),
+                                         ("f32", 4224), ("bf16x3", 2433), ("bf16x3", 2560), ("bf16x3", 3001)])
+def test_power_method_on_half_of_r(precision, n):
+    """A symmetric R read by half against the same R with one entry moved to the
+    next number, which is read whole: sums of FP64 products in another order
+    (20 products, n eps each: 2e-11 at most) and the moved entry (2^-24 of 1e-2
+    relative to the largest eigenvalue)."""
+    dtype = np.float64 if precision == "f64" else np.float32
+    R = symmetric(n, n).astype(dtype)
+    got = []
+    for moved in (False, True):
+        if moved:
+            R[0, n - 1] = np.nextafter(R[0, n - 1], dtype(1))
+        got.append(ent.entropy_estimate(torch.from_numpy(R).to(DEV), "chebyshev", 4, 128, 5, precision=precision,
+                                        flags=ent.FLAG_SKIP_TRACE_CHECK))
+    print(f"[power half {precision} n={n}] u {got[0].u:.15f} whole {got[1].u:.15f}", flush=True)
+    assert 0.2 < got[0].u < 2.0 and abs(got[0].u / got[1].u - 1) <= 1e-9
