@@ -532,12 +532,11 @@ __device__ __forceinline__ void setup_interval_body(double *__restrict__ scal, i
   __syncthreads();
   if (method != 1) return;
   const double u = su;
-  const double pi = 3.141592653589793238462643383279502884;
-  for (int w = threadIdx.x; w <= m; w += blockDim.x) {
-    double a;
-    if (lo == 0.0) {
+  if (lo == 0.0) {
+    for (int w = threadIdx.x; w <= m; w += blockDim.x) {
       // Lemma 3: alpha_0 = (u/2)(ln(u/4)+1), alpha_1 = (u/4)(2 ln(u/4)+3),
       // alpha_w = (-1)^w u / (w^3 - w)
+      double a;
       if (w == 0) {
         a = 0.5 * u * (log(0.25 * u) + 1.0);
       } else if (w == 1) {
@@ -546,33 +545,57 @@ __device__ __forceinline__ void setup_interval_body(double *__restrict__ scal, i
         const double dw = (double)w;
         a = ((w & 1) ? -u : u) / (dw * dw * dw - dw);
       }
-    } else {
-      // Chebyshev projection of x ln x on [lo, u] by an N-point Gauss-Chebyshev
-      // rule, N = 1024 (2(m+1) beyond degree 511): independent of m, so the
-      // partial sums over the degree are nested
-      const int N = (m + 1) <= 512 ? 1024 : 2 * (m + 1);
-      double acc = 0.0;
-      for (int i = 0; i < N; ++i) {
-        const double th = pi * ((double)i + 0.5) / (double)N;
-        const double x = 0.5 * (u + lo) + 0.5 * (u - lo) * cos(th);
-        const double hx = x > 0.0 ? x * log(x) : 0.0;
-        acc += hx * cos((double)w * th);
-      }
-      a = (2.0 / (double)N) * acc;
-      if (w == 0) a *= 0.5;
+      scal[S_ALPHA + w] = a;
     }
-    scal[S_ALPHA + w] = a;
+    return;
+  }
+  // Chebyshev projection of x ln x on [lo, u] by an N-point Gauss-Chebyshev
+  // rule, N = 1024 (2(m+1) beyond degree 511): independent of m, so the partial
+  // sums over the degree are nested.  The function's values at up to kNodes
+  // nodes at a time stand in LDS and a wave sums a coefficient, its cosines
+  // cos(w th_i) = cos(pi j / 2N), j = w (2i + 1) mod 4N, from a table where N is
+  // kNodes (one thread per coefficient and a logarithm and two cosines per node:
+  // 518 us at m = 40, now 11).
+  constexpr int kNodes = 1024;
+  __shared__ double hx[kNodes], table[4 * kNodes];
+  const int N = (m + 1) <= 512 ? kNodes : 2 * (m + 1);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  if (N == kNodes) {
+    for (int j = threadIdx.x; j < 4 * kNodes; j += blockDim.x) table[j] = cospi((double)j / (2.0 * kNodes));
+    __syncthreads();
+  }
+  auto cosine = [&](int64_t j) {
+    j %= 4 * (int64_t)N;
+    return N == kNodes ? table[j] : cospi((double)j / (2.0 * (double)N));
+  };
+  for (int base = 0; base < N; base += kNodes) {
+    const int nodes = N - base < kNodes ? N - base : kNodes;
+    for (int i = threadIdx.x; i < nodes; i += blockDim.x) {
+      const double x = 0.5 * (u + lo) + 0.5 * (u - lo) * cosine(2 * (base + i) + 1);
+      hx[i] = x > 0.0 ? x * log(x) : 0.0;
+    }
+    __syncthreads();
+    for (int w = wv; w <= m; w += nw) {
+      double acc = 0.0;
+      for (int i = lane; i < nodes; i += 64) acc += hx[i] * cosine((int64_t)w * (2 * (base + i) + 1));
+      acc = wave_sum(acc);
+      if (lane == 0) {
+        if (base > 0) acc += scal[S_ALPHA + w];
+        if (base + kNodes >= N) acc *= (w == 0 ? 1.0 : 2.0) / (double)N;
+        scal[S_ALPHA + w] = acc;
+      }
+    }
+    __syncthreads();
   }
 }
-
-__global__ void setup_interval_kernel(double *__restrict__ scal, int32_t method, int32_t m,
+__global__ __launch_bounds__(1024) void setup_interval_kernel(double *__restrict__ scal, int32_t method, int32_t m,
                                       double c, double u_fixed, double lo, double norm_div) {
   setup_interval_body(scal, method, m, c, u_fixed, lo, norm_div);
 }
 
 hipError_t launch_setup_interval(double *scal, int32_t method, int32_t m, double c, double u_fixed,
                                  double lo, hipStream_t st, double norm_div) {
-  setup_interval_kernel<<<1, 256, 0, st>>>(scal, method, m, c, u_fixed, lo, norm_div);
+  setup_interval_kernel<<<1, lo == 0.0 ? 256 : 1024, 0, st>>>(scal, method, m, c, u_fixed, lo, norm_div);
   return hipGetLastError();
 }
 

@@ -75,3 +75,24 @@ def test_power_method_on_half_of_r(precision, n):
                                         flags=ent.FLAG_SKIP_TRACE_CHECK))
     print(f"[power half {precision} n={n}] u {got[0].u:.15f} whole {got[1].u:.15f}", flush=True)
     assert 0.2 < got[0].u < 2.0 and abs(got[0].u / got[1].u - 1) <= 1e-9
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 5, 63, 64, 255, 511, 512, 513, 700, 1100])
+def test_cutoff_coefficients(orc, m):
+    """The projection on [lo, u] of every degree, from the moments the call
+    reports: cosines to half an ulp and N terms of size <= 1/e added pairwise
+    over 64 lanes (oracle: in turn), N eps / e each side, per coefficient; the
+    moments of one probe are at most |g|^2 = n each."""
+    n, s, lo, u = 24, 3, 1e-3, 0.5
+    R = torch.from_numpy(symmetric(n, 5) * 0.5).to(DEV)
+    nodes = orc.cutoff_nodes(m)
+    a = orc.cheb_interp_coeffs(lo, u, m, nodes)
+    bar = 2 * nodes * 2.3e-16 / np.e * (m + 1) * n
+    _, per, mom = ent.entropy_estimate_detail(R, "chebyshev", m, s, 2, precision="f64", u_fixed=u, cutoff=lo,
+                                              flags=ent.FLAG_SKIP_TRACE_CHECK)
+    want = -(a[:, None] * mom).sum(axis=0)
+    print(f"[cutoff m={m}] {np.max(np.abs(per - want)):.2e} bar {bar:.2e}", flush=True)
+    assert np.max(np.abs(per - want)) <= bar
+    got = ent.entropy_estimate_batched([R, R], "chebyshev", m, s, 2, precision="f64", u_fixed=u, cutoff=lo,
+                                       flags=ent.FLAG_SKIP_TRACE_CHECK)
+    assert abs(got[0].entropy - np.mean(want)) <= bar + 1e-10 * abs(np.mean(want))
