@@ -703,9 +703,12 @@ int32_t power_blocks_split(int64_t n_pad) { return (int32_t)(n_pad / 32); }
 // 16-column blocks (about 1024 workgroups in all): part p of band b goes to
 // ypart[p][row], and a second pass adds the parts in order, scales, and
 // forms the norm partials per 256 rows.
+// Up to n_pad = 1536 the second launch costs more than the idle CUs: one
+// against parts, us a product: n = 400 4.8 / 6.9, 1000 6.2 / 7.0, 1500 7.6 /
+// 8.1, 1800 8.9 / 8.8, 2300 9.7 / 9.7.
 int32_t power_split_parts(int64_t n_pad) {
   const int64_t nb = n_pad / 32, nkb = n_pad / 16;
-  if (nb % 256 == 0) return 1;
+  if (nb % 256 == 0 || n_pad <= 1536) return 1;
   int64_t p = 1;
   while (nb * p < 1024 && 2 * p * 16 <= nkb) p *= 2;
   return (int32_t)p;
