@@ -612,8 +612,15 @@ template <typename T>
 hipError_t launch_batch_power_gemv(const BatchMat *mats, const int2 *ptiles, int32_t nptiles,
                                    const double *x, const double *pprev, double *y, double *pout,
                                    hipStream_t st);
+// The same reading half of each symmetric matrix: stiles lists (matrix, tile of
+// 128 x 128, power_sym_parts (parts + 1) / 2 of them), tiles (matrix, 64 rows).
+template <typename T>
+hipError_t launch_batch_power_sym(const BatchMat *mats, const int2 *stiles, int32_t nstiles, const int2 *tiles,
+                                  int32_t ntiles, const double *x, const double *pprev, T *V, double *y,
+                                  double *pout, hipStream_t st);
+// half: the triples are those of launch_batch_power_sym
 hipError_t launch_batch_power_rq(const BatchMat *mats, int32_t count, const double *p,
-                                 int32_t trial, hipStream_t st);
+                                 int32_t trial, hipStream_t st, bool half = false);
 hipError_t launch_batch_setup(const BatchMat *mats, int32_t count, int32_t method, int32_t m,
                               double c, double u_fixed, double lo, hipStream_t st,
                               double norm_div = 0.0);

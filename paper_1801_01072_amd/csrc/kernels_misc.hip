@@ -199,17 +199,15 @@ __global__ __launch_bounds__(256) void power_gemv_kernel(const T *__restrict__ R
 // HBM (the combination adds 4 us): n = 8192, FP64 103 -> 50 us a product, FP32
 // 48 -> 28; more at power_sym_pays.
 template <typename T>
-__global__ __launch_bounds__(256) void power_sym_part_kernel(const T *__restrict__ R, int64_t ldr, int64_t n,
-                                                             const double *__restrict__ x,
-                                                             double *__restrict__ part) {
+__device__ __forceinline__ void power_sym_body(const T *__restrict__ R, int64_t ldr, int64_t n,
+                                               const double *__restrict__ x, double *__restrict__ part, int64_t rb,
+                                               int64_t cb, bool cols) {
   constexpr int VEC = 16 / sizeof(T), LPR = kSymTile / VEC, H = 64 / LPR;  // lanes per row, rows at a time
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
   __shared__ double buf[4][16][65];
   __shared__ double xr[kSymTile];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int half = lane / LPR, cl = (lane % LPR) * VEC;
-  int64_t rb, cb;
-  sym_tile(blockIdx.x, rb, cb);
   const int64_t c0 = cb * kSymTile + cl, w0 = rb * kSymTile + 32 * w;
   if (tid < kSymTile) xr[tid] = rb * kSymTile + tid < n ? x[rb * kSymTile + tid] : 0.0;
   __syncthreads();
@@ -266,7 +264,7 @@ __global__ __launch_bounds__(256) void power_sym_part_kernel(const T *__restrict
     const int64_t r = w0 + ch * 16 * H + lane / (4 / H);
     if (lane % (4 / H) == 0 && r < n) part[cb * n + r] = s;
   }
-  if (rb != cb) {
+  if (cols) {
     double(*cs)[kSymTile] = (double(*)[kSymTile])buf;
     __syncthreads();
 #pragma unroll
@@ -281,16 +279,23 @@ __global__ __launch_bounds__(256) void power_sym_part_kernel(const T *__restrict
   }
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void power_sym_part_kernel(const T *__restrict__ R, int64_t ldr, int64_t n,
+                                                             const double *__restrict__ x,
+                                                             double *__restrict__ part) {
+  int64_t rb, cb;
+  sym_tile(blockIdx.x, rb, cb);
+  power_sym_body<T>(R, ldr, n, x, part, rb, cb, rb != cb);
+}
+
 // y = sum of the parts (stride rows apart), scaled; 64 rows a workgroup, each
 // wave a quarter of the parts.
-__global__ __launch_bounds__(256) void power_sym_combine_kernel(const double *__restrict__ part, int32_t nparts,
-                                                                int64_t stride, int64_t n,
-                                                                const double *__restrict__ x, PowerPrev prev,
-                                                                double *__restrict__ y,
-                                                                double *__restrict__ part3) {
+__device__ __forceinline__ void power_sym_sum(const double *__restrict__ part, int32_t nparts, int64_t stride,
+                                              int64_t n, const double *__restrict__ x, const PowerPrev &prev,
+                                              double *__restrict__ y, double *__restrict__ part3, int64_t blk) {
   __shared__ double sums[4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t r = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t r = blk * 64 + lane;
   const int32_t p0 = nparts * w / 4, p1 = nparts * (w + 1) / 4;
   double s = 0.0;
   if (r < n) {
@@ -308,7 +313,15 @@ __global__ __launch_bounds__(256) void power_sym_combine_kernel(const double *__
     xy = xs * yv;
     xx = xs * xs;
   }
-  block_power_partials(yy, xy, xx, part3, blockIdx.x);
+  block_power_partials(yy, xy, xx, part3, blk);
+}
+
+__global__ __launch_bounds__(256) void power_sym_combine_kernel(const double *__restrict__ part, int32_t nparts,
+                                                                int64_t stride, int64_t n,
+                                                                const double *__restrict__ x, PowerPrev prev,
+                                                                double *__restrict__ y,
+                                                                double *__restrict__ part3) {
+  power_sym_sum(part, nparts, stride, n, x, prev, y, part3, blockIdx.x);
 }
 
 int32_t power_blocks_sym(int64_t n) { return (int32_t)((n + 63) / 64); }
@@ -1428,6 +1441,54 @@ __global__ __launch_bounds__(256) void batch_power_gemv_kernel(const BatchMat *_
   power_gemv_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, prev, y + M.xoff, pout + M.pboff, t.y);
 }
 
+// The same from half of each matrix that equals its transpose (its answer is on
+// the device; another one's mirror tiles are read too), the sums in the
+// matrix's V block V: stiles (matrix, tile), tiles (matrix, 64 rows).
+template <typename T>
+__global__ __launch_bounds__(256) void batch_power_sym_kernel(const BatchMat *__restrict__ mats,
+                                                              const int2 *__restrict__ stiles,
+                                                              const double *__restrict__ x, T *V) {
+  const int2 t = uniform_load(stiles + blockIdx.x);
+  const BatchMat M = uniform_load(mats + t.x);
+  double *part = (double *)(V + M.voff);
+  int64_t rb, cb;
+  sym_tile(t.y, rb, cb);
+  const bool sym = batch_pairs(M);
+  power_sym_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, part, rb, cb, sym && rb != cb);
+  if (sym || rb == cb) return;
+  __syncthreads();
+  power_sym_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, part, cb, rb, false);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void batch_power_sym_combine_kernel(const BatchMat *__restrict__ mats,
+                                                                      const int2 *__restrict__ tiles,
+                                                                      const double *x, const double *pprev,
+                                                                      const T *V, double *y, double *pout) {
+  const int2 t = tiles[blockIdx.x];
+  const BatchMat &M = mats[t.x];
+  if ((int64_t)t.y * 64 >= M.n) return;
+  const PowerPrev prev = {nullptr, pprev ? pprev + M.pboff : nullptr, (int32_t)((M.n + 63) / 64)};
+  power_sym_sum((const double *)(V + M.voff), (int32_t)((M.n + kSymTile - 1) / kSymTile), M.n, M.n, x + M.xoff, prev,
+                y + M.xoff, pout + M.pboff, t.y);
+}
+
+template <typename T>
+hipError_t launch_batch_power_sym(const BatchMat *mats, const int2 *stiles, int32_t nstiles, const int2 *tiles,
+                                  int32_t ntiles, const double *x, const double *pprev, T *V, double *y,
+                                  double *pout, hipStream_t st) {
+  if (pprev == pout) return hipErrorInvalidValue;
+  batch_power_sym_kernel<T><<<(unsigned)nstiles, 256, 0, st>>>(mats, stiles, x, V);
+  batch_power_sym_combine_kernel<T><<<(unsigned)ntiles, 256, 0, st>>>(mats, tiles, x, pprev, V, y, pout);
+  return hipGetLastError();
+}
+template hipError_t launch_batch_power_sym<double>(const BatchMat *, const int2 *, int32_t, const int2 *, int32_t,
+                                                   const double *, const double *, double *, double *, double *,
+                                                   hipStream_t);
+template hipError_t launch_batch_power_sym<float>(const BatchMat *, const int2 *, int32_t, const int2 *, int32_t,
+                                                  const double *, const double *, float *, double *, double *,
+                                                  hipStream_t);
+
 template <typename T>
 hipError_t launch_batch_power_gemv(const BatchMat *mats, const int2 *ptiles, int32_t nptiles,
                                    const double *x, const double *pprev, double *y, double *pout,
@@ -1445,16 +1506,16 @@ template hipError_t launch_batch_power_gemv<float>(const BatchMat *, const int2 
 
 // One block per matrix: its final product's triples and Rayleigh quotient.
 __global__ __launch_bounds__(256) void batch_power_rq_kernel(const BatchMat *__restrict__ mats, const double *p,
-                                                             int32_t trial) {
+                                                             int32_t trial, bool half) {
   __shared__ double norm3[3];
   const BatchMat &M = mats[blockIdx.x];
-  power_reduce_body(p + M.pboff, M.pblk, norm3);
+  power_reduce_body(p + M.pboff, half ? (int32_t)((M.n + 63) / 64) : M.pblk, norm3);
   power_rq_body(M.scal, norm3, trial);
 }
 
 hipError_t launch_batch_power_rq(const BatchMat *mats, int32_t count, const double *p,
-                                 int32_t trial, hipStream_t st) {
-  batch_power_rq_kernel<<<(unsigned)count, 256, 0, st>>>(mats, p, trial);
+                                 int32_t trial, hipStream_t st, bool half) {
+  batch_power_rq_kernel<<<(unsigned)count, 256, 0, st>>>(mats, p, trial, half);
   return hipGetLastError();
 }
 

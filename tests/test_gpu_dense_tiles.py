@@ -96,3 +96,27 @@ def test_cutoff_coefficients(orc, m):
     got = ent.entropy_estimate_batched([R, R], "chebyshev", m, s, 2, precision="f64", u_fixed=u, cutoff=lo,
                                        flags=ent.FLAG_SKIP_TRACE_CHECK)
     assert abs(got[0].entropy - np.mean(want)) <= bar + 1e-10 * abs(np.mean(want))
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_batch_power_method_on_half(precision):
+    """A batch large enough to read half of each symmetric matrix (and both
+    halves of any other) against single estimates, which at these sizes read
+    all of it: the same FP64 sums in another order, 20 products of n eps each."""
+    dtype = np.float64 if precision == "f64" else np.float32
+    ns = [1, 2, 63, 127, 128, 129, 255, 257, 384, 1000] + [1160 if precision == "f32" else 808] * 18
+    mats = []
+    for b, n in enumerate(ns):
+        R = symmetric(n, b).astype(dtype)
+        if b in (3, 9, 12):
+            R[0, n - 1] += dtype(0.01)
+        mats.append(torch.from_numpy(R).to(DEV))
+    assert sum(M.nbytes for M in mats) >= 96 << 20
+    g = ent.Graph(mats, "chebyshev", 3, 20, 9, precision=precision, flags=ent.FLAG_SKIP_TRACE_CHECK)
+    for _ in range(3):
+        res = g.launch()
+        for b, M in enumerate(mats):
+            one = ent.entropy_estimate(M, "chebyshev", 3, 20, 9 + b, precision=precision,
+                                       flags=ent.FLAG_SKIP_TRACE_CHECK)
+            assert abs(res[b].u / one.u - 1) <= 1e-10, (ns[b], res[b].u, one.u)
+    g.destroy()
