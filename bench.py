@@ -128,6 +128,14 @@ def describe(cfg, precision, store):
             f"{cfg['dist']} probes, t={cfg['t']}, {precision}")
 
 
+def products_run(m, method):
+    """(products, degree whose plain recurrence has as many) of an estimate on
+    a symmetric R, which takes two moments from each product."""
+    moments = m if method == "chebyshev" else m + 1
+    products = (moments + 1) // 2
+    return products, products if method == "chebyshev" else products - 1
+
+
 def csr_step_bytes(n, nnz, s, m, vbytes, method):
     """Algorithmic HBM bytes of the m product steps: the CSR arrays, the probe
     sign bits and the V blocks each step must read and write once."""
@@ -261,18 +269,22 @@ def bench_batch(args, cfg):
     ms_per_step = 1e3 * elapsed / args.steps
     log(f"timed {args.steps} batch launches: {ms_per_step:.2f} ms per batch of {count}")
     tms = [g.time_eager()[1] for _ in range(3)]
-    avg_step_ms = float(np.mean([x["steps_ms"] / x["step_launches"] for x in tms]))
+    nsteps = m if cfg["method"] == "chebyshev" else m + 1
+    # a matrix equal to its transpose takes two moments from each product; a
+    # persistent launch counts the moments as its steps
+    run = np.array([products_run(m, cfg["method"])[0] if torch.equal(M, M.T) else nsteps for M in mats])
+    steps_run = int(run.max())
+    avg_step_ms = float(np.mean([x["steps_ms"] for x in tms])) / steps_run
     phases = {k: float(np.mean([x[k] for x in tms])) for k in ("total_ms", "power_ms", "steps_ms", "epilogue_ms", "other_ms")}
-    flop = 2.0 * sum_n2 * s
+    flop = 2.0 * s * float(np.sum(ns.astype(np.float64) ** 2 * run)) / steps_run
     achieved = flop / (avg_step_ms * 1e-3) / 1e12
     peak = MFMA_PEAK_TFLOPS[precision]
-    nsteps = m if cfg["method"] == "chebyshev" else m + 1
     persistent = g.window_bytes > 0
     bf = precision == "bf16x3"
     if persistent:
         # one launch runs every recurrence step of every matrix
         kernel = "batch_bf16x3_persistent_kernel" if bf else "batch_dense_persistent_kernel"
-        launch_ms, flop_launch = avg_step_ms * nsteps, flop * nsteps
+        launch_ms, flop_launch = avg_step_ms * steps_run, flop * steps_run
     else:
         kernel = "batch_bf16x3_step_kernel" if bf else "batch_dense_step_kernel"
         launch_ms, flop_launch = avg_step_ms, flop
@@ -325,7 +337,7 @@ def bench_batch(args, cfg):
                      "traffic": measured_traffic(kernel, args.workload + ("" if precision == "f32" else "_" + precision)),
                      "kernel": kernel,
                      "avg_launch_ms": launch_ms, "algorithmic_flop_per_launch": flop_launch,
-                     "ms_per_recurrence_step": avg_step_ms, "launches_per_batch": 1 if persistent else nsteps},
+                     "ms_per_recurrence_step": avg_step_ms, "launches_per_batch": 1 if persistent else steps_run},
         "cpu_baseline": cpu,
         "phases_ms": phases,
         "accuracy": {"sampled_matrices": len(idx),
@@ -829,25 +841,34 @@ def bench_single(args, cfg):
         nnz = int(Rd[0][-1]) if host_R is None else int(host_R[0][-1])
         vb = 8 if precision == "f64" else 4
         hp = int(last_t["csr_band"])
+        # these matrices are symmetric: two moments per product (a multi-step
+        # tridiagonal launch counts moments), and the last one stores no block
+        _, mr = products_run(m, cfg["method"])
+        blk = n * s * vb
         if hp == 1 and int(last_t["steps_fused"]) >= 2:
             # tridiagonal input, several steps per launch
             kernel = "tri_fused_kernel"
-            tot_bytes, steps = tri_fused_bytes(n, s, m, vb, cfg["method"], int(last_t["steps_fused"]))
+            nf = (int(last_t["steps_fused"]) + 1) // 2
+            tot_bytes, steps = tri_fused_bytes(n, s, mr, vb, cfg["method"], nf)
+            tot_bytes -= (2 if cfg["method"] == "chebyshev" else 1) * blk
         elif hp == 1:
             # tridiagonal input: the three-row stencil kernel
             kernel = "tri_step_kernel"
-            tot_bytes, steps = tri_step_bytes(n, s, m, vb, cfg["method"])
+            tot_bytes, steps = tri_step_bytes(n, s, mr, vb, cfg["method"])
+            tot_bytes -= blk if cfg["method"] == "chebyshev" else 0
         elif hp > 0 and int(last_t["steps_fused"]) == 2:
             # banded input, two steps per launch
             kernel = "band_pair_kernel"
-            tot_bytes, steps = band_pair_bytes(n, hp, s, m, vb, cfg["method"])
+            tot_bytes, steps = band_pair_bytes(n, hp, s, mr, vb, cfg["method"])
         elif hp > 0:
             # banded input: the step ran on the 16-row slabs
             kernel = "band_step_kernel"
-            tot_bytes, steps = band_step_bytes(n, hp, s, m, vb, cfg["method"])
+            tot_bytes, steps = band_step_bytes(n, hp, s, mr, vb, cfg["method"])
+            tot_bytes -= blk if cfg["method"] == "chebyshev" else 0
         else:
             kernel = "csr_step_kernel"
-            tot_bytes, steps = csr_step_bytes(n, nnz, s, m, vb, cfg["method"])
+            tot_bytes, steps = csr_step_bytes(n, nnz, s, mr, vb, cfg["method"])
+            tot_bytes -= blk if cfg["method"] == "chebyshev" else 0
         per_launch = tot_bytes / steps
         achieved = per_launch / (avg_step_ms * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -245,7 +245,8 @@ void ent_options_default(ent_options *opt);
  * estimate is not finite.
  *
  * Forward schedules (Taylor, Chebyshev): for a real R equal to its transpose
- * (checked in every call, entry by entry) the vectors of step k give two
+ * (checked in every call, entry by entry; a Hermitian R by its real form) the
+ * vectors of step k give two
  * moments, V_k.V_{k+1} and V_{k+1}.V_{k+1} (T_a T_b = (T_{a+b} + T_{|a-b|})/2;
  * Taylor: W_k.Y_k and W_{k+1}.Y_k), so m moments take about m / 2 products; the
  * values are those of one moment per product up to rounding.  Any other R
@@ -403,11 +404,15 @@ typedef struct {
   double step_max_ms;    /* longest single product launch                     */
   double epilogue_ms;    /* separate epilogue kernels (BF16x3 path), summed   */
   double other_ms;       /* probes, trace check, setup and reductions         */
-  int32_t step_launches;
-  int32_t power_launches; /* product launches of the power method: t + 1 per
-                            trial, fewer for a banded or tridiagonal CSR R,
-                            whose products after a trial's first run up to
-                            ENT_POWER_FUSE (1..10, default 10) per launch  */
+  int32_t step_launches; /* launches of the product kernel (half the plain
+                            recurrence's for a symmetric R); a persistent
+                            batch launch counts the plain recurrence's steps  */
+  int32_t power_launches; /* products of the power method, one launch or pair
+                            of launches each: t + 1 per trial; 1 in all for a
+                            dense R with n <= 192; fewer for a banded or
+                            tridiagonal CSR R, whose products after a
+                            trial's first run up to ENT_POWER_FUSE (1..10,
+                            default 10) per launch                            */
   int32_t epilogue_launches;
   int32_t csr_band;      /* CSR R: padded half-bandwidth (4, 8 or 16) of the
                             banded step kernel that ran, 1 for the
@@ -417,11 +422,13 @@ typedef struct {
                             banded FP32 two-step kernel (the last step of
                             an odd count runs alone, in other_ms;
                             ENT_BAND_PAIRS=0 runs one step per launch); for
-                            the tridiagonal kernel the steps of the first
-                            launch, the m steps split into launches of at
-                            most ENT_TRI_FUSE steps (1..10, default 10) as
-                            evenly as possible, longer first (a one-step
-                            launch in other_ms); steps_ms and step_launches
+                            the tridiagonal kernel the moments of the first
+                            launch, the moments split into launches of at
+                            most ENT_TRI_FUSE (1..10, default 10; with two
+                            moments per product the default is 20 moments,
+                            ten products) as evenly as possible, longer
+                            first (a one-product launch in other_ms);
+                            steps_ms and step_launches
                             then cover the multi-step launches; 1
                             otherwise, also where the two more V blocks
                             the multi-step launches need do not fit       */
@@ -445,7 +452,7 @@ ent_status ent_last_timing(ent_timing *out);
  *   batch when ENT_FLAG_AUTOTUNE is set; the cache persists as JSON in the
  *   file named by the environment variable ENT_AUTOTUNE_CACHE), then captures
  *   the whole launch sequence into a hipGraph on a private stream.
- *   The m recurrence steps of every matrix run by default as ONE persistent
+ *   The recurrence steps of every matrix run by default as ONE persistent
  *   launch: its workgroups (as many as are resident at once) take (matrix,
  *   row tile, step) items from a device schedule.  Each matrix belongs to one
  *   XCD and only workgroups on that XCD take its items; per XCD, matrices of
