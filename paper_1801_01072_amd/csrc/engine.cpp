@@ -709,6 +709,16 @@ ent_status enqueue_power(const ent_matrix *R, const T *Rc, int64_t ldr, int32_t 
     if (launches) *launches = q * (t + 1);
     return ENT_OK;
   }
+  if (!band && !trid) {
+    HIP_TRY(power_trials(t, q, ent::power_blocks_spmv(n), part3, norm, scal, st, [&](int32_t trial) {
+      return ent::launch_power_start(x0, n, seed, trial, st);
+    }, [&](int32_t it, const ent::PowerPrev &prev, double *part, int32_t *nblk) {
+      return ent::launch_power_spmv<T>(R->row_ptr, R->col_idx, (const T *)R->values, n, R->nnz, it & 1 ? x1 : x0, prev,
+                                       it & 1 ? x0 : x1, part, nblk, st);
+    }));
+    if (launches) *launches = q * (t + 1);
+    return ENT_OK;
+  }
   for (int32_t trial = 0; trial < q; ++trial) {
     HIP_TRY(ent::launch_power_start(x0, n, seed, trial, st));
     double *xin = x0, *xout = x1;
@@ -739,13 +749,11 @@ ent_status enqueue_power(const ent_matrix *R, const T *Rc, int64_t ldr, int32_t 
         // banded CSR: the same product on the slabs of the step kernel
         nblk = ent::power_blocks_csr(n);
         HIP_TRY(ent::launch_power_band<T>(band, hp, n, xin, in_norm, xout, part3, nblk, st));
-      } else if (trid) {
+      } else {
         // tridiagonal CSR: the same product on the packed diagonals
         nblk = ent::power_blocks_csr(n);
         HIP_TRY(ent::launch_power_tri<T>(trid, n, xin, in_norm, xout, part3, nblk, st));
-      } else
-        HIP_TRY(ent::launch_power_spmv<T>(R->row_ptr, R->col_idx, (const T *)R->values, n, R->nnz,
-                                          xin, in_norm, xout, part3, &nblk, st));
+      }
       HIP_TRY(ent::launch_power_reduce(part3, nblk, norm, st));
       std::swap(xin, xout);
       in_norm = norm;

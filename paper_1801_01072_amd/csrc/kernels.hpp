@@ -152,6 +152,8 @@ constexpr int32_t kPowerSelfSum = 1024;  // most triples summed by every workgro
 // *nblk receives the number of blocks.
 int32_t power_blocks_dense(int64_t n);
 int32_t power_blocks_csr(int64_t n);
+// of the general CSR product: few enough for the next product to sum their triples
+int32_t power_blocks_spmv(int64_t n);
 // The same product reading half of an R that equals its transpose; part holds
 // power_sym_parts(n) * n doubles, nblk is power_blocks_sym(n).
 int32_t power_blocks_sym(int64_t n);
@@ -168,7 +170,7 @@ hipError_t launch_power_gemv(const T *R, int64_t ldr, int64_t n, const double *x
 template <typename T>
 // (nnz only picks the lanes per row: 1, 2, 4 or 8 by the mean row length)
 hipError_t launch_power_spmv(const int64_t *rp, const int32_t *ci, const T *val, int64_t n,
-                             int64_t nnz, const double *x, const double *in_norm, double *y,
+                             int64_t nnz, const double *x, const PowerPrev &prev, double *y,
                              double *part3, int32_t *nblk, hipStream_t st);
 // norm3[0..2] = fixed-order sums of the nblk block triples.
 hipError_t launch_power_reduce(const double *part3, int32_t nblk, double *norm3, hipStream_t st);
