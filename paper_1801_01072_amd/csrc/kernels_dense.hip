@@ -67,6 +67,7 @@ struct DenseChunk {
   static_assert(KPL % VEC == 0, "a lane's A values must be whole 16-byte pieces");
   static_assert((BK * G) % 256 == 0, "V pieces must split over the 4 waves");
   static_assert(4 * ES <= G, "V rows too short for the swizzle");
+  static constexpr int LDS = NST * (VBYTES + ABYTES);  // every stage
   // V row r sits at r * RB bytes, its 16-byte groups XOR-swizzled so that
   // the four 16-lane groups of an MFMA B-operand read (rows t, VEC+t, 2VEC+t,
   // 3VEC+t of a piece, 16 consecutive probes each) fall on disjoint banks
@@ -122,9 +123,16 @@ struct BatchHook {
 // permuted consistently for A and B).  A ragged last chunk (n not a multiple of
 // BK) reads A into registers at the start, column min(k, n - 1) element by
 // element: V_k is zero in rows k >= n, so those products vanish.
+//
+// lds: the workgroup's stages, DenseChunk::LDS bytes.  It is the kernel's only
+// __shared__ object (the persistent kernel's two words stand behind the stages):
+// with a single one the compiler adds no waits of its own between the direct
+// loads into one stage and the reads of another; a second one gives it alias
+// scopes, and every chunk's reads then wait for all loads (FP64 persistent
+// batch, 40 symmetric matrices of n = 2000: 9.23 -> 7.89 ms a call).
 template <typename T, int BN, int WR, int EC, int BUDGET = kChunkLds, bool PRE = false, typename H = DenseNoHook>
-__device__ __forceinline__ bool dense_step_tile(const DenseStepArgs &a, int tm, int tn, int64_t kbeg,
-                                                int64_t kend, T *yout, H hook = H{}) {
+__device__ __forceinline__ bool dense_step_tile(unsigned char *lds, const DenseStepArgs &a, int tm, int tn,
+                                                int64_t kbeg, int64_t kend, T *yout, H hook = H{}) {
   using M = Mfma16<T>;
   using v4 = typename M::v4;
   using C = DenseChunk<T, BN, WR, BUDGET>;
@@ -136,11 +144,8 @@ __device__ __forceinline__ bool dense_step_tile(const DenseStepArgs &a, int tm, 
   // stage s at lds + s * STAGE: the V_k chunk (VBYTES), then the A values of
   // the 4 waves (ABYTES)
   constexpr int STAGE = C::VBYTES + C::ABYTES, NST = C::NST;
-  // one LDS array (the epilogue's per-wave dot sums reuse it after the
-  // products): with a single LDS object the compiler adds no waits of its own
-  // between the direct loads into one stage and the reads of another
-  static_assert(NST * STAGE >= 3 * 4 * BN * 8, "the dot sums fit in the stages");
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[NST * STAGE];
+  // the epilogue's per-wave dot sums reuse the stages after the products
+  static_assert(C::LDS >= 3 * 4 * BN * 8, "the dot sums fit in the stages");
   double(*red)[4][BN] = (double(*)[4][BN])lds;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -451,9 +456,10 @@ __device__ __forceinline__ bool dense_step_tile(const DenseStepArgs &a, int tm, 
 
 template <typename T, int BN, int WR>
 __global__ __launch_bounds__(256) void dense_step_kernel(DenseStepArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[DenseChunk<T, BN, WR>::LDS];
   const int ntn = (int)(a.ldv / BN);
   const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-  dense_step_tile<T, BN, WR, 4>(a, b / ntn, b % ntn, 0, a.n, nullptr);
+  dense_step_tile<T, BN, WR, 4>(lds, a, b / ntn, b % ntn, 0, a.n, nullptr);
 }
 
 // Split-K product (a kernel of its own, so the fused kernel's code is not
@@ -461,6 +467,7 @@ __global__ __launch_bounds__(256) void dense_step_kernel(DenseStepArgs a) {
 // tiles of one split (same V_k rows) are neighbours.
 template <typename T, int BN, int WR>
 __global__ __launch_bounds__(256) void dense_step_split_kernel(DenseStepArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[DenseChunk<T, BN, WR>::LDS];
   const int ntn = (int)(a.ldv / BN);
   const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
   const int ntl = a.ntile * ntn;
@@ -468,7 +475,7 @@ __global__ __launch_bounds__(256) void dense_step_split_kernel(DenseStepArgs a) 
   const int64_t kbeg = (int64_t)ks * a.kper;
   const int64_t kend = kbeg + a.kper < a.n ? kbeg + a.kper : a.n;
   T *yout = (T *)a.party + (int64_t)ks * (int64_t)a.ntile * 64 * a.ldv;
-  dense_step_tile<T, BN, WR, 4>(a, t / ntn, t % ntn, kbeg, kend, yout);
+  dense_step_tile<T, BN, WR, 4>(lds, a, t / ntn, t % ntn, kbeg, kend, yout);
 }
 
 // Split-K epilogue: y = a sum_ks party[ks] (split order), z = c1 y + c2 b V_k
@@ -986,10 +993,12 @@ __device__ __forceinline__ bool batch_dense_args(const BatchPersistArgs &pa, con
 // (x) and 64 probes (y).
 template <typename T, int WR>
 __global__ __launch_bounds__(256) void batch_dense_step_kernel(BatchPersistArgs pa, int k, const int2 *tiles) {
+  constexpr int BUDGET = sizeof(T) == 4 ? kGroupedLds : kChunkLds;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[DenseChunk<T, 64, WR, BUDGET>::LDS];
   const int2 tl = tiles[blockIdx.x];
   DenseStepArgs a{};
   if (!batch_dense_args<T>(pa, pa.mats[tl.x], k, a)) return;
-  dense_step_tile<T, 64, WR, kBatchCols<WR>, sizeof(T) == 4 ? kGroupedLds : kChunkLds>(a, tl.y, (int)blockIdx.y, 0, a.n, nullptr);
+  dense_step_tile<T, 64, WR, kBatchCols<WR>, BUDGET>(lds, a, tl.y, (int)blockIdx.y, 0, a.n, nullptr);
 }
 
 // Persistent batch steps: each workgroup takes (matrix, row tile, step)
@@ -1006,7 +1015,9 @@ __global__ __launch_bounds__(256) void batch_dense_step_kernel(BatchPersistArgs 
 // an XCD has 126 tiles a step and they wait for each other).
 template <typename T, int WR>
 __global__ __launch_bounds__(256, 2) void batch_dense_persistent_kernel(BatchPersistArgs pa) {
-  __shared__ int sh[2];
+  constexpr int LDS = DenseChunk<T, 64, WR>::LDS;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS + 2 * sizeof(int)];
+  int *sh = (int *)(lds + LDS);
   int next = sched_reserve(pa.sched);
   for (;;) {
     const int i = sched_item(pa.sched, next, sh);
@@ -1021,7 +1032,8 @@ __global__ __launch_bounds__(256, 2) void batch_dense_persistent_kernel(BatchPer
     }
     a.ldv = 64;
     BatchHook hook{pa.sched, it.x, it.z * M.ntile, sh + 1, &next};
-    if (!dense_step_tile<T, 64, WR, kBatchCols<WR>, kChunkLds, sizeof(T) == 4 && WR == 1, BatchHook>(a, it.y, 0, 0, a.n, nullptr, hook))
+    if (!dense_step_tile<T, 64, WR, kBatchCols<WR>, kChunkLds, sizeof(T) == 4 && WR == 1, BatchHook>(lds, a, it.y, 0, 0, a.n, nullptr,
+                                                                                                           hook))
       return;
     sched_release(pa.sched, it.x);
   }
