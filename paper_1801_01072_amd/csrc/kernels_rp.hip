@@ -508,8 +508,11 @@ __global__ __launch_bounds__(1024) void tridiag_large_kernel(double *__restrict_
 // changes in the leading minors of T - x I, p_r = (d_r - x) p_{r-1} -
 // e_{r-1}^2 p_{r-2} (the pivots p_r / p_{r-1} without their divisions, 182 us
 // with them at N = 128), on T scaled by a power of two to norm <= 1:
-// a pivot below 2^-220 counts as -2^-220, so four steps cannot leave the range
-// of doubles and the pair is scaled, exactly, every fourth step.  A workgroup
+// a pivot below 2^-200 counts as -2^-200.  The pair is scaled, exactly, every
+// fourth step, to a larger value in [1/2, 1) whose successor may be 2^-201
+// already: four more such pivots leave 2^-1001 (the five before the first scaling
+// 2^-1000), a normal double.  At zero the signs, and with them the count of
+// every later row, would be lost.  A workgroup
 // per eigenvalue fills the chip where one for all of them left it idle:
 // s = 128 71 us.
 __global__ __launch_bounds__(256) void sturm_eig_kernel(const double *__restrict__ de, int32_t N,
@@ -543,7 +546,7 @@ __global__ __launch_bounds__(256) void sturm_eig_kernel(const double *__restrict
   a = ldexp(a, ex);
   b = ldexp(b, ex);
   const double tnorm = fmax(fabs(a), fabs(b));
-  constexpr double kPivot = 0x1p-220;
+  constexpr double kPivot = 0x1p-200;
   __syncthreads();
   for (int it = 0; it < 64; ++it) {
     if (!(b - a > fmax(4.440892098500626e-16 * fmax(fabs(a), fabs(b)), 1e-22 * tnorm))) break;

@@ -38,3 +38,30 @@ def test_all_singular_values(orc, s, kind):
     err = float(np.max(np.abs(lam - want)) / want.max())
     print(f"[rp spectrum {kind} s={s}] {err:.2e}", flush=True)
     assert np.all(np.diff(sig) <= 0) and err <= (n + 4 * s) * 2.3e-16
+
+
+@pytest.mark.parametrize("s", [32, 160])
+@pytest.mark.parametrize("first", [2, 3, 4])
+def test_repeated_values_met_exactly(orc, s, first):
+    """A count sketch of a diagonal R on rows of chosen buckets: a Gram matrix
+    diag(256 + 1, .., eight 144, ten 143.5, 0, ..) / 2^20 whose 144 the first split
+    of [0, 257] into 257 parts meets exactly, eight pivots in turn being zero.
+    Every square, sum and point of the split is exact but 143.5's (p^2 within
+    2 eps); the bisection ends at 2 ulp."""
+    seed, n = 5, 4000
+    rows = {}
+    for j in range(n):
+        rows.setdefault(orc.sketch_bucket(seed, j, s), []).append(j)
+    p = np.zeros(n)
+    p[rows[0][:2]] = 16.0, 1.0
+    for q in range(8):
+        p[rows[first + q][0]] = 12.0
+    for q in range(10):
+        p[rows[first + 8 + q][0]] = np.sqrt(143.5)
+    p /= 1024.0
+    k = 20
+    _, sig, _ = ent.entropy_estimate_detail(torch.from_numpy(np.diag(p)).to(DEV), "randproj", 1, 1, seed, rank_k=k,
+                                            sketch_width=s, precision="f64", sketch="count",
+                                            flags=ent.FLAG_SKIP_TRACE_CHECK)
+    want = np.array([np.sqrt(257.0)] + [12.0] * 8 + [np.sqrt(143.5)] * 10 + [0.0]) / 1024.0
+    assert np.allclose(np.asarray(sig), want, rtol=1e-14, atol=1e-12)
