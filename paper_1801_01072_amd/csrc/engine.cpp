@@ -1087,8 +1087,10 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     ldr = ldc;
   }
   if (banded) {
-    HIP_TRY(ent::launch_band_pack<T>(R->row_ptr, R->col_idx, (const T *)R->values, n, hp, band, st));
-    if (ask) HIP_TRY(ent::launch_band_check<T>(band, n, hp, scal, asym.word, st));
+    HIP_TRY(ent::launch_band_pack<T>(R->row_ptr, R->col_idx, (const T *)R->values, n, hp, band, scal, st));
+    if (ask)
+      HIP_TRY(ent::launch_band_check<T>(R->row_ptr, R->col_idx, (const T *)R->values, band, n, hp, scal, asym.word,
+                                        st));
   } else if (tri)
     HIP_TRY(ent::launch_tri_pack<T>(R->row_ptr, R->col_idx, (const T *)R->values, n, trid, ttmp,
                                     (check_trace || normalize) ? scal + ent::S_TRACE : nullptr, st));

@@ -25,6 +25,7 @@ enum ScalarSlot {
   S_SE = 9,     // standard error
   S_SYM = 10,   // int32: nonzero if R differs from its transpose somewhere
   S_SYM_NET = 11,  // int64 scratch of the CSR comparison
+  S_REPEATS = 12,  // int32: nonzero if a CSR row's columns do not ascend (banded packing)
   S_ALPHA = 16  // alpha_0 .. alpha_m (Chebyshev) follow
 };
 
@@ -385,14 +386,16 @@ hipError_t launch_csr_half_bandwidth(const int64_t *rp, const int32_t *ci, int64
 int32_t band_half_width_padded(int32_t hbw);
 // Elements of the 16-row slab storage, and the slabs from the CSR arrays.
 size_t band_pack_elems(int64_t n, int32_t hp);
+// (scal[S_REPEATS], which must start at 0, is set where a row's columns do not
+// ascend strictly: its slab values may be sums of entries)
 template <typename T>
 hipError_t launch_band_pack(const int64_t *rp, const int32_t *ci, const T *val, int64_t n, int32_t hp,
-                            T *band, hipStream_t st);
-// Trace of the slabs' matrix and whether it equals its transpose, as
-// launch_dense_check leaves them.
+                            T *band, double *scal, hipStream_t st);
+// Trace of the packed matrix (entries added in FP64) and whether the slabs'
+// equals its transpose, as launch_dense_check leaves them.
 template <typename T>
-hipError_t launch_band_check(const T *band, int64_t n, int32_t hp, double *scal, int32_t *host_flag,
-                             hipStream_t st);
+hipError_t launch_band_check(const int64_t *rp, const int32_t *ci, const T *val, const T *band, int64_t n,
+                             int32_t hp, double *scal, int32_t *host_flag, hipStream_t st);
 struct BandStepArgs {
   const void *band;    // slabs (launch_band_pack), element type T
   int64_t n;

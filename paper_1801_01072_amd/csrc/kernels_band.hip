@@ -153,7 +153,7 @@ template <typename T, int KS>
 __global__ __launch_bounds__(256) void band_pack_kernel(const int64_t *__restrict__ rp,
                                                         const int32_t *__restrict__ ci,
                                                         const T *__restrict__ val, int64_t n,
-                                                        T *__restrict__ band) {
+                                                        T *__restrict__ band, int32_t *__restrict__ repeats) {
   constexpr int HP = BandShape<KS>::HP, K = BandShape<KS>::K;
   __shared__ T slab[4][16][K + 1];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, q = l >> 4, i = l & 15;
@@ -184,6 +184,7 @@ __global__ __launch_bounds__(256) void band_pack_kernel(const int64_t *__restric
 #pragma unroll
     for (int k = 0; k < KS; ++k) out[k] = slab[w][i][4 * k + q];
   } else {
+    if (l == 0) *repeats = 1;  // (every wave that comes here stores the same)
 #pragma unroll
     for (int k = 0; k < KS; ++k) out[k] = T(0);
     const int64_t row = 16 * b + i;
@@ -207,21 +208,22 @@ __global__ __launch_bounds__(256) void band_pack_kernel(const int64_t *__restric
 
 template <typename T>
 hipError_t launch_band_pack(const int64_t *rp, const int32_t *ci, const T *val, int64_t n, int32_t hp,
-                            T *band, hipStream_t st) {
+                            T *band, double *scal, hipStream_t st) {
   const int64_t nb = (n + 15) / 16;
   const unsigned blocks = (unsigned)((nb + 3) / 4);
+  int32_t *rep = (int32_t *)(scal + S_REPEATS);
   switch (hp) {
-    case 4: band_pack_kernel<T, 6><<<blocks, 256, 0, st>>>(rp, ci, val, n, band); break;
-    case 8: band_pack_kernel<T, 8><<<blocks, 256, 0, st>>>(rp, ci, val, n, band); break;
-    case 16: band_pack_kernel<T, 12><<<blocks, 256, 0, st>>>(rp, ci, val, n, band); break;
+    case 4: band_pack_kernel<T, 6><<<blocks, 256, 0, st>>>(rp, ci, val, n, band, rep); break;
+    case 8: band_pack_kernel<T, 8><<<blocks, 256, 0, st>>>(rp, ci, val, n, band, rep); break;
+    case 16: band_pack_kernel<T, 12><<<blocks, 256, 0, st>>>(rp, ci, val, n, band, rep); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 template hipError_t launch_band_pack<float>(const int64_t *, const int32_t *, const float *, int64_t, int32_t,
-                                            float *, hipStream_t);
+                                            float *, double *, hipStream_t);
 template hipError_t launch_band_pack<double>(const int64_t *, const int32_t *, const double *, int64_t, int32_t,
-                                             double *, hipStream_t);
+                                             double *, double *, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // R = R^T on the slabs.  A workgroup takes four blocks (64 rows) and the block
@@ -230,9 +232,15 @@ template hipError_t launch_band_pack<double>(const int64_t *, const int32_t *, c
 // with its mirror.  Reads each slab once (plus the overlap): HBM-bound.  The
 // trace comes with it (tmp: one partial sum per workgroup), where the CSR
 // kernel would look for the diagonal in the column indices (n = 1e7: 1.05 ms).
+// Where the packing met a row whose columns do not ascend (repeats), a slab value
+// may be a sum of entries rounded to T, and the diagonal entries are added one by
+// one from the CSR arrays instead, in FP64.
 // ---------------------------------------------------------------------------
 template <typename T, int KS>
-__global__ __launch_bounds__(256) void band_check_kernel(const T *__restrict__ band, int64_t n,
+__global__ __launch_bounds__(256) void band_check_kernel(const int64_t *__restrict__ rp,
+                                                         const int32_t *__restrict__ ci,
+                                                         const T *__restrict__ val, const T *__restrict__ band,
+                                                         int64_t n, const int32_t *__restrict__ repeats,
                                                          int32_t *__restrict__ asym, double *__restrict__ tmp) {
   constexpr int HP = BandShape<KS>::HP, K = BandShape<KS>::K;
   constexpr int NBK = 4;                 // blocks checked per workgroup pass
@@ -240,6 +248,7 @@ __global__ __launch_bounds__(256) void band_check_kernel(const T *__restrict__ b
   __shared__ T rows[ROWS][K + 1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t nb = (n + 15) / 16;
+  const bool rep = *repeats != 0;
   bool bad = false;
   double tr = 0.0;  // wave 0: rows lane, lane + 64, ... of the workgroup's
   for (int64_t b0 = (int64_t)blockIdx.x * NBK; b0 < nb; b0 += (int64_t)gridDim.x * NBK) {
@@ -261,7 +270,11 @@ __global__ __launch_bounds__(256) void band_check_kernel(const T *__restrict__ b
       const T x = rows[r][HP + (r & 15) + d], y = rows[rm][HP + r - (rm & ~15)];
       if (!(x == y)) bad = true;
     }
-    if (w == 0) tr += (double)rows[lane][HP + (lane & 15)];
+    const int64_t row = 16 * b0 + lane;
+    if (w == 0 && !rep) tr += (double)rows[lane][HP + (lane & 15)];
+    if (w == 0 && rep && row < n)
+      for (int64_t e = rp[row]; e < rp[row + 1]; ++e)
+        if (ci[e] == row) tr += (double)val[e];
   }
   if (__any(bad) && lane == 0) atomicOr(asym, 1);
   if (w == 0) {
@@ -271,22 +284,25 @@ __global__ __launch_bounds__(256) void band_check_kernel(const T *__restrict__ b
 }
 
 template <typename T>
-hipError_t launch_band_check(const T *band, int64_t n, int32_t hp, double *scal, int32_t *host_flag,
-                             hipStream_t st) {
+hipError_t launch_band_check(const int64_t *rp, const int32_t *ci, const T *val, const T *band, int64_t n,
+                             int32_t hp, double *scal, int32_t *host_flag, hipStream_t st) {
   int32_t *asym = (int32_t *)(scal + S_SYM);
+  const int32_t *rep = (const int32_t *)(scal + S_REPEATS);
   double *tmp = scal + 4096;
   const int64_t nb = (n + 15) / 16, want = (nb + 3) / 4;
   const unsigned blocks = (unsigned)(want < 4096 ? want : 4096);
   switch (hp) {
-    case 4: band_check_kernel<T, 6><<<blocks, 256, 0, st>>>(band, n, asym, tmp); break;
-    case 8: band_check_kernel<T, 8><<<blocks, 256, 0, st>>>(band, n, asym, tmp); break;
-    case 16: band_check_kernel<T, 12><<<blocks, 256, 0, st>>>(band, n, asym, tmp); break;
+    case 4: band_check_kernel<T, 6><<<blocks, 256, 0, st>>>(rp, ci, val, band, n, rep, asym, tmp); break;
+    case 8: band_check_kernel<T, 8><<<blocks, 256, 0, st>>>(rp, ci, val, band, n, rep, asym, tmp); break;
+    case 16: band_check_kernel<T, 12><<<blocks, 256, 0, st>>>(rp, ci, val, band, n, rep, asym, tmp); break;
     default: return hipErrorInvalidValue;
   }
   return launch_check_finish(tmp, (int32_t)blocks, scal, host_flag, st);
 }
-template hipError_t launch_band_check<float>(const float *, int64_t, int32_t, double *, int32_t *, hipStream_t);
-template hipError_t launch_band_check<double>(const double *, int64_t, int32_t, double *, int32_t *, hipStream_t);
+template hipError_t launch_band_check<float>(const int64_t *, const int32_t *, const float *, const float *, int64_t,
+                                             int32_t, double *, int32_t *, hipStream_t);
+template hipError_t launch_band_check<double>(const int64_t *, const int32_t *, const double *, const double *, int64_t,
+                                              int32_t, double *, int32_t *, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Row pieces: lane (q, c) of a 64-probe chunk handles probes 4c .. 4c+3.

@@ -283,3 +283,32 @@ def test_band_power_fused(orc, monkeypatch, hb, hp, dtype, n):
         assert tl["power_launches"] == q * (1 + -(-t // 10)) and tl1["power_launches"] == q * (t + 1)
         assert abs(res.p1_est - ref.p1_est) <= 1e-12 * ref.p1_est
         assert abs(res.p1_est - res1.p1_est) <= 1e-12 * res1.p1_est
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("hb", [2, 4, 8])
+def test_trace_adds_repeated_entries_in_fp64(hb, dtype):
+    """A symmetric banded R whose diagonal entries of rows 1 .. 1024 are given as
+    2^-11 and 2^-36: their sum is a tie that FP32 rounds to 2^-11, so a trace of
+    rounded sums is off by 2^-26.  Every trace here is exact in FP64."""
+    n, prec = 2048, "f32" if dtype == np.float32 else "f64"
+    rows = []
+    for i in range(n):
+        e = [(j, 2.0 ** -20) for j in range(max(0, i - 2 * hb), min(n, i + 2 * hb + 1)) if j != i]
+        e.append((i, 2.0 ** -11))
+        if 1 <= i <= 1024:
+            e.append((i, 2.0 ** -36))
+        rows.append(sorted(e))
+
+    def call(rows):
+        rp = np.cumsum([0] + [len(r) for r in rows]).astype(np.int64)
+        ci = np.array([c for r in rows for c, _ in r], np.int32)
+        val = np.array([v for r in rows for _, v in r], dtype)
+        return run((rp, ci, val, n), "chebyshev", 8, 16, 3, precision=prec, flags=ent.FLAG_CSR_BANDED,
+                   trace_tol=2.0 ** -28)
+
+    with pytest.raises(ent.EntropyError, match="trace"):
+        call(rows)  # 1 + 2^-26
+    k = [c for c, _ in rows[0]].index(0)
+    rows[0][k] = (0, 2.0 ** -11 - 2.0 ** -26)
+    assert call(rows)[3] > 1  # 1: accepted, by a banded kernel
