@@ -252,3 +252,70 @@ def test_batch(orc, precision, flags, changed):
                 print(f"[pairs batch {precision} {flags} {method} changed {touch}] b={b} per-probe {e:.2e}", flush=True)
                 assert e <= tol_for(precision)
         g.destroy()
+
+
+def hub_csr(n, h, chain, entry=0.0):
+    """Laplacian / trace of a star with hub h, and a chain through all vertices
+    where `chain` (more than three entries a row); `entry` is added to R[h, n - 1]."""
+    A = np.zeros((n, n))
+    A[h, :] = A[:, h] = -1.0
+    if chain:
+        i = np.arange(n - 1)
+        A[i, i + 1] = A[i + 1, i] = -0.5
+    np.fill_diagonal(A, 0.0)
+    np.fill_diagonal(A, -A.sum(axis=1))
+    A /= np.trace(A)
+    A[h, n - 1] += entry
+    return A
+
+
+@pytest.mark.parametrize("n", [512, 514, 1500])  # hub rows up to, just over and far over a wave's
+@pytest.mark.parametrize("chain", [False, True])
+@pytest.mark.parametrize("entry", [0.0, 1e-9])
+def test_hub_rows(orc, n, chain, entry):
+    """One row much longer than the others, at the start, inside and at the end:
+    the right values, from half the products exactly where R = R^T."""
+    import scipy.sparse as sp
+
+    m, s = 9, 8
+    for h in (0, 700 % n, n - 2):
+        A = hub_csr(n, h, chain, entry)
+        csr = sparse_csr(sp.csr_matrix(A))
+        ent.timing_enable(True)
+        try:
+            check(orc, to_dev(csr, np.float64), lambda V: A @ V, n, "chebyshev", m, s, 3, 0, "f64", f"hub {h}",
+                  flags=ent.FLAG_CSR_GENERAL if chain else 0)
+            steps = ent.last_timing()["step_launches"]
+        finally:
+            ent.timing_enable(False)
+        assert steps == (m if entry else (m + 1) // 2)
+
+
+def test_hub_row_costs_no_more_than_it_saves():
+    """A star of 200000 vertices, u given: one product for two moments, against
+    Clenshaw's three for the same degree, which asks nothing about R^T."""
+    import time
+
+    n = 200_000
+    i = torch.arange(1, n, device=DEV)
+    z, v = torch.zeros_like(i), torch.arange(n, device=DEV)
+    rows, cols = torch.cat([i, z, v]), torch.cat([z, i, v])
+    d = torch.ones(n, dtype=torch.float64, device=DEV)
+    d[0] = n - 1
+    vals = torch.cat([torch.full((2 * n - 2,), -1.0, dtype=torch.float64, device=DEV), d]) / (2.0 * (n - 1))
+    order = torch.argsort(rows * n + cols)
+    rp = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
+    torch.cumsum(torch.bincount(rows, minlength=n), dim=0, out=rp[1:])
+    R = (rp, cols[order].to(torch.int32).contiguous(), vals[order].contiguous(), n)
+
+    def best(flags):
+        times = []
+        for _ in range(4):
+            t = time.perf_counter()
+            ent.entropy_estimate(R, "chebyshev", 2, 16, 1, u_fixed=1.0, flags=flags)
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    pairs, clenshaw = best(0), best(ent.FLAG_CLENSHAW)
+    print(f"[hub] pairs {1e3 * pairs:.1f} ms, Clenshaw {1e3 * clenshaw:.1f} ms", flush=True)
+    assert pairs < clenshaw
