@@ -120,3 +120,56 @@ def test_batch_power_method_on_half(precision):
                                        flags=ent.FLAG_SKIP_TRACE_CHECK)
             assert abs(res[b].u / one.u - 1) <= 1e-10, (ns[b], res[b].u, one.u)
     g.destroy()
+
+
+def split_values(R):
+    """R as a BF16x3 call multiplies it: the sum of its bf16 parts, in FP32."""
+    X = torch.from_numpy(R)
+    hi = X.to(torch.bfloat16).float()
+    return (hi + (X - hi).to(torch.bfloat16).float()).numpy()
+
+
+@pytest.mark.parametrize("precision,n", [("f64", 2897), ("f64", 3001), ("f64", 3072), ("f32", 4097), ("f32", 4162),
+                                         ("f32", 4224), ("bf16x3", 2433), ("bf16x3", 2560), ("bf16x3", 3001)])
+@pytest.mark.parametrize("t", [1, 20])
+def test_power_estimate_on_half_of_r(orc, precision, n, t):
+    """p~1 itself (u is clamped at 1) of a symmetric R, read by half, and of the
+    same R with one entry moved, read whole, against the oracle's power method
+    from the same start vector: t + 1 products, n eps each, 2e-11 at most."""
+    R = symmetric(n, n).astype(np.float64 if precision == "f64" else np.float32)
+    for moved in (0.0, 0.01):
+        R[0, n - 1] += R.dtype.type(moved)
+        res = ent.entropy_estimate(torch.from_numpy(R).to(DEV), "chebyshev", 4, 128, 5, precision=precision,
+                                   power_iters=t, flags=ent.FLAG_SKIP_TRACE_CHECK)
+        want = orc.power_method((split_values(R) if precision == "bf16x3" else R).astype(np.float64), t, 1, 5)
+        assert abs(res.p1_est / want - 1) <= 2e-11, (moved, res.p1_est, want)
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("t", [1, 20])
+def test_batch_power_estimate_on_half(orc, precision, t):
+    """p~1 of every matrix of a batch large enough to read half of each symmetric
+    one, three of another kind among them, against the oracle's."""
+    dtype = np.float64 if precision == "f64" else np.float32
+    ns = [1, 2, 63, 127, 128, 129, 255, 257, 384, 1000] + [1160 if precision == "f32" else 808] * 18
+    host = []
+    for b, n in enumerate(ns):
+        R = symmetric(n, b).astype(dtype)
+        if b in (3, 7, 9, 12):
+            R[0, n - 1] += dtype(0.01)
+        host.append(R)
+    assert sum(R.nbytes for R in host) >= 96 << 20
+    mats = [torch.from_numpy(R).to(DEV) for R in host]
+    want = [orc.power_method(R.astype(np.float64), t, 1, 9 + b) for b, R in enumerate(host)]
+    g = ent.Graph(mats, "chebyshev", 3, 20, 9, precision=precision, power_iters=t, flags=ent.FLAG_SKIP_TRACE_CHECK)
+    for turn in range(3):
+        if turn == 2:  # one more of the other kind, and one less, on replay
+            for b, d in ((5, 0.02), (9, -0.01)):
+                host[b][0, -1] += dtype(d)
+                if b == 9:
+                    host[b][0, -1] = host[b][-1, 0]
+                mats[b].copy_(torch.from_numpy(host[b]))
+                want[b] = orc.power_method(host[b].astype(np.float64), t, 1, 9 + b)
+        for b, r in enumerate(g.launch()):
+            assert abs(r.p1_est / want[b] - 1) <= 2e-11, (turn, ns[b], r.p1_est, want[b])
+    g.destroy()
