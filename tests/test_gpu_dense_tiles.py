@@ -7,6 +7,8 @@ matrices: sizes whose K-split is not a power of two, with a ragged last split.
 The reference is the plain recurrence in FP64 numpy on the library's own
 probes; FP64 bar 1e-10 relative as in the other parity tests, FP32 TOL_F32.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -173,3 +175,36 @@ def test_batch_power_estimate_on_half(orc, precision, t):
         for b, r in enumerate(g.launch()):
             assert abs(r.p1_est / want[b] - 1) <= 2e-11, (turn, ns[b], r.p1_est, want[b])
     g.destroy()
+
+
+def direct_tiles(n, s):
+    """The library's rule: 0 where the tiled kernel runs."""
+    f = getattr(ent._lib, "_ZN3ent18dense_direct_tilesEli")
+    f.argtypes, f.restype = [ctypes.c_int64, ctypes.c_int32], ctypes.c_int32
+    return f(n, s)
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("schedule", ["chebyshev", "taylor", "clenshaw"])
+@pytest.mark.parametrize("n,s,split", [(2111, 130, True), (3001, 100, True), (2048, 200, True), (300, 1500, False),
+                                       (257, 2100, False)])
+@pytest.mark.parametrize("moved", [0.0, 0.01])
+def test_every_schedule_on_tiles(orc, precision, schedule, n, s, split, moved):
+    """The K-split product with its epilogue, and the whole tile, in each
+    schedule: sizes past the small-problem kernels' rule, both kinds of R."""
+    m, seed, u = 4, 11, 0.9
+    assert n > 192 and direct_tiles(n, s) == 0
+    R = symmetric(n, n)
+    R[0, n - 1] += moved
+    flags = ent.FLAG_SKIP_TRACE_CHECK | (ent.FLAG_CLENSHAW if schedule == "clenshaw" else 0)
+    ent.timing_enable(True)
+    try:
+        _, per, _ = ent.entropy_estimate_detail(torch.from_numpy(R).to(DEV), "taylor" if schedule == "taylor" else "chebyshev",
+                                                m, s, seed, precision=precision, u_fixed=u, probe_dist="gaussian",
+                                                flags=flags)
+        t = ent.last_timing()
+    finally:
+        ent.timing_enable(False)
+    _, want = reference(orc, lambda V: R @ V, n, "taylor" if schedule == "taylor" else "chebyshev", m, s, seed, 1, u)
+    e = float(np.max(np.abs(per - want)) / max(np.mean(np.abs(want)), 1.0))
+    assert (t["epilogue_launches"] > 0) == split and e <= tol_for(precision), (t, e)
