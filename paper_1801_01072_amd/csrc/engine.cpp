@@ -2684,8 +2684,10 @@ ent_status batch_create(const ent_matrix *Rs, int32_t count, int32_t method, int
   // more than a second launch, the sums fit the matrix's V block and its tiles
   // the table of the other form.  Whole against half, us a product: 64 matrices of
   // n <= 2048 FP32 (328 MB) 62 / 43, 32 of 1024 (128 MB) 23.0 / 21.2, 20 of 1024
-  // (80 MB) 16.0 / 16.6, 600 of 200 (92 MB) 36 / 26; 40 of 2000 FP64 206 / 128;
-  // for matrices unequal to their transpose 23.0 / 28.1 (32 of 1024 FP32)
+  // (80 MB) 16.0 / 16.6, 600 of 200 (92 MB) 36 / 26; 40 of 2000 FP64 206 / 128.
+  // The line is where the larger matrices begin to gain; many small ones would
+  // from fewer bytes on.  Matrices unequal to their transpose are read whole either
+  // way (kRowGroups)
   bool fits = !g->bf16 && (size_t)roff * esz >= ((size_t)96 << 20);
   for (const auto &M : g->mats) {
     const int64_t nb = ent::power_sym_parts(M.n);

@@ -618,7 +618,9 @@ hipError_t launch_batch_power_gemv(const BatchMat *mats, const int2 *ptiles, int
                                    const double *x, const double *pprev, double *y, double *pout,
                                    hipStream_t st);
 // The same reading half of each symmetric matrix: stiles lists (matrix, tile of
-// 128 x 128, power_sym_parts (parts + 1) / 2 of them), tiles (matrix, 64 rows).
+// 128 x 128, power_sym_parts (parts + 1) / 2 of them), tiles (matrix, 64 rows); a
+// matrix unequal to its transpose is read whole, its triples those of
+// launch_batch_power_gemv.
 template <typename T>
 hipError_t launch_batch_power_sym(const BatchMat *mats, const int2 *stiles, int32_t nstiles, const int2 *tiles,
                                   int32_t ntiles, const double *x, const double *pprev, T *V, double *y,

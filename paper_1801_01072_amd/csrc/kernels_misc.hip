@@ -1475,35 +1475,52 @@ __global__ __launch_bounds__(256) void batch_power_gemv_kernel(const BatchMat *_
 }
 
 // The same from half of each matrix that equals its transpose (its answer is on
-// the device; another one's mirror tiles are read too), the sums in the
-// matrix's V block V: stiles (matrix, tile), tiles (matrix, 64 rows).
+// the device), the sums in the matrix's V block V: stiles (matrix, tile), tiles
+// (matrix, 64 rows).  Any other matrix is passed by here and multiplied whole by
+// the second launch, whose workgroups come in kRowGroups groups of one per entry
+// of tiles: a matrix read whole takes all of them, every fourth block of 8 rows
+// each, and a combination of 64 rows those of the first group.  us a product, for
+// matrices unequal to their transpose (40 of 2000 FP64; 64 of up to 2048 FP64; 32
+// of 1024 FP32): both halves by tiles 220 + 8, 128 + 6, 23.7 + 4.8; row blocks
+// dealt to the workgroups of the first launch, which hold too many registers for
+// it, 221 + 5, 139 + 5, 37 + 5; this way 8 + 214, 5 + 121, 4.6 + 24.9 (one group 9
+// + 217, 6 + 127, 4.6 + 30; eight 7 + 213, 5 + 119, 4.6 + 23.6), where every matrix
+// is read whole 209, 114, 23.5.  Combining 64 symmetric ones of up to 2048 takes
+// 6.2 us with four groups, 7.3 with eight, 5.2 with none.
+constexpr int kRowGroups = 4;
+
 template <typename T>
 __global__ __launch_bounds__(256) void batch_power_sym_kernel(const BatchMat *__restrict__ mats,
                                                               const int2 *__restrict__ stiles,
                                                               const double *__restrict__ x, T *V) {
   const int2 t = uniform_load(stiles + blockIdx.x);
   const BatchMat M = uniform_load(mats + t.x);
-  double *part = (double *)(V + M.voff);
+  if (!batch_pairs(M)) return;
   int64_t rb, cb;
   sym_tile(t.y, rb, cb);
-  const bool sym = batch_pairs(M);
-  power_sym_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, part, rb, cb, sym && rb != cb);
-  if (sym || rb == cb) return;
-  __syncthreads();
-  power_sym_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, part, cb, rb, false);
+  power_sym_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, (double *)(V + M.voff), rb, cb, rb != cb);
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void batch_power_sym_combine_kernel(const BatchMat *__restrict__ mats,
-                                                                      const int2 *__restrict__ tiles,
+                                                                      const int2 *__restrict__ tiles, int32_t ntiles,
                                                                       const double *x, const double *pprev,
                                                                       const T *V, double *y, double *pout) {
-  const int2 t = tiles[blockIdx.x];
+  const int32_t group = (int32_t)blockIdx.x / ntiles;
+  const int2 t = tiles[(int32_t)blockIdx.x - group * ntiles];
   const BatchMat &M = mats[t.x];
-  if ((int64_t)t.y * 64 >= M.n) return;
-  const PowerPrev prev = {nullptr, pprev ? pprev + M.pboff : nullptr, (int32_t)((M.n + 63) / 64)};
-  power_sym_sum((const double *)(V + M.voff), (int32_t)((M.n + kSymTile - 1) / kSymTile), M.n, M.n, x + M.xoff, prev,
-                y + M.xoff, pout + M.pboff, t.y);
+  PowerPrev prev = {nullptr, pprev ? pprev + M.pboff : nullptr, M.pblk};
+  if (batch_pairs(M)) {
+    if (group > 0 || (int64_t)t.y * 64 >= M.n) return;
+    prev.nblk = (int32_t)((M.n + 63) / 64);
+    power_sym_sum((const double *)(V + M.voff), (int32_t)((M.n + kSymTile - 1) / kSymTile), M.n, M.n, x + M.xoff,
+                  prev, y + M.xoff, pout + M.pboff, t.y);
+  } else {
+    for (int blk = t.y * 8 + group; blk < t.y * 8 + 8 && blk < M.pblk; blk += kRowGroups) {
+      __syncthreads();  // the block before is done with its sums in LDS
+      power_gemv_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, prev, y + M.xoff, pout + M.pboff, blk);
+    }
+  }
 }
 
 template <typename T>
@@ -1512,7 +1529,8 @@ hipError_t launch_batch_power_sym(const BatchMat *mats, const int2 *stiles, int3
                                   double *pout, hipStream_t st) {
   if (pprev == pout) return hipErrorInvalidValue;
   batch_power_sym_kernel<T><<<(unsigned)nstiles, 256, 0, st>>>(mats, stiles, x, V);
-  batch_power_sym_combine_kernel<T><<<(unsigned)ntiles, 256, 0, st>>>(mats, tiles, x, pprev, V, y, pout);
+  batch_power_sym_combine_kernel<T><<<(unsigned)ntiles * kRowGroups, 256, 0, st>>>(mats, tiles, ntiles, x, pprev, V, y,
+                                                                                pout);
   return hipGetLastError();
 }
 template hipError_t launch_batch_power_sym<double>(const BatchMat *, const int2 *, int32_t, const int2 *, int32_t,
@@ -1542,7 +1560,7 @@ __global__ __launch_bounds__(256) void batch_power_rq_kernel(const BatchMat *__r
                                                              int32_t trial, bool half) {
   __shared__ double norm3[3];
   const BatchMat &M = mats[blockIdx.x];
-  power_reduce_body(p + M.pboff, half ? (int32_t)((M.n + 63) / 64) : M.pblk, norm3);
+  power_reduce_body(p + M.pboff, half && batch_pairs(M) ? (int32_t)((M.n + 63) / 64) : M.pblk, norm3);
   power_rq_body(M.scal, norm3, trial);
 }
 
