@@ -687,6 +687,14 @@ hipError_t launch_trace_dense(const T *R, int64_t ldr, int64_t n, double *scal, 
 template hipError_t launch_trace_dense<double>(const double *, int64_t, int64_t, double *, hipStream_t, double *, int64_t);
 template hipError_t launch_trace_dense<float>(const float *, int64_t, int64_t, double *, hipStream_t, double *, int64_t);
 
+// Tile t of the triangle: columns of tiles bj, in each the tiles bi <= bj.
+__device__ __forceinline__ void check_tile(int64_t t, int64_t &bi, int64_t &bj) {
+  bj = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
+  while (bj * (bj + 1) / 2 > t) --bj;
+  while ((bj + 1) * (bj + 2) / 2 <= t) ++bj;
+  bi = t - bj * (bj + 1) / 2;
+}
+
 // Trace and symmetry in one pass over R (HBM-bound: every element is read
 // once).  A workgroup takes a 64 x 64 tile (bi, bj),
 // bi <= bj, and its mirror image, both read along rows; the tile is compared
@@ -696,10 +704,8 @@ template hipError_t launch_trace_dense<float>(const float *, int64_t, int64_t, d
 template <typename T>
 __device__ __forceinline__ bool dense_check_tile(const T *__restrict__ R, int64_t ldr, int64_t n, int64_t t,
                                                  T (*tile)[65], double *__restrict__ tmp) {
-  int64_t bj = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-  while (bj * (bj + 1) / 2 > t) --bj;
-  while ((bj + 1) * (bj + 2) / 2 <= t) ++bj;
-  const int64_t bi = t - bj * (bj + 1) / 2;
+  int64_t bi, bj;
+  check_tile(t, bi, bj);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t r0 = 64 * bi, c0 = 64 * bj;
   T x[16], y[16];
@@ -724,11 +730,34 @@ __device__ __forceinline__ bool dense_check_tile(const T *__restrict__ R, int64_
   return __any(bad) != 0;
 }
 
+// Sets a flag that many waves may set to the same value, for later kernels: a
+// store, where atomics would take turns at its address (12 ns each).
+__device__ __forceinline__ void raise_flag(int32_t *p) {
+  __hip_atomic_store(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// An R that rounding has made unequal to its transpose everywhere is read only
+// by the workgroups that start before the first mismatch is known; the later ones
+// leave their part of the trace (n = 8192 FP64 391 us when every wave set the flag
+// by an atomic, 21 now; 4096 FP32 100 and 13; 93 and 13 for an R equal to its
+// transpose, with this or without).  The first kCheckFirst workgroups start
+// together and need not look.
+constexpr unsigned kCheckFirst = 1024;
+
 template <typename T>
 __global__ __launch_bounds__(256) void dense_check_kernel(const T *__restrict__ R, int64_t ldr, int64_t n,
                                                           double *__restrict__ tmp, int32_t *__restrict__ asym) {
   __shared__ T tile[64][65];
-  if (dense_check_tile<T>(R, ldr, n, blockIdx.x, tile, tmp) && (threadIdx.x & 63) == 0) atomicOr(asym, 1);
+  if (blockIdx.x >= kCheckFirst && __syncthreads_or(*(volatile int32_t *)asym) != 0) {
+    int64_t bi, bj;
+    check_tile(blockIdx.x, bi, bj);
+    if (bi != bj || threadIdx.x >= 64) return;
+    const int64_t r = 64 * bi + threadIdx.x;
+    const double d = wave_sum(r < n ? (double)R[r * ldr + r] : 0.0);
+    if (threadIdx.x == 0) tmp[bi] = d;
+    return;
+  }
+  if (dense_check_tile<T>(R, ldr, n, blockIdx.x, tile, tmp) && (threadIdx.x & 63) == 0) raise_flag(asym);
 }
 
 // Batch: the tiles of matrix blockIdx.y dealt to the workgroups of its row of
@@ -744,8 +773,8 @@ __global__ __launch_bounds__(256) void batch_check_kernel(const BatchMat *__rest
     if (dense_check_tile<T>((const T *)M.R, M.ldr, M.n, t, tile, nullptr)) bad = true;
   }
   if (bad && (threadIdx.x & 63) == 0) {
-    atomicOr((int32_t *)(M.scal + S_SYM), 1);
-    atomicOr(tail, 1);
+    raise_flag((int32_t *)(M.scal + S_SYM));
+    raise_flag(tail);
   }
 }
 
@@ -902,11 +931,10 @@ hipError_t launch_validate_csr(const int64_t *rp, const int32_t *ci, int64_t n, 
 // (r, c) needs exactly one entry (c, r) of the same value.  Row c is searched
 // from its first entry (short rows: a tridiagonal row has three, adjacent in
 // memory to the row's own); its range is checked before it is read, as row_ptr
-// is validated in the same pass.  A row c of more than kSymScan entries is not
-// searched (one long row met by every other would cost n^2 reads): the matrix
-// then counts as not symmetric.  Nor does such a row look its own entries up, one
-// after the other in one thread: their mirrors meet it (star of 200000 vertices:
-// 125 -> 24 ms).
+// is validated in the same pass.  With a row of more than kSymScan entries the
+// matrix counts as not symmetric: searched by every other row it would cost n^2
+// reads, and looking its own entries up, one after the other in one thread, as
+// much time again as all else (star of 200000 vertices: 125 -> 33 ms).
 constexpr int64_t kSymScan = 64;
 
 template <typename T>
@@ -922,38 +950,28 @@ __global__ __launch_bounds__(256) void validate_csr_rows_kernel(const int64_t *_
       bad = true;
       continue;
     }
-    int64_t hr = 0;
-    if (val && b - a <= kSymScan && !asym) {
-      for (int64_t e = a; e < b; ++e) {
-        const int64_t c = ci[e];
-        if (c < 0 || c >= n) {
-          bad = true;
-          continue;
-        }
+    if (b - a > kSymScan) asym = true;
+    for (int64_t e = a; e < b; ++e) {
+      const int64_t c = ci[e];
+      if (c < 0 || c >= n) {
+        bad = true;
+      } else {
         const int64_t d = c > r ? c - r : r - c;
-        hr = d > hr ? d : hr;
-        if (d == 0 || asym) continue;
-        const int64_t a2 = rp[c], b2 = rp[c + 1];
-        int found = 0;
-        if (a2 >= 0 && b2 <= nnz && b2 - a2 <= kSymScan) {
-          for (int64_t f = a2; f < b2; ++f)
-            if (ci[f] == r) found += val[f] == val[e] ? 1 : 2;
+        hb = d > hb ? d : hb;
+        if (val && d != 0 && !asym) {
+          const int64_t a2 = rp[c], b2 = rp[c + 1];
+          int found = 0;
+          if (a2 >= 0 && b2 <= nnz && b2 - a2 <= kSymScan) {
+            for (int64_t f = a2; f < b2; ++f)
+              if (ci[f] == r) found += val[f] == val[e] ? 1 : 2;
+          }
+          asym = found != 1;
         }
-        asym = found != 1;
       }
-    } else {
-      for (int64_t e = a; e < b; ++e) {
-        const int64_t c = ci[e];
-        if (c < 0 || c >= n) bad = true;
-        const int64_t d = c > r ? c - r : r - c;
-        hr = d > hr ? d : hr;
-      }
-      if (hr > 0) asym = true;  // (read with val only)
     }
-    hb = hr > hb ? hr : hb;
   }
   if (bad) atomicOr(flag, 1);
-  if (val && __any(asym) && (threadIdx.x & 63) == 0) atomicOr(flag + 2, 1);
+  if (__any(asym) && (threadIdx.x & 63) == 0) atomicOr(flag + 2, 1);
   // n < 2^31 (int32 column indices), so the half-bandwidth fits
   int32_t h = (int32_t)hb;
   for (int off = 32; off > 0; off >>= 1) {

@@ -208,3 +208,62 @@ def test_every_schedule_on_tiles(orc, precision, schedule, n, s, split, moved):
     _, want = reference(orc, lambda V: R @ V, n, "taylor" if schedule == "taylor" else "chebyshev", m, s, seed, 1, u)
     e = float(np.max(np.abs(per - want)) / max(np.mean(np.abs(want)), 1.0))
     assert (t["epilogue_launches"] > 0) == split and e <= tol_for(precision), (t, e)
+
+
+@pytest.mark.parametrize("n", [3000, 4100])  # up to 1128 and 2145 tiles of 64 x 64: all known at the start, and not
+@pytest.mark.parametrize("kind", ["rounded", "corner", "equal"])
+def test_symmetry_answer_and_trace(n, kind):
+    """Products run and the trace for an R that differs from its transpose almost
+    everywhere, in one place of the last tile, and nowhere: the trace to n eps of
+    its FP64 sum (every term at least 0.4 / n)."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    R = torch.randn((n, n), generator=g, dtype=torch.float64, device=DEV) * (0.01 / n ** 1.5)
+    R = R + R.T + torch.diag(torch.rand(n, generator=g, dtype=torch.float64, device=DEV) + 0.5) / n
+    if kind == "rounded":
+        R = R * (1 + (torch.rand((n, n), generator=g, dtype=torch.float64, device=DEV) - 0.5) * 4e-16)
+    elif kind == "corner":
+        R[n - 1, n - 2] *= 1 + 1e-12
+    trace = float(torch.diagonal(R).sum())
+    ent.timing_enable(True)
+    try:
+        for _ in range(3):
+            for side in (-1, 1):
+                ent.entropy_estimate(R / trace if side < 0 else R, "chebyshev", 6, 8, 1, u_fixed=1.0,
+                                     trace_tol=max(abs(trace - 1), 0.0) + n * 2.3e-16 if side > 0 else n * 2.3e-16)
+            assert ent.last_timing()["step_launches"] == (3 if kind == "equal" else 6)
+    finally:
+        ent.timing_enable(False)
+    if abs(trace - 1) > 1e-9:
+        with pytest.raises(ent.EntropyError, match="trace"):
+            ent.entropy_estimate(R, "chebyshev", 6, 8, 1, u_fixed=1.0, trace_tol=abs(trace - 1) - n * 2.3e-16)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_mismatches_everywhere_cost_no_more_than_none(dtype):
+    """The check of an R that rounding made unequal to its transpose everywhere,
+    against the same R's in Clenshaw, which asks nothing (u given, one step each):
+    the check reads R once, less than a power product of the same call does."""
+    import time
+
+    n = 8192
+    g = torch.Generator(device=DEV).manual_seed(3)
+    R = torch.rand((n, n), generator=g, dtype=dtype, device=DEV) / n ** 2
+    R = R + R.T + torch.eye(n, dtype=dtype, device=DEV) / n
+
+    def best(M, **kw):
+        times = []
+        for _ in range(6):
+            t = time.perf_counter()
+            ent.entropy_estimate(M, "chebyshev", 2, 8, 1, precision="f64" if dtype == torch.float64 else "f32",
+                                 u_fixed=1.0, flags=ent.FLAG_SKIP_TRACE_CHECK, **kw)
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    equal = best(R)
+    A = R * (1 + (torch.rand((n, n), generator=g, dtype=dtype, device=DEV) - 0.5) * (4e-16 if dtype == torch.float64 else 3e-7))
+    unequal = best(A)
+    one = R.clone()
+    one[0, n - 1] *= 1.5
+    late = best(one)
+    print(f"[check {dtype}] equal {1e6 * equal:.0f} us, everywhere {1e6 * unequal:.0f}, in one place {1e6 * late:.0f}", flush=True)
+    assert unequal <= 1.05 * late
