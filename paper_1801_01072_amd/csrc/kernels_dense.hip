@@ -85,6 +85,18 @@ namespace {
 template <int WR>
 constexpr int kBatchCols = WR == 1 ? 4 : 1;
 
+// LDS of a tile: its stages and, for a persistent kernel, the two words behind them
+// with which its waves agree on the next item.  The kernel's only LDS object: with a
+// single one the compiler adds no waits of its own between the direct loads into
+// one stage and the reads of another; a second one gives it alias scopes, and every
+// chunk's reads then wait for all loads (FP64 persistent batch, 40 symmetric
+// matrices of n = 2000: 9.23 -> 7.89 ms a call).  Named as it stands, not by a
+// pointer, which changes the schedule of the K loop (n = 8192 FP64 589 -> 603 us a
+// step).
+constexpr int kHookLds = 2 * sizeof(int);
+template <int BYTES>
+__shared__ __attribute__((aligned(1024))) unsigned char tile_lds[BYTES];
+
 // What a persistent kernel does inside a tile: ready() once R's first loads are
 // out and before anything of the step before is read (false: give up, the tile
 // returns false), products_done() before the epilogue.
@@ -123,16 +135,9 @@ struct BatchHook {
 // permuted consistently for A and B).  A ragged last chunk (n not a multiple of
 // BK) reads A into registers at the start, column min(k, n - 1) element by
 // element: V_k is zero in rows k >= n, so those products vanish.
-//
-// lds: the workgroup's stages, DenseChunk::LDS bytes.  It is the kernel's only
-// __shared__ object (the persistent kernel's two words stand behind the stages):
-// with a single one the compiler adds no waits of its own between the direct
-// loads into one stage and the reads of another; a second one gives it alias
-// scopes, and every chunk's reads then wait for all loads (FP64 persistent
-// batch, 40 symmetric matrices of n = 2000: 9.23 -> 7.89 ms a call).
 template <typename T, int BN, int WR, int EC, int BUDGET = kChunkLds, bool PRE = false, typename H = DenseNoHook>
-__device__ __forceinline__ bool dense_step_tile(unsigned char *lds, const DenseStepArgs &a, int tm, int tn,
-                                                int64_t kbeg, int64_t kend, T *yout, H hook = H{}) {
+__device__ __forceinline__ bool dense_step_tile(const DenseStepArgs &a, int tm, int tn, int64_t kbeg,
+                                                int64_t kend, T *yout, H hook = H{}) {
   using M = Mfma16<T>;
   using v4 = typename M::v4;
   using C = DenseChunk<T, BN, WR, BUDGET>;
@@ -141,12 +146,13 @@ __device__ __forceinline__ bool dense_step_tile(unsigned char *lds, const DenseS
   constexpr int NVL = C::NVL, NAL = C::NAL, APL = C::APL;
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
 
-  // stage s at lds + s * STAGE: the V_k chunk (VBYTES), then the A values of
+  // stage s at tile_lds<BYTES> + s * STAGE: the V_k chunk (VBYTES), then the A values of
   // the 4 waves (ABYTES)
   constexpr int STAGE = C::VBYTES + C::ABYTES, NST = C::NST;
   // the epilogue's per-wave dot sums reuse the stages after the products
   static_assert(C::LDS >= 3 * 4 * BN * 8, "the dot sums fit in the stages");
-  double(*red)[4][BN] = (double(*)[4][BN])lds;
+  constexpr int BYTES = C::LDS + (H::on ? kHookLds : 0);
+  double(*red)[4][BN] = (double(*)[4][BN])tile_lds<BYTES>;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -270,22 +276,22 @@ __device__ __forceinline__ bool dense_step_tile(unsigned char *lds, const DenseS
     // R does not depend on the step before: its loads go out ahead of the wait
     if (ragged) load_ragged();
     for (int c = 0; c < NST; ++c)
-      if (c < nfull) issue_a(c, lds + c * STAGE);
+      if (c < nfull) issue_a(c, tile_lds<BYTES> + c * STAGE);
     if (!hook.ready()) {
       dense_wait_vm<0>();
       return false;
     }
     load_epilogue();
     for (int c = 0; c < NST; ++c)
-      if (c < nfull + (ragged ? 1 : 0)) issue_v(c, lds + c * STAGE);
+      if (c < nfull + (ragged ? 1 : 0)) issue_v(c, tile_lds<BYTES> + c * STAGE);
   } else {
     if (ragged) load_ragged();
     load_epilogue();
     for (int c = 0; c < NST; ++c) {
       if (c < nfull)
-        issue(c, lds + c * STAGE);
+        issue(c, tile_lds<BYTES> + c * STAGE);
       else if (c == nfull && ragged)
-        issue_v(c, lds + c * STAGE);
+        issue_v(c, tile_lds<BYTES> + c * STAGE);
     }
   }
   // wait until at most k chunks' loads of this wave are in flight (k < NST)
@@ -319,10 +325,10 @@ __device__ __forceinline__ bool dense_step_tile(unsigned char *lds, const DenseS
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     if (c + NST < nfull)
-      issue(c + NST, lds + s0 * STAGE);
+      issue(c + NST, tile_lds<BYTES> + s0 * STAGE);
     else if (c + NST == nfull && ragged)
-      issue_v(nfull, lds + s0 * STAGE);
-    if (c + 1 < nfull) read_frag(nxt, lds + (s0 == NST - 1 ? 0 : s0 + 1) * STAGE);
+      issue_v(nfull, tile_lds<BYTES> + s0 * STAGE);
+    if (c + 1 < nfull) read_frag(nxt, tile_lds<BYTES> + (s0 == NST - 1 ? 0 : s0 + 1) * STAGE);
     mfma_frag(cur);
   };
   if (nfull > 0) {
@@ -333,7 +339,7 @@ __device__ __forceinline__ bool dense_step_tile(unsigned char *lds, const DenseS
       wait_chunks(ahead);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    read_frag(fx, lds);
+    read_frag(fx, tile_lds<BYTES>);
   }
   int c = 0, s0 = 0;
   for (; c + 1 < nfull; c += 2) {
@@ -347,7 +353,7 @@ __device__ __forceinline__ bool dense_step_tile(unsigned char *lds, const DenseS
     s0 = s0 == NST - 1 ? 0 : s0 + 1;
   }
   if (ragged) {
-    unsigned char *st = lds + s0 * STAGE;
+    unsigned char *st = tile_lds<BYTES> + s0 * STAGE;
     dense_wait_vm<0>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
@@ -456,10 +462,9 @@ __device__ __forceinline__ bool dense_step_tile(unsigned char *lds, const DenseS
 
 template <typename T, int BN, int WR>
 __global__ __launch_bounds__(256) void dense_step_kernel(DenseStepArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[DenseChunk<T, BN, WR>::LDS];
   const int ntn = (int)(a.ldv / BN);
   const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-  dense_step_tile<T, BN, WR, 4>(lds, a, b / ntn, b % ntn, 0, a.n, nullptr);
+  dense_step_tile<T, BN, WR, 4>(a, b / ntn, b % ntn, 0, a.n, nullptr);
 }
 
 // Split-K product (a kernel of its own, so the fused kernel's code is not
@@ -467,7 +472,6 @@ __global__ __launch_bounds__(256) void dense_step_kernel(DenseStepArgs a) {
 // tiles of one split (same V_k rows) are neighbours.
 template <typename T, int BN, int WR>
 __global__ __launch_bounds__(256) void dense_step_split_kernel(DenseStepArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[DenseChunk<T, BN, WR>::LDS];
   const int ntn = (int)(a.ldv / BN);
   const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
   const int ntl = a.ntile * ntn;
@@ -475,7 +479,7 @@ __global__ __launch_bounds__(256) void dense_step_split_kernel(DenseStepArgs a) 
   const int64_t kbeg = (int64_t)ks * a.kper;
   const int64_t kend = kbeg + a.kper < a.n ? kbeg + a.kper : a.n;
   T *yout = (T *)a.party + (int64_t)ks * (int64_t)a.ntile * 64 * a.ldv;
-  dense_step_tile<T, BN, WR, 4>(lds, a, t / ntn, t % ntn, kbeg, kend, yout);
+  dense_step_tile<T, BN, WR, 4>(a, t / ntn, t % ntn, kbeg, kend, yout);
 }
 
 // Split-K epilogue: y = a sum_ks party[ks] (split order), z = c1 y + c2 b V_k
@@ -994,11 +998,10 @@ __device__ __forceinline__ bool batch_dense_args(const BatchPersistArgs &pa, con
 template <typename T, int WR>
 __global__ __launch_bounds__(256) void batch_dense_step_kernel(BatchPersistArgs pa, int k, const int2 *tiles) {
   constexpr int BUDGET = sizeof(T) == 4 ? kGroupedLds : kChunkLds;
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[DenseChunk<T, 64, WR, BUDGET>::LDS];
   const int2 tl = tiles[blockIdx.x];
   DenseStepArgs a{};
   if (!batch_dense_args<T>(pa, pa.mats[tl.x], k, a)) return;
-  dense_step_tile<T, 64, WR, kBatchCols<WR>, BUDGET>(lds, a, tl.y, (int)blockIdx.y, 0, a.n, nullptr);
+  dense_step_tile<T, 64, WR, kBatchCols<WR>, BUDGET>(a, tl.y, (int)blockIdx.y, 0, a.n, nullptr);
 }
 
 // Persistent batch steps: each workgroup takes (matrix, row tile, step)
@@ -1016,8 +1019,7 @@ __global__ __launch_bounds__(256) void batch_dense_step_kernel(BatchPersistArgs 
 template <typename T, int WR>
 __global__ __launch_bounds__(256, 2) void batch_dense_persistent_kernel(BatchPersistArgs pa) {
   constexpr int LDS = DenseChunk<T, 64, WR>::LDS;
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS + 2 * sizeof(int)];
-  int *sh = (int *)(lds + LDS);
+  int *sh = (int *)(tile_lds<LDS + kHookLds> + LDS);
   int next = sched_reserve(pa.sched);
   for (;;) {
     const int i = sched_item(pa.sched, next, sh);
@@ -1032,7 +1034,7 @@ __global__ __launch_bounds__(256, 2) void batch_dense_persistent_kernel(BatchPer
     }
     a.ldv = 64;
     BatchHook hook{pa.sched, it.x, it.z * M.ntile, sh + 1, &next};
-    if (!dense_step_tile<T, 64, WR, kBatchCols<WR>, kChunkLds, sizeof(T) == 4 && WR == 1, BatchHook>(lds, a, it.y, 0, 0, a.n, nullptr,
+    if (!dense_step_tile<T, 64, WR, kBatchCols<WR>, kChunkLds, sizeof(T) == 4 && WR == 1, BatchHook>(a, it.y, 0, 0, a.n, nullptr,
                                                                                                            hook))
       return;
     sched_release(pa.sched, it.x);
