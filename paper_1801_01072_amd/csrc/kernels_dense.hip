@@ -134,8 +134,10 @@ struct BatchHook {
 // MFMA k-slot q of call t is column kcol(q, t) (the k order inside a chunk is
 // permuted consistently for A and B).  A ragged last chunk (n not a multiple of
 // BK) reads A into registers at the start, column min(k, n - 1) element by
-// element: V_k is zero in rows k >= n, so those products vanish.
-template <typename T, int BN, int WR, int EC, int BUDGET = kChunkLds, bool PRE = false, typename H = DenseNoHook>
+// element: V_k is zero in rows k >= n, so those products vanish.  RAG false: there
+// is none (see dense_step_launch).
+template <typename T, int BN, int WR, int EC, int BUDGET = kChunkLds, bool PRE = false, typename H = DenseNoHook,
+          bool RAG = true>
 __device__ __forceinline__ bool dense_step_tile(const DenseStepArgs &a, int tm, int tn, int64_t kbeg,
                                                 int64_t kend, T *yout, H hook = H{}) {
   using M = Mfma16<T>;
@@ -180,7 +182,7 @@ __device__ __forceinline__ bool dense_step_tile(const DenseStepArgs &a, int tm, 
   }
 
   const int nfull = (int)((kend - kbeg) / BK);
-  const bool ragged = kbeg + (int64_t)nfull * BK < kend;
+  const bool ragged = RAG && kbeg + (int64_t)nfull * BK < kend;
 
   using LdsPtr = __attribute__((address_space(3))) void *;
   auto issue_v = [&](int c, unsigned char *st) {
@@ -460,17 +462,17 @@ __device__ __forceinline__ bool dense_step_tile(const DenseStepArgs &a, int tm, 
   return true;
 }
 
-template <typename T, int BN, int WR>
+template <typename T, int BN, int WR, bool RAG>
 __global__ __launch_bounds__(256) void dense_step_kernel(DenseStepArgs a) {
   const int ntn = (int)(a.ldv / BN);
   const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-  dense_step_tile<T, BN, WR, 4>(a, b / ntn, b % ntn, 0, a.n, nullptr);
+  dense_step_tile<T, BN, WR, 4, kChunkLds, false, DenseNoHook, RAG>(a, b / ntn, b % ntn, 0, a.n, nullptr);
 }
 
 // Split-K product (a kernel of its own, so the fused kernel's code is not
 // shaped by this path): tile order row tile fastest within a K-split, so the
 // tiles of one split (same V_k rows) are neighbours.
-template <typename T, int BN, int WR>
+template <typename T, int BN, int WR, bool RAG>
 __global__ __launch_bounds__(256) void dense_step_split_kernel(DenseStepArgs a) {
   const int ntn = (int)(a.ldv / BN);
   const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
@@ -479,7 +481,7 @@ __global__ __launch_bounds__(256) void dense_step_split_kernel(DenseStepArgs a) 
   const int64_t kbeg = (int64_t)ks * a.kper;
   const int64_t kend = kbeg + a.kper < a.n ? kbeg + a.kper : a.n;
   T *yout = (T *)a.party + (int64_t)ks * (int64_t)a.ntile * 64 * a.ldv;
-  dense_step_tile<T, BN, WR, 4>(a, t / ntn, t % ntn, kbeg, kend, yout);
+  dense_step_tile<T, BN, WR, 4, kChunkLds, false, DenseNoHook, RAG>(a, t / ntn, t % ntn, kbeg, kend, yout);
 }
 
 // Split-K epilogue: y = a sum_ks party[ks] (split order), z = c1 y + c2 b V_k
@@ -1083,6 +1085,25 @@ hipError_t launch_dense_split_epilogue(const DenseStepArgs &a, hipStream_t st) {
 template hipError_t launch_dense_split_epilogue<double>(const DenseStepArgs &, hipStream_t);
 template hipError_t launch_dense_split_epilogue<float>(const DenseStepArgs &, hipStream_t);
 
+// FP64 with n a multiple of the chunk: the instance without a ragged one, whose
+// branches in every step cost 1 to 2% (n = 8192, 256 probes 594.7 us a step with
+// them, 585.5 without; 4096, 64 46.4 / 45.4; 2200, 128 31.5 / 30.8).  FP32 gains
+// nothing by it (8192, 256 304 / 306).
+template <typename T, int BN, bool RAG>
+static void dense_step_launch_as(const DenseStepArgs &a, unsigned grid, hipStream_t st) {
+  if (a.ksplit > 1)
+    dense_step_split_kernel<T, BN, 1, RAG><<<grid, 256, 0, st>>>(a);
+  else
+    dense_step_kernel<T, BN, 1, RAG><<<grid, 256, 0, st>>>(a);
+}
+template <typename T, int BN>
+static void dense_step_launch(const DenseStepArgs &a, unsigned grid, hipStream_t st) {
+  if (sizeof(T) == 8 && a.n % DenseChunk<T, BN, 1>::BK == 0)
+    dense_step_launch_as<T, BN, sizeof(T) != 8>(a, grid, st);
+  else
+    dense_step_launch_as<T, BN, true>(a, grid, st);
+}
+
 template <typename T>
 hipError_t launch_dense_step(const DenseStepArgs &a, hipStream_t st, bool epilogue) {
   if (a.direct > 0) return launch_dense_direct<T>(a, st);
@@ -1091,20 +1112,11 @@ hipError_t launch_dense_step(const DenseStepArgs &a, hipStream_t st, bool epilog
                        a.nptile != a.ntile * 4))
     return hipErrorInvalidValue;
   const unsigned grid = (unsigned)(a.ntile * ntn * (a.ksplit > 1 ? a.ksplit : 1));
-  if (a.ksplit > 1) {
-    switch (a.bn) {
-      case 64: dense_step_split_kernel<T, 64, 1><<<grid, 256, 0, st>>>(a); break;
-      case 128: dense_step_split_kernel<T, 128, 1><<<grid, 256, 0, st>>>(a); break;
-      case 256: dense_step_split_kernel<T, 256, 1><<<grid, 256, 0, st>>>(a); break;
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    switch (a.bn) {
-      case 64: dense_step_kernel<T, 64, 1><<<grid, 256, 0, st>>>(a); break;
-      case 128: dense_step_kernel<T, 128, 1><<<grid, 256, 0, st>>>(a); break;
-      case 256: dense_step_kernel<T, 256, 1><<<grid, 256, 0, st>>>(a); break;
-      default: return hipErrorInvalidValue;
-    }
+  switch (a.bn) {
+    case 64: dense_step_launch<T, 64>(a, grid, st); break;
+    case 128: dense_step_launch<T, 128>(a, grid, st); break;
+    case 256: dense_step_launch<T, 256>(a, grid, st); break;
+    default: return hipErrorInvalidValue;
   }
   if (a.ksplit > 1 && epilogue) {
     const hipError_t e = hipGetLastError();
