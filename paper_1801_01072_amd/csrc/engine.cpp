@@ -2554,15 +2554,41 @@ ent_status batch_autotune(ent_graph_s *g, bool stepwise_only) {
   return batch_set_schedule(g, best_win);
 }
 
-std::string batch_tune_key(const ent_graph_s *g) {
+// Whether any of the batch's matrices differs from its transpose, as they stand.
+template <typename T>
+ent_status batch_differs(ent_graph_s *g, bool *differs) {
+  ent_status rc = batch_upload(g, g->bf16 ? 2 : 1);
+  if (rc != ENT_OK) return rc;
+  HIP_TRY(ent::launch_fill(g->scal, (int64_t)g->count * g->sb, 0.0, g->stream));
+  if (!g->bf16 && g->src_f64)
+    HIP_TRY((ent::launch_batch_convert<double, T>(g->mats_d, g->count, g->max_elems, g->stream)));
+  else if (!g->bf16)
+    HIP_TRY((ent::launch_batch_convert<float, T>(g->mats_d, g->count, g->max_elems, g->stream)));
+  HIP_TRY(ent::launch_zero(g->tail_d, sizeof(int32_t), g->stream));
+  HIP_TRY(ent::launch_batch_check<T>(g->mats_d, g->count, g->max_n, g->tail_d, g->stream));
+  int32_t tail = 0;
+  HIP_TRY(hipMemcpyAsync(&tail, g->tail_d, sizeof(tail), hipMemcpyDeviceToHost, g->stream));
+  HIP_TRY(hipStreamSynchronize(g->stream));
+  *differs = tail != 0;
+  return ENT_OK;
+}
+
+// Raised with every change of the step kernels or of the schedule that makes an
+// earlier timing say nothing (a saved file outlives the library).
+constexpr int kTuneGeneration = 2;
+
+// What the best choice depends on: a batch with a matrix unequal to its transpose
+// runs twice the steps of one without.
+std::string batch_tune_key(const ent_graph_s *g, bool differs) {
   int64_t sum2 = 0;
   for (auto &M : g->mats) sum2 += M.n * M.n;
   int bucket = 0;
   while ((int64_t(1) << (bucket + 1)) <= sum2) ++bucket;
   char buf[256];
-  std::snprintf(buf, sizeof(buf), "gfx950|%s|batch|count=%d|log2sum_n2=%d|s=%d|maxn=%lld|m=%d|%s",
-                g->bf16 ? "bf16x3" : (g->comp_f64 ? "f64" : "f32"), g->count, bucket, g->s,
-                (long long)g->max_n, g->m, (g->o.flags & ENT_FLAG_BATCH_STEPWISE) ? "stepwise" : "any");
+  std::snprintf(buf, sizeof(buf), "gfx950|%d|%s|batch|count=%d|log2sum_n2=%d|s=%d|maxn=%lld|%s|m=%d|%s|%s",
+                kTuneGeneration, g->bf16 ? "bf16x3" : (g->comp_f64 ? "f64" : "f32"), g->count, bucket, g->s,
+                (long long)g->max_n, g->method == ENT_CHEBYSHEV ? "chebyshev" : "taylor", g->m,
+                differs ? "mixed" : "symmetric", (g->o.flags & ENT_FLAG_BATCH_STEPWISE) ? "stepwise" : "any");
   return buf;
 }
 
@@ -2766,15 +2792,24 @@ ent_status batch_create(const ent_matrix *Rs, int32_t count, int32_t method, int
   // persistent schedule with a 1 GB window
   if (const char *env = std::getenv("ENT_SCHED_SPIN_LIMIT")) g->spin_limit = std::atoi(env);
   const bool stepwise = (op.o.flags & ENT_FLAG_BATCH_STEPWISE) != 0;
-  const std::string key = batch_tune_key(g);
+  const bool tune = (op.o.flags & ENT_FLAG_AUTOTUNE) != 0;
+  std::string key;  // made, at the cost of a pass over R, only where an entry may be
   int choice = -1;  // wr | (window in MB) << 2
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     tune_load_locked();
+    if (!tune && g_tune.empty()) key = "none";
+  }
+  if (key.empty()) {
+    bool differs = false;
+    rc = (g->bf16 ? g->src_f64 : g->comp_f64) ? batch_differs<double>(g, &differs) : batch_differs<float>(g, &differs);
+    if (rc != ENT_OK) return fail_free(rc);
+    key = batch_tune_key(g, differs);
+    std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find(key);
     if (it != g_tune.end()) choice = it->second;
   }
-  if (choice < 0 && (op.o.flags & ENT_FLAG_AUTOTUNE)) {
+  if (choice < 0 && tune) {
     rc = batch_autotune(g, stepwise);
     if (rc != ENT_OK) return fail_free(rc);
     choice = g->wr | (int)((g->window >> 20) << 2);

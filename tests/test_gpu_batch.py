@@ -179,3 +179,32 @@ def test_persistent_wait_bound_reports_failure(monkeypatch):
     g = ent.Graph([R], "chebyshev", 12, 64, 1, precision="f32")
     assert np.isfinite(g.launch()[0].entropy)
     g.destroy()
+
+
+def test_autotune_choices_are_kept_apart(tmp_path, monkeypatch):
+    """The step shape and schedule are timed for what runs: each method, and both
+    kinds of batch (one matrix unequal to its transpose doubles the steps)."""
+    import json
+
+    path = tmp_path / "tune.json"
+    monkeypatch.setenv("ENT_AUTOTUNE_CACHE", str(path))
+
+    def keys():
+        return set(json.loads(path.read_text()))
+
+    mats = [W.dense_density(W.spectrum_exp(n, n / 5.0), 31 + n) for n in (96, 130, 150)]
+    mats = [0.5 * (R + R.T) for R in mats]
+    seen = []
+    for changed in (False, True):
+        if changed:
+            mats[1][0, 5] += 1e-3
+        dev = [torch.from_numpy(R).to(DEV) for R in mats]
+        for method in ("chebyshev", "taylor"):
+            for again in (0, 1):
+                g = ent.Graph(dev, method, 7, 16, 1, precision="f64",
+                              flags=ent.FLAG_AUTOTUNE | ent.FLAG_SKIP_TRACE_CHECK)
+                g.launch()
+                g.destroy()
+                seen.append(keys())
+    new = [len(b - a) for a, b in zip(seen, seen[1:])]
+    assert new == [0, 1, 0, 1, 0, 1, 0], new
