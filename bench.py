@@ -73,6 +73,8 @@ KERNEL_SOURCES = {
     "batch_bf16x3_persistent_kernel": "kernels_bf16.hip",
     "dense_step_kernel": "kernels_dense.hip",
     "dense_step_split_kernel": "kernels_dense.hip",
+    "dense_direct_kernel": "kernels_dense.hip",
+    "dense_resident_kernel": "kernels_dense.hip",
     "batch_dense_step_kernel": "kernels_dense.hip",
     "batch_dense_persistent_kernel": "kernels_dense.hip",
     "csr_step_kernel": "kernels_csr.hip",
@@ -230,6 +232,47 @@ def band_step_bytes(n, hp, s, m, vbytes, method):
         writes = method == "chebyshev" or k < steps - 1
         tot += slabs + signs + blk * (reads_vk + reads_vm1 + writes)
     return tot, steps
+
+
+def sparse_model(n, nnz, hp, s, m, vbytes, method, fused):
+    """(kernel, algorithmic HBM bytes of its launches, launches) of an estimate
+    on a symmetric CSR R: two moments per product (a multi-step tridiagonal
+    launch counts moments), and the launch with the last product stores no block
+    (a Taylor recurrence's last step never does)."""
+    products, mr = products_run(m, method)
+    blk = n * s * vbytes
+    unstored = 1 if method == "chebyshev" else 0  # of a last product alone
+    if hp == 1 and fused >= 2:
+        # tridiagonal input, several steps per launch
+        tot, steps = tri_fused_bytes(n, s, mr, vbytes, method, (fused + 1) // 2)
+        return "tri_fused_kernel", tot - (unstored + 1) * blk, steps
+    if hp == 1:
+        # tridiagonal input: the three-row stencil kernel
+        tot, steps = tri_step_bytes(n, s, mr, vbytes, method)
+        return "tri_step_kernel", tot - unstored * blk, steps
+    if hp > 0 and fused == 2:
+        # banded input, two steps per launch (a last product alone is not counted)
+        tot, steps = band_pair_bytes(n, hp, s, mr, vbytes, method)
+        return "band_pair_kernel", tot - (0 if products % 2 else (unstored + 1) * blk), steps
+    if hp > 0:
+        # banded input: the step ran on the 16-row slabs
+        tot, steps = band_step_bytes(n, hp, s, mr, vbytes, method)
+        return "band_step_kernel", tot - unstored * blk, steps
+    tot, steps = csr_step_bytes(n, nnz, s, mr, vbytes, method)
+    return "csr_step_kernel", tot - unstored * blk, steps
+
+
+def dense_kernel(n, s, precision, split):
+    """Name of the kernel that runs an estimate's dense products (the library's
+    rules: R in registers, short workgroups for small problems, tiles)."""
+    if precision == "bf16x3":
+        return "bf16x3_gemm_kernel"
+    if n <= 192:
+        return "dense_resident_kernel"
+    rows, probes = (n + 63) // 64 * 4, (s + 15) // 16
+    if n * n * 16 * probes <= 4.2e8 and any(rows * -(-probes // ns) <= 256 for ns in (1, 2, 4)):
+        return "dense_direct_kernel"
+    return "dense_step_split_kernel" if split else "dense_step_kernel"
 
 
 def bench_batch(args, cfg):
@@ -487,7 +530,7 @@ def bench_learned(args, cfg):
     avg_step_ms = float(np.mean([x["steps_ms"] / x["step_launches"] for x in tms]))
     split = int(tms[-1]["epilogue_launches"]) > 0
     avg_epi_ms = float(np.mean([x["epilogue_ms"] / max(x["epilogue_launches"], 1) for x in tms]))
-    step_kernel = "dense_step_split_kernel" if split else "dense_step_kernel"
+    step_kernel = dense_kernel(n, s, precision, split)
     flop = 2.0 * n * n * s
     achieved = flop / (avg_step_ms * 1e-3) / 1e12
     peak = MFMA_PEAK_TFLOPS[precision]
@@ -823,8 +866,7 @@ def bench_single(args, cfg):
         # FP32/FP64: the split-K form runs when the tile grid is small (its
         # product kernel, with the split reduction in a separate epilogue)
         split = precision != "bf16x3" and int(last_t["epilogue_launches"]) > 0
-        kernel = ("bf16x3_gemm_kernel" if precision == "bf16x3" else
-                  ("dense_step_split_kernel" if split else "dense_step_kernel"))
+        kernel = dense_kernel(2 * n if herm else n, s, precision, split)
         # a complex n x n by n x s product is 8 n^2 s real flops (the real 2n x 2n form)
         flop = (8.0 if herm else 2.0) * n * n * s
         achieved = flop / (avg_step_ms * 1e-3) / 1e12
@@ -841,34 +883,7 @@ def bench_single(args, cfg):
         nnz = int(Rd[0][-1]) if host_R is None else int(host_R[0][-1])
         vb = 8 if precision == "f64" else 4
         hp = int(last_t["csr_band"])
-        # these matrices are symmetric: two moments per product (a multi-step
-        # tridiagonal launch counts moments), and the last one stores no block
-        _, mr = products_run(m, cfg["method"])
-        blk = n * s * vb
-        if hp == 1 and int(last_t["steps_fused"]) >= 2:
-            # tridiagonal input, several steps per launch
-            kernel = "tri_fused_kernel"
-            nf = (int(last_t["steps_fused"]) + 1) // 2
-            tot_bytes, steps = tri_fused_bytes(n, s, mr, vb, cfg["method"], nf)
-            tot_bytes -= (2 if cfg["method"] == "chebyshev" else 1) * blk
-        elif hp == 1:
-            # tridiagonal input: the three-row stencil kernel
-            kernel = "tri_step_kernel"
-            tot_bytes, steps = tri_step_bytes(n, s, mr, vb, cfg["method"])
-            tot_bytes -= blk if cfg["method"] == "chebyshev" else 0
-        elif hp > 0 and int(last_t["steps_fused"]) == 2:
-            # banded input, two steps per launch
-            kernel = "band_pair_kernel"
-            tot_bytes, steps = band_pair_bytes(n, hp, s, mr, vb, cfg["method"])
-        elif hp > 0:
-            # banded input: the step ran on the 16-row slabs
-            kernel = "band_step_kernel"
-            tot_bytes, steps = band_step_bytes(n, hp, s, mr, vb, cfg["method"])
-            tot_bytes -= blk if cfg["method"] == "chebyshev" else 0
-        else:
-            kernel = "csr_step_kernel"
-            tot_bytes, steps = csr_step_bytes(n, nnz, s, mr, vb, cfg["method"])
-            tot_bytes -= blk if cfg["method"] == "chebyshev" else 0
+        kernel, tot_bytes, steps = sparse_model(n, nnz, hp, s, m, vb, cfg["method"], int(last_t["steps_fused"]))
         per_launch = tot_bytes / steps
         achieved = per_launch / (avg_step_ms * 1e-3) / 1e9
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -887,8 +902,7 @@ def bench_single(args, cfg):
         ms_p, _ = time_estimates(ent, Rd, cfg, pseed, kwp, args.steps, args.warmup)
         st_ms, epi_ms, ph, _ = kernel_timing(ent, Rd, cfg, pseed, kwp, 3)
         r_p, per_p, _ = ent.entropy_estimate_detail(Rd, cfg["method"], m, s, pseed, **kwp)
-        k_p = ("bf16x3_gemm_kernel" if prec == "bf16x3" else
-               ("dense_step_split_kernel" if epi_ms > 0 else "dense_step_kernel"))
+        k_p = dense_kernel(2 * n if herm else n, s, prec, epi_ms > 0)
         flop = (8.0 if herm else 2.0) * n * n * s
         ach = flop / (st_ms * 1e-3) / 1e12
         forms[prec] = {"value": 1e3 / ms_p, "unit": "estimates/s", "ms_per_step": ms_p,
