@@ -1161,15 +1161,65 @@ template hipError_t launch_realify<float, float>(const float *, int64_t, int64_t
 // ---------------------------------------------------------------------------
 // Reductions
 // ---------------------------------------------------------------------------
+// A sum with the rounding errors of its additions beside it (Knuth's two-sum).
+// h_j = -sum alpha_k d_kj cancels to a few per cent of its terms, and a moment from
+// dots in pairs is the difference of two sums, one of them doubled: with plain
+// sums an FP64 estimate at n = 512, m = 30 (p_i ~ 1/i) came out twice as far from
+// its exact value as with one dot per moment (4.0e-15 and 1.7e-15 relative), with
+// these as far (3.0e-15 and 3.1e-15 on other inputs), and at n = 8192 half as far
+// (2.0e-15 and 4.2e-15).  Bound by latency either way: 31 slots of 1024 partials
+// 15 -> 26 us (two slots' loads for one), 51 of 512 13.5 -> 18.7, 31 of 32 2.8 ->
+// 3.9; a batch's, eight tiles in flight, 16.6 -> 11.2.
+struct Sum2 {
+  double s = 0.0, c = 0.0;
+  __device__ __forceinline__ void add(double x) {
+#pragma clang fp contract(off)
+    const double t = s + x, z = t - s;
+    c += (s - (t - z)) + (x - z);
+    s = t;
+  }
+  __device__ __forceinline__ void add_product(double a, double b) {
+#pragma clang fp contract(off)
+    const double p = a * b;
+    c += __builtin_fma(a, b, -p);
+    add(p);
+  }
+};
+
+// Tiles [i0, i1) of slot k's sum for probe j; dots in pairs: d_k = 2 (sum of slot
+// k) - d_{k mod 2} for k >= 2, both sums term by term.
+__device__ __forceinline__ Sum2 moment_terms(const double *__restrict__ part, int32_t k, bool pair, int32_t ntile,
+                                             int64_t ldv, int64_t j, int32_t i0, int32_t i1) {
+  const double *p = part + (int64_t)k * ntile * ldv + j;
+  Sum2 acc;
+  const bool half = pair && k >= 2;
+  const double *g = part + (int64_t)(half ? k & 1 : k) * ntile * ldv + j;
+  const double f = half ? 2.0 : 1.0;
+  constexpr int U = 8;  // tiles in flight
+  for (int32_t i = i0; i < i1; i += U) {
+    double a[U], b[U];
+#pragma unroll
+    for (int e = 0; e < U; ++e) {
+      const int64_t o = (int64_t)(i + e < i1 ? i + e : i0) * ldv;
+      a[e] = i + e < i1 ? p[o] : 0.0;
+      b[e] = half && i + e < i1 ? g[o] : 0.0;
+    }
+#pragma unroll
+    for (int e = 0; e < U; ++e) {
+      acc.add(f * a[e]);
+      acc.add(-b[e]);
+    }
+  }
+  return acc;
+}
+
 __device__ __forceinline__ void reduce_moments_body(const double *__restrict__ part, int32_t nslot,
-                                                    int32_t ntile, int64_t ldv, int32_t s,
+                                                    int32_t ntile, int64_t ldv, int32_t s, bool pair,
                                                     double *__restrict__ d, int64_t t) {
   if (t >= (int64_t)nslot * s) return;
   const int32_t k = (int32_t)(t / s), j = (int32_t)(t % s);
-  const double *p = part + (int64_t)k * ntile * ldv + j;
-  double acc = 0.0;
-  for (int32_t i = 0; i < ntile; ++i) acc += p[(int64_t)i * ldv];
-  d[(int64_t)k * s + j] = acc;
+  const Sum2 v = moment_terms(part, k, pair, ntile, ldv, j, 0, ntile);
+  d[(int64_t)k * s + j] = v.s + v.c;
 }
 
 // One estimate's moments: workgroup = (slot, 64 probes); wave w sums the
@@ -1180,34 +1230,33 @@ __device__ __forceinline__ void reduce_moments_body(const double *__restrict__ p
 // slots x 256 probes: 57 -> 13 us).
 constexpr int kReduceWaves = 16;
 __global__ __launch_bounds__(64 * kReduceWaves) void reduce_moments_kernel(const double *__restrict__ part, int32_t nslot,
-                                                             int32_t ntile, int64_t ldv, int32_t s,
+                                                             int32_t ntile, int64_t ldv, int32_t s, bool pair,
                                                              double *__restrict__ d) {
-  __shared__ double q[kReduceWaves][64];
+  __shared__ double q[2][kReduceWaves][64];
   const int k = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int j = blockIdx.y * 64 + lane;
   const int32_t per = (ntile + kReduceWaves - 1) / kReduceWaves;
   const int32_t i0 = w * per, i1 = i0 + per < ntile ? i0 + per : ntile;
-  double acc = 0.0;
-  if (j < s) {
-    const double *p = part + (int64_t)k * ntile * ldv + j;
-#pragma unroll 8
-    for (int32_t i = i0; i < i1; ++i) acc += p[(int64_t)i * ldv];
-  }
-  q[w][lane] = acc;
+  Sum2 acc;
+  if (j < s) acc = moment_terms(part, k, pair, ntile, ldv, j, i0, i1);
+  q[0][w][lane] = acc.s;
+  q[1][w][lane] = acc.c;
   __syncthreads();
   if (w == 0 && j < s) {
-    double sum = q[0][lane];
 #pragma unroll
-    for (int i = 1; i < kReduceWaves; ++i) sum += q[i][lane];
-    d[(int64_t)k * s + j] = sum;
+    for (int i = 1; i < kReduceWaves; ++i) {
+      acc.add(q[0][i][lane]);
+      acc.c += q[1][i][lane];
+    }
+    d[(int64_t)k * s + j] = acc.s + acc.c;
   }
 }
 
 hipError_t launch_reduce_moments(const double *part, int32_t nslot, int32_t ntile, int64_t ldv,
-                                 int32_t s, double *d, hipStream_t st) {
+                                 int32_t s, bool pair, double *d, hipStream_t st) {
   if (nslot < 1 || s < 1) return hipSuccess;
   reduce_moments_kernel<<<dim3((unsigned)nslot, (unsigned)((s + 63) / 64)), 64 * kReduceWaves, 0, st>>>(
-      part, nslot, ntile, ldv, s, d);
+      part, nslot, ntile, ldv, s, pair, d);
   return hipGetLastError();
 }
 
@@ -1221,10 +1270,10 @@ hipError_t launch_reduce_moments(const double *part, int32_t nslot, int32_t ntil
 // 12 -> 6 us).
 constexpr int kFinalThreads = 1024;
 
-__device__ __forceinline__ void final_body(double *__restrict__ d, double *__restrict__ scal,
+__device__ __forceinline__ void final_body(const double *__restrict__ d, double *__restrict__ scal,
                                            int32_t method, int32_t m, int32_t s,
                                            double *__restrict__ h) {
-  __shared__ double red[kFinalThreads / 64], sums[kFinalThreads];
+  __shared__ double red[kFinalThreads / 64], sums[2][kFinalThreads];
   __shared__ double smean;
   const int tid = threadIdx.x, nwv = kFinalThreads / 64;
   int sp = 64;  // probes per pass
@@ -1236,7 +1285,7 @@ __device__ __forceinline__ void final_body(double *__restrict__ d, double *__res
   double acc = 0.0;
   for (int jb = 0; jb < s; jb += sp) {
     const int j = jb + jl;
-    double v = 0.0;
+    Sum2 v;
     if (j < s) {
       if (method == FINAL_CLENSHAW) {
         // Algorithm 5: g^T f_m g = (alpha_0 g^T g + g^T y_0 - g^T y_2) / 2, with
@@ -1244,40 +1293,28 @@ __device__ __forceinline__ void final_body(double *__restrict__ d, double *__res
         if (q == 0) {
           const double gg = d[(int64_t)(m + 1) * s + j];
           const double y2 = m >= 2 ? d[(int64_t)2 * s + j] : 0.0;
-          v = -0.5 * (alpha[0] * gg + d[j] - y2);
-        }
-      } else if (method == FINAL_CHEB_PAIRS) {
-        // d_w = 2 (half sum of slot w) - d_{w mod 2}, written back
-        const double d0 = d[j], d1 = d[(int64_t)s + j];
-        if (q == 0) v = -(alpha[0] * d0 + alpha[1] * d1);
-        for (int k = 2 + q; k <= m; k += 4 * tp) {
-          double r[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) r[e] = k + e * tp <= m ? d[(int64_t)(k + e * tp) * s + j] : 0.0;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int w = k + e * tp;
-            if (w > m) break;
-            const double dw = 2.0 * r[e] - ((w & 1) ? d1 : d0);
-            d[(int64_t)w * s + j] = dw;
-            v -= alpha[w] * dw;
-          }
+          v.s = -0.5 * (alpha[0] * gg + d[j] - y2);
         }
       } else if (method == 1) {
 #pragma unroll 4
-        for (int k = q; k <= m; k += tp) v -= alpha[k] * d[(int64_t)k * s + j];
+        for (int k = q; k <= m; k += tp) v.add_product(-alpha[k], d[(int64_t)k * s + j]);
       } else {
 #pragma unroll 4
-        for (int k = 1 + q; k <= m; k += tp) v += d[(int64_t)k * s + j] / (double)k;
+        for (int k = 1 + q; k <= m; k += tp) v.add(d[(int64_t)k * s + j] / (double)k);
       }
     }
-    sums[tid] = v;
+    sums[0][tid] = v.s;
+    sums[1][tid] = v.c;
     __syncthreads();
     if (q == 0 && j < s) {
-      for (int i = 1; i < tp; ++i) v += sums[i * sp + jl];
-      if (method == 0) v = log(1.0 / u) + u * v;
-      h[j] = v;
-      acc += v;
+      for (int i = 1; i < tp; ++i) {
+        v.add(sums[0][i * sp + jl]);
+        v.c += sums[1][i * sp + jl];
+      }
+      double hj = v.s + v.c;
+      if (method == 0) hj = log(1.0 / u) + u * hj;
+      h[j] = hj;
+      acc += hj;
     }
     __syncthreads();
   }
@@ -1307,7 +1344,7 @@ __device__ __forceinline__ void final_body(double *__restrict__ d, double *__res
 
 // The results go to pinned host memory with the last stores of the estimate
 // (three copies behind it cost 10 to 20 us together).
-__global__ __launch_bounds__(kFinalThreads) void final_kernel(double *__restrict__ d, double *__restrict__ scal, int32_t method,
+__global__ __launch_bounds__(kFinalThreads) void final_kernel(const double *__restrict__ d, double *__restrict__ scal, int32_t method,
                              int32_t m, int32_t s, double *__restrict__ h, double *__restrict__ host,
                              int32_t host_moments) {
   final_body(d, scal, method, m, s, h);
@@ -1324,7 +1361,7 @@ __global__ __launch_bounds__(kFinalThreads) void final_kernel(double *__restrict
   __threadfence_system();
 }
 
-hipError_t launch_final(double *d, double *scal, int32_t method, int32_t m, int32_t s,
+hipError_t launch_final(const double *d, double *scal, int32_t method, int32_t m, int32_t s,
                         double *h, hipStream_t st, double *host, bool host_moments) {
   final_kernel<<<1, kFinalThreads, 0, st>>>(d, scal, method, m, s, h, host, host_moments);
   return hipGetLastError();
@@ -1599,29 +1636,30 @@ hipError_t launch_batch_setup(const BatchMat *mats, int32_t count, int32_t metho
   return hipGetLastError();
 }
 
-__global__ void batch_reduce_kernel(const BatchMat *__restrict__ mats, const double *part,
+__global__ void batch_reduce_kernel(const BatchMat *__restrict__ mats, const double *part, int32_t method,
                                     int32_t nslot, int64_t ldv, int32_t s, double *d) {
   const BatchMat &M = mats[blockIdx.y];
+  const bool pair = method == 1 && batch_pairs(M);
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < (int64_t)nslot * s;
        t += (int64_t)gridDim.x * blockDim.x)
-    reduce_moments_body(part + M.poff, nslot, M.ntile, ldv, s, d + M.doff, t);
+    reduce_moments_body(part + M.poff, nslot, M.ntile, ldv, s, pair, d + M.doff, t);
 }
 
-hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double *part,
+hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double *part, int32_t method,
                                int32_t nslot, int64_t ldv, int32_t s, double *d, hipStream_t st) {
   const int64_t per = ((int64_t)nslot * s + 255) / 256;
   dim3 grid((unsigned)(per < 64 ? per : 64), (unsigned)count);
-  batch_reduce_kernel<<<grid, 256, 0, st>>>(mats, part, nslot, ldv, s, d);
+  batch_reduce_kernel<<<grid, 256, 0, st>>>(mats, part, method, nslot, ldv, s, d);
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(kFinalThreads) void batch_final_kernel(const BatchMat *__restrict__ mats, double *d,
+__global__ __launch_bounds__(kFinalThreads) void batch_final_kernel(const BatchMat *__restrict__ mats, const double *d,
                                    int32_t method, int32_t m, int32_t s, double *h) {
   const BatchMat &M = mats[blockIdx.x];
-  final_body(d + M.doff, M.scal, method == 1 && batch_pairs(M) ? FINAL_CHEB_PAIRS : method, m, s, h + M.hoff);
+  final_body(d + M.doff, M.scal, method, m, s, h + M.hoff);
 }
 
-hipError_t launch_batch_final(const BatchMat *mats, int32_t count, double *d, int32_t method,
+hipError_t launch_batch_final(const BatchMat *mats, int32_t count, const double *d, int32_t method,
                               int32_t m, int32_t s, double *h, hipStream_t st) {
   batch_final_kernel<<<(unsigned)count, kFinalThreads, 0, st>>>(mats, d, method, m, s, h);
   return hipGetLastError();

@@ -319,3 +319,31 @@ def test_hub_row_costs_no_more_than_it_saves():
     pairs, clenshaw = best(0), best(ent.FLAG_CLENSHAW)
     print(f"[hub] pairs {1e3 * pairs:.1f} ms, Clenshaw {1e3 * clenshaw:.1f} ms", flush=True)
     assert pairs < clenshaw
+
+
+@pytest.mark.parametrize("n,s", [(2048, 256), (1024, 64), (192, 64)])
+@pytest.mark.parametrize("changed", [False, True])
+def test_moment_sums_in_fp64(orc, n, s, changed):
+    """Moments of a diagonal R whose Chebyshev vectors are exact, so that sums alone
+    round: R in {0, 1/4, 1/2}, u = 1/2, T_w in {-1, 0, 1}, V_k = T_k g.  A partial sum
+    over 16 or 64 rows carries a few half-ulps of its size, independent of each
+    other: at most 0.1 n eps over the probes, root mean square, with the doubling of
+    a pair; the additions of the partials one by one would carry 0.7 n eps (1.4)."""
+    m, seed = 8, 21
+    x = np.array([-1.0, 0.0, 1.0])[np.arange(n) % 3]
+    R = np.diag((x + 1.0) / 4.0)
+    if changed:
+        R[0, n - 1] = 2.0 ** -60  # one moment per product, the same vectors to 1e-18
+    G = orc.probe_block(seed, 1, 0, n, s)
+    _, _, mom = ent.entropy_estimate_detail(torch.from_numpy(R).to(DEV), "chebyshev", m, s, seed, precision="f64",
+                                            u_fixed=0.5, probe_dist="gaussian", flags=ent.FLAG_SKIP_TRACE_CHECK)
+    g2 = G.astype(np.longdouble) ** 2
+    prev, cur = np.ones(n), x
+    for w in range(m + 1):
+        t = prev if w == 0 else cur
+        want = (t[:, None] * g2).sum(axis=0)
+        rms = float(np.sqrt(np.mean((mom[w] - want) ** 2)))
+        print(f"[sums n={n} w={w}] {rms / (n * 2.0 ** -52):.3f} n eps", flush=True)
+        assert rms <= 0.4 * n * 2.0 ** -52
+        if w > 0:
+            prev, cur = cur, 2.0 * x * cur - prev
