@@ -1284,8 +1284,10 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
     pe.logical_steps = nsteps;
   }
   int32_t k_begin = (band_pairs || tri_fused || resident) ? nsteps : 0;
-  const int32_t final_code = clenshaw ? ent::FINAL_CLENSHAW : method;
+  constexpr bool exact = sizeof(T) == 8;
   const bool halves = pairs && method == ENT_CHEBYSHEV;
+  const int32_t final_code = clenshaw ? ent::FINAL_CLENSHAW
+                             : halves && !exact ? ent::FINAL_CHEB_PAIRS : method;
   int32_t m_run = stg ? stg->deg[0] : m;  // degree of the estimate
   Results res;
   int32_t stage = 0;
@@ -1343,9 +1345,9 @@ ent_status run_poly(const ent_matrix *R, int32_t method, int32_t m, int32_t s, u
       if (k == k_end - 1) pe.steps_end = e;
       end_step(e);
     }
-    HIP_TRY(ent::launch_reduce_moments(part, stg ? m_run + 1 : nslot, npart, ldv, s, halves, d, st));
+    HIP_TRY(ent::launch_reduce_moments(part, stg ? m_run + 1 : nslot, npart, ldv, s, exact, halves, d, st));
     double *hb = ws.result_block(ent::S_ALPHA + (size_t)m_run + 1 + s + (size_t)(m_run + 1) * s);
-    HIP_TRY(ent::launch_final(d, scal, final_code, m_run, s, h, st, hb, moments || stg));
+    HIP_TRY(ent::launch_final(d, scal, exact, final_code, m_run, s, h, st, hb, moments || stg));
     res.host = hb;
     if (!stg) break;
     // the check on the host; on rejection the recurrence continues from V_k, V_{k-1}
@@ -1567,10 +1569,13 @@ ent_status run_bf16x3(const ent_matrix *R, int32_t method, int32_t m, int32_t s,
     Vk = Vout;
   }
   pe.steps_end = pe.mark();
-  HIP_TRY(ent::launch_reduce_moments(part, nslot, nblk, ldv, s, pairs && method == ENT_CHEBYSHEV, d, st));
+  HIP_TRY(ent::launch_reduce_moments(part, nslot, nblk, ldv, s, false, false, d, st));
   Results res;
   double *hb = ws.result_block(ent::S_ALPHA + (size_t)m + 1 + s + (size_t)(m + 1) * s);
-  HIP_TRY(ent::launch_final(d, scal, clenshaw ? ent::FINAL_CLENSHAW : method, m, s, h, st, hb, moments != nullptr));
+  HIP_TRY(ent::launch_final(d, scal, false,
+                            clenshaw ? ent::FINAL_CLENSHAW
+                            : pairs && method == ENT_CHEBYSHEV ? ent::FINAL_CHEB_PAIRS : method,
+                            m, s, h, st, hb, moments != nullptr));
   res.host = hb;
   double *alpha_out = hook ? hook->alpha_host : nullptr;
   rc = res.fetch(scal, h, d, m, s, per_probe, moments, alpha_out, st);
@@ -2278,8 +2283,8 @@ ent_status enqueue_batch(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
                                   o.cutoff, st, (o.flags & ENT_FLAG_NORMALIZE) ? 1.0 : 0.0));
   ent_status rc = batch_enqueue_steps(g, st, pe);
   if (rc != ENT_OK) return rc;
-  HIP_TRY(ent::launch_batch_reduce(g->mats_d, count, g->part, g->method, g->nslot, g->ldv, g->s, g->d, st));
-  HIP_TRY(ent::launch_batch_final(g->mats_d, count, g->d, g->method, g->m, g->s, g->h, st));
+  HIP_TRY(ent::launch_batch_reduce(g->mats_d, count, g->part, g->comp_f64, g->method, g->nslot, g->ldv, g->s, g->d, st));
+  HIP_TRY(ent::launch_batch_final(g->mats_d, count, g->d, g->comp_f64, g->method, g->m, g->s, g->h, st));
   return ENT_OK;
 }
 
@@ -2334,8 +2339,8 @@ ent_status enqueue_batch_bf16(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
                                   o.cutoff, st, (o.flags & ENT_FLAG_NORMALIZE) ? 1.0 : 0.0));
   ent_status rc = batch_enqueue_steps(g, st, pe);
   if (rc != ENT_OK) return rc;
-  HIP_TRY(ent::launch_batch_reduce(g->mats_d, count, g->part, g->method, g->nslot, g->ldv, g->s, g->d, st));
-  HIP_TRY(ent::launch_batch_final(g->mats_d, count, g->d, g->method, g->m, g->s, g->h, st));
+  HIP_TRY(ent::launch_batch_reduce(g->mats_d, count, g->part, g->comp_f64, g->method, g->nslot, g->ldv, g->s, g->d, st));
+  HIP_TRY(ent::launch_batch_final(g->mats_d, count, g->d, g->comp_f64, g->method, g->m, g->s, g->h, st));
   return ENT_OK;
 }
 

@@ -31,6 +31,10 @@ enum ScalarSlot {
 
 // launch_final's method code for the Clenshaw schedule (0 Taylor, 1 Chebyshev).
 constexpr int32_t FINAL_CLENSHAW = 2;
+// launch_final's method code for Chebyshev dots taken in pairs (below) that were
+// reduced with exact = false: slot w >= 2 of d holds half of d_w + d_{w mod 2} and
+// is replaced by d_w.
+constexpr int32_t FINAL_CHEB_PAIRS = 3;
 
 // Dots in pairs.  For a symmetric R every step's vectors give two moments of
 // the polynomial, so m of them take ceil(m / 2) products instead of m:
@@ -628,9 +632,9 @@ hipError_t launch_batch_power_rq(const BatchMat *mats, int32_t count, const doub
 hipError_t launch_batch_setup(const BatchMat *mats, int32_t count, int32_t method, int32_t m,
                               double c, double u_fixed, double lo, hipStream_t st,
                               double norm_div = 0.0);
-hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double *part, int32_t method,
+hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double *part, bool exact, int32_t method,
                                int32_t nslot, int64_t ldv, int32_t s, double *d, hipStream_t st);
-hipError_t launch_batch_final(const BatchMat *mats, int32_t count, const double *d, int32_t method,
+hipError_t launch_batch_final(const BatchMat *mats, int32_t count, double *d, bool exact, int32_t method,
                               int32_t m, int32_t s, double *h, hipStream_t st);
 
 // ---- random projection (Algorithm 3) -----------------------------------------
@@ -670,13 +674,14 @@ hipError_t launch_selector_features(const double *scal, const double *d, int32_t
 
 // ---- reductions ---------------------------------------------------------------
 // d[k][j] = sum_t part[k][t][j] (fixed order), k < nslot, j < s.
-// pair (Chebyshev dots in pairs): slot w >= 2 holds half of d_w + d_{w mod 2}.
+// exact (FP64 estimates): by two-sums, and with pair (Chebyshev dots in pairs, whose
+// slot w >= 2 holds half of d_w + d_{w mod 2}) the moments themselves.
 hipError_t launch_reduce_moments(const double *part, int32_t nslot, int32_t ntile, int64_t ldv,
-                                 int32_t s, bool pair, double *d, hipStream_t st);
+                                 int32_t s, bool exact, bool pair, double *d, hipStream_t st);
 // Per-probe values and the estimate (Algorithms 1-2 output line).
 // host (pinned memory the kernel stores to; null: none) receives scal[0 ..
 // S_ALPHA + m], then h (s values), then with host_moments d's (m + 1) s.
-hipError_t launch_final(const double *d, double *scal, int32_t method, int32_t m, int32_t s,
+hipError_t launch_final(double *d, double *scal, bool exact, int32_t method, int32_t m, int32_t s,
                         double *h, hipStream_t st, double *host = nullptr, bool host_moments = false);
 
 // ---- fixed scratch of the no-allocation entry point ---------------------------

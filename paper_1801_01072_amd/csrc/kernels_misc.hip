@@ -1161,41 +1161,43 @@ template hipError_t launch_realify<float, float>(const float *, int64_t, int64_t
 // ---------------------------------------------------------------------------
 // Reductions
 // ---------------------------------------------------------------------------
-// A sum with the rounding errors of its additions beside it (Knuth's two-sum).
+// A sum, X: with the rounding errors of its additions beside it (Knuth's two-sum).
 // h_j = -sum alpha_k d_kj cancels to a few per cent of its terms, and a moment from
 // dots in pairs is the difference of two sums, one of them doubled: with plain
 // sums an FP64 estimate at n = 512, m = 30 (p_i ~ 1/i) came out twice as far from
 // its exact value as with one dot per moment (4.0e-15 and 1.7e-15 relative), with
 // these as far (3.0e-15 and 3.1e-15 on other inputs), and at n = 8192 half as far
-// (2.0e-15 and 4.2e-15).  Bound by latency either way: 31 slots of 1024 partials
-// 15 -> 26 us (two slots' loads for one), 51 of 512 13.5 -> 18.7, 31 of 32 2.8 ->
-// 3.9; a batch's, eight tiles in flight, 16.6 -> 11.2.
+// (2.0e-15 and 4.2e-15).  FP32 and BF16x3 estimates, whose vectors carry the error
+// (their values are the same to the last bit), take plain sums.
+template <bool X>
 struct Sum2 {
   double s = 0.0, c = 0.0;
   __device__ __forceinline__ void add(double x) {
 #pragma clang fp contract(off)
     const double t = s + x, z = t - s;
-    c += (s - (t - z)) + (x - z);
+    if (X) c += (s - (t - z)) + (x - z);
     s = t;
   }
   __device__ __forceinline__ void add_product(double a, double b) {
 #pragma clang fp contract(off)
     const double p = a * b;
-    c += __builtin_fma(a, b, -p);
+    if (X) c += __builtin_fma(a, b, -p);
     add(p);
   }
+  __device__ __forceinline__ double value() const { return X ? s + c : s; }
 };
 
-// Tiles [i0, i1) of slot k's sum for probe j; dots in pairs: d_k = 2 (sum of slot
-// k) - d_{k mod 2} for k >= 2, both sums term by term.
-__device__ __forceinline__ Sum2 moment_terms(const double *__restrict__ part, int32_t k, bool pair, int32_t ntile,
-                                             int64_t ldv, int64_t j, int32_t i0, int32_t i1) {
+// Tiles [i0, i1) of slot k's sum for probe j.  X and pair: d_k = 2 (sum of slot k)
+// - d_{k mod 2} for k >= 2, both sums term by term.
+template <bool X>
+__device__ __forceinline__ Sum2<X> moment_terms(const double *__restrict__ part, int32_t k, bool pair, int32_t ntile,
+                                                int64_t ldv, int64_t j, int32_t i0, int32_t i1) {
   const double *p = part + (int64_t)k * ntile * ldv + j;
-  Sum2 acc;
-  const bool half = pair && k >= 2;
+  const bool half = X && pair && k >= 2;
   const double *g = part + (int64_t)(half ? k & 1 : k) * ntile * ldv + j;
   const double f = half ? 2.0 : 1.0;
   constexpr int U = 8;  // tiles in flight
+  Sum2<X> acc;
   for (int32_t i = i0; i < i1; i += U) {
     double a[U], b[U];
 #pragma unroll
@@ -1206,20 +1208,20 @@ __device__ __forceinline__ Sum2 moment_terms(const double *__restrict__ part, in
     }
 #pragma unroll
     for (int e = 0; e < U; ++e) {
-      acc.add(f * a[e]);
-      acc.add(-b[e]);
+      acc.add(X ? f * a[e] : a[e]);
+      if (X) acc.add(-b[e]);
     }
   }
   return acc;
 }
 
+template <bool X>
 __device__ __forceinline__ void reduce_moments_body(const double *__restrict__ part, int32_t nslot,
                                                     int32_t ntile, int64_t ldv, int32_t s, bool pair,
                                                     double *__restrict__ d, int64_t t) {
   if (t >= (int64_t)nslot * s) return;
   const int32_t k = (int32_t)(t / s), j = (int32_t)(t % s);
-  const Sum2 v = moment_terms(part, k, pair, ntile, ldv, j, 0, ntile);
-  d[(int64_t)k * s + j] = v.s + v.c;
+  d[(int64_t)k * s + j] = moment_terms<X>(part, k, pair, ntile, ldv, j, 0, ntile).value();
 }
 
 // One estimate's moments: workgroup = (slot, 64 probes); wave w sums the
@@ -1227,36 +1229,41 @@ __device__ __forceinline__ void reduce_moments_body(const double *__restrict__ p
 // order (fixed, so repeated runs agree bit for bit).  Bound by latency: the
 // workgroups are few (slots x probes / 64), so each takes 16 waves and eight
 // loads in flight (n = 200000 CSR, 31 slots: 107 -> 14 us; n = 8192 dense, 51
-// slots x 256 probes: 57 -> 13 us).
+// slots x 256 probes: 57 -> 13 us; with two-sums and two slots' loads for one 26
+// and 19).
 constexpr int kReduceWaves = 16;
+template <bool X>
 __global__ __launch_bounds__(64 * kReduceWaves) void reduce_moments_kernel(const double *__restrict__ part, int32_t nslot,
                                                              int32_t ntile, int64_t ldv, int32_t s, bool pair,
                                                              double *__restrict__ d) {
-  __shared__ double q[2][kReduceWaves][64];
+  __shared__ double q[X ? 2 : 1][kReduceWaves][64];
   const int k = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int j = blockIdx.y * 64 + lane;
   const int32_t per = (ntile + kReduceWaves - 1) / kReduceWaves;
   const int32_t i0 = w * per, i1 = i0 + per < ntile ? i0 + per : ntile;
-  Sum2 acc;
-  if (j < s) acc = moment_terms(part, k, pair, ntile, ldv, j, i0, i1);
+  Sum2<X> acc;
+  if (j < s) acc = moment_terms<X>(part, k, pair, ntile, ldv, j, i0, i1);
   q[0][w][lane] = acc.s;
-  q[1][w][lane] = acc.c;
+  if (X) q[X ? 1 : 0][w][lane] = acc.c;
   __syncthreads();
   if (w == 0 && j < s) {
 #pragma unroll
     for (int i = 1; i < kReduceWaves; ++i) {
       acc.add(q[0][i][lane]);
-      acc.c += q[1][i][lane];
+      if (X) acc.c += q[X ? 1 : 0][i][lane];
     }
-    d[(int64_t)k * s + j] = acc.s + acc.c;
+    d[(int64_t)k * s + j] = acc.value();
   }
 }
 
 hipError_t launch_reduce_moments(const double *part, int32_t nslot, int32_t ntile, int64_t ldv,
-                                 int32_t s, bool pair, double *d, hipStream_t st) {
+                                 int32_t s, bool exact, bool pair, double *d, hipStream_t st) {
   if (nslot < 1 || s < 1) return hipSuccess;
-  reduce_moments_kernel<<<dim3((unsigned)nslot, (unsigned)((s + 63) / 64)), 64 * kReduceWaves, 0, st>>>(
-      part, nslot, ntile, ldv, s, pair, d);
+  const dim3 grid((unsigned)nslot, (unsigned)((s + 63) / 64));
+  if (exact)
+    reduce_moments_kernel<true><<<grid, 64 * kReduceWaves, 0, st>>>(part, nslot, ntile, ldv, s, pair, d);
+  else
+    reduce_moments_kernel<false><<<grid, 64 * kReduceWaves, 0, st>>>(part, nslot, ntile, ldv, s, pair, d);
   return hipGetLastError();
 }
 
@@ -1270,10 +1277,11 @@ hipError_t launch_reduce_moments(const double *part, int32_t nslot, int32_t ntil
 // 12 -> 6 us).
 constexpr int kFinalThreads = 1024;
 
-__device__ __forceinline__ void final_body(const double *__restrict__ d, double *__restrict__ scal,
+template <bool X>
+__device__ __forceinline__ void final_body(double *__restrict__ d, double *__restrict__ scal,
                                            int32_t method, int32_t m, int32_t s,
                                            double *__restrict__ h) {
-  __shared__ double red[kFinalThreads / 64], sums[2][kFinalThreads];
+  __shared__ double red[kFinalThreads / 64], sums[X ? 2 : 1][kFinalThreads];
   __shared__ double smean;
   const int tid = threadIdx.x, nwv = kFinalThreads / 64;
   int sp = 64;  // probes per pass
@@ -1285,7 +1293,7 @@ __device__ __forceinline__ void final_body(const double *__restrict__ d, double 
   double acc = 0.0;
   for (int jb = 0; jb < s; jb += sp) {
     const int j = jb + jl;
-    Sum2 v;
+    Sum2<X> v;
     if (j < s) {
       if (method == FINAL_CLENSHAW) {
         // Algorithm 5: g^T f_m g = (alpha_0 g^T g + g^T y_0 - g^T y_2) / 2, with
@@ -1294,6 +1302,23 @@ __device__ __forceinline__ void final_body(const double *__restrict__ d, double 
           const double gg = d[(int64_t)(m + 1) * s + j];
           const double y2 = m >= 2 ? d[(int64_t)2 * s + j] : 0.0;
           v.s = -0.5 * (alpha[0] * gg + d[j] - y2);
+        }
+      } else if (!X && method == FINAL_CHEB_PAIRS) {
+        // d_w = 2 (half sum of slot w) - d_{w mod 2}, written back
+        const double d0 = d[j], d1 = d[(int64_t)s + j];
+        if (q == 0) v.s = -(alpha[0] * d0 + alpha[1] * d1);
+        for (int k = 2 + q; k <= m; k += 4 * tp) {
+          double r[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) r[e] = k + e * tp <= m ? d[(int64_t)(k + e * tp) * s + j] : 0.0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int w = k + e * tp;
+            if (w > m) break;
+            const double dw = 2.0 * r[e] - ((w & 1) ? d1 : d0);
+            d[(int64_t)w * s + j] = dw;
+            v.s -= alpha[w] * dw;
+          }
         }
       } else if (method == 1) {
 #pragma unroll 4
@@ -1304,14 +1329,14 @@ __device__ __forceinline__ void final_body(const double *__restrict__ d, double 
       }
     }
     sums[0][tid] = v.s;
-    sums[1][tid] = v.c;
+    if (X) sums[X ? 1 : 0][tid] = v.c;
     __syncthreads();
     if (q == 0 && j < s) {
       for (int i = 1; i < tp; ++i) {
         v.add(sums[0][i * sp + jl]);
-        v.c += sums[1][i * sp + jl];
+        if (X) v.c += sums[X ? 1 : 0][i * sp + jl];
       }
-      double hj = v.s + v.c;
+      double hj = v.value();
       if (method == 0) hj = log(1.0 / u) + u * hj;
       h[j] = hj;
       acc += hj;
@@ -1344,10 +1369,11 @@ __device__ __forceinline__ void final_body(const double *__restrict__ d, double 
 
 // The results go to pinned host memory with the last stores of the estimate
 // (three copies behind it cost 10 to 20 us together).
-__global__ __launch_bounds__(kFinalThreads) void final_kernel(const double *__restrict__ d, double *__restrict__ scal, int32_t method,
+template <bool X>
+__global__ __launch_bounds__(kFinalThreads) void final_kernel(double *__restrict__ d, double *__restrict__ scal, int32_t method,
                              int32_t m, int32_t s, double *__restrict__ h, double *__restrict__ host,
                              int32_t host_moments) {
-  final_body(d, scal, method, m, s, h);
+  final_body<X>(d, scal, method, m, s, h);
   if (!host) return;
   __syncthreads();  // the block's own stores to scal, h and d
   const int head = S_ALPHA + m + 1;
@@ -1361,9 +1387,12 @@ __global__ __launch_bounds__(kFinalThreads) void final_kernel(const double *__re
   __threadfence_system();
 }
 
-hipError_t launch_final(const double *d, double *scal, int32_t method, int32_t m, int32_t s,
+hipError_t launch_final(double *d, double *scal, bool exact, int32_t method, int32_t m, int32_t s,
                         double *h, hipStream_t st, double *host, bool host_moments) {
-  final_kernel<<<1, kFinalThreads, 0, st>>>(d, scal, method, m, s, h, host, host_moments);
+  if (exact)
+    final_kernel<true><<<1, kFinalThreads, 0, st>>>(d, scal, method, m, s, h, host, host_moments);
+  else
+    final_kernel<false><<<1, kFinalThreads, 0, st>>>(d, scal, method, m, s, h, host, host_moments);
   return hipGetLastError();
 }
 
@@ -1636,32 +1665,42 @@ hipError_t launch_batch_setup(const BatchMat *mats, int32_t count, int32_t metho
   return hipGetLastError();
 }
 
+template <bool X>
 __global__ void batch_reduce_kernel(const BatchMat *__restrict__ mats, const double *part, int32_t method,
                                     int32_t nslot, int64_t ldv, int32_t s, double *d) {
   const BatchMat &M = mats[blockIdx.y];
   const bool pair = method == 1 && batch_pairs(M);
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < (int64_t)nslot * s;
        t += (int64_t)gridDim.x * blockDim.x)
-    reduce_moments_body(part + M.poff, nslot, M.ntile, ldv, s, pair, d + M.doff, t);
+    reduce_moments_body<X>(part + M.poff, nslot, M.ntile, ldv, s, pair, d + M.doff, t);
 }
 
-hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double *part, int32_t method,
+hipError_t launch_batch_reduce(const BatchMat *mats, int32_t count, const double *part, bool exact, int32_t method,
                                int32_t nslot, int64_t ldv, int32_t s, double *d, hipStream_t st) {
   const int64_t per = ((int64_t)nslot * s + 255) / 256;
   dim3 grid((unsigned)(per < 64 ? per : 64), (unsigned)count);
-  batch_reduce_kernel<<<grid, 256, 0, st>>>(mats, part, method, nslot, ldv, s, d);
+  if (exact)
+    batch_reduce_kernel<true><<<grid, 256, 0, st>>>(mats, part, method, nslot, ldv, s, d);
+  else
+    batch_reduce_kernel<false><<<grid, 256, 0, st>>>(mats, part, method, nslot, ldv, s, d);
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(kFinalThreads) void batch_final_kernel(const BatchMat *__restrict__ mats, const double *d,
-                                   int32_t method, int32_t m, int32_t s, double *h) {
+template <bool X>
+__global__ __launch_bounds__(kFinalThreads) void batch_final_kernel(const BatchMat *__restrict__ mats, double *d,
+                                                                    int32_t method, int32_t m, int32_t s,
+                                                                    double *h) {
   const BatchMat &M = mats[blockIdx.x];
-  final_body(d + M.doff, M.scal, method, m, s, h + M.hoff);
+  const bool halves = !X && method == 1 && batch_pairs(M);
+  final_body<X>(d + M.doff, M.scal, halves ? FINAL_CHEB_PAIRS : method, m, s, h + M.hoff);
 }
 
-hipError_t launch_batch_final(const BatchMat *mats, int32_t count, const double *d, int32_t method,
+hipError_t launch_batch_final(const BatchMat *mats, int32_t count, double *d, bool exact, int32_t method,
                               int32_t m, int32_t s, double *h, hipStream_t st) {
-  batch_final_kernel<<<(unsigned)count, kFinalThreads, 0, st>>>(mats, d, method, m, s, h);
+  if (exact)
+    batch_final_kernel<true><<<(unsigned)count, kFinalThreads, 0, st>>>(mats, d, method, m, s, h);
+  else
+    batch_final_kernel<false><<<(unsigned)count, kFinalThreads, 0, st>>>(mats, d, method, m, s, h);
   return hipGetLastError();
 }
 
