@@ -277,7 +277,8 @@ __device__ __forceinline__ int xcc_id() {
 // queue without waiting for it, sched_item waits and gives it to the workgroup.
 // The loops around these begin with a convergent operation and branch on scalar
 // values: a loop that began with thread 0's branch would let the compiler send
-// the other lanes straight to the barrier behind it.
+// the other lanes straight to the barrier behind it.  That it did not is checked
+// on the built code (tests/test_kernel_code.py).
 __device__ __forceinline__ int sched_reserve(const SchedArgs &s) {
   __builtin_amdgcn_wave_barrier();
   int q = 0;

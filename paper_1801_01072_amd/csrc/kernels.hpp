@@ -277,8 +277,8 @@ hipError_t launch_dense_step(const DenseStepArgs &a, hipStream_t st, bool epilog
 template <typename T>
 hipError_t launch_dense_split_epilogue(const DenseStepArgs &a, hipStream_t st);
 // K-splits for a dense step whose tile grid (ntile x ldv/bn) has fewer than
-// 512 workgroups (two per CU): a power of two up to 16 while every split
-// keeps >= 256 columns.
+// 512 workgroups (two per CU): any number up to 16 of at least 256 columns each
+// (3, 5, 6 and 7 among them), the one with the cheapest rounds of workgroups.
 int32_t dense_step_splits(int64_t n, int32_t ntile, int64_t ldv, int32_t bn);
 // 16-probe tiles per workgroup of the small-problem step kernel (1, 2 or 4),
 // or 0 where the tiled kernel is the faster one.

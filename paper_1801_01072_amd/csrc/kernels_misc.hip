@@ -350,7 +350,7 @@ template hipError_t launch_power_sym<float>(const float *, int64_t, int64_t, con
 
 int32_t power_blocks_dense(int64_t n) { return (int32_t)((n + 7) / 8); }
 // At most kPowerSelfSum workgroups, so that the next product sums the triples:
-// n = 200000, 13 entries a row, FP64 24 us in 4096 workgroups and 5.9 for the
+// n = 200000, 20.6 entries a row, FP64 24 us in 4096 workgroups and 5.9 for the
 // sum, 26 us in 1024 without one; n = 40000 an estimate of 20 products 840 -> 795.
 int32_t power_blocks_spmv(int64_t n) {
   const int64_t b = (n + 31) / 32;
@@ -767,14 +767,15 @@ __global__ __launch_bounds__(256) void batch_check_kernel(const BatchMat *__rest
   __shared__ T tile[64][65];
   const BatchMat &M = mats[blockIdx.y];
   const int64_t nb = (M.n + 63) / 64, nt = nb * (nb + 1) / 2;
-  bool bad = false;
   for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
-    __syncthreads();
-    if (dense_check_tile<T>((const T *)M.R, M.ldr, M.n, t, tile, nullptr)) bad = true;
-  }
-  if (bad && (threadIdx.x & 63) == 0) {
-    raise_flag((int32_t *)(M.scal + S_SYM));
-    raise_flag(tail);
+    // a workgroup ends with the first tile that has a mismatch
+    if (__syncthreads_or(dense_check_tile<T>((const T *)M.R, M.ldr, M.n, t, tile, nullptr))) {
+      if (threadIdx.x == 0) {
+        raise_flag((int32_t *)(M.scal + S_SYM));
+        raise_flag(tail);
+      }
+      return;
+    }
   }
 }
 
