@@ -2265,8 +2265,8 @@ ent_status enqueue_batch(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
       for (int32_t it = 0; it <= o.power_iters; ++it) {
         pout = it & 1 ? g->part : g->p0;  // the steps' partials are not in use yet
         if (g->power_half)
-          HIP_TRY(ent::launch_batch_power_sym<T>(g->mats_d, g->ptiles_d, g->nptiles, g->tiles1_d, g->ntiles1, xin, pprev,
-                                                 (T *)g->VA, xout, pout, st));
+          HIP_TRY(ent::launch_batch_power_sym<T>(g->mats_d, g->ptiles_d, g->nptiles, g->tiles1_d, g->ntiles1, g->scal,
+                                                 g->sb, xin, pprev, (T *)g->VA, xout, pout, st));
         else
           HIP_TRY(ent::launch_batch_power_gemv<T>(g->mats_d, g->ptiles_d, g->nptiles, xin, pprev, xout, pout, st));
         std::swap(xin, xout);

@@ -1562,46 +1562,65 @@ __global__ __launch_bounds__(256) void batch_power_gemv_kernel(const BatchMat *_
 // The same from half of each matrix that equals its transpose (its answer is on
 // the device), the sums in the matrix's V block V: stiles (matrix, tile), tiles
 // (matrix, 64 rows).  Any other matrix is passed by here and multiplied whole by
-// the second launch, whose workgroups come in kRowGroups groups of one per entry
-// of tiles: a matrix read whole takes all of them, every fourth block of 8 rows
-// each, and a combination of 64 rows those of the first group.  us a product, for
-// matrices unequal to their transpose (40 of 2000 FP64; 64 of up to 2048 FP64; 32
-// of 1024 FP32): both halves by tiles 220 + 8, 128 + 6, 23.7 + 4.8; row blocks
-// dealt to the workgroups of the first launch, which hold too many registers for
-// it, 221 + 5, 139 + 5, 37 + 5; this way 8 + 214, 5 + 121, 4.6 + 24.9 (one group 9
-// + 217, 6 + 127, 4.6 + 30; eight 7 + 213, 5 + 119, 4.6 + 23.6), where every matrix
-// is read whole 209, 114, 23.5.  Combining 64 symmetric ones of up to 2048 takes
-// 6.2 us with four groups, 7.3 with eight, 5.2 with none.
+// the second launch, a workgroup per entry of tiles or, while these are few,
+// kRowGroups of them: group g takes every fourth block of 8 rows from the g-th on,
+// and a combination of 64 rows is the first group's.  Row blocks dealt to the
+// workgroups of the first launch, which hold too many registers for it, were
+// slower (32 of 1024 FP32 37 + 5 us a product against 4.6 + 24.9).  us a product,
+// matrices of up to 2048, first + second launch, one group / four:
+//   symmetric   48 FP32 44 + 5.5 / 5.6, 128 FP32 133 + 11.4 / 12.9, 1024 FP32
+//               1017 + 69 / 91, 512 FP64 890 + 34 / 44
+//   any other   48 FP32 6 + 97 / 85, 128 FP32 15 + 222 / 215, 512 FP32 56 + 842 /
+//               834, 48 FP64 5 + 151 / 145, 512 FP64 40 + 1467 / 1457
+// where every matrix is read whole 84, 209, 819 and 144, 1439 us.
 constexpr int kRowGroups = 4;
+constexpr int32_t kRowGroupTiles = 4096;
+// Waves per SIMD of the second launch, for its two bodies in one kernel: a wave
+// more spills in either type (others: 512 FP64 1467 -> 1538 us, 1024 FP32 1645 ->
+// 1996), and without a bound a symmetric batch waits longer (1024 FP32 69 -> 89).
+template <typename T>
+constexpr int kCombineWaves = sizeof(T) == 4 ? 6 : 7;
+
+// The answers of the symmetry check, sb apart from scal on: a matrix's is read
+// beside its descriptor, not behind it (512 others, FP32, passed by: 73 -> 56 us;
+// 1024 symmetric FP32 1052 -> 1017).
+struct SymFlags {
+  const double *scal;
+  int64_t sb;
+  __device__ __forceinline__ int32_t of(int32_t b) const {
+    return uniform_load((const int32_t *)(scal + b * sb + S_SYM));
+  }
+};
 
 template <typename T>
 __global__ __launch_bounds__(256) void batch_power_sym_kernel(const BatchMat *__restrict__ mats,
-                                                              const int2 *__restrict__ stiles,
+                                                              const int2 *__restrict__ stiles, SymFlags flags,
                                                               const double *__restrict__ x, T *V) {
   const int2 t = uniform_load(stiles + blockIdx.x);
+  const int32_t differs = flags.of(t.x);
   const BatchMat M = uniform_load(mats + t.x);
-  if (!batch_pairs(M)) return;
+  if (differs) return;
   int64_t rb, cb;
   sym_tile(t.y, rb, cb);
   power_sym_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, (double *)(V + M.voff), rb, cb, rb != cb);
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void batch_power_sym_combine_kernel(const BatchMat *__restrict__ mats,
-                                                                      const int2 *__restrict__ tiles, int32_t ntiles,
-                                                                      const double *x, const double *pprev,
-                                                                      const T *V, double *y, double *pout) {
-  const int32_t group = (int32_t)blockIdx.x / ntiles;
-  const int2 t = tiles[(int32_t)blockIdx.x - group * ntiles];
-  const BatchMat &M = mats[t.x];
+__global__ __launch_bounds__(256, kCombineWaves<T>) void batch_power_sym_combine_kernel(
+    const BatchMat *__restrict__ mats, const int2 *__restrict__ tiles, SymFlags flags, const double *x,
+    const double *pprev, const T *V, double *y, double *pout) {
+  const int32_t group = (int32_t)blockIdx.y, groups = (int32_t)gridDim.y;
+  const int2 t = uniform_load(tiles + blockIdx.x);
+  const int32_t differs = flags.of(t.x);
+  const BatchMat M = uniform_load(mats + t.x);
   PowerPrev prev = {nullptr, pprev ? pprev + M.pboff : nullptr, M.pblk};
-  if (batch_pairs(M)) {
+  if (!differs) {
     if (group > 0 || (int64_t)t.y * 64 >= M.n) return;
     prev.nblk = (int32_t)((M.n + 63) / 64);
     power_sym_sum((const double *)(V + M.voff), (int32_t)((M.n + kSymTile - 1) / kSymTile), M.n, M.n, x + M.xoff,
                   prev, y + M.xoff, pout + M.pboff, t.y);
   } else {
-    for (int blk = t.y * 8 + group; blk < t.y * 8 + 8 && blk < M.pblk; blk += kRowGroups) {
+    for (int blk = t.y * 8 + group; blk < t.y * 8 + 8 && blk < M.pblk; blk += groups) {
       __syncthreads();  // the block before is done with its sums in LDS
       power_gemv_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, prev, y + M.xoff, pout + M.pboff, blk);
     }
@@ -1610,20 +1629,22 @@ __global__ __launch_bounds__(256) void batch_power_sym_combine_kernel(const Batc
 
 template <typename T>
 hipError_t launch_batch_power_sym(const BatchMat *mats, const int2 *stiles, int32_t nstiles, const int2 *tiles,
-                                  int32_t ntiles, const double *x, const double *pprev, T *V, double *y,
-                                  double *pout, hipStream_t st) {
+                                  int32_t ntiles, const double *scal, int64_t sb, const double *x,
+                                  const double *pprev, T *V, double *y, double *pout, hipStream_t st) {
   if (pprev == pout) return hipErrorInvalidValue;
-  batch_power_sym_kernel<T><<<(unsigned)nstiles, 256, 0, st>>>(mats, stiles, x, V);
-  batch_power_sym_combine_kernel<T><<<(unsigned)ntiles * kRowGroups, 256, 0, st>>>(mats, tiles, ntiles, x, pprev, V, y,
-                                                                                pout);
+  const SymFlags flags = {scal, sb};
+  const int32_t groups = ntiles <= kRowGroupTiles ? kRowGroups : 1;
+  batch_power_sym_kernel<T><<<(unsigned)nstiles, 256, 0, st>>>(mats, stiles, flags, x, V);
+  batch_power_sym_combine_kernel<T><<<dim3((unsigned)ntiles, (unsigned)groups), 256, 0, st>>>(mats, tiles, flags, x,
+                                                                                              pprev, V, y, pout);
   return hipGetLastError();
 }
 template hipError_t launch_batch_power_sym<double>(const BatchMat *, const int2 *, int32_t, const int2 *, int32_t,
-                                                   const double *, const double *, double *, double *, double *,
-                                                   hipStream_t);
+                                                   const double *, int64_t, const double *, const double *, double *,
+                                                   double *, double *, hipStream_t);
 template hipError_t launch_batch_power_sym<float>(const BatchMat *, const int2 *, int32_t, const int2 *, int32_t,
-                                                  const double *, const double *, float *, double *, double *,
-                                                  hipStream_t);
+                                                  const double *, int64_t, const double *, const double *, float *,
+                                                  double *, double *, hipStream_t);
 
 template <typename T>
 hipError_t launch_batch_power_gemv(const BatchMat *mats, const int2 *ptiles, int32_t nptiles,

@@ -177,6 +177,25 @@ def test_batch_power_estimate_on_half(orc, precision, t):
     g.destroy()
 
 
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_batch_power_estimate_of_many(orc, precision):
+    """The same for more than 4096 tiles of 64 rows, where a matrix read whole
+    has a workgroup to each: one in seven of another kind."""
+    dtype = np.float64 if precision == "f64" else np.float32
+    kinds = [symmetric(n, n).astype(dtype) for n in (193, 200, 255, 256)] + [symmetric(130, 3).astype(dtype)]
+    host = [kinds[b % 5].copy() for b in range(1150)]
+    for R in host[::7]:
+        R[0, -1] += dtype(0.01)
+    assert sum(R.nbytes for R in host) >= 96 << 20 and sum((len(R) + 63) // 64 for R in host) > 4096
+    want = [orc.power_method(R.astype(np.float64), 2, 1, 9 + b) for b, R in enumerate(host)]
+    g = ent.Graph([torch.from_numpy(R).to(DEV) for R in host], "chebyshev", 3, 20, 9, precision=precision,
+                  power_iters=2, flags=ent.FLAG_SKIP_TRACE_CHECK)
+    for turn in range(2):
+        for b, r in enumerate(g.launch()):
+            assert abs(r.p1_est / want[b] - 1) <= 2e-11, (turn, b, r.p1_est, want[b])
+    g.destroy()
+
+
 def direct_tiles(n, s):
     """The library's rule: 0 where the tiled kernel runs."""
     f = getattr(ent._lib, "_ZN3ent18dense_direct_tilesEli")
