@@ -2120,6 +2120,7 @@ struct ent_graph_s {
   ent_options o{};
   bool src_f64 = false, comp_f64 = false;
   bool power_half = false;  // ptiles: 128 x 128 tiles on or below the diagonal
+  bool power_rows = false;  // then a matrix unequal to its transpose is read by rows
   int64_t ldv = 0, sb = 0, max_n = 0, max_npad = 0, max_elems = 0, xlen = 0;
   int32_t wr = 1, ntiles1 = 0, ntiles2 = 0, nptiles = 0;
   std::vector<ent::BatchMat> mats;
@@ -2266,13 +2267,13 @@ ent_status enqueue_batch(ent_graph_s *g, hipStream_t st, PhaseEvents *pe) {
         pout = it & 1 ? g->part : g->p0;  // the steps' partials are not in use yet
         if (g->power_half)
           HIP_TRY(ent::launch_batch_power_sym<T>(g->mats_d, g->ptiles_d, g->nptiles, g->tiles1_d, g->ntiles1, g->scal,
-                                                 g->sb, xin, pprev, (T *)g->VA, xout, pout, st));
+                                                 g->sb, g->power_rows, xin, pprev, (T *)g->VA, xout, pout, st));
         else
           HIP_TRY(ent::launch_batch_power_gemv<T>(g->mats_d, g->ptiles_d, g->nptiles, xin, pprev, xout, pout, st));
         std::swap(xin, xout);
         pprev = pout;
       }
-      HIP_TRY(ent::launch_batch_power_rq(g->mats_d, count, pout, trial, st, g->power_half));
+      HIP_TRY(ent::launch_batch_power_rq(g->mats_d, count, pout, trial, st, g->power_half, g->power_rows));
     }
     if (pe) {
       pe->power_end = pe->mark();
@@ -2715,14 +2716,24 @@ ent_status batch_create(const ent_matrix *Rs, int32_t count, int32_t method, int
   // (80 MB) 16.0 / 16.6, 600 of 200 (92 MB) 36 / 26; 40 of 2000 FP64 206 / 128.
   // The line is where the larger matrices begin to gain; many small ones would
   // from fewer bytes on.  Matrices unequal to their transpose are read whole either
-  // way (kRowGroups)
+  // way: by rows where the average row is longer than 768 (512 in FP64), else by
+  // tiles, whose sums are not one short row after another.  Rows against tiles, us a
+  // product of both launches, n of 129-192, 193-256, 257-384, 385-512, 513-768,
+  // 769-1024 (1200 to 64 matrices): FP32 101 / 56, 70 / 47, 64 / 46, 61 / 47, 50 /
+  // 48, 45 / 45; FP64 109 / 65, 99 / 74, 81 / 78, 95 / 91, 88 / 92, 83 / 88
   bool fits = !g->bf16 && (size_t)roff * esz >= ((size_t)96 << 20);
   for (const auto &M : g->mats) {
     const int64_t nb = ent::power_sym_parts(M.n);
     fits = fits && nb * (nb + 1) / 2 <= M.pblk && nb * M.n * 8 <= M.n_pad * g->ldv * (int64_t)esz;
   }
   if (fits) {
+    double rows = 0, elems = 0;
+    for (const auto &M : g->mats) {
+      rows += (double)M.n;
+      elems += (double)M.n * (double)M.n;
+    }
     g->power_half = true;
+    g->power_rows = elems > (esz == 4 ? 768.0 : 512.0) * rows;
     g->ptiles.clear();
     for (int32_t b : order) {
       const int64_t nb = ent::power_sym_parts(g->mats[b].n);

@@ -620,15 +620,15 @@ hipError_t launch_batch_power_gemv(const BatchMat *mats, const int2 *ptiles, int
                                    hipStream_t st);
 // The same reading half of each symmetric matrix: stiles lists (matrix, tile of
 // 128 x 128, power_sym_parts (parts + 1) / 2 of them), tiles (matrix, 64 rows); a
-// matrix unequal to its transpose is read whole, its triples those of
-// launch_batch_power_gemv.  Matrix b's scal is scal + b * sb.
+// matrix unequal to its transpose is read whole, by tiles or by rows, then its
+// triples are those of launch_batch_power_gemv.  Matrix b's scal is scal + b * sb.
 template <typename T>
 hipError_t launch_batch_power_sym(const BatchMat *mats, const int2 *stiles, int32_t nstiles, const int2 *tiles,
-                                  int32_t ntiles, const double *scal, int64_t sb, const double *x,
-                                  const double *pprev, T *V, double *y, double *pout, hipStream_t st);
+                                  int32_t ntiles, const double *scal, int64_t sb, bool rows,
+                                  const double *x, const double *pprev, T *V, double *y, double *pout, hipStream_t st);
 // half: the triples are those of launch_batch_power_sym
 hipError_t launch_batch_power_rq(const BatchMat *mats, int32_t count, const double *p,
-                                 int32_t trial, hipStream_t st, bool half = false);
+                                 int32_t trial, hipStream_t st, bool half = false, bool rows = false);
 hipError_t launch_batch_setup(const BatchMat *mats, int32_t count, int32_t method, int32_t m,
                               double c, double u_fixed, double lo, hipStream_t st,
                               double norm_div = 0.0);

@@ -1561,11 +1561,12 @@ __global__ __launch_bounds__(256) void batch_power_gemv_kernel(const BatchMat *_
 
 // The same from half of each matrix that equals its transpose (its answer is on
 // the device), the sums in the matrix's V block V: stiles (matrix, tile), tiles
-// (matrix, 64 rows).  Any other matrix is passed by here and multiplied whole by
-// the second launch, a workgroup per entry of tiles or, while these are few,
-// kRowGroups of them: group g takes every fourth block of 8 rows from the g-th on,
-// and a combination of 64 rows is the first group's.  Row blocks dealt to the
-// workgroups of the first launch, which hold too many registers for it, were
+// (matrix, 64 rows).  Of any other matrix the mirror tiles are read too or, with
+// rows, it is passed by here and multiplied by rows in the second launch (which is
+// faster where stands at its caller): a workgroup per entry of tiles there or, while
+// these are few, kRowGroups of them, group g taking every fourth block of 8 rows
+// from the g-th on; a combination of 64 rows is the first group's.  Row blocks dealt
+// to the workgroups of the first launch, which hold too many registers for it, were
 // slower (32 of 1024 FP32 37 + 5 us a product against 4.6 + 24.9).  us a product,
 // matrices of up to 2048, first + second launch, one group / four:
 //   symmetric   48 FP32 44 + 5.5 / 5.6, 128 FP32 133 + 11.4 / 12.9, 1024 FP32
@@ -1587,6 +1588,7 @@ constexpr int kCombineWaves = sizeof(T) == 4 ? 6 : 7;
 struct SymFlags {
   const double *scal;
   int64_t sb;
+  bool rows;
   __device__ __forceinline__ int32_t of(int32_t b) const {
     return uniform_load((const int32_t *)(scal + b * sb + S_SYM));
   }
@@ -1599,10 +1601,14 @@ __global__ __launch_bounds__(256) void batch_power_sym_kernel(const BatchMat *__
   const int2 t = uniform_load(stiles + blockIdx.x);
   const int32_t differs = flags.of(t.x);
   const BatchMat M = uniform_load(mats + t.x);
-  if (differs) return;
+  if (differs && flags.rows) return;
   int64_t rb, cb;
   sym_tile(t.y, rb, cb);
-  power_sym_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, (double *)(V + M.voff), rb, cb, rb != cb);
+  double *part = (double *)(V + M.voff);
+  power_sym_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, part, rb, cb, !differs && rb != cb);
+  if (!differs || rb == cb) return;
+  __syncthreads();
+  power_sym_body<T>((const T *)M.R, M.ldr, M.n, x + M.xoff, part, cb, rb, false);
 }
 
 template <typename T>
@@ -1614,7 +1620,7 @@ __global__ __launch_bounds__(256, kCombineWaves<T>) void batch_power_sym_combine
   const int32_t differs = flags.of(t.x);
   const BatchMat M = uniform_load(mats + t.x);
   PowerPrev prev = {nullptr, pprev ? pprev + M.pboff : nullptr, M.pblk};
-  if (!differs) {
+  if (!differs || !flags.rows) {
     if (group > 0 || (int64_t)t.y * 64 >= M.n) return;
     prev.nblk = (int32_t)((M.n + 63) / 64);
     power_sym_sum((const double *)(V + M.voff), (int32_t)((M.n + kSymTile - 1) / kSymTile), M.n, M.n, x + M.xoff,
@@ -1629,22 +1635,22 @@ __global__ __launch_bounds__(256, kCombineWaves<T>) void batch_power_sym_combine
 
 template <typename T>
 hipError_t launch_batch_power_sym(const BatchMat *mats, const int2 *stiles, int32_t nstiles, const int2 *tiles,
-                                  int32_t ntiles, const double *scal, int64_t sb, const double *x,
-                                  const double *pprev, T *V, double *y, double *pout, hipStream_t st) {
+                                  int32_t ntiles, const double *scal, int64_t sb, bool rows,
+                                  const double *x, const double *pprev, T *V, double *y, double *pout, hipStream_t st) {
   if (pprev == pout) return hipErrorInvalidValue;
-  const SymFlags flags = {scal, sb};
-  const int32_t groups = ntiles <= kRowGroupTiles ? kRowGroups : 1;
+  const SymFlags flags = {scal, sb, rows};
+  const int32_t groups = rows && ntiles <= kRowGroupTiles ? kRowGroups : 1;
   batch_power_sym_kernel<T><<<(unsigned)nstiles, 256, 0, st>>>(mats, stiles, flags, x, V);
   batch_power_sym_combine_kernel<T><<<dim3((unsigned)ntiles, (unsigned)groups), 256, 0, st>>>(mats, tiles, flags, x,
                                                                                               pprev, V, y, pout);
   return hipGetLastError();
 }
 template hipError_t launch_batch_power_sym<double>(const BatchMat *, const int2 *, int32_t, const int2 *, int32_t,
-                                                   const double *, int64_t, const double *, const double *, double *,
-                                                   double *, double *, hipStream_t);
+                                                   const double *, int64_t, bool, const double *, const double *,
+                                                   double *, double *, double *, hipStream_t);
 template hipError_t launch_batch_power_sym<float>(const BatchMat *, const int2 *, int32_t, const int2 *, int32_t,
-                                                  const double *, int64_t, const double *, const double *, float *,
-                                                  double *, double *, hipStream_t);
+                                                  const double *, int64_t, bool, const double *, const double *,
+                                                  float *, double *, double *, hipStream_t);
 
 template <typename T>
 hipError_t launch_batch_power_gemv(const BatchMat *mats, const int2 *ptiles, int32_t nptiles,
@@ -1663,16 +1669,16 @@ template hipError_t launch_batch_power_gemv<float>(const BatchMat *, const int2 
 
 // One block per matrix: its final product's triples and Rayleigh quotient.
 __global__ __launch_bounds__(256) void batch_power_rq_kernel(const BatchMat *__restrict__ mats, const double *p,
-                                                             int32_t trial, bool half) {
+                                                             int32_t trial, bool half, bool rows) {
   __shared__ double norm3[3];
   const BatchMat &M = mats[blockIdx.x];
-  power_reduce_body(p + M.pboff, half && batch_pairs(M) ? (int32_t)((M.n + 63) / 64) : M.pblk, norm3);
+  power_reduce_body(p + M.pboff, half && (!rows || batch_pairs(M)) ? (int32_t)((M.n + 63) / 64) : M.pblk, norm3);
   power_rq_body(M.scal, norm3, trial);
 }
 
 hipError_t launch_batch_power_rq(const BatchMat *mats, int32_t count, const double *p,
-                                 int32_t trial, hipStream_t st, bool half) {
-  batch_power_rq_kernel<<<(unsigned)count, 256, 0, st>>>(mats, p, trial, half);
+                                 int32_t trial, hipStream_t st, bool half, bool rows) {
+  batch_power_rq_kernel<<<(unsigned)count, 256, 0, st>>>(mats, p, trial, half, rows);
   return hipGetLastError();
 }
 

@@ -177,16 +177,20 @@ def test_batch_power_estimate_on_half(orc, precision, t):
     g.destroy()
 
 
-@pytest.mark.parametrize("precision", ["f64", "f32"])
-def test_batch_power_estimate_of_many(orc, precision):
-    """The same for more than 4096 tiles of 64 rows, where a matrix read whole
-    has a workgroup to each: one in seven of another kind."""
+@pytest.mark.parametrize("precision,ns,count", [
+    ("f64", [193, 200, 255, 256, 130], 1150), ("f32", [193, 200, 255, 256, 130], 1150),
+    ("f64", [1, 64, 65, 511, 512, 513], 110), ("f64", [513, 640, 641], 40),
+    ("f32", [127, 769, 770, 895, 896], 55), ("f32", [800, 769], 330)])
+def test_batch_power_estimate_of_others(orc, precision, ns, count):
+    """The same on both sides of the rule that reads a matrix unequal to its
+    transpose by tiles or by rows, and for more than 4096 tiles of 64 rows: one in
+    seven of that kind."""
     dtype = np.float64 if precision == "f64" else np.float32
-    kinds = [symmetric(n, n).astype(dtype) for n in (193, 200, 255, 256)] + [symmetric(130, 3).astype(dtype)]
-    host = [kinds[b % 5].copy() for b in range(1150)]
+    kinds = [symmetric(n, n).astype(dtype) for n in ns]
+    host = [kinds[b % len(ns)].copy() for b in range(count)]
     for R in host[::7]:
         R[0, -1] += dtype(0.01)
-    assert sum(R.nbytes for R in host) >= 96 << 20 and sum((len(R) + 63) // 64 for R in host) > 4096
+    assert sum(R.nbytes for R in host) >= 96 << 20
     want = [orc.power_method(R.astype(np.float64), 2, 1, 9 + b) for b, R in enumerate(host)]
     g = ent.Graph([torch.from_numpy(R).to(DEV) for R in host], "chebyshev", 3, 20, 9, precision=precision,
                   power_iters=2, flags=ent.FLAG_SKIP_TRACE_CHECK)
